@@ -407,8 +407,9 @@ laser_status laser_sta_folded_forward(const void* t, const void* h, const void* 
  * q, k, v, lens, sizes and gamma as for laser_sta_forward (one head, sigmoid gates). Arithmetic in fp32 from the stored
  * inputs; sums in a fixed order (results are reproducible run to run).
  * Built for training batches, which hold one or a few targets per sample: d_q, d <= 256 (wider rows return
- * LASER_ERR_UNSUPPORTED), and up to eight candidates per user in one pass over k and v; more are taken eight at a
- * time, one pass each, the later passes adding to dk_out and dv_out (correct for any C, fast for few). work is caller-owned scratch of at least laser_sta_backward_work_bytes(U, C, L, d_q, w)
+ * LASER_ERR_UNSUPPORTED), any number of candidates per user: more than four in bf16 with d_q in {32, 64, 128} and d in
+ * {64, 128} run on the matrix cores, other cases up to eight candidates in one pass over k and v, more eight at a time,
+ * one pass each, the later passes adding to dk_out and dv_out. work is caller-owned scratch of at least laser_sta_backward_work_bytes(U, C, L, d_q, w)
  * bytes (partial dq sums; contents unspecified on return); the library allocates nothing.
  * All pointers are device pointers, 16-byte aligned (lens 4-byte); work is enqueued on `stream`.
  * Errors: LASER_ERR_NULL, LASER_ERR_SHAPE (sizes, gamma, work_bytes too small), LASER_ERR_DTYPE, LASER_ERR_ALIGN,

@@ -136,6 +136,8 @@ struct StaBwdArgs {        // gradients of STA: dq [U,C,d_q], dk [U,L,d_q], dv [
 bool sta_backward_supports(const StaBwdArgs& a);
 size_t sta_backward_work_bytes(int U, int C, int L, int d_q, int w);
 laser_status sta_backward_launch(const StaBwdArgs& a);
+bool sta_bwd_mfma_supports(const StaBwdArgs& a);   // many candidates per user: the matrix-core form
+laser_status sta_bwd_mfma_launch(const StaBwdArgs& a, int* groups);
 
 struct GstaBwdArgs {       // gradients of GSTA from dz = d loss / d z [U,C,d] (fp32)
   const void* seg;         // H' [U,C,S,d]

@@ -13,6 +13,8 @@
 // segment sit in registers in the same lane layout.
 // sta_bwd_wide_kernel (bf16, the usual widths, up to four candidates; further down): the forward kernels' lane layout,
 // several items per wave-wide load.
+// More candidates per user than that run on the matrix cores where the widths allow it (sta_backward_mfma.hip), else on
+// sta_bwd_kernel, eight candidates a pass.
 // In both, dq is summed over a workgroup's waves in LDS and over a user's workgroups by a second small kernel, in a
 // fixed order (deterministic), and items at or past the valid length get zero gradients.
 #include <cstdlib>
@@ -486,7 +488,11 @@ laser_status sta_backward_launch(const StaBwdArgs& a) {
   const long long blocks = (long long)a.U * groups;
   if (blocks > 0x7fffffffLL) return LASER_ERR_SHAPE;
   const size_t lds = sizeof(float) * (size_t)(a.C < SB_CMAX ? a.C : SB_CMAX) * a.d_q * 4;
-  if (sta_bwd_wide_supports(a)) {
+  if (sta_bwd_mfma_supports(a)) {
+    const laser_status st = sta_bwd_mfma_launch(a, &groups);
+    if (st != LASER_OK) return st;
+    if (groups == 1) return LASER_OK;
+  } else if (sta_bwd_wide_supports(a)) {
     const unsigned nb = (unsigned)blocks;
     switch (a.d_q * 1000 + a.d) {
       case 32064: sta_bwd_wide_launch<32, 64>(a, nb, spg, groups); break;

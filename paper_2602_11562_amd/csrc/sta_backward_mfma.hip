@@ -1,0 +1,376 @@
+// Backward pass of STA on the bf16 matrix cores, for more than a few candidates per user (the equations stand at the
+// top of sta_backward.hip). With C candidates sharing a history all five products are dense contractions:
+//   S = Q K^T,  D = dH'_i V^T  (exact bf16 products, fp32 sums),  g = sigmoid(S / gamma),  ds = D g (1 - g) / gamma,
+//   dV_i = G^T dH'_i,  dK_i = dS^T Q   (contracted over the candidates),   dQ = dS K   (contracted over the items).
+// g and ds are fp32 and stay so: each enters its product as three bf16 parts (head, remainder, remainder of that: 24
+// bits), three MFMAs on the same other operand, so the pass keeps fp32 precision at a third of the bf16 rate, still
+// five times the rate of the fp32 matrix instructions.
+//
+// Two kinds of workgroup in one launch, because the two contractions want the scores the other way round:
+//   items   a wave owns 32 items of one segment (their K and V rows are operands in registers, dK and dV accumulators)
+//           and walks the candidates in blocks of 32 (rows of Q and dH'_i in LDS). S and D come out with lane = item and
+//           candidates along the registers, which is, per 16 candidates, the left operand of dV and dK; the right
+//           operand is the transpose load of the same LDS rows.
+//   queries a wave owns 32 candidates (Q, and dH'_i of the segment in work, in registers) and walks the items of a run
+//           of segments (rows of K and V in LDS); S and D are computed once more with lane = candidate, ds is the left
+//           operand of dQ and the transpose load of the K rows the right one.
+// Computing S and D twice costs 2 (d_q + d) of 3 (d_q + d) + 9 d_q + 3 d multiply-adds and replaces a transposition of ds
+// through LDS; neither kind waits for the other and nothing but Q's partial sums crosses workgroups.
+// A workgroup's four waves split over segments when a segment has few item tiles (or a user few candidate tiles):
+// short segments and small candidate sets leave no wave idle. Rows past the end of a segment or past the last candidate
+// are zeros in LDS, so they add nothing to any sum (padding of the history is never read).
+//
+// What bounds it: LDS reads and MFMA issue share the time (two workgroups of four waves per compute unit: 256
+// registers a wave); at 64 users x 64 candidates, L = 2048, w = 128, d = d_q = 64 (lengths 410 .. 2048) the launch takes
+// 30 us for the 92 MB it cannot do without, eight passes of the one-item-per-wave kernel took 1840 us.
+#include "laser_internal.h"
+#include "sta_mfma_tile.h"
+
+namespace laser {
+
+// Position of 16-byte chunk c of row r in an LDS tile with rows of D bf16 values and no padding. Both access patterns
+// stay free of bank conflicts: 16 consecutive rows at one chunk (operand reads, 16 bytes a lane) and four consecutive
+// rows at four neighbouring chunks (transpose loads, 8 bytes a lane).
+template <int D>
+__device__ __forceinline__ int swz(int r, int c) {
+  if constexpr (D == 128) return r * 256 + ((c ^ (((r & 3) << 2) | ((r >> 2) & 3))) << 4);
+  else if constexpr (D == 64) return r * 128 + ((c ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3))) << 4);
+  else return r * 64 + ((c ^ ((r >> 2) & 3)) << 4);
+}
+
+// operand whose lanes are the rows of a tile: row l32, k-slots 16 ks + 8 h ..
+template <int D>
+__device__ __forceinline__ bf16x8 tile_rows(const unsigned char* t, int l32, int h, int ks) {
+  return *reinterpret_cast<const bf16x8*>(t + swz<D>(l32, 2 * ks + h));
+}
+// operand whose lanes are the columns of a tile: column 32 db + l32, k-slots rows 16 s + {4h..4h+3, 8+4h..8+4h+3}
+// (lane i of a 16-lane group supplies the address of row i / 4, columns 4 (i % 4) .. and receives column i of four rows)
+template <int D>
+__device__ __forceinline__ bf16x8 tile_cols(const unsigned char* t, int lane, int s, int db) {
+  const int h = lane >> 5, i16 = lane & 15, col = db * 32 + (lane & 16) + 4 * (i16 & 3);
+  const int r = s * 16 + h * 4 + (i16 >> 2);
+  const int sub = (col & 4) * 2;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(t + swz<D>(r, col >> 3) + sub));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(t + swz<D>(r + 8, col >> 3) + sub));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// eight fp32 values as the sum of three bf16 operands (each remainder is exact)
+struct Split3 { bf16x8 p[3]; };
+__device__ __forceinline__ Split3 split3(const f32x16& x, int s) {
+  Split3 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float a = x[s * 8 + e];
+    const __bf16 h0 = (__bf16)a;
+    const float r1 = a - (float)h0;
+    const __bf16 h1 = (__bf16)r1;
+    o.p[0][e] = h0;
+    o.p[1][e] = h1;
+    o.p[2][e] = (__bf16)(r1 - (float)h1);
+  }
+  return o;
+}
+
+// rows [0, rows) of a matrix with row pitch `pitch` elements into a 32-row tile, zeros after them; nt threads share it
+template <int D>
+__device__ __forceinline__ void stage_rows(unsigned char* t, const unsigned short* src, size_t pitch, int rows, int tid,
+                                           int nt) {
+  constexpr int CH = D / 8;
+  for (int e = tid; e < 32 * CH; e += nt) {
+    const int r = e / CH, c = e % CH;
+    u32x4 x = {0u, 0u, 0u, 0u};
+    if (r < rows) x = *reinterpret_cast<const u32x4*>(src + (size_t)r * pitch + c * 8);
+    *reinterpret_cast<u32x4*>(t + swz<D>(r, c)) = x;
+  }
+}
+
+struct StaBwdMfmaShape {
+  int wi, ws_i;        // items: waves per segment, segments per workgroup (wi * ws_i = 4)
+  int nsb, ntb;        // segment blocks, blocks of wi item tiles per segment
+  int wc, ws_q;        // queries: candidate tiles and segments in work per workgroup (wc * ws_q = 4)
+  int nct, groups, spg;
+};
+
+template <int DQ, int D>
+__global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned short* __restrict__ q,
+                                                              const unsigned short* __restrict__ k,
+                                                              const unsigned short* __restrict__ v,
+                                                              const unsigned short* __restrict__ dhp,
+                                                              const int32_t* __restrict__ lens, int C, int L, int w,
+                                                              int S, StaBwdMfmaShape sh, int query_blocks,
+                                                              float neg_scale_log2e, float inv_gamma,
+                                                              float* __restrict__ dk, float* __restrict__ dv,
+                                                              float* __restrict__ dq_part) {
+  constexpr int KQ = DQ / 16, KV = D / 16, QB = DQ / 32, VB = D / 32;
+  constexpr int QBYTES = 32 * DQ * 2, VBYTES = 32 * D * 2;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // ds in the place of D, g in the place of S
+  auto gates = [&](f32x16& s, f32x16& dd) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float g = gate(s[r], neg_scale_log2e);
+      s[r] = g;
+      dd[r] = dd[r] * g * (1.0f - g) * inv_gamma;
+    }
+  };
+  f32x16 zero16;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero16[r] = 0.0f;
+
+  if ((int)blockIdx.x >= query_blocks) {
+    // ------------------------------------------------------------------ items: dK and dV
+    int b = blockIdx.x - query_blocks;
+    const int tb = b % sh.ntb;
+    b /= sh.ntb;
+    const int sb = b % sh.nsb, u = b / sh.nsb;
+    const int si = wave / sh.wi, ti = tb * sh.wi + wave % sh.wi;
+    const int seg = sb * sh.ws_i + si;
+    const int n = __builtin_amdgcn_readfirstlane(valid_len(lens, u, L));
+    const int lo = seg * w + ti * 32;                    // (seg may be past S: then lo >= hi_all)
+    int seg_end = seg < S ? seg * w + w : 0;
+    if (seg_end > L) seg_end = L;
+    const int rows_all = seg_end - lo < 32 ? seg_end - lo : 32;           // rows of the tile to write (<= 0: none)
+    const int rows = (seg_end < n ? seg_end : n) - lo < 32 ? (seg_end < n ? seg_end : n) - lo : 32;
+    const bool work_here = rows > 0;                     // wave-uniform
+    // the first segment of the workgroup starts earliest: past the valid length there, nobody computes
+    const bool any = sb * sh.ws_i * w + tb * sh.wi * 32 < n;
+
+    bf16x8 kf[KQ], vf[KV];
+    f32x16 dka[QB], dva[VB];
+#pragma unroll
+    for (int i = 0; i < QB; ++i) dka[i] = zero16;
+#pragma unroll
+    for (int i = 0; i < VB; ++i) dva[i] = zero16;
+    if (any) {
+      if (work_here) {
+        const size_t row = (size_t)u * L + lo + (l32 < rows ? l32 : rows - 1);
+#pragma unroll
+        for (int ks = 0; ks < KQ; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(k + row * DQ + ks * 16 + h * 8);
+#pragma unroll
+        for (int ks = 0; ks < KV; ++ks) vf[ks] = *reinterpret_cast<const bf16x8*>(v + row * D + ks * 16 + h * 8);
+      }
+      unsigned char* Qs = lds;
+      unsigned char* Hs = lds + QBYTES + si * VBYTES;
+      const int hseg = seg < S ? seg : S - 1;
+      for (int c0 = 0; c0 < C; c0 += 32) {
+        const int nc = C - c0 < 32 ? C - c0 : 32;
+        __syncthreads();
+        stage_rows<DQ>(Qs, q + ((size_t)u * C + c0) * DQ, DQ, nc, tid, 256);
+        stage_rows<D>(Hs, dhp + (((size_t)u * C + c0) * S + hseg) * D, (size_t)S * D, nc, tid % (64 * sh.wi), 64 * sh.wi);
+        __syncthreads();
+        if (work_here) {
+          f32x16 s = zero16, dd = zero16;
+#pragma unroll
+          for (int ks = 0; ks < KQ; ++ks)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_rows<DQ>(Qs, l32, h, ks), kf[ks], s, 0, 0, 0);
+#pragma unroll
+          for (int ks = 0; ks < KV; ++ks)
+            dd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_rows<D>(Hs, l32, h, ks), vf[ks], dd, 0, 0, 0);
+          gates(s, dd);
+#pragma unroll
+          for (int st = 0; st < 2; ++st) {
+            const Split3 gs = split3(s, st);
+#pragma unroll
+            for (int db = 0; db < VB; ++db) {
+              const bf16x8 x = tile_cols<D>(Hs, lane, st, db);
+#pragma unroll
+              for (int p = 2; p >= 0; --p) dva[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gs.p[p], x, dva[db], 0, 0, 0);
+            }
+            const Split3 ds = split3(dd, st);
+#pragma unroll
+            for (int db = 0; db < QB; ++db) {
+              const bf16x8 x = tile_cols<DQ>(Qs, lane, st, db);
+#pragma unroll
+              for (int p = 2; p >= 0; --p) dka[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds.p[p], x, dka[db], 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+    // lane = column, registers = items: whole 128-byte pieces of a row per store; rows past the valid length get zeros
+    float* dkr = dk + ((size_t)u * L + lo) * DQ + l32;
+    float* dvr = dv + ((size_t)u * L + lo) * D + l32;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = 8 * (r >> 2) + 4 * h + (r & 3);
+      if (row < rows_all) {
+        const bool ok = row < rows;
+#pragma unroll
+        for (int db = 0; db < QB; ++db) __builtin_nontemporal_store(ok ? dka[db][r] : 0.0f, dkr + (size_t)row * DQ + db * 32);
+#pragma unroll
+        for (int db = 0; db < VB; ++db) __builtin_nontemporal_store(ok ? dva[db][r] : 0.0f, dvr + (size_t)row * D + db * 32);
+      }
+    }
+  } else {
+    // ------------------------------------------------------------------ queries: dQ over a run of segments
+    int b = blockIdx.x;
+    const int grp = b % sh.groups;
+    b /= sh.groups;
+    const int ct = b % sh.nct, u = b / sh.nct;
+    const int sq = wave / sh.wc;                                       // which of the segments in work
+    const int cbase = (ct * sh.wc + wave % sh.wc) * 32;
+    const bool mine = cbase < C;
+    const int n = __builtin_amdgcn_readfirstlane(valid_len(lens, u, L));
+    const int i_beg = grp * sh.spg;
+    int i_end = i_beg + sh.spg < S ? i_beg + sh.spg : S;
+    const int valid_segs = (n + w - 1) / w;
+    if (i_end > valid_segs) i_end = valid_segs;
+    const int tiles = (w + 31) / 32;                                   // (w <= L)
+    unsigned char* Ks = lds + sq * (QBYTES + VBYTES);
+    unsigned char* Vs = Ks + QBYTES;
+    const int crow = cbase + l32 < C ? cbase + l32 : C - 1;            // (rows past the last candidate are not stored)
+
+    bf16x8 qf[KQ], hf[KV];
+    f32x16 dqa[QB];
+#pragma unroll
+    for (int i = 0; i < QB; ++i) dqa[i] = zero16;
+#pragma unroll
+    for (int ks = 0; ks < KQ; ++ks)
+      qf[ks] = *reinterpret_cast<const bf16x8*>(q + ((size_t)u * C + crow) * DQ + ks * 16 + h * 8);
+    for (int i0 = i_beg; i0 < i_end; i0 += sh.ws_q) {
+      const int i = i0 + sq;
+      const bool live = i < i_end;
+      const int lo = live ? i * w : 0;
+      int hi = live ? (i * w + w < L ? i * w + w : L) : 0;
+      if (hi > n) hi = n;
+      if (live) {
+#pragma unroll
+        for (int ks = 0; ks < KV; ++ks)
+          hf[ks] = *reinterpret_cast<const bf16x8*>(dhp + (((size_t)u * C + crow) * S + i) * D + ks * 16 + h * 8);
+      }
+      for (int t = 0; t < tiles; ++t) {
+        const int left = hi - lo - t * 32;
+        const int rows = left < 0 ? 0 : (left < 32 ? left : 32);
+        if (i0 * w + t * 32 >= n && sh.ws_q == 1) break;               // workgroup-uniform: the history ends here
+        const size_t r0 = (size_t)u * L + lo + (rows > 0 ? t * 32 : 0);
+        __syncthreads();
+        stage_rows<DQ>(Ks, k + r0 * DQ, DQ, rows, tid % (64 * sh.wc), 64 * sh.wc);
+        stage_rows<D>(Vs, v + r0 * D, D, rows, tid % (64 * sh.wc), 64 * sh.wc);
+        __syncthreads();
+        if (rows > 0 && mine) {
+          f32x16 s = zero16, dd = zero16;
+#pragma unroll
+          for (int ks = 0; ks < KQ; ++ks)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_rows<DQ>(Ks, l32, h, ks), qf[ks], s, 0, 0, 0);
+#pragma unroll
+          for (int ks = 0; ks < KV; ++ks)
+            dd = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tile_rows<D>(Vs, l32, h, ks), hf[ks], dd, 0, 0, 0);
+          gates(s, dd);
+#pragma unroll
+          for (int st = 0; st < 2; ++st) {
+            const Split3 ds = split3(dd, st);
+#pragma unroll
+            for (int db = 0; db < QB; ++db) {
+              const bf16x8 x = tile_cols<DQ>(Ks, lane, st, db);
+#pragma unroll
+              for (int p = 2; p >= 0; --p) dqa[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds.p[p], x, dqa[db], 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+    // the waves that shared these candidates add up in a fixed order
+    if (sh.ws_q > 1) {
+      __syncthreads();
+      float* red = reinterpret_cast<float*>(lds);
+      if (sq > 0) {
+        float* o = red + ((size_t)((sq - 1) * sh.wc + wave % sh.wc) * QB * 16) * 64 + lane;
+#pragma unroll
+        for (int db = 0; db < QB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[(db * 16 + r) * 64] = dqa[db][r];
+      }
+      __syncthreads();
+      if (sq > 0) return;
+      for (int o = 1; o < sh.ws_q; ++o) {
+        const float* src = red + ((size_t)((o - 1) * sh.wc + wave) * QB * 16) * 64 + lane;
+#pragma unroll
+        for (int db = 0; db < QB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dqa[db][r] += src[(db * 16 + r) * 64];
+      }
+    }
+    float* out = dq_part + (((size_t)u * sh.groups + grp) * C) * DQ + l32;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int c = cbase + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (c < C)
+#pragma unroll
+        for (int db = 0; db < QB; ++db) out[(size_t)c * DQ + db * 32] = dqa[db][r];
+    }
+  }
+}
+
+static int waves_for(int tiles) { return tiles >= 3 ? 4 : tiles; }   // 1, 2 or 4 waves share the tiles
+
+static StaBwdMfmaShape sta_bwd_mfma_shape(const StaBwdArgs& a, int max_groups) {
+  StaBwdMfmaShape s;
+  const int seg = a.w < a.L ? a.w : a.L, tiles = (seg + 31) / 32, ct = (a.C + 31) / 32;
+  s.wi = waves_for(tiles);
+  s.ws_i = 4 / s.wi;
+  s.nsb = (a.S + s.ws_i - 1) / s.ws_i;
+  s.ntb = (tiles + s.wi - 1) / s.wi;
+  s.wc = waves_for(ct);
+  s.ws_q = 4 / s.wc;
+  s.nct = (ct + s.wc - 1) / s.wc;
+  // runs of segments: two workgroups per compute unit (as many as fit at once), each run a multiple of the segments in
+  // work; every further run costs a partial sum of dQ in memory
+  const long long users = (long long)a.U * s.nct;
+  long long g = (512 + users - 1) / users;
+  if (g > max_groups) g = max_groups;
+  long long spg = (a.S + g - 1) / g;
+  spg = (spg + s.ws_q - 1) / s.ws_q * s.ws_q;
+  if (spg > a.S) spg = a.S;
+  s.spg = (int)spg;
+  s.groups = (a.S + s.spg - 1) / s.spg;
+  return s;
+}
+
+// From five candidates on. Up to four the several-items-per-wave kernel streams the history once and is mostly the
+// faster one (2048 users x 4, L = 1000, w = 10, 32 / 128: 586 us against 819 us here; 512 x 4, L = 2000, w = 64, 128 / 128:
+// 356 against 470 us; 64 / 64 the other way round, 188 against 126 us); beyond four the alternative is one item per wave,
+// eight candidates a pass: 512 x 5, L = 1000, w = 10, 32 / 128: 260 against 168 us, 512 x 8, w = 64, 128 / 128: 475 against
+// 158 us.
+bool sta_bwd_mfma_supports(const StaBwdArgs& a) {
+  return a.dt == LASER_BF16 && !a.grads_bf16 && a.C > 4 && (a.d_q == 32 || a.d_q == 64 || a.d_q == 128) &&
+         (a.d == 64 || a.d == 128);
+}
+
+template <int DQ, int D>
+static laser_status launch_shape(const StaBwdArgs& a, const StaBwdMfmaShape& s, float* part) {
+  const long long qb = (long long)a.U * s.nct * s.groups, ib = (long long)a.U * s.nsb * s.ntb;
+  if (qb + ib > 0x7fffffffLL) return LASER_ERR_SHAPE;
+  const int items = 32 * DQ * 2 + s.ws_i * 32 * D * 2, queries = s.ws_q * (32 * DQ * 2 + 32 * D * 2);
+  const int reduce = (s.ws_q - 1) * s.wc * DQ * 32 * 4;
+  int lds = items > queries ? items : queries;
+  if (reduce > lds) lds = reduce;
+  const float inv_gamma = 1.0f / a.gamma;
+  hipLaunchKernelGGL((sta_bwd_mfma_kernel<DQ, D>), dim3((unsigned)(qb + ib)), dim3(256), lds, a.stream,
+                     (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,
+                     (const unsigned short*)a.dhp, a.lens, a.C, a.L, a.w < a.L ? a.w : a.L, a.S, s, (int)qb,
+                     -1.4426950408889634f * inv_gamma, inv_gamma, static_cast<float*>(a.dk), static_cast<float*>(a.dv),
+                     part);
+  return launch_status();
+}
+
+// groups: in, the partial sums of dQ that a.work holds per user; out, how many were written (1: straight into a.dq)
+laser_status sta_bwd_mfma_launch(const StaBwdArgs& a, int* groups) {
+  if (!sta_bwd_mfma_supports(a)) return LASER_ERR_UNSUPPORTED;
+  const StaBwdMfmaShape s = sta_bwd_mfma_shape(a, *groups);
+  *groups = s.groups;
+  float* part = s.groups == 1 ? a.dq : a.work;
+  switch (a.d_q * 1000 + a.d) {
+    case 32064: return launch_shape<32, 64>(a, s, part);
+    case 32128: return launch_shape<32, 128>(a, s, part);
+    case 64064: return launch_shape<64, 64>(a, s, part);
+    case 64128: return launch_shape<64, 128>(a, s, part);
+    case 128064: return launch_shape<128, 64>(a, s, part);
+    default: return launch_shape<128, 128>(a, s, part);
+  }
+}
+
+}  // namespace laser

@@ -1,0 +1,58 @@
+"""GPU parity of STA's backward pass on the matrix cores (more than four candidates, bf16) at the edges of its tiles and
+of its split into workgroups, against the fp64 checker. Both products with fp32 factors (the gates, the score gradients)
+carry 24 bits, so the bounds are those of an fp32 sum: 1e-5, dk per user as in test_sta_backward_gpu.py (a row of dk
+is a sum of signed terms that may cancel)."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+
+from parity_util import to_device, to_host_f64, vec_rel_err
+from test_sta_backward_gpu import BWD_TOL, _store
+
+pytestmark = pytest.mark.gpu
+
+laser = pytest.importorskip("paper_2602_11562_amd")
+
+# C, L, d_q, d, w, lens
+CASES = {
+    "five_candidates_one_item_tile": (5, 96, 32, 64, 32, [96, 33, 32, 31, 1, 0]),     # tile edges of the valid length
+    "33_candidates_segments_of_one_item": (33, 12, 64, 64, 1, [12, 5]),
+    "64_candidates_short_segments": (64, 130, 128, 64, 10, [130, 101]),              # four segments per workgroup
+    "65_candidates_two_tiles_a_segment": (65, 200, 64, 128, 33, [200, 34]),          # 33 items: a tile of one row
+    "130_candidates_long_segment": (130, 700, 128, 128, 300, [700, 301, 257]),       # several item blocks per segment
+    "one_long_segment": (9, 260, 32, 128, 1000, [260, 129]),                         # w > L
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_sta_backward_on_the_matrix_cores(name):
+    import torch
+    C, L, dq, d, w, lens = CASES[name]
+    U, S = len(lens), -(-L // w)
+    rng = np.random.default_rng(4100 + sum(map(ord, name)))
+    (qs, qv), (ks, kv), (vs, vv), (gs, gv) = (_store(rng.normal(size=s), "bf16")
+                                              for s in ((U, C, dq), (U, L, dq), (U, L, d), (U, C, S, d)))
+    lens = np.array(lens, dtype=np.int32)
+    for u, n in enumerate(lens):      # padding rows may hold anything
+        ks[u, n:] = 0x7fc0
+        vs[u, n:] = 0x7fc0
+    gamma = math.sqrt(dq)
+    print(f"case {name}", flush=True)
+    ref = oracle.sta_backward(qv, kv, vv, lens, w, gamma, gv)
+    args = (to_device(qs), to_device(ks), to_device(vs), to_device(lens), to_device(gs), w, gamma)
+    got = laser.laser_sta_backward(*args)
+    torch.cuda.synchronize()
+    for nm, a, b in zip(("dq", "dk", "dv"), got, ref):
+        a = to_host_f64(a)
+        assert np.isfinite(a).all() and not a[b == 0].any()
+        if nm == "dk":
+            a, b = a.reshape(U, -1), b.reshape(U, -1)
+        err = vec_rel_err(a, b)
+        print(f"  {nm}: max relative error {err:.3e}", flush=True)
+        assert err <= BWD_TOL, nm
+    again = laser.laser_sta_backward(*args)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(got, again))      # fixed summation order
