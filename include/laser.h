@@ -57,7 +57,7 @@ typedef enum { LASER_F32 = 0, LASER_BF16 = 1, LASER_DTYPE_ANY_INT = 0x7fffffff }
  * and return LASER_ERR_UNSUPPORTED when the shape is outside that kernel's range. */
 typedef enum {
   LASER_STA_AUTO = 0,
-  LASER_STA_GENERIC = 1, /* fp32 FMA, any shape, either dtype                        */
+  LASER_STA_GENERIC = 1, /* fp32 arithmetic, any shape, either dtype                 */
   LASER_STA_MFMA = 2,    /* bf16 MFMA, many candidates per user                      */
   LASER_STA_STREAM = 3,  /* bf16, few candidates per user, HBM streaming             */
   LASER_STA_MFMA_CACHED = 4, /* LASER_STA_MFMA with H' stored cacheable instead of with the non-temporal hint: for a

@@ -189,6 +189,8 @@ laser_status fused_stream_launch(const FusedArgs& a);
 // Each launcher returns LASER_ERR_UNSUPPORTED (launching nothing) when the shape is outside its range.
 bool sta_generic_supports(const StaArgs& a);
 laser_status sta_generic_launch(const StaArgs& a);
+bool sta_f32_supports(const StaArgs& a);   // fp32 storage at the usual widths: the generic variant's matrix-core form
+laser_status sta_f32_launch(const StaArgs& a);
 bool sta_mfma_supports(const StaArgs& a);
 laser_status sta_mfma_launch(const StaArgs& a);
 bool sta_stream_supports(const StaArgs& a);

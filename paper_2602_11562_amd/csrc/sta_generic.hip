@@ -7,8 +7,8 @@
 // fp32 (coalesced global reads, shared by the four candidates). Per chunk a wave first gives
 // one lane per item the score dot product and the gate, then gives one lane per value column
 // the gated sum over the chunk. Sums run over items in ascending order in fp32, so results
-// are deterministic. This is the correctness path (fp32 tolerance) and the fallback for shapes
-// the MFMA and streaming kernels do not take.
+// are deterministic. This is the fallback for shapes the MFMA, fp32 matrix-core (sta_f32.hip) and
+// streaming kernels do not take.
 #include "laser_internal.h"
 
 namespace laser {
@@ -148,6 +148,7 @@ bool sta_generic_supports(const StaArgs& a) {
 
 laser_status sta_generic_launch(const StaArgs& a) {
   if (!sta_generic_supports(a)) return LASER_ERR_UNSUPPORTED;
+  if (sta_f32_supports(a)) return sta_f32_launch(a);
   const int TI = gen_pick_ti(a.d_q, a.d, a.heads);
   const size_t lds = gen_lds_bytes(TI, a.d_q, a.d, a.heads);
   const unsigned blocks = (unsigned)((long long)a.U * ((a.C + GEN_WAVES - 1) / GEN_WAVES) * a.S);
