@@ -198,6 +198,8 @@ laser_status sta_stream_launch(const StaArgs& a);
 
 bool gsta_generic_supports(const GstaArgs& a);
 laser_status gsta_generic_launch(const GstaArgs& a);
+bool gsta_rows_supports(const GstaArgs& a);   // d in {64, 128}: the generic variant's form with the matrices in registers
+laser_status gsta_rows_launch(const GstaArgs& a);
 bool gsta_tiled_supports(const GstaArgs& a);
 laser_status gsta_tiled_launch(const GstaArgs& a);
 bool gsta_split_supports(const GstaArgs& a);
