@@ -69,7 +69,7 @@ typedef enum {
 typedef enum {
   LASER_GSTA_AUTO = 0,
   LASER_GSTA_GENERIC = 1, /* fp32 arithmetic, any shape                               */
-  LASER_GSTA_TILED = 2,   /* bf16 storage, a tile of pairs per workgroup, MFMA, any M */
+  LASER_GSTA_TILED = 2,   /* bf16 storage, d in {64, 128}: 1 to 16 pairs per workgroup, MFMA, any M and S */
   LASER_GSTA_SPLIT = 3,   /* bf16 storage, M = 1: projection / streaming / output kernels; z_out is the scratch */
   LASER_GSTA_ONE = 4,     /* bf16 storage, M = 1: the same three steps in one launch, 32 pairs per workgroup */
   LASER_GSTA_VARIANT_ANY_INT = 0x7fffffff
@@ -471,7 +471,8 @@ laser_status laser_gsta_backward(const void* seg, const void* t0, const void* wq
                                  laser_dtype dt, void* dseg_out, float* dt0_out, float* dwq_out, float* dwk_out,
                                  float* dwv_out, void* work, size_t work_bytes, void* stream);
 
-/* Name of the STA / GSTA kernel AUTO would pick for a shape (static strings; host only, no GPU needed). */
+/* Name of the STA / GSTA kernel AUTO would pick for a shape in a batch that fills the machine (smaller ones may take
+ * another form; static strings; host only, no GPU needed). */
 const char* laser_sta_kernel_name(int C, int d_q, int d, int w, laser_dtype dt);
 const char* laser_gsta_kernel_name(int C, int S, int d, laser_dtype dt);               /* one layer (M = 1) */
 const char* laser_gsta_kernel_name_layers(int C, int S, int d, int M, laser_dtype dt);

@@ -3,7 +3,7 @@
 // their softmax weights while they are still on chip, so the transformed H' is neither written nor read back
 // (it is written as well when the caller wants it). One layer, bf16, d = 128, d_ff in {64, 128}.
 //
-// Three launches, the outer two shared with the split form of GSTA (gsta_tiled.hip):
+// Three launches, the outer two shared with the split form of GSTA (gsta_one.hip):
 //   gsta_r_kernel     r = (t0 W_q) W_k^T / sqrt(d)   tiles of 32 pairs, MFMA                       -> z rows
 //   ffn_pool_kernel   below: a wave walks pairs       H' rows -> s rows (on chip), z rows (r) -> z rows (p)
 //   gsta_out_kernel   z = t0 + p W_v                  tiles of 32 pairs, MFMA             z rows -> z rows

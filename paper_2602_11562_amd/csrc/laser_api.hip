@@ -105,10 +105,16 @@ static laser_sta_variant pick_sta(const StaArgs& a) {
   return LASER_STA_GENERIC;
 }
 
-static laser_gsta_variant pick_gsta(const GstaArgs& a) {
+// the form for a batch that fills the machine
+static laser_gsta_variant pick_gsta_full(const GstaArgs& a) {
   if (gsta_one_supports(a)) return LASER_GSTA_ONE;
   if (gsta_split_supports(a)) return LASER_GSTA_SPLIT;
   return gsta_tiled_supports(a) ? LASER_GSTA_TILED : LASER_GSTA_GENERIC;
+}
+
+static laser_gsta_variant pick_gsta(const GstaArgs& a) {
+  if (gsta_tiled_supports(a) && a.M == 1 && gsta_tile_preferred(a)) return LASER_GSTA_TILED;
+  return pick_gsta_full(a);
 }
 
 static laser_status run_sta(const StaArgs& a, laser_sta_variant variant) {
@@ -133,7 +139,7 @@ static laser_status run_gsta(const GstaArgs& a, laser_gsta_variant variant) {
   if (variant == LASER_GSTA_AUTO) variant = pick_gsta(a);
   switch (variant) {
     case LASER_GSTA_GENERIC: return gsta_generic_launch(a);
-    case LASER_GSTA_TILED: return gsta_tiled_launch(a);
+    case LASER_GSTA_TILED: return gsta_tiled_supports(a) ? gsta_tile_launch(a) : LASER_ERR_UNSUPPORTED;
     case LASER_GSTA_SPLIT: return gsta_split_launch(a);
     case LASER_GSTA_ONE: return gsta_one_launch(a);
     default: return LASER_ERR_UNSUPPORTED;
@@ -141,8 +147,8 @@ static laser_status run_gsta(const GstaArgs& a, laser_gsta_variant variant) {
 }
 
 // GSTA and the two other views of Sec. 3.4.4 from one pass over H' where the GSTA kernel writes them itself (the
-// one-kernel form, up to the number of recent rows it can stage, and the split form's streaming kernel); a second
-// launch over H' otherwise
+// one-kernel form, up to the number of recent rows it can stage, the split form's streaming kernel and the tiled form);
+// a second launch over H' otherwise
 static laser_status run_gsta_views(GstaArgs& ga, MultiresArgs& ma) {
   const laser_gsta_variant variant = pick_gsta(ga);
   if (variant == LASER_GSTA_ONE) {
@@ -157,11 +163,11 @@ static laser_status run_gsta_views(GstaArgs& ga, MultiresArgs& ma) {
     ma.pool_out = nullptr;
     return multires_launch(ma);
   }
-  if (variant == LASER_GSTA_SPLIT) {
+  if (variant == LASER_GSTA_SPLIT || variant == LASER_GSTA_TILED) {
     ga.pool_out = ma.pool_out;
     ga.recent_out = ma.recent_out;
     ga.r = ma.r;
-    return run_gsta(ga, LASER_GSTA_SPLIT);
+    return run_gsta(ga, variant);
   }
   const laser_status s = run_gsta(ga, variant);
   if (s != LASER_OK) return s;
@@ -753,7 +759,7 @@ const char* laser_gsta_kernel_name_layers(int C, int S, int d, int M, laser_dtyp
   GstaArgs a{};
   a.U = 1; a.C = C; a.L = S; a.w = 1; a.S = S; a.d = d; a.M = M; a.dt = dt;
   if (C <= 0 || S <= 0 || d <= 0 || M <= 0 || (dt != LASER_F32 && dt != LASER_BF16)) return "invalid";
-  switch (pick_gsta(a)) {
+  switch (pick_gsta_full(a)) {
     case LASER_GSTA_SPLIT: return "gsta_split_bf16";
     case LASER_GSTA_ONE: return "gsta_one_bf16";
     case LASER_GSTA_TILED: return "gsta_tiled_bf16";

@@ -41,7 +41,7 @@ struct GstaArgs {
   laser_dtype dt;
   float* z_out;
   hipStream_t stream;
-  // optional: the views of laser_multires_forward from the same pass over H' (one-kernel form only)
+  // optional, bf16: the views of laser_multires_forward from the same launch (one-kernel, split and tiled forms)
   void* pool_out = nullptr;
   void* recent_out = nullptr;
   int r = 0;
@@ -198,10 +198,11 @@ laser_status sta_stream_launch(const StaArgs& a);
 
 bool gsta_generic_supports(const GstaArgs& a);
 laser_status gsta_generic_launch(const GstaArgs& a);
-bool gsta_rows_supports(const GstaArgs& a);   // d in {64, 128}: the generic variant's form with the matrices in registers
-laser_status gsta_rows_launch(const GstaArgs& a);
-bool gsta_tiled_supports(const GstaArgs& a);
-laser_status gsta_tiled_launch(const GstaArgs& a);
+// d in {64, 128}: tiles of 1 to 16 pairs, any number of layers (the tiled variant; the generic one for fp32 storage)
+bool gsta_tile_supports(const GstaArgs& a);
+laser_status gsta_tile_launch(const GstaArgs& a);
+bool gsta_tile_preferred(const GstaArgs& a);   // one layer, bf16: a batch too small for the forms that fill the machine
+inline bool gsta_tiled_supports(const GstaArgs& a) { return a.dt == LASER_BF16 && gsta_tile_supports(a); }
 bool gsta_split_supports(const GstaArgs& a);
 laser_status gsta_split_launch(const GstaArgs& a);
 laser_status gsta_r_launch(const GstaArgs& a);     // first launch of the split form alone: r into the z rows

@@ -1,0 +1,73 @@
+"""GPU parity at the edges of the GSTA kernel with tiles of 1 to 16 pairs, against the fp64 checker. fp32 storage is held to 1e-5 and bf16 to 2e-2 per vector, as everywhere (TOL)."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+
+from parity_util import TOL, to_device, to_host_f64, vec_rel_err
+from test_sta_backward_gpu import _store
+
+pytestmark = pytest.mark.gpu
+
+laser = pytest.importorskip("paper_2602_11562_amd")
+
+# dtype, U, C, L, w, d, M: pairs per workgroup 1, 2, 4, 8, 16 and a last workgroup that is not full; blocks of H' that
+# stay in registers (four and eight rows a lane) and blocks that are read again in every layer
+GSTA_CASES = {
+    "one_pair_long": ("bf16", 1, 1, 700, 1, 128, 3),
+    "resident_f32": ("f32", 3, 5, 130, 9, 128, 2),
+    "streamed_f32": ("f32", 3, 3, 1000, 3, 64, 2),
+    "two_pairs_a_workgroup_f32": ("f32", 3, 343, 12, 5, 64, 2),
+    "four_pairs_a_workgroup_eight_rows": ("bf16", 3, 229, 60, 1, 128, 2),
+    "eight_pairs_a_workgroup_f32": ("f32", 3, 457, 30, 1, 128, 1),
+    "eight_pairs_a_workgroup_streamed": ("bf16", 3, 417, 180, 2, 128, 2),
+    "eight_pairs_a_workgroup_d64": ("bf16", 3, 1367, 40, 1, 64, 2),
+    "sixteen_pairs_a_workgroup": ("bf16", 3, 700, 32, 1, 128, 2),
+    "sixteen_pairs_a_workgroup_f32": ("f32", 3, 1400, 20, 1, 64, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(GSTA_CASES))
+def test_gsta_tiled(name):
+    import torch
+    dtype, U, C, L, w, d, M = GSTA_CASES[name]
+    S = -(-L // w)
+    rng = np.random.default_rng(6100 + sum(map(ord, name)))
+    lens = np.array(([L, max(1, L // 3), 0] * U)[:U], dtype=np.int32)
+    cnt = oracle.segment_counts(lens, L, w)
+    Hs, Hv = _store(rng.normal(size=(U, C, S, d)), dtype)
+    ts, tv = _store(rng.normal(size=(U, C, d)), dtype)
+    (wqs, wqv), (wks, wkv), (wvs, wvv) = (_store(rng.normal(size=(M, d, d)) / math.sqrt(d), dtype) for _ in range(3))
+    print(f"case {name}", flush=True)
+    for u, n in enumerate(lens):      # rows of segments without a valid item are never read
+        Hs[u, :, -(-int(n) // w):] = np.nan if dtype == "f32" else 0x7fc0
+    z = laser.laser_gsta_forward(to_device(Hs), to_device(ts), to_device(wqs), to_device(wks), to_device(wvs),
+                                 to_device(lens), L, w, variant=laser.GSTA_GENERIC if dtype == "f32" else laser.GSTA_TILED)
+    torch.cuda.synchronize()
+    pick = slice(None) if C <= 8 else [0, 1, 2, 3, 5, 8, C // 2, C - 2, C - 1]
+    ref = oracle.gsta_forward(Hv[:, pick], tv[:, pick], wqv, wkv, wvv, cnt)
+    assert vec_rel_err(to_host_f64(z)[:, pick], ref) <= TOL[dtype]
+    assert np.array_equal(to_host_f64(z)[lens == 0], tv[lens == 0])     # z = t0 exactly without a valid segment
+
+
+# pairs, S, d, r: the views from the tiled form (waves that share a pair, one and several pairs a wave, streamed rows) and,
+# from 8193 pairs with 33 rows on, from the split form; equal to the two entry points apart, bit for bit
+@pytest.mark.parametrize("P,S,d,r", [(3, 5, 128, 5), (300, 40, 128, 3), (1200, 9, 64, 1), (2500, 70, 128, 8),
+                                     (5000, 33, 64, 0), (8193, 33, 128, 2)])
+def test_views_of_every_form(P, S, d, r):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
+    seg, t0 = rnd(P, 1, S, d), rnd(P, 1, d)
+    W = [(rnd(1, d, d).float() / math.sqrt(d)).bfloat16() for _ in range(3)]
+    lens = torch.randint(0, S + 1, (P,), device="cuda", generator=gen, dtype=torch.int32)
+    lens[0] = 0
+    print(f"P {P} S {S} d {d} r {r}", flush=True)
+    z, pool, recent = laser.laser_gsta_forward_multires(seg, t0, *W, lens, S, 1, r)
+    z2 = laser.laser_gsta_forward(seg, t0, *W, lens, S, 1)
+    pool2, recent2 = laser.laser_multires_forward(seg, lens, S, 1, r)
+    torch.cuda.synchronize()
+    assert torch.equal(z, z2) and torch.equal(pool.view(torch.int16), pool2.view(torch.int16))
+    assert r == 0 or torch.equal(recent.view(torch.int16), recent2.view(torch.int16))
