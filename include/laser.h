@@ -457,7 +457,7 @@ laser_status laser_sta_backward_static(const void* q, const void* k, const void*
  *   dt0_out  [U,C,d]   fp32  d loss / d t0
  *   dwq_out, dwk_out, dwv_out [M,d,d] fp32, summed over all pairs in a fixed order
  * seg, t0, wq, wk, wv, lens and the sizes as for laser_gsta_forward. Arithmetic in fp32 from the stored inputs; dseg_out
- * is rounded once to dt. Generic kernels (one workgroup per pair, H' and, with several layers, its gradient in LDS): d <= 256,
+ * is rounded once to dt. Limits: d <= 256,
  * M <= 8 and S d sizeof(dt) + ((M > 1 ? S d : 0) + (M + 7) d + 2 S + 4) * 4 bytes <= 150 KB; other shapes return LASER_ERR_UNSUPPORTED. work is caller-owned scratch
  * of at least laser_gsta_backward_work_bytes(U, C, d, M) bytes (six d-vectors per pair and layer, whose outer products
  * are the weight gradients, and partial sums of those); the library allocates nothing.

@@ -5,8 +5,8 @@
 // The layers' inputs t_l are kept from a first forward sweep; the backward sweep replays a layer's q', r, a, p and
 // applies the chain rule. All three weight gradients of a pair and layer are outer products of d-vectors,
 //   dW_v = p (x) do,   dW_k = dr (x) q',   dW_q = t_l (x) dq',
-// so the pair kernel only writes those six vectors to the caller's scratch, and two small kernels sum the outer
-// products over all pairs in a fixed order (deterministic).
+// so the pair kernel only writes those six vectors to the caller's scratch, and gsta_bwd_w_kernel sums the outer
+// products over all pairs in a fixed order (deterministic). d in {64, 128} runs on gsta_backward_tile.hip instead.
 #include "laser_internal.h"
 
 namespace laser {
@@ -223,79 +223,81 @@ __global__ __launch_bounds__(GB_THREADS) void gsta_bwd_kernel(const T* __restric
   for (int e = nv * d + tid; e < S * d; e += GB_THREADS) store_from_f32(dH, (size_t)e, 0.0f);
 }
 
-// dW[l][x][y] = sum over pairs of A[pair][l][x] * B[pair][l][y]. Two steps, both in a fixed order: the pairs are cut
-// into chunks, a workgroup sums one chunk for a 32 x 32 tile of one matrix (pairs ascending), and a second kernel adds
-// the chunks' partial matrices in ascending order.
-__global__ __launch_bounds__(256) void gsta_bwd_w_partial_kernel(const float* __restrict__ pv, int P, int M, int d,
-                                                                 int chunks, float* __restrict__ part) {
-  // a 32 x 32 tile of one matrix per workgroup, 2 x 2 entries per thread; the two vectors of 64 pairs at a time are
-  // staged in LDS (32 consecutive floats of each), so every global load is a 32-byte piece and is used 32 times
-  constexpr int TP = 64, TW = 32;
-  __shared__ float As[TP][TW + 1], Bs[TP][TW + 1];
-  const int tiles = (d + TW - 1) / TW;
+// dW[l][x][y] = sum over pairs of A[pair][l][x] * B[pair][l][y]: a contraction over the pairs, on the fp32 matrix
+// instructions. A workgroup owns a 16 x 16 tile of one matrix; its sixteen waves take every sixteenth run of four pairs (the
+// four k-slots of an MFMA, operands straight from the scratch in 64-byte runs, eight steps in flight) and add up in LDS in a
+// fixed order. With few tiles (d = 64, one or two layers) the pairs are cut into eight chunks as well, one per XCD (the
+// workgroup number modulo eight), whose matrices a second launch adds: the launch is bound by what the eight L2s fetch, and
+// so each fetches an eighth of the vectors instead of all. 4096 pairs, d = 64: 10.3 us for the two launches, 15 us without
+// chunks; 2048 pairs, d = 128: 9.8 us without, 12.9 us with them. (The form before, tiles of 32 x 32 on the vector ALUs in up
+// to 32 chunks: 25 and 30 us.)
+constexpr int GB_CHUNKS = 8;
+__global__ __launch_bounds__(1024) void gsta_bwd_w_kernel(const float* __restrict__ pv, int P, int M, int d, int chunks,
+                                                          float* __restrict__ part, float* __restrict__ dwq,
+                                                          float* __restrict__ dwk, float* __restrict__ dwv) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr int NW = 16, AHEAD = 8;
+  __shared__ f32x4 red[NW][64];
+  const int tiles = (d + 15) / 16;
   int bid = blockIdx.x;
+  const int chunk = bid % chunks;
+  bid /= chunks;
   const int ty = bid % tiles;
   bid /= tiles;
   const int tx = bid % tiles;
   bid /= tiles;
-  const int which = bid % 3;     // 0: dW_v (p, do), 1: dW_k (dr, q'), 2: dW_q (t_l, dq')
-  bid /= 3;
-  const int l = bid % M, chunk = bid / M;
-  const int tid = threadIdx.x, r = tid / 16, c = tid % 16;
-  const int per = (P + chunks - 1) / chunks;
-  const int p0 = chunk * per, p1 = (p0 + per) < P ? (p0 + per) : P;
-  const float* a = pv + ((size_t)l * 6 + 2 * which) * d + tx * TW;
-  const float* b = pv + ((size_t)l * 6 + 2 * which + 1) * d + ty * TW;
+  const int which = bid % 3, l = bid / 3;   // 0: dW_v (p, do), 1: dW_k (dr, q'), 2: dW_q (t_l, dq')
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int x = tx * 16 + l16 < d ? tx * 16 + l16 : d - 1, y = ty * 16 + l16 < d ? ty * 16 + l16 : d - 1;
+  const float* a = pv + ((size_t)l * 6 + 2 * which) * d + x;
+  const float* b = pv + ((size_t)l * 6 + 2 * which + 1) * d + y;
   const size_t stride = (size_t)M * 6 * d;
-  const int spr = tid / 4, sc = (tid % 4) * 8;   // staging: pair row and first of this thread's eight columns
-  float acc[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
-  for (int pb = p0; pb < p1; pb += TP) {
-    const int pr = pb + spr;
+  const int per = ((P + chunks - 1) / chunks + 3) / 4 * 4;
+  const int beg = chunk * per, end = beg + per < P ? beg + per : P;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int p0 = beg + wave * 4; p0 < end; p0 += 4 * NW * AHEAD) {
+    float av[AHEAD], bv[AHEAD];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool oka = pr < p1 && tx * TW + sc + e < d, okb = pr < p1 && ty * TW + sc + e < d;
-      As[spr][sc + e] = oka ? a[(size_t)pr * stride + sc + e] : 0.0f;
-      Bs[spr][sc + e] = okb ? b[(size_t)pr * stride + sc + e] : 0.0f;
+    for (int s = 0; s < AHEAD; ++s) {
+      const int p = p0 + s * 4 * NW + g;
+      const size_t at = (size_t)(p < end ? p : end - 1) * stride;
+      av[s] = a[at];
+      bv[s] = b[at];
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int pp = 0; pp < TP; ++pp) {   // pairs in ascending order (rows past the chunk hold zeros)
-      const float a0 = As[pp][2 * r], a1 = As[pp][2 * r + 1], b0 = Bs[pp][2 * c], b1 = Bs[pp][2 * c + 1];
-      acc[0][0] = fmaf(a0, b0, acc[0][0]);
-      acc[0][1] = fmaf(a0, b1, acc[0][1]);
-      acc[1][0] = fmaf(a1, b0, acc[1][0]);
-      acc[1][1] = fmaf(a1, b1, acc[1][1]);
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) {        // pairs past the end of the chunk add nothing
+      const bool ok = p0 + s * 4 * NW + g < end;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? av[s] : 0.0f, ok ? bv[s] : 0.0f, acc, 0, 0, 0);
     }
-    __syncthreads();
   }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (tid >= 256) return;
+  const int ln = tid & 63, r = tid >> 6;     // register r of lane ln: row 4 (ln / 16) + r, column ln % 16
+  float sum = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int jx = 0; jx < 2; ++jx) {
-      const int x = tx * TW + 2 * r + i, y = ty * TW + 2 * c + jx;
-      if (x < d && y < d) part[((((size_t)chunk * M + l) * 3 + which) * d + x) * d + y] = acc[i][jx];
-    }
+  for (int o = 0; o < NW; ++o) sum += red[o][ln][r];
+  const int xo = tx * 16 + 4 * (ln >> 4) + r, yo = ty * 16 + (ln & 15);
+  if (xo >= d || yo >= d) return;
+  if (chunks > 1) {
+    part[((((size_t)chunk * 3 + which) * M + l) * d + xo) * d + yo] = sum;
+  } else {
+    float* out = which == 0 ? dwv : (which == 1 ? dwk : dwq);
+    out[((size_t)l * d + xo) * d + yo] = sum;
+  }
 }
 
-__global__ __launch_bounds__(256) void gsta_bwd_w_reduce_kernel(const float* __restrict__ part, int M, int d, int chunks,
+__global__ __launch_bounds__(256) void gsta_bwd_w_reduce_kernel(const float* __restrict__ part, long long per_matrix,
                                                                 float* __restrict__ dwq, float* __restrict__ dwk,
                                                                 float* __restrict__ dwv) {
-  const long long per_l = (long long)3 * d * d, total = (long long)M * per_l;
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;     // (l, which, x, y)
-  if (e >= total) return;
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;     // (which, l, x, y)
+  if (e >= 3 * per_matrix) return;
   float acc = 0.0f;
-  for (int c = 0; c < chunks; ++c) acc += part[(size_t)c * total + e];
-  const int l = (int)(e / per_l);
-  const long long r = e - (long long)l * per_l;
-  const int which = (int)(r / ((long long)d * d));
-  const long long xy = r - (long long)which * d * d;
-  float* out = which == 0 ? dwv : (which == 1 ? dwk : dwq);
-  out[(size_t)l * d * d + xy] = acc;
-}
-
-static int gsta_bwd_chunks(int P) {
-  int c = (P + 63) / 64;
-  return c < 1 ? 1 : (c > 32 ? 32 : c);
+#pragma unroll
+  for (int c = 0; c < GB_CHUNKS; ++c) acc += part[(size_t)c * 3 * per_matrix + e];
+  float* out = e < per_matrix ? dwv : (e < 2 * per_matrix ? dwk : dwq);
+  out[e % per_matrix] = acc;
 }
 
 static size_t gsta_bwd_lds(const GstaBwdArgs& a) {
@@ -309,17 +311,19 @@ bool gsta_backward_supports(const GstaBwdArgs& a) {
   return a.d <= GB_MAXD && a.M <= GB_MAXM && gsta_bwd_lds(a) <= 150 * 1024;
 }
 
-// per-pair vectors [P][M][6][d], then the chunks' partial weight gradients [chunks][M][3][d][d]
+// per-pair vectors [P][M][6][d], then the chunks' partial weight gradients [chunks][3][M][d][d]
 size_t gsta_backward_work_bytes(int U, int C, int d, int M) {
-  const size_t P = (size_t)U * C;
-  return (P * M * 6 * d + (size_t)gsta_bwd_chunks((int)P) * M * 3 * d * d) * sizeof(float);
+  return ((size_t)U * C * M * 6 * d + (size_t)GB_CHUNKS * M * 3 * d * d) * sizeof(float);
 }
 
 laser_status gsta_backward_launch(const GstaBwdArgs& a) {
   if (!gsta_backward_supports(a)) return LASER_ERR_UNSUPPORTED;
   const int P = a.U * a.C;
   const size_t lds = gsta_bwd_lds(a);
-  if (a.dt == LASER_BF16) {
+  if (gsta_bwd_tile_supports(a)) {
+    const laser_status st = gsta_bwd_tile_launch(a);
+    if (st != LASER_OK) return st;
+  } else if (a.dt == LASER_BF16) {
     auto kern = gsta_bwd_kernel<unsigned short>;
     if (lds > 48 * 1024 &&
         hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -338,14 +342,16 @@ laser_status gsta_backward_launch(const GstaBwdArgs& a) {
                        a.L, a.d, a.w, a.S, a.M, (float*)a.dseg, a.dt0, a.work);
   }
   if (launch_status() != LASER_OK) return LASER_ERR_LAUNCH;
-  const int tiles = (a.d + 31) / 32, chunks = gsta_bwd_chunks(P);
+  const int tiles = (a.d + 15) / 16, wgs = a.M * 3 * tiles * tiles;
+  const int chunks = wgs < 128 && P >= 256 ? GB_CHUNKS : 1;
   float* part = a.work + (size_t)P * a.M * 6 * a.d;
-  hipLaunchKernelGGL(gsta_bwd_w_partial_kernel, dim3((unsigned)(chunks * a.M * 3 * tiles * tiles)), dim3(256), 0,
-                     a.stream, a.work, P, a.M, a.d, chunks, part);
-  if (launch_status() != LASER_OK) return LASER_ERR_LAUNCH;
-  const long long total = (long long)a.M * 3 * a.d * a.d;
-  hipLaunchKernelGGL(gsta_bwd_w_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, a.stream, part, a.M,
-                     a.d, chunks, a.dwq, a.dwk, a.dwv);
+  hipLaunchKernelGGL(gsta_bwd_w_kernel, dim3((unsigned)(chunks * wgs)), dim3(1024), 0, a.stream, a.work, P, a.M, a.d, chunks,
+                     part, a.dwq, a.dwk, a.dwv);
+  const laser_status st = launch_status();
+  if (chunks == 1 || st != LASER_OK) return st;
+  const long long per_matrix = (long long)a.M * a.d * a.d;
+  hipLaunchKernelGGL(gsta_bwd_w_reduce_kernel, dim3((unsigned)((3 * per_matrix + 255) / 256)), dim3(256), 0, a.stream, part,
+                     per_matrix, a.dwq, a.dwk, a.dwv);
   return launch_status();
 }
 

@@ -160,6 +160,8 @@ struct GstaBwdArgs {       // gradients of GSTA from dz = d loss / d z [U,C,d] (
 bool gsta_backward_supports(const GstaBwdArgs& a);
 size_t gsta_backward_work_bytes(int U, int C, int d, int M);
 laser_status gsta_backward_launch(const GstaBwdArgs& a);
+bool gsta_bwd_tile_supports(const GstaBwdArgs& a);   // d in {64, 128}: the pair kernel in tiles of 1 to 16 pairs
+laser_status gsta_bwd_tile_launch(const GstaBwdArgs& a);
 
 struct FusedArgs {         // the whole path with one GSTA layer and H' never stored: z [U,C,d] fp32 from q, k, v, t0, weights
   const void* q;
