@@ -620,6 +620,7 @@ laser_status laser_sta_folded_forward(const void* t, const void* h, const void* 
   s = run_project(qa, LASER_PROJECT_AUTO);
   if (s != LASER_OK) return s;
   sa.reread = true;
+  if (sta_few_folded_supports(sa, pa)) return sta_few_folded_launch(sa, pa);
   s = run_sta(sa, LASER_STA_AUTO);
   if (s != LASER_OK) return s;
   return run_project_heads(pa, LASER_PROJECT_AUTO);

@@ -197,6 +197,10 @@ bool sta_mfma_supports(const StaArgs& a);
 laser_status sta_mfma_launch(const StaArgs& a);
 bool sta_stream_supports(const StaArgs& a);
 laser_status sta_stream_launch(const StaArgs& a);
+bool sta_few_supports(const StaArgs& a);   // at most eight query rows per user: the stream variant's matrix-core form
+laser_status sta_few_launch(const StaArgs& a);
+bool sta_few_folded_supports(const StaArgs& a, const ProjHeadsArgs& p);   // the same over raw items, W_v in the launch
+laser_status sta_few_folded_launch(const StaArgs& a, const ProjHeadsArgs& p);
 
 bool gsta_generic_supports(const GstaArgs& a);
 laser_status gsta_generic_launch(const GstaArgs& a);

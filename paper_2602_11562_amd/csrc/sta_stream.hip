@@ -1,4 +1,5 @@
-// STA for few candidates per user (C <= 8): an HBM streaming kernel on the vector ALUs.
+// STA for one or two candidates per user (up to eight with two heads, with softmax and in the fused form): an HBM
+// streaming kernel on the vector ALUs. More candidates: sta_few.hip.
 //
 // With one or a few candidates the STA equation of Sec. 3.4.2 does about one flop per byte of history read, so
 // the matrix cores have nothing to amortise and the only thing that matters is that K and V are read once, in
@@ -602,28 +603,28 @@ static void launch_c(const StaArgs& a, float nsl) {
   int classes = (a.lens != nullptr && blocks >= 4096 && (unsigned long long)blocks * 4 <= 0x7fffffffULL) ? 4 : 1;
   const int cls_forced = tuning_int("LASER_STREAM_CLASSES", 0);   // tuning builds only
   if (cls_forced >= 1 && cls_forced <= 8 && (unsigned long long)blocks * cls_forced <= 0x7fffffffULL) classes = cls_forced;
+#define LASER_STREAM_SHORT(CM, SM)                                                                                   \
+  hipLaunchKernelGGL((sta_stream_short_kernel<DQ, D, CM, HEADS, SM>), dim3(blocks), dim3(256), 0, a.stream,        \
+                     (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,   \
+                     a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, nsl, (unsigned short*)a.seg_out, a.seg_cnt,   \
+                     (a.k == a.v && DQ == D) ? 1 : 0)
 #define LASER_STREAM_LAUNCH(CM)                                                                                      \
   do {                                                                                                               \
-    if (short_seg && a.softmax)                                                                                      \
-      hipLaunchKernelGGL((sta_stream_short_kernel<DQ, D, CM, HEADS, true>), dim3(blocks), dim3(256), 0, a.stream,  \
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,       \
-                         a.lens, a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, nsl, (unsigned short*)a.seg_out, a.seg_cnt,     \
-                         (a.k == a.v && DQ == D) ? 1 : 0);                                                           \
-    else if (short_seg)                                                                                              \
-      hipLaunchKernelGGL((sta_stream_short_kernel<DQ, D, CM, HEADS, false>), dim3(blocks), dim3(256), 0, a.stream, \
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,       \
-                         a.lens, a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, nsl, (unsigned short*)a.seg_out, a.seg_cnt,     \
-                         (a.k == a.v && DQ == D) ? 1 : 0);                                                           \
-    else                                                                                                             \
-      hipLaunchKernelGGL((sta_stream_kernel<DQ, D, CM, HEADS>), dim3(blocks * classes), dim3(256), 0, a.stream,    \
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,       \
-                         a.lens, a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,               \
-                         (unsigned short*)a.seg_out, a.seg_cnt, StreamFusedTail{});                                  \
+    if (short_seg && a.softmax) LASER_STREAM_SHORT(CM, true);                                                        \
+    else if constexpr (HEADS == 2 || CM <= 2) {   /* (one head, more rows: sta_few_kernel) */                        \
+      if (short_seg) LASER_STREAM_SHORT(CM, false);                                                                  \
+      else                                                                                                           \
+        hipLaunchKernelGGL((sta_stream_kernel<DQ, D, CM, HEADS>), dim3(blocks * classes), dim3(256), 0, a.stream,  \
+                           (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,     \
+                           a.lens, a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,             \
+                           (unsigned short*)a.seg_out, a.seg_cnt, StreamFusedTail{});                                \
+    }                                                                                                                \
   } while (0)
   if (a.C <= 1) LASER_STREAM_LAUNCH(1);
   else if (a.C <= 2) LASER_STREAM_LAUNCH(2);
   else if (a.C <= 4) LASER_STREAM_LAUNCH(4);
   else LASER_STREAM_LAUNCH(8);
+#undef LASER_STREAM_SHORT
 #undef LASER_STREAM_LAUNCH
 }
 
@@ -672,6 +673,7 @@ laser_status fused_stream_launch(const FusedArgs& a) {
 
 laser_status sta_stream_launch(const StaArgs& a) {
   if (!sta_stream_supports(a)) return LASER_ERR_UNSUPPORTED;
+  if (sta_few_supports(a)) return sta_few_launch(a);
   const float nsl = -1.4426950408889634f / a.gamma;
   const int key = a.d_q * 1000 + a.d;
 #define LASER_STREAM_SHAPE(DQ_, D_)                    \
