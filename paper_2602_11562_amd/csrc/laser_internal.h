@@ -242,6 +242,14 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float x) {
   return __builtin_bit_cast(unsigned short, h);
 }
 
+// 16 bytes of an input read once: NT with the non-temporal hint
+typedef unsigned int stream16 __attribute__((ext_vector_type(4)));
+template <bool NT>
+__device__ __forceinline__ stream16 load_stream16(const void* p) {
+  if (NT) return __builtin_nontemporal_load(reinterpret_cast<const stream16*>(p));
+  return *reinterpret_cast<const stream16*>(p);
+}
+
 template <typename T>
 __device__ __forceinline__ float load_as_f32(const T* p, size_t i);
 template <>
@@ -258,6 +266,22 @@ __device__ __forceinline__ void store_from_f32<float>(float* p, size_t i, float 
 template <>
 __device__ __forceinline__ void store_from_f32<unsigned short>(unsigned short* p, size_t i, float x) {
   p[i] = f32_to_bf16_bits(x);
+}
+
+// Histories of more valid items than the last-level cache (256 MB) can hold for whoever reads them next are read with the
+// non-temporal hint, 10 to 15 % faster (a plain sweep of 512 MB by small workgroups: 6.2 -> 7.0 TB/s; STA over 4096 x 4096
+// items of 256 bytes, 1 GB of them valid: 185 -> 159 us; the folded form of 2048 users: 119 -> 108 us); smaller ones are left
+// in the cache, where the next pass finds them (82 MB read again: 12.5 us plain, 13.7 with the hint).
+constexpr float STREAM_BYTES = 288.0e6f;
+__device__ __forceinline__ int valid_len(const int32_t* lens, int u, int L);
+__device__ __forceinline__ float wave_sum_rows(float x);
+// The decision of a wave that lives long enough to take the mean length of 64 users first
+__device__ __forceinline__ bool past_cache(const int32_t* lens, int U, int L, int item_bytes, int lane) {
+  const float all = (float)U * (float)item_bytes;
+  if (all * (float)L < STREAM_BYTES) return false;
+  if (lens == nullptr) return true;
+  const float n = (float)valid_len(lens, (int)((long long)lane * U >> 6), L);
+  return wave_sum_rows(n) * (1.0f / 64.0f) * all >= STREAM_BYTES;
 }
 
 // Valid length of user u, clamped to [0, L]; lens == nullptr means full length.

@@ -180,8 +180,8 @@ __device__ __forceinline__ void unpack8b(const u32x4b& r, float (&x)[8]) {
 }
 
 // GB16: dk and dv are written in bf16 (the storage type of k and v: half the bytes of the two largest outputs) instead
-// of fp32; the sums are fp32 either way and rounded once.
-template <int DQ, int D, int CMAX, bool GB16>
+// of fp32; the sums are fp32 either way and rounded once. NT: items and gradients with the non-temporal hint.
+template <int DQ, int D, int CMAX, bool GB16, bool NT>
 __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short* __restrict__ q,
                                                            const unsigned short* __restrict__ k,
                                                            const unsigned short* __restrict__ v,
@@ -222,17 +222,21 @@ __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short*
   const unsigned short* vU = v + (size_t)u * L * D;
   G* dkU = static_cast<G*>(dk) + (size_t)u * L * DQ;
   G* dvU = static_cast<G*>(dv) + (size_t)u * L * D;
-  auto store8 = [](G* dst, const float (&x)[8]) {   // eight consecutive gradient values: 16 or 32 bytes
+  auto put = [](auto* dst, const auto& x) {
+    if constexpr (NT) __builtin_nontemporal_store(x, dst);
+    else *dst = x;
+  };
+  auto store8 = [&](G* dst, const float (&x)[8]) {   // eight consecutive gradient values: 16 or 32 bytes
     if constexpr (GB16) {
       u32x4b o;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         o[e] = (unsigned)f32_to_bf16_bits(x[2 * e]) | ((unsigned)f32_to_bf16_bits(x[2 * e + 1]) << 16);
-      *reinterpret_cast<u32x4b*>(dst) = o;
+      put(reinterpret_cast<u32x4b*>(dst), o);
     } else {
       f32x4b* d4 = reinterpret_cast<f32x4b*>(dst);
-      d4[0] = f32x4b{x[0], x[1], x[2], x[3]};
-      d4[1] = f32x4b{x[4], x[5], x[6], x[7]};
+      put(d4, f32x4b{x[0], x[1], x[2], x[3]});
+      put(d4 + 1, f32x4b{x[4], x[5], x[6], x[7]});
     }
   };
 
@@ -266,13 +270,13 @@ __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short*
         for (int kl = 0; kl < NKL; ++kl) {
           int row = base + kl * RQ + rq;
           row = row < hi ? row : hi - 1;
-          kn[kl] = *reinterpret_cast<const u32x4b*>(kU + (size_t)row * DQ + cq * 8);
+          kn[kl] = load_stream16<NT>(kU + (size_t)row * DQ + cq * 8);
         }
 #pragma unroll
         for (int vl = 0; vl < NVL; ++vl) {
           int row = base + vl * RV + rv;
           row = row < hi ? row : hi - 1;
-          vn[vl] = *reinterpret_cast<const u32x4b*>(vU + (size_t)row * D + cv * 8);
+          vn[vl] = load_stream16<NT>(vU + (size_t)row * D + cv * 8);
         }
       };
       load_chunk(lo);
@@ -396,9 +400,11 @@ static void sta_bwd_shape(int U, int S, int w, int* spg, int* groups) {
 
 static bool sta_bwd_wide_supports(const StaBwdArgs& a);
 
-// length classes: worth their empty workgroups once the launch is several rounds of workgroups and lengths differ
+// length classes: worth their empty workgroups once the launch is several rounds of workgroups and lengths differ, but not
+// for short segments, whose runs are short whatever the history: in plain order the workgroups in flight sweep memory front
+// to back (2048 users x 100 segments of 10 items, lengths 200..1000: 240 us with four classes, 211 with one)
 static int sta_bwd_classes(const StaBwdArgs& a, unsigned blocks) {
-  int classes = (a.lens != nullptr && blocks >= 4096 && (unsigned long long)blocks * 4 <= 0x7fffffffULL) ? 4 : 1;
+  int classes = (a.lens != nullptr && a.w > 32 && blocks >= 4096 && (unsigned long long)blocks * 4 <= 0x7fffffffULL) ? 4 : 1;
   const int cls_forced = tuning_int("LASER_STREAM_CLASSES", 0);   // tuning builds only, shared with the forward kernel
   if (cls_forced >= 1 && cls_forced <= 8 && (unsigned long long)blocks * cls_forced <= 0x7fffffffULL) classes = cls_forced;
   return classes;
@@ -462,23 +468,26 @@ static void sta_bwd_wide_launch(const StaBwdArgs& a, unsigned blocks, int spg, i
   const float inv_gamma = 1.0f / a.gamma;
   const float nsl = -1.4426950408889634f * inv_gamma;
   const int classes = sta_bwd_classes(a, blocks);
+  // Histories and gradients that together are more than the last-level cache (256 MB) holds, with the non-temporal hint:
+  // 2048 users x 1000 items of 320 bytes (1.05 GB) 211 -> 196 us; 256 such users (131 MB) 28 -> 34 us
+  const bool nt = (double)a.U * a.L * (DQ + D) * (a.grads_bf16 ? 4 : 6) >= 600.0e6;
+#define LASER_BWD_WIDE_AS(CM, GB, NT)                                                                                \
+  hipLaunchKernelGGL((sta_bwd_wide_kernel<DQ, D, CM, GB, NT>), dim3(blocks * classes), dim3(256), 0, a.stream,      \
+                     (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,            \
+                     (const unsigned short*)a.dhp, a.lens, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,      \
+                     inv_gamma, a.dk, a.dv, a.work)
 #define LASER_BWD_WIDE(CM)                                                                                           \
   do {                                                                                                               \
-    if (a.grads_bf16)                                                                                                \
-      hipLaunchKernelGGL((sta_bwd_wide_kernel<DQ, D, CM, true>), dim3(blocks * classes), dim3(256), 0, a.stream,    \
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,        \
-                         (const unsigned short*)a.dhp, a.lens, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,  \
-                         inv_gamma, a.dk, a.dv, a.work);                                                             \
-    else                                                                                                             \
-      hipLaunchKernelGGL((sta_bwd_wide_kernel<DQ, D, CM, false>), dim3(blocks * classes), dim3(256), 0, a.stream,   \
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,        \
-                         (const unsigned short*)a.dhp, a.lens, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,  \
-                         inv_gamma, a.dk, a.dv, a.work);                                                             \
+    if (a.grads_bf16 && nt) LASER_BWD_WIDE_AS(CM, true, true);                                                       \
+    else if (a.grads_bf16) LASER_BWD_WIDE_AS(CM, true, false);                                                       \
+    else if (nt) LASER_BWD_WIDE_AS(CM, false, true);                                                                 \
+    else LASER_BWD_WIDE_AS(CM, false, false);                                                                        \
   } while (0)
   if (a.C <= 1) LASER_BWD_WIDE(1);
   else if (a.C <= 2) LASER_BWD_WIDE(2);
   else LASER_BWD_WIDE(4);
 #undef LASER_BWD_WIDE
+#undef LASER_BWD_WIDE_AS
 }
 
 laser_status sta_backward_launch(const StaBwdArgs& a) {

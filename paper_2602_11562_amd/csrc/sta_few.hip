@@ -161,9 +161,14 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
   for (int f = 0; f < Sh::KF; ++f) kfo[f] = (krow_of(f) * DQ + ((lane % KCH) ^ few_swz<KCH>(krow_of(f))) * 8) * 2;
 #pragma unroll
   for (int f = 0; f < Sh::VF; ++f) vfo[f] = (vrow_of(f) * D + ((lane % VCH) ^ few_swz<VCH>(vrow_of(f))) * 8) * 2;
-  auto dma = [&](unsigned dst, unsigned off, const void* src) {   // 16 bytes per lane to LDS dst + 16 * lane
+  // 16 bytes per lane to LDS dst + 16 * lane; items of a large history with the non-temporal hint
+  auto dma = [&](unsigned dst, unsigned off, const void* src) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n" ::"s"(dst), "v"(off), "s"(src) : "memory");
   };
+  auto dma_nt = [&](unsigned dst, unsigned off, const void* src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n" ::"s"(dst), "v"(off), "s"(src) : "memory");
+  };
+  const bool nt = __builtin_amdgcn_readfirstlane(past_cache(lens, (int)(units / runs), L, FOLD ? D * 2 : (DQ + D) * 2, lane));
   // requests tile t of a unit into ring buffer b (with the unit's queries when it is the first) and returns how many
   // fetches that were. Rows past the end repeat the last valid one (their gates are zero).
   auto fetch = [&](const Unit& x, int t, int b) {
@@ -180,7 +185,12 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
     }
     const unsigned short* kt = x.k + (size_t)t0 * DQ;
     const unsigned short* vt = x.v + (size_t)t0 * D;
-    if (last >= FEW_TI - 1) {
+    if (last >= FEW_TI - 1 && nt) {
+#pragma unroll
+      for (int f = 0; f < Sh::KF; ++f) dma_nt(base + f * 1024, kfo[f], kt);
+#pragma unroll
+      for (int f = 0; f < Sh::VF; ++f) dma_nt(base + Sh::KB + f * 1024, vfo[f], vt);
+    } else if (last >= FEW_TI - 1) {
 #pragma unroll
       for (int f = 0; f < Sh::KF; ++f) dma(base + f * 1024, kfo[f], kt);
 #pragma unroll

@@ -42,7 +42,8 @@ struct StreamFusedTail {
   float* z;                   // [P, D]
 };
 
-template <int DQ, int D, int CMAX, int HEADS, bool FUSED = false>
+// NT: keys and values with the non-temporal hint (stream_past_cache).
+template <int DQ, int D, int CMAX, int HEADS, bool NT, bool FUSED = false>
 __global__ __launch_bounds__(256) void sta_stream_kernel(const unsigned short* __restrict__ q,
                                                          const unsigned short* __restrict__ k,
                                                          const unsigned short* __restrict__ v,
@@ -151,13 +152,13 @@ __global__ __launch_bounds__(256) void sta_stream_kernel(const unsigned short* _
       for (int kl = 0; kl < NKL; ++kl) {
         int row = j0 + kl * RQ + rq;
         row = row < hi ? row : hi - 1;
-        r.k[uu][kl] = *reinterpret_cast<const u32x4*>(kU + (size_t)row * DQ + cq * 8);
+        r.k[uu][kl] = load_stream16<NT>(kU + (size_t)row * DQ + cq * 8);
       }
 #pragma unroll
       for (int vl = 0; vl < NVL; ++vl) {
         int row = j0 + vl * RV + rv;
         row = row < hi ? row : hi - 1;
-        r.v[uu][vl] = *reinterpret_cast<const u32x4*>(vU + (size_t)row * D + cv * 8);
+        r.v[uu][vl] = load_stream16<NT>(vU + (size_t)row * D + cv * 8);
       }
     }
   };
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(256) void sta_stream_kernel(const unsigned short* _
 // sigmoid gates). Every value lane keeps a running maximum m and denominator l of its row group's scores (base 2)
 // beside its sums, rescaling them when the maximum moves; at the end of a segment the row groups agree on the
 // largest maximum, rescale once more, and the reduced sums are divided by the reduced denominator.
-template <int DQ, int D, int CMAX, int HEADS, bool SOFTMAX>
+template <int DQ, int D, int CMAX, int HEADS, bool SOFTMAX, bool NT>
 __global__ __launch_bounds__(256) void sta_stream_short_kernel(const unsigned short* __restrict__ q,
                                                                const unsigned short* __restrict__ k,
                                                                const unsigned short* __restrict__ v,
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(256) void sta_stream_short_kernel(const unsigned sh
     for (int kl = 0; kl < NKL; ++kl) {
       int row = base + kl * RQ + rq;
       row = row < hi ? row : hi - 1;
-      r.k[kl] = *reinterpret_cast<const u32x4*>(kU + (size_t)row * DQ + cq * 8);
+      r.k[kl] = load_stream16<NT>(kU + (size_t)row * DQ + cq * 8);
     }
     if (alias) {
 #pragma unroll
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(256) void sta_stream_short_kernel(const unsigned sh
     for (int vl = 0; vl < NVL; ++vl) {
       int row = base + vl * RV + rv;
       row = row < hi ? row : hi - 1;
-      r.v[vl] = *reinterpret_cast<const u32x4*>(vU + (size_t)row * D + cv * 8);
+      r.v[vl] = load_stream16<NT>(vU + (size_t)row * D + cv * 8);
     }
   };
   float acc[CMAX][8];
@@ -579,6 +580,14 @@ bool sta_stream_supports(const StaArgs& a) {
   return (long long)a.U * a.S <= 0x7fffffffLL;   // an upper bound of the grid size
 }
 
+// Whether the histories are certainly more than the last-level cache holds for whoever reads them next. The lengths are on
+// the device: lengths spread evenly over the logarithm of [L / 64, L] fill a quarter of the arrays, hence four times the size
+// from which the hint pays on full ones (STREAM_BYTES, with its measurements).
+static bool stream_past_cache(const int32_t* lens, int U, int L, int d_q, int d) {
+  const double bytes = (double)U * L * (d_q + d) * 2.0;
+  return bytes >= (lens ? 4.0 : 1.0) * STREAM_BYTES;
+}
+
 template <int DQ, int D, int HEADS>
 static void launch_c(const StaArgs& a, float nsl) {
   // runs of segments per user: the whole user per workgroup once that still gives every compute unit eight
@@ -603,21 +612,25 @@ static void launch_c(const StaArgs& a, float nsl) {
   int classes = (a.lens != nullptr && blocks >= 4096 && (unsigned long long)blocks * 4 <= 0x7fffffffULL) ? 4 : 1;
   const int cls_forced = tuning_int("LASER_STREAM_CLASSES", 0);   // tuning builds only
   if (cls_forced >= 1 && cls_forced <= 8 && (unsigned long long)blocks * cls_forced <= 0x7fffffffULL) classes = cls_forced;
-#define LASER_STREAM_SHORT(CM, SM)                                                                                   \
-  hipLaunchKernelGGL((sta_stream_short_kernel<DQ, D, CM, HEADS, SM>), dim3(blocks), dim3(256), 0, a.stream,        \
+  const bool nt = stream_past_cache(a.lens, a.U, a.L, DQ, a.k == a.v ? 0 : D);
+#define LASER_STREAM_SHORT(CM, SM, NT)                                                                                   \
+  hipLaunchKernelGGL((sta_stream_short_kernel<DQ, D, CM, HEADS, SM, NT>), dim3(blocks), dim3(256), 0, a.stream,        \
                      (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,   \
                      a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, nsl, (unsigned short*)a.seg_out, a.seg_cnt,   \
                      (a.k == a.v && DQ == D) ? 1 : 0)
+#define LASER_STREAM_LONG(CM, NT)                                                                                      \
+  hipLaunchKernelGGL((sta_stream_kernel<DQ, D, CM, HEADS, NT>), dim3(blocks * classes), dim3(256), 0, a.stream,     \
+                     (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,    \
+                     a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,                              \
+                     (unsigned short*)a.seg_out, a.seg_cnt, StreamFusedTail{})
 #define LASER_STREAM_LAUNCH(CM)                                                                                      \
   do {                                                                                                               \
-    if (short_seg && a.softmax) LASER_STREAM_SHORT(CM, true);                                                        \
+    if (short_seg && a.softmax) LASER_STREAM_SHORT(CM, true, false);                                                 \
     else if constexpr (HEADS == 2 || CM <= 2) {   /* (one head, more rows: sta_few_kernel) */                        \
-      if (short_seg) LASER_STREAM_SHORT(CM, false);                                                                  \
-      else                                                                                                           \
-        hipLaunchKernelGGL((sta_stream_kernel<DQ, D, CM, HEADS>), dim3(blocks * classes), dim3(256), 0, a.stream,  \
-                           (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,     \
-                           a.lens, a.cand_off, a.P, a.C, a.L, a.w, a.S, spg, groups, a.U, classes, nsl,             \
-                           (unsigned short*)a.seg_out, a.seg_cnt, StreamFusedTail{});                                \
+      if (short_seg && nt) LASER_STREAM_SHORT(CM, false, true);                                                      \
+      else if (short_seg) LASER_STREAM_SHORT(CM, false, false);                                                      \
+      else if (nt) LASER_STREAM_LONG(CM, true);                                                                      \
+      else LASER_STREAM_LONG(CM, false);                                                                             \
     }                                                                                                                \
   } while (0)
   if (a.C <= 1) LASER_STREAM_LAUNCH(1);
@@ -625,6 +638,7 @@ static void launch_c(const StaArgs& a, float nsl) {
   else if (a.C <= 4) LASER_STREAM_LAUNCH(4);
   else LASER_STREAM_LAUNCH(8);
 #undef LASER_STREAM_SHORT
+#undef LASER_STREAM_LONG
 #undef LASER_STREAM_LAUNCH
 }
 
@@ -644,16 +658,22 @@ static void fused_stream_launch_c(const FusedArgs& a, float nsl) {
   const int classes = (a.lens != nullptr && blocks >= 4096) ? 4 : 1;   // longest histories first, as above
   const StreamFusedTail ft{(const unsigned short*)a.t0, (const unsigned short*)a.wq, (const unsigned short*)a.wk,
                            (const unsigned short*)a.wv, a.z_out};
-#define LASER_FUSED_STREAM(CM)                                                                                       \
-  hipLaunchKernelGGL((sta_stream_kernel<DQ, D, CM, 1, true>), dim3(blocks * classes), dim3(256), 0, a.stream,        \
+#define LASER_FUSED_STREAM_AS(CM, NT)                                                                                  \
+  hipLaunchKernelGGL((sta_stream_kernel<DQ, D, CM, 1, NT, true>), dim3(blocks * classes), dim3(256), 0, a.stream,    \
                      (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,     \
                      (const int32_t*)nullptr, 0, a.C, a.L, a.w, a.S, a.S, 1, a.U, classes, nsl,                      \
                      (unsigned short*)nullptr, a.seg_cnt, ft)
+#define LASER_FUSED_STREAM(CM)                                                                                       \
+  do {                                                                                                               \
+    if (stream_past_cache(a.lens, a.U, a.L, DQ, D)) LASER_FUSED_STREAM_AS(CM, true);                                 \
+    else LASER_FUSED_STREAM_AS(CM, false);                                                                           \
+  } while (0)
   if (a.C <= 1) LASER_FUSED_STREAM(1);
   else if (a.C <= 2) LASER_FUSED_STREAM(2);
   else if (a.C <= 4) LASER_FUSED_STREAM(4);
   else LASER_FUSED_STREAM(8);
 #undef LASER_FUSED_STREAM
+#undef LASER_FUSED_STREAM_AS
 }
 
 laser_status fused_stream_launch(const FusedArgs& a) {
