@@ -1049,10 +1049,49 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
 }
 
 // ------------------------------------------------------------------------------------------ host side
-static int pick_nw(int C) {
-  const int vv = tuning_int("LASER_STA_NW", 0);   // tuning builds: waves (32 candidates each) per workgroup
+// the direct-to-LDS form's shapes
+static bool is_direct(const StaArgs& a) {
+  return a.heads == 1 && !a.softmax && a.d_q == 128 && a.d == 128 && tuning_int("LASER_STA_NODMA", 0) == 0;
+}
+
+// Waves (32 candidates each) per workgroup. Segments shorter than a staged tile (64 items) keep the waves of a workgroup
+// waiting for each other once per segment: two workgroups of four waves on a compute unit are then better than one of eight,
+// and waste fewer candidate slots (64 users x 256 candidates x 100 segments of 10 items, d_q = 32, d = 128, two heads: 104 ->
+// 102 us; 64 x 320, w = 20: 74 -> 64; 10 x 400, w = 32, 64/64: 36 -> 25); from w = 64 on eight are (32 x 256, L = 4096,
+// w = 128, 64/64: 21 against 24 us; 8 x 512, w = 256: 21 against 25).
+static int pick_nw(const StaArgs& a) {
+  const int vv = tuning_int("LASER_STA_NW", 0);   // tuning builds
   if (vv == 1 || vv == 2 || vv == 4 || vv == 8) return vv;
-  return C > 128 ? 8 : (C > 64 ? 4 : (C > 32 ? 2 : 1));
+  if (a.C > 128 && (is_direct(a) || a.w >= TI)) return 8;
+  return a.C > 64 ? 4 : (a.C > 32 ? 2 : 1);
+}
+
+// Consecutive segments per workgroup of the register-staged forms (they share the query registers and the prefetch
+// pipeline). One and two waves: as many as still leave a few workgroups per compute unit (64 users x 64 candidates x 16
+// segments, two waves: 15.1 us with 512 workgroups of two segments, 11.2 us with 1024 of one). Four waves, two workgroups on
+// a compute unit, and eight, one on it: the smallest estimate of rounds of workgroups times the length of one, in segments,
+// with half a segment for its start and half a round for the last one. It follows the measured times to within a tenth (two
+// heads, w = 10, four waves, 12800 segments in all, 1 / 2 / 4 / 6 / 8 / 12 / 16 per workgroup: 114, 102, 98, 96, 101, 105,
+// 119 us); 48 users x 512 candidates, w = 40: 58 -> 42 us, 40 x 130, w = 50: 28 -> 22 us against as many segments as filled
+// the chip once.
+static int pick_spw(const StaArgs& a, int nw, int ctiles) {
+  const long long per = (long long)a.U * ctiles;
+  int best = 1;
+  if (nw < 4) {
+    while (best < 8 && per * ((a.S + 2 * best - 1) / (2 * best)) >= 2048 / nw) best *= 2;
+    return best;
+  }
+  const double slots = nw == 8 ? 256.0 : 512.0;
+  double least = 0.0;
+  for (int spw : {1, 2, 3, 4, 6, 8, 12, 16}) {
+    const double rounds = per * ((a.S + spw - 1) / spw) / slots;
+    const double cost = (nw == 8 && rounds <= 1.0 ? 1.0 : (rounds > 0.5 ? rounds : 0.5) + 0.5) * (spw + 0.5);
+    if (spw == 1 || cost < least) {
+      best = spw;
+      least = cost;
+    }
+  }
+  return best;
 }
 
 bool sta_mfma_supports(const StaArgs& a) {
@@ -1063,7 +1102,7 @@ bool sta_mfma_supports(const StaArgs& a) {
   if (a.heads != 1 && a.heads != 2 && a.heads != 4) return false;
   if (a.heads == 4 && (a.d_q < 64 || a.d != 128)) return false;
   if (a.C < 9) return false;   // fewer candidates than that: the streaming kernel's range
-  const int nw = pick_nw(a.C);
+  const int nw = pick_nw(a);
   const long long ctiles = (a.C + CW * nw - 1) / (CW * nw);
   return (long long)a.U * ctiles * a.S <= 0x7fffffffLL;
 }
@@ -1136,21 +1175,13 @@ static void launch_nw(const StaArgs& a, int nw, int spw, int ctiles, int sruns, 
 
 laser_status sta_mfma_launch(const StaArgs& a) {
   if (!sta_mfma_supports(a)) return LASER_ERR_UNSUPPORTED;
-  const int nw = pick_nw(a.C);
+  const int nw = pick_nw(a);
   const int ctiles = (a.C + CW * nw - 1) / (CW * nw);
-  // consecutive segments per workgroup (they share the query registers and the prefetch pipeline): as many as
-  // still leave one eight-wave workgroup, or two smaller ones, per compute unit
-  // (smaller workgroups: more of them fit a compute unit, so more are wanted; 64 users x 64 candidates x 16
-  // segments, two waves: 15.1 us with 512 workgroups of two segments, 11.2 us with 1024 of one)
-  const long long want = 2048 / nw;
-  int spw = 1;
-  while (spw < 8 && (long long)a.U * ctiles * ((a.S + 2 * spw - 1) / (2 * spw)) >= want) spw *= 2;
+  int spw = pick_spw(a, nw, ctiles);
   // the direct-to-LDS kernels take a compute unit's LDS per workgroup: as many segments per workgroup as bring the
   // launch down to one round of 256 workgroups, eight at most (16 users x 128 candidates x 40 segments: 640
   // workgroups of one segment 32.9 us in the register-staged form, 224 of three segments 26.8 us in this one)
-  const bool direct = a.heads == 1 && !a.softmax && a.d_q == 128 && a.d == 128 && (nw == 8 || nw == 4) &&
-                      tuning_int("LASER_STA_NODMA", 0) == 0;
-  if (direct) {
+  if (is_direct(a) && (nw == 8 || nw == 4)) {
     const long long per_seg = (long long)a.U * ctiles * a.S;
     spw = (int)((per_seg + 255) / 256 < 8 ? (per_seg + 255) / 256 : 8);
     if (spw < 1) spw = 1;
