@@ -42,6 +42,10 @@ __device__ __forceinline__ float over_groups(float x) {
   return both(__uint_as_float(s[0]), __uint_as_float(s[1]));
 }
 
+// What an online softmax subtracts from its scores when the largest so far is m: scores of -inf alone (or none) then have
+// weight zero without a difference of infinities, and one of NaN or +inf gives NaN.
+__device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 0.0f : m; }
+
 // Per storage type: the left operand's tile in LDS (16 pairs x D values of fp32 meaning), a wave's share of a matrix, and
 // the product of the two.
 template <typename T, int D> struct Prod;

@@ -106,9 +106,8 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {                               // one pass over the rows of H'
-      constexpr float NEG = -3.0e38f;
       const int pj = PW < NW ? wave / WPP : wave * PPW + i;
-      float r8[8], acc[8], m = NEG, den = 0.0f;
+      float r8[8], acc[8], m = -INFINITY, den = 0.0f;
       {
         const f32x4 a = *reinterpret_cast<const f32x4*>(rr + pj * RP + gl * 8);
         const f32x4 b = *reinterpret_cast<const f32x4*>(rr + pj * RP + gl * 8 + 4);
@@ -135,8 +134,9 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
           s[k] = row_sum<LPR>(s[k]);
           if (((k0 + k) * WPP + wp) * RPW + grp < nv[i]) mx = fmaxf(mx, s[k]);
         }
+        const float ref = softmax_ref(mx);
         if (!RES) {
-          const float corr = X::ex(m - mx);
+          const float corr = X::ex(m - ref);
           den *= corr;
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[e] *= corr;
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
 #pragma unroll
         for (int k = 0; k < R; ++k) {
           hi[k].pin();
-          const float p = ((k0 + k) * WPP + wp) * RPW + grp < nv[i] ? X::ex(s[k] - m) : 0.0f;
+          const float p = ((k0 + k) * WPP + wp) * RPW + grp < nv[i] ? X::ex(s[k] - ref) : 0.0f;
           den += p;
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, hi[k].get(e), acc[e]);
@@ -155,12 +155,14 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
 #pragma unroll
           for (int k = 0; k < R; ++k) hi[k] = ahead[k];
       }
-      const float mw = over_groups<LPR, true>(m), f = X::ex(m - mw);
+      const float mw = over_groups<LPR, true>(m), f = X::ex(m - softmax_ref(mw));
       den = over_groups<LPR, false>(den * f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = over_groups<LPR, false>(acc[e] * f);
-      if constexpr (WPP == 1) {                                   // p; zero without a valid segment
-        const float inv = den > 0.0f ? 1.0f / den : 0.0f;
+      // p, zero without a valid segment (by their number: a denominator of NaN, or of zero where every score is -inf, has to
+      // reach the result)
+      if constexpr (WPP == 1) {
+        const float inv = nv[i] > 0 ? 1.0f / den : 0.0f;
         if (grp == 0)
 #pragma unroll
           for (int e = 0; e < 8; ++e) X::put(bq, pj, gl * 8 + e, acc[e] * inv);
@@ -170,8 +172,8 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
           *reinterpret_cast<f32x4*>(&part[wave][gl * 8 + 4]) = f32x4{acc[4], acc[5], acc[6], acc[7]};
         }
         if (lane == 0) {
-          pml[wave][0] = mw;
-          pml[wave][1] = den;
+          pml[wave][0] = nv[i] > 0 ? mw : 0.0f;
+          pml[wave][1] = nv[i] > 0 ? den : 1.0f;
         }
       }
     }
@@ -183,13 +185,14 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
         float m = pml[j * WPP][0], num = 0.0f, den = 0.0f;
 #pragma unroll
         for (int o = 1; o < WPP; ++o) m = fmaxf(m, pml[j * WPP + o][0]);
+        m = softmax_ref(m);
 #pragma unroll
         for (int o = 0; o < WPP; ++o) {
           const float f = X::ex(pml[j * WPP + o][0] - m);
           den = fmaf(pml[j * WPP + o][1], f, den);
           num = fmaf(part[j * WPP + o][y], f, num);
         }
-        X::put(bq, j, y, den > 0.0f ? num / den : 0.0f);
+        X::put(bq, j, y, num / den);
       }
       __syncthreads();
     }

@@ -71,3 +71,41 @@ def test_views_of_every_form(P, S, d, r):
     torch.cuda.synchronize()
     assert torch.equal(z, z2) and torch.equal(pool.view(torch.int16), pool2.view(torch.int16))
     assert r == 0 or torch.equal(recent.view(torch.int16), recent2.view(torch.int16))
+
+
+# pairs per workgroup 1, 2, 4, 8, 16 (few pairs: several waves share a pair's rows) and, for S = 300, rows that are streamed
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("P,S", [(12, 9), (300, 9), (600, 20), (1100, 9), (2100, 9), (12, 300), (2100, 300)])
+def test_values_that_are_not_finite_reach_the_result(P, S, dtype):
+    """A valid segment vector that is not finite, or scores that overflow, make z NaN as in the softmax they stand for; a pair
+    whose scores are all near the lowest finite value still has the weights of its softmax. Other pairs are untouched."""
+    import torch
+    d, w = 128, 3
+    L = S * w
+    rng = np.random.default_rng(6600 + P + S)
+    Hs, Hv = _store(rng.normal(size=(P, S, d)), dtype)
+    ts, tv = _store(rng.normal(size=(P, d)), dtype)
+    (wqs, wqv), (wks, wkv), (wvs, wvv) = (_store(rng.normal(size=(1, d, d)) / math.sqrt(d), dtype) for _ in range(3))
+    nv = np.full(P, S)
+    nv[1], nv[8] = S // 2, 0
+    special = {0: (0, np.nan), 1: (S // 2 - 1, np.inf), 2: (S // 2, -np.inf), 3: (S - 1, np.nan), 4: (5, np.inf)}
+    for p, (row, x) in special.items():
+        Hs[p, row, 7] = x if dtype == "f32" else {np.inf: 0x7f80, -np.inf: 0xff80}.get(x, 0x7fc0)
+    # scores of one value x in the units of the kernel's exponential (base 2 for bf16): below -3e38 and finite, past the range
+    unit = 1.0 if dtype == "f32" else 1.4426950408889634
+    for p, x in ((5, -3.2e38), (6, -1e39)):
+        ts[p], tv[p] = _store(1e10 * tv[p], dtype)
+        r = wkv[0] @ (tv[p] @ wqv[0]) / math.sqrt(d)
+        Hs[p], Hv[p] = _store(np.broadcast_to(x / unit * r / (r @ r), (S, d)), dtype)
+    lens = (nv * w).astype(np.int32)
+    print(f"P {P} S {S} {dtype}", flush=True)
+    z = laser.laser_gsta_forward(to_device(Hs[:, None]), to_device(ts[:, None]), to_device(wqs), to_device(wks), to_device(wvs),
+                                 to_device(lens), L, w)
+    torch.cuda.synchronize()
+    got = to_host_f64(z)[:, 0]
+    for p in (0, 1, 2, 3, 4, 6):
+        assert np.isnan(got[p]).all(), p
+    fine = [5, 7, 8, 9, 10, P - 1]
+    ref = oracle.gsta_forward(Hv[fine][:, None], tv[fine][:, None], wqv, wkv, wvv, oracle.segment_counts(lens[fine], L, w))
+    assert vec_rel_err(got[fine], ref[:, 0]) <= TOL[dtype]
+    assert np.isfinite(np.delete(got, (0, 1, 2, 3, 4, 6), axis=0)).all()
