@@ -233,7 +233,7 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
           for (int e = 0; e < 8; ++e) store_from_f32(pool, (size_t)pr * D + gl * 8 + e, nv[i] > 0 ? best[e] : 0.0f);
       } else if (grp == 0) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) part[wave][gl * 8 + e] = best[e];
+        for (int e = 0; e < 8; ++e) part[wave][gl * 8 + e] = nv[i] > 0 ? best[e] : 0.0f;
       }
     }
     if constexpr (WPP > 1) {
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__
         float m = part[j * WPP][y];
 #pragma unroll
         for (int o = 1; o < WPP; ++o) m = fmaxf(m, part[j * WPP + o][y]);
-        if (pbase + j < P) store_from_f32(pool, (size_t)(pbase + j) * D + y, m > -INFINITY ? m : 0.0f);
+        if (pbase + j < P) store_from_f32(pool, (size_t)(pbase + j) * D + y, m);
       }
     }
   }

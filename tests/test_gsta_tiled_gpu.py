@@ -109,3 +109,25 @@ def test_values_that_are_not_finite_reach_the_result(P, S, dtype):
     ref = oracle.gsta_forward(Hv[fine][:, None], tv[fine][:, None], wqv, wkv, wvv, oracle.segment_counts(lens[fine], L, w))
     assert vec_rel_err(got[fine], ref[:, 0]) <= TOL[dtype]
     assert np.isfinite(np.delete(got, (0, 1, 2, 3, 4, 6), axis=0)).all()
+
+
+@pytest.mark.parametrize("P,S", [(3, 5), (300, 40), (1200, 9), (2500, 70), (4097, 9)])   # tiled form, one-kernel form
+def test_pooled_columns_of_minus_infinity(P, S):
+    """The pooled view is a selection of stored values: -inf where that is all a column holds, not the zero of a pair without
+    a valid segment. (z of such a pair is NaN in every form.)"""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
+    seg, t0 = rnd(P, 1, S, 128), rnd(P, 1, 128)
+    W = [(rnd(1, 128, 128).float() / math.sqrt(128)).bfloat16() for _ in range(3)]
+    seg[0, 0, :, 5] = -math.inf
+    seg[1, 0, :2, 127] = -math.inf
+    seg[2] = -math.inf
+    lens = torch.full((P,), S, device="cuda", dtype=torch.int32)
+    lens[1], lens[2] = 2, 0
+    print(f"P {P} S {S}", flush=True)
+    _, pool, _ = laser.laser_gsta_forward_multires(seg, t0, *W, lens, S, 1, 0)
+    torch.cuda.synchronize()
+    for p, n in ((0, S), (1, 2)):
+        assert torch.equal(pool[p, 0], seg[p, 0, :n].max(dim=0).values)
+    assert not pool[2].any()
