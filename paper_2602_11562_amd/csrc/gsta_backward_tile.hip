@@ -177,10 +177,9 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
-      constexpr float NEG = -3.0e38f;
       const int pj = PW < NW ? wave / WPP : wave * PPW + i;
       float* blk = rr_of(pj, l);
-      float r8[8], acc[8], m = NEG, den = 0.0f;
+      float r8[8], acc[8], m = -INFINITY, den = 0.0f;
       lds_row8(r8, blk + gl * 8);
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
@@ -202,14 +201,14 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
             if (gl == 0) blk[3 * RP + 4 + row] = s[k];
           }
         }
-        const float corr = X::ex(m - mx);
+        const float ref = softmax_ref(mx), corr = X::ex(m - ref);
         den *= corr;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] *= corr;
         m = mx;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-          const float p = ((k0 + k) * WPP + wp) * RPW + grp < nv[i] ? X::ex(s[k] - m) : 0.0f;
+          const float p = ((k0 + k) * WPP + wp) * RPW + grp < nv[i] ? X::ex(s[k] - ref) : 0.0f;
           den += p;
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, h[k].get(e), acc[e]);
@@ -218,19 +217,20 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
 #pragma unroll
           for (int k = 0; k < R; ++k) h[k] = ahead[k];
       }
-      const float mw = over_groups<LPR, true>(m), f = X::ex(m - mw);
+      const float mw = over_groups<LPR, true>(m), f = X::ex(m - softmax_ref(mw));
       den = over_groups<LPR, false>(den * f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = over_groups<LPR, false>(acc[e] * f);
-      const float inv = den > 0.0f ? 1.0f / den : 0.0f;           // (no valid segment: p = 0)
+      // no valid segment: p = 0 (by their number, as in the forward kernel)
+      const float inv = nv[i] > 0 ? 1.0f / den : 0.0f;
       if (WPP == 1) {
         if (lane == 0) {
-          blk[3 * RP] = mw;
+          blk[3 * RP] = softmax_ref(mw);
           blk[3 * RP + 1] = inv;
         }
       } else if (lane == 0) {
-        pml[wave * 4] = mw;
-        pml[wave * 4 + 1] = den;
+        pml[wave * 4] = nv[i] > 0 ? mw : 0.0f;
+        pml[wave * 4 + 1] = nv[i] > 0 ? den : 1.0f;
       }
       gather(i, acc, inv, [&](int j, int y, float x) { rr_of(j, l)[2 * RP + y] = x; });
     }
@@ -241,13 +241,14 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
         float m = pml[j * WPP * 4], num = 0.0f, den = 0.0f;
 #pragma unroll
         for (int o = 1; o < WPP; ++o) m = fmaxf(m, pml[(j * WPP + o) * 4]);
+        m = softmax_ref(m);
 #pragma unroll
         for (int o = 0; o < WPP; ++o) {
           const float f = X::ex(pml[(j * WPP + o) * 4] - m);
           den = fmaf(pml[(j * WPP + o) * 4 + 1], f, den);
           num = fmaf(part[(j * WPP + o) * RP + y], f, num);
         }
-        const float inv = den > 0.0f ? 1.0f / den : 0.0f;
+        const float inv = 1.0f / den;
         float* blk = rr_of(j, l);
         blk[2 * RP + y] = num * inv;
         if (y == 0) {

@@ -57,3 +57,53 @@ def test_gsta_backward_tiles(name):
     again = laser.laser_gsta_backward(*args)
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(got, again))      # fixed summation order
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("P,S", [(12, 9), (300, 9), (600, 20), (1100, 9), (2100, 9)])   # 1, 2, 4, 8, 16 pairs a workgroup
+@pytest.mark.parametrize("M", [1, 2])
+def test_values_that_are_not_finite_reach_the_gradients(P, S, M, dtype):
+    """A valid segment vector that is not finite, or scores that overflow: the pair's gradients are NaN, as those of the
+    softmax they stand for, and other pairs' are untouched; scores near the lowest finite value still have their softmax."""
+    import torch
+    d, w = 128, 3
+    L = S * w
+    rng = np.random.default_rng(7600 + P + S + M)
+    Hs, Hv = _store(rng.normal(size=(P, S, d)), dtype)
+    ts, tv = _store(rng.normal(size=(P, d)), dtype)
+    (wqs, wqv), (wks, wkv), (wvs, wvv) = (_store(rng.normal(size=(M, d, d)) / math.sqrt(d), dtype) for _ in range(3))
+    dz = rng.normal(size=(P, d)).astype(np.float32)
+    nv = np.full(P, S)
+    nv[1], nv[8] = S // 2, 0
+    for p, row, x in ((0, 0, np.nan), (1, S // 2 - 1, np.inf), (2, S // 2, -np.inf), (3, S - 1, np.nan), (4, 5, np.inf)):
+        Hs[p, row, 7] = x if dtype == "f32" else {np.inf: 0x7f80, -np.inf: 0xff80}.get(x, 0x7fc0)
+    # equal scores of one value, as in the forward test: past the range, and (pair 5) below -3e38 and finite
+    unit = 1.0 if dtype == "f32" else 1.4426950408889634
+    for p, x in ((5, -3.2e38), (6, -1e39)):
+        ts[p], tv[p] = _store(1e10 * tv[p], dtype)
+        r = wkv[0] @ (tv[p] @ wqv[0]) / math.sqrt(d)
+        Hs[p], Hv[p] = _store(np.broadcast_to(x / unit * r / (r @ r), (S, d)), dtype)
+    lens = (nv * w).astype(np.int32)
+    print(f"P {P} S {S} M {M} {dtype}", flush=True)
+    args = [to_device(x) for x in (Hs[:, None], ts[:, None], wqs, wks, wvs, lens, dz[:, None])]
+    dseg, dt0 = laser.laser_gsta_backward(*args, L, w)[:2]
+    torch.cuda.synchronize()
+    dseg, dt0 = to_host_f64(dseg)[:, 0], to_host_f64(dt0)[:, 0]
+    nans = (0, 1, 2, 3, 4, 6)
+    for p in nans:
+        assert np.isnan(dt0[p]).all() and np.isnan(dseg[p, :nv[p]]).all() and not dseg[p, nv[p]:].any(), p
+    fine = [7, 8, 9, 10, P - 1]
+    cnt = oracle.segment_counts(lens[fine], L, w)
+    ref = oracle.gsta_backward(Hv[fine][:, None], tv[fine][:, None], wqv, wkv, wvv, cnt, dz[fine][:, None].astype(np.float64))
+    assert vec_rel_err(dseg[fine], ref[0][:, 0]) <= TOL[dtype]
+    assert vec_rel_err(dt0[fine], ref[1][:, 0]) <= 1e-5
+    others = np.delete(np.arange(P), nans + (5,))
+    assert np.isfinite(dt0[others]).all() and np.isfinite(dseg[others]).all()
+    if M == 1:
+        # pair 5: p is its one row, whose outer product with dz (1e28 times every other pair's) is dW_v. (Its score gradients
+        # are differences of numbers of that size, so nothing is said about the others.)
+        lens[list(nans)] = 0
+        args[5] = to_device(lens)
+        dwv = to_host_f64(laser.laser_gsta_backward(*args, L, w)[4])[0]
+        ref = np.outer(Hv[5, 0], dz[5].astype(np.float64))
+        assert vec_rel_err(dwv.reshape(1, -1), ref.reshape(1, -1)) <= 1e-5
