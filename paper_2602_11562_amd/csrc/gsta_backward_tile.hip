@@ -86,11 +86,13 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
   typename X::Operand rk, rv, rq;
   X::load_cols(cq, wq, n0, lane);
   f32x4 t, g;                                                     // pair g4 + r, column col
+  bool some[4];                                                   // the pair has a valid segment
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int p = pbase + g4 + r < P ? pbase + g4 + r : P - 1;
     t[r] = g4 + r < PW ? load_as_f32(t0, (size_t)p * D + col) : 0.0f;
     g[r] = g4 + r < PW ? dz[(size_t)p * D + col] : 0.0f;
+    some[r] = valid_len(lens, p / C, L) > 0;
   }
   X::load_rows(rk, wk, n0, lane);
   int nv[PPW];
@@ -118,10 +120,13 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     for (int r = 0; r < 4; ++r)
       if (g4 + r < PW) X::put(b, g4 + r, col, x[r]);
   };
-  auto put_scratch = [&](int l, int slot, const f32x4& x) {       // one of the six vectors of a pair and layer
+  // one of the six vectors of a pair and layer: zeros without a valid segment, like p and dr there (products of a zero with
+  // a target or gradient that is not finite are NaN)
+  auto put_scratch = [&](int l, int slot, const f32x4& x) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (g4 + r < PW && pbase + g4 + r < P) pv[(((size_t)(pbase + g4 + r) * M + l) * 6 + slot) * D + col] = x[r];
+      if (g4 + r < PW && pbase + g4 + r < P)
+        pv[(((size_t)(pbase + g4 + r) * M + l) * 6 + slot) * D + col] = some[r] ? x[r] : 0.0f;
   };
   auto put_rows = [&](int l, int off, const f32x4& x, float f) {  // into the (pair, layer) block
 #pragma unroll

@@ -107,3 +107,28 @@ def test_values_that_are_not_finite_reach_the_gradients(P, S, M, dtype):
         dwv = to_host_f64(laser.laser_gsta_backward(*args, L, w)[4])[0]
         ref = np.outer(Hv[5, 0], dz[5].astype(np.float64))
         assert vec_rel_err(dwv.reshape(1, -1), ref.reshape(1, -1)) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("P", [12, 300, 600, 1100, 2100])
+def test_pairs_without_a_segment_add_nothing_to_the_weight_gradients(P, dtype):
+    """Whatever their target and upstream gradient hold: the latter passes through to dt0 and that is all."""
+    import torch
+    d, S, M = 128, 5, 2
+    rng = np.random.default_rng(7700 + P)
+    Hs, _ = _store(rng.normal(size=(P, 1, S, d)), dtype)
+    ts, _ = _store(rng.normal(size=(P, 1, d)), dtype)
+    W = [to_device(_store(rng.normal(size=(M, d, d)) / math.sqrt(d), dtype)[0]) for _ in range(3)]
+    dz = rng.normal(size=(P, 1, d)).astype(np.float32)
+    lens = np.full(P, S, dtype=np.int32)
+    lens[3] = lens[8] = 0
+    print(f"P {P} {dtype}", flush=True)
+    call = lambda: laser.laser_gsta_backward(to_device(Hs), to_device(ts), *W, to_device(lens), to_device(dz), S, 1)
+    plain = call()
+    ts[3, 0, 7] = np.nan if dtype == "f32" else 0x7fc0
+    dz[8, 0, 9] = np.inf
+    got = call()
+    torch.cuda.synchronize()
+    for a, b in zip(got[2:], plain[2:]):
+        assert torch.equal(a, b)
+    assert torch.equal(got[1], to_device(dz).where(to_device(lens == 0)[:, None, None], got[1]))
