@@ -11,7 +11,7 @@
 //
 // Split: a workgroup owns a user, 16 or 32 candidates and a segment (a few segments when they are short); its four waves
 // take alternate item tiles of a segment, so that a single request still spreads over the chip, and their sums meet in LDS
-// in a fixed order. Items past the end of a segment repeat its last valid row under a gate of exactly zero.
+// in a fixed order. Items past the end of a segment have a gate of exactly zero and zeros for values.
 //
 // Bound: the fp32 matrix rate, 157 TFLOP/s (one 16 x 16 tile with d = d_q = 64 is 1024 cycles of one SIMD), and for small
 // calls the load - score - gate - sum chain of one tile. Against the generic kernel (one candidate a wave, a score per
@@ -79,6 +79,11 @@ __global__ __launch_bounds__(256) void sta_f32_kernel(const float* __restrict__ 
 #pragma unroll
         for (int db = 0; db < DB; ++db) vf[r][db] = vU[(size_t)row * D + db * 16];
       }
+      if (t0 + 16 > hi)   // the rows past the end are zeros: the last one may hold an infinity, which a zero gate would make NaN
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int db = 0; db < DB; ++db) vf[r][db] = t0 + g * 4 + r < hi ? vf[r][db] : 0.0f;
 #pragma unroll
       for (int c = 0; c < NCT; ++c) {
         f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};

@@ -45,3 +45,33 @@ def test_sta_f32(name):
                                  v[u:u + 1].astype(np.float64), lens[u:u + 1], w, gamma)
         ref = ref[0] if isinstance(ref, tuple) else ref
         assert vec_rel_err(got[u:u + 1], ref) <= TOL["f32"], u
+
+
+@pytest.mark.parametrize("x", [np.inf, -np.inf, np.nan], ids=["inf", "-inf", "nan"])
+@pytest.mark.parametrize("name", ["one_candidate_one_item_segments", "17_candidates_two_tiles", "33_candidates_three_tiles",
+                                  "many_users_two_candidate_tiles"])
+def test_not_finite_items_stay_in_their_segment(name, x):
+    """An infinite value is an infinite sum, also in the last valid row, which stands in for the rows past it."""
+    import torch
+    C, L, dq, d, w, lens = STA_CASES[name]
+    U, gamma = len(lens), math.sqrt(dq)
+    if U > 8:
+        lens = [max(n, 6) for n in lens]
+    rng = np.random.default_rng(5200 + sum(map(ord, name)))
+    q, k, v = (rng.normal(size=s).astype(np.float32) for s in ((U, C, dq), (U, L, dq), (U, L, d)))
+    lens = np.array(lens, dtype=np.int32)
+    kn, vn = k.copy(), v.copy()
+    last = min(w, lens[0]) - 1            # the last valid item of the first segment: a column
+    vn[0, last, 3] = x
+    kn[1, lens[1] - 1] = np.nan           # the last valid item of a user: its whole segment
+    print(f"case {name} {x}", flush=True)
+    seg, _ = laser.laser_sta_forward(to_device(q), to_device(kn), to_device(vn), to_device(lens), w, gamma)
+    torch.cuda.synchronize()
+    got = to_host_f64(seg)
+    bad = np.zeros(got.shape, dtype=bool)
+    bad[0, :, 0, 3] = True
+    bad[1, :, (lens[1] - 1) // w] = True
+    assert np.array_equal(~np.isfinite(got), bad)
+    assert np.array_equal(got[0, :, 0, 3], np.full(C, x), equal_nan=True)
+    ref, _ = oracle.sta_forward(q[:2].astype(np.float64), k[:2].astype(np.float64), v[:2].astype(np.float64), lens[:2], w, gamma)
+    assert vec_rel_err(np.where(bad[:2], 0.0, got[:2]), np.where(bad[:2], 0.0, ref)) <= TOL["f32"]
