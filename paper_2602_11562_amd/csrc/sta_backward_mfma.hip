@@ -18,7 +18,8 @@
 // through LDS; neither kind waits for the other and nothing but Q's partial sums crosses workgroups.
 // A workgroup's four waves split over segments when a segment has few item tiles (or a user few candidate tiles):
 // short segments and small candidate sets leave no wave idle. Rows past the end of a segment or past the last candidate
-// are zeros in LDS, so they add nothing to any sum (padding of the history is never read).
+// are zeros in LDS, so they add nothing to any finite sum (padding of the history is never read); a wave whose sums come out
+// not finite forms them again over the valid rows alone.
 //
 // What bounds it: LDS reads and MFMA issue share the time (two workgroups of four waves per compute unit: 256
 // registers a wave); at 64 users x 64 candidates, L = 2048, w = 128, d = d_q = 64 (lengths 410 .. 2048) the launch takes
@@ -84,6 +85,46 @@ __device__ __forceinline__ void stage_rows(unsigned char* t, const unsigned shor
     *reinterpret_cast<u32x4*>(t + swz<D>(r, c)) = x;
   }
 }
+
+// Whether a wave's sums hold a value that is not finite (zero times it is NaN)
+template <int N>
+__device__ __forceinline__ bool any_not_finite(const f32x16 (&x)[N], float zero = 0.0f) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero = fmaf(x[i][r], 0.0f, zero);
+  return __any(!(zero == 0.0f));
+}
+
+// A row in the layout of the plain sums: lane l holds elements l, l + 64, ..
+template <int D>
+struct PlainRow {
+  static constexpr int T = (D + 63) / 64;
+  float x[T];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int t = 0; t < T; ++t) x[t] = 0.0f;
+  }
+  __device__ __forceinline__ void load(const unsigned short* p, int lane) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) x[t] = lane + 64 * t < D ? bf16_bits_to_f32(p[lane + 64 * t]) : 0.0f;
+  }
+  __device__ __forceinline__ void store(float* p, int lane) const {
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (lane + 64 * t < D) p[lane + 64 * t] = x[t];
+  }
+  __device__ __forceinline__ float dot(const PlainRow& o) const {
+    float s = 0.0f;
+#pragma unroll
+    for (int t = 0; t < T; ++t) s = fmaf(x[t], o.x[t], s);
+    return wave_sum_rows(s);
+  }
+  __device__ __forceinline__ void add(float f, const PlainRow& o) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) x[t] = fmaf(f, o.x[t], x[t]);
+  }
+};
 
 struct StaBwdMfmaShape {
   int wi, ws_i;        // items: waves per segment, segments per workgroup (wi * ws_i = 4)
@@ -191,13 +232,36 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
         }
       }
     }
+    // Sums that are not finite once more without the tiles: there a zero row that pads the candidates meets an infinite key
+    // or value, and the zero parts of a split gate an infinite dH', and give NaN where the sum has none.
+    const bool plain = work_here && (any_not_finite(dka) || any_not_finite(dva));
+    if (__builtin_expect(plain, 0)) {
+      for (int row = 0; row < rows; ++row) {
+        const size_t j = (size_t)u * L + lo + row;
+        PlainRow<DQ> kr, qr, dkr;
+        PlainRow<D> vr, hr, dvr;
+        kr.load(k + j * DQ, lane);
+        vr.load(v + j * D, lane);
+        dkr.zero();
+        dvr.zero();
+        for (int c = 0; c < C; ++c) {
+          qr.load(q + ((size_t)u * C + c) * DQ, lane);
+          hr.load(dhp + (((size_t)u * C + c) * S + seg) * D, lane);
+          const float gt = gate(kr.dot(qr), neg_scale_log2e);
+          dvr.add(gt, hr);
+          dkr.add(vr.dot(hr) * gt * (1.0f - gt) * inv_gamma, qr);
+        }
+        dkr.store(dk + j * DQ, lane);
+        dvr.store(dv + j * D, lane);
+      }
+    }
     // lane = column, registers = items: whole 128-byte pieces of a row per store; rows past the valid length get zeros
     float* dkr = dk + ((size_t)u * L + lo) * DQ + l32;
     float* dvr = dv + ((size_t)u * L + lo) * D + l32;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = 8 * (r >> 2) + 4 * h + (r & 3);
-      if (row < rows_all) {
+      if (row < rows_all && !(plain && row < rows)) {
         const bool ok = row < rows;
 #pragma unroll
         for (int db = 0; db < QB; ++db) __builtin_nontemporal_store(ok ? dka[db][r] : 0.0f, dkr + (size_t)row * DQ + db * 32);
@@ -293,6 +357,26 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
 #pragma unroll
           for (int r = 0; r < 16; ++r) dqa[db][r] += src[(db * 16 + r) * 64];
       }
+    }
+    if (__builtin_expect(any_not_finite(dqa), 0)) {   // as for the items: padding rows of a tile meet an infinite dH'
+      for (int c = cbase; c < C && c < cbase + 32; ++c) {
+        PlainRow<DQ> qr, kr, dqr;
+        PlainRow<D> hr, vr;
+        qr.load(q + ((size_t)u * C + c) * DQ, lane);
+        dqr.zero();
+        for (int i = i_beg; i < i_end; ++i) {
+          hr.load(dhp + (((size_t)u * C + c) * S + i) * D, lane);
+          const int hi = i * w + w < n ? i * w + w : n;
+          for (int j = i * w; j < hi; ++j) {
+            kr.load(k + ((size_t)u * L + j) * DQ, lane);
+            vr.load(v + ((size_t)u * L + j) * D, lane);
+            const float gt = gate(qr.dot(kr), neg_scale_log2e);
+            dqr.add(vr.dot(hr) * gt * (1.0f - gt) * inv_gamma, kr);
+          }
+        }
+        dqr.store(dq_part + (((size_t)u * sh.groups + grp) * C + c) * DQ, lane);
+      }
+      return;
     }
     float* out = dq_part + (((size_t)u * sh.groups + grp) * C) * DQ + l32;
 #pragma unroll

@@ -56,3 +56,41 @@ def test_sta_backward_on_the_matrix_cores(name):
     again = laser.laser_sta_backward(*args)
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(got, again))      # fixed summation order
+
+
+def _classes(x):
+    return np.where(np.isnan(x), 2, np.where(np.isposinf(x), 1, np.where(np.isneginf(x), -1, 0)))
+
+
+# which input, its value, and where: candidates and items that share their tile with padding
+@pytest.mark.parametrize("what", ["k", "v", "dh"])
+@pytest.mark.parametrize("bits", [0x7f80, 0xff80, 0x7fc0], ids=["inf", "-inf", "nan"])
+@pytest.mark.parametrize("name", ["five_candidates_one_item_tile", "33_candidates_segments_of_one_item",
+                                  "64_candidates_short_segments", "65_candidates_two_tiles_a_segment", "one_long_segment"])
+def test_not_finite_values_as_in_the_plain_sums(name, bits, what):
+    """Infinities and NaN give the gradients that the sums over the valid items and the present candidates give: padding of
+    the tiles takes no part."""
+    import torch
+    C, L, dq, d, w, lens = CASES[name]
+    U, S = len(lens), -(-L // w)
+    rng = np.random.default_rng(4200 + sum(map(ord, name)))
+    (qs, qv), (ks, kv), (vs, vv), (gs, gv) = (_store(rng.normal(size=s), "bf16")
+                                              for s in ((U, C, dq), (U, L, dq), (U, L, d), (U, C, S, d)))
+    lens = np.array(lens, dtype=np.int32)
+    x = {0x7f80: np.inf, 0xff80: -np.inf, 0x7fc0: np.nan}[bits]
+    at = {"k": (ks, kv, (0, lens[0] - 1, 3)), "v": (vs, vv, (0, lens[0] - 1, 3)), "dh": (gs, gv, (1, C - 1, (lens[1] - 1) // w, 5))}
+    stored, value, index = at[what]
+    stored[index], value[index] = bits, x
+    gamma = math.sqrt(dq)
+    print(f"case {name} {what} {x}", flush=True)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = oracle.sta_backward(qv, kv, vv, lens, w, gamma, gv)
+    got = laser.laser_sta_backward(to_device(qs), to_device(ks), to_device(vs), to_device(lens), to_device(gs), w, gamma)
+    torch.cuda.synchronize()
+    for nm, a, b in zip(("dq", "dk", "dv"), got, ref):
+        a = to_host_f64(a)
+        assert np.array_equal(_classes(a), _classes(b)), nm
+        a, b = np.where(np.isfinite(b), a, 0.0), np.where(np.isfinite(b), b, 0.0)
+        if nm == "dk":
+            a, b = a.reshape(U, -1), b.reshape(U, -1)
+        assert vec_rel_err(a, b) <= BWD_TOL, nm
