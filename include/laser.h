@@ -460,7 +460,7 @@ laser_status laser_sta_backward_static(const void* q, const void* k, const void*
  * is rounded once to dt. Limits: d <= 256,
  * M <= 8 and S d sizeof(dt) + ((M > 1 ? S d : 0) + (M + 7) d + 2 S + 4) * 4 bytes <= 150 KB; other shapes return LASER_ERR_UNSUPPORTED. work is caller-owned scratch
  * of at least laser_gsta_backward_work_bytes(U, C, d, M) bytes (six d-vectors per pair and layer, whose outer products
- * are the weight gradients, and partial sums of those); the library allocates nothing.
+ * are the weight gradients, and for many pairs partial sums of those); the library allocates nothing.
  * All pointers are device pointers, 16-byte aligned (lens 4-byte); outputs are fully overwritten; work is enqueued on
  * `stream`. Errors: LASER_ERR_NULL, LASER_ERR_SHAPE (sizes, work_bytes too small), LASER_ERR_DTYPE, LASER_ERR_ALIGN,
  * LASER_ERR_UNSUPPORTED, LASER_ERR_LAUNCH. Nothing is launched on an error.

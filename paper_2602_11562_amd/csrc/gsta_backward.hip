@@ -311,9 +311,19 @@ bool gsta_backward_supports(const GstaBwdArgs& a) {
   return a.d <= GB_MAXD && a.M <= GB_MAXM && gsta_bwd_lds(a) <= 150 * 1024;
 }
 
-// per-pair vectors [P][M][6][d], then the chunks' partial weight gradients [chunks][3][M][d][d]
+static int gsta_bwd_workgroups(int d, int M) { return M * 3 * ((d + 15) / 16) * ((d + 15) / 16); }
+
+// From 449 pairs on, where scratch with one set of partial weight gradients per 64 pairs, which programs may have kept from
+// an earlier size, holds eight.
+static int gsta_bwd_chunks(size_t P, int d, int M) {
+  return gsta_bwd_workgroups(d, M) < 128 && P > (GB_CHUNKS - 1) * 64 ? GB_CHUNKS : 1;
+}
+
+// per-pair vectors [P][M][6][d], then the chunks' partial weight gradients [chunks][3][M][d][d] if there are several
 size_t gsta_backward_work_bytes(int U, int C, int d, int M) {
-  return ((size_t)U * C * M * 6 * d + (size_t)GB_CHUNKS * M * 3 * d * d) * sizeof(float);
+  const size_t P = (size_t)U * C;
+  const int chunks = gsta_bwd_chunks(P, d, M);
+  return (P * M * 6 * d + (chunks > 1 ? (size_t)chunks * M * 3 * d * d : 0)) * sizeof(float);
 }
 
 laser_status gsta_backward_launch(const GstaBwdArgs& a) {
@@ -342,8 +352,7 @@ laser_status gsta_backward_launch(const GstaBwdArgs& a) {
                        a.L, a.d, a.w, a.S, a.M, (float*)a.dseg, a.dt0, a.work);
   }
   if (launch_status() != LASER_OK) return LASER_ERR_LAUNCH;
-  const int tiles = (a.d + 15) / 16, wgs = a.M * 3 * tiles * tiles;
-  const int chunks = wgs < 128 && P >= 256 ? GB_CHUNKS : 1;
+  const int wgs = gsta_bwd_workgroups(a.d, a.M), chunks = gsta_bwd_chunks((size_t)P, a.d, a.M);
   float* part = a.work + (size_t)P * a.M * 6 * a.d;
   hipLaunchKernelGGL(gsta_bwd_w_kernel, dim3((unsigned)(chunks * wgs)), dim3(1024), 0, a.stream, a.work, P, a.M, a.d, chunks,
                      part, a.dwq, a.dwk, a.dwv);

@@ -331,3 +331,14 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers(lib, tmp_pat
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=120)
     assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
     assert "0 failure(s)" in r.stdout
+
+
+def test_gsta_backward_scratch_is_no_larger_than_it_was(lib):
+    """Programs keep scratch of the size that the library once asked for: the vectors of all pairs and one set of partial weight
+    gradients per 64 pairs, 32 at most."""
+    lib.laser_gsta_backward_work_bytes.restype = ctypes.c_size_t
+    for d in (8, 64, 128, 256):
+        for M in (1, 2, 3, 8):
+            for P in [1, 2, 63, 64, 65, 255, 256, 257, 447, 448, 449, 512, 513, 2048, 100000]:
+                most = (P * M * 6 * d + min(32, -(-P // 64)) * M * 3 * d * d) * 4
+                assert P * M * 6 * d * 4 <= lib.laser_gsta_backward_work_bytes(P, 1, d, M) <= most, (d, M, P)
