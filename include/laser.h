@@ -57,7 +57,7 @@ typedef enum { LASER_F32 = 0, LASER_BF16 = 1, LASER_DTYPE_ANY_INT = 0x7fffffff }
  * and return LASER_ERR_UNSUPPORTED when the shape is outside that kernel's range. */
 typedef enum {
   LASER_STA_AUTO = 0,
-  LASER_STA_GENERIC = 1, /* fp32 arithmetic, any shape, either dtype                 */
+  LASER_STA_GENERIC = 1, /* fp32 FMA, any shape, either dtype                        */
   LASER_STA_MFMA = 2,    /* bf16 MFMA, many candidates per user                      */
   LASER_STA_STREAM = 3,  /* bf16, few candidates per user, HBM streaming             */
   LASER_STA_MFMA_CACHED = 4, /* LASER_STA_MFMA with H' stored cacheable instead of with the non-temporal hint: for a
@@ -68,7 +68,7 @@ typedef enum {
 /* Which GSTA kernel runs. */
 typedef enum {
   LASER_GSTA_AUTO = 0,
-  LASER_GSTA_GENERIC = 1, /* fp32 arithmetic, any shape                               */
+  LASER_GSTA_GENERIC = 1, /* fp32 FMA, one workgroup per pair, any shape              */
   LASER_GSTA_TILED = 2,   /* bf16 storage, d in {64, 128}: 1 to 16 pairs per workgroup, MFMA, any M and S */
   LASER_GSTA_SPLIT = 3,   /* bf16 storage, M = 1: projection / streaming / output kernels; z_out is the scratch */
   LASER_GSTA_ONE = 4,     /* bf16 storage, M = 1: the same three steps in one launch, 32 pairs per workgroup */

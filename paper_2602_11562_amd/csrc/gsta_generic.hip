@@ -1,5 +1,5 @@
-// Generic GSTA kernel: fp32 FMA arithmetic, one workgroup per (user, candidate), any shape (fp32 storage with d = 64 or
-// d = 128 runs on gsta_tiled.hip).
+// Generic GSTA kernel: fp32 FMA arithmetic, one workgroup per (user, candidate), any shape (unless it is asked for by name,
+// fp32 storage with d = 64 or d = 128 runs on gsta_tiled.hip).
 //
 // Per layer l (Sec. 3.4.3): a_l = softmax((t W_q)(H' W_k)^T / sqrt(d)), o_l = a_l (H' W_v), t += o_l.
 // The two products with H' are re-associated, which is exact up to rounding:
@@ -101,7 +101,6 @@ bool gsta_generic_supports(const GstaArgs& a) {
 
 laser_status gsta_generic_launch(const GstaArgs& a) {
   if (!gsta_generic_supports(a)) return LASER_ERR_UNSUPPORTED;
-  if (a.dt == LASER_F32 && gsta_tile_supports(a)) return gsta_tile_launch(a);
   const size_t lds = sizeof(float) * (4 * (size_t)a.d + a.S);
   const unsigned blocks = (unsigned)gsta_pairs(a);
   if (blocks == 0) return LASER_OK;

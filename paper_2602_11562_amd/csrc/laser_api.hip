@@ -118,7 +118,10 @@ static laser_gsta_variant pick_gsta(const GstaArgs& a) {
 }
 
 static laser_status run_sta(const StaArgs& a, laser_sta_variant variant) {
-  if (variant == LASER_STA_AUTO) variant = pick_sta(a);
+  if (variant == LASER_STA_AUTO) {
+    variant = pick_sta(a);
+    if (variant == LASER_STA_GENERIC && sta_generic_supports(a) && sta_f32_supports(a)) return sta_f32_launch(a);
+  }
   laser_status s;
   switch (variant) {
     case LASER_STA_GENERIC: s = sta_generic_launch(a); break;
@@ -136,7 +139,10 @@ static laser_status run_sta(const StaArgs& a, laser_sta_variant variant) {
 }
 
 static laser_status run_gsta(const GstaArgs& a, laser_gsta_variant variant) {
-  if (variant == LASER_GSTA_AUTO) variant = pick_gsta(a);
+  if (variant == LASER_GSTA_AUTO) {
+    variant = pick_gsta(a);
+    if (variant == LASER_GSTA_GENERIC && gsta_generic_supports(a) && gsta_tile_supports(a)) return gsta_tile_launch(a);
+  }
   switch (variant) {
     case LASER_GSTA_GENERIC: return gsta_generic_launch(a);
     case LASER_GSTA_TILED: return gsta_tiled_supports(a) ? gsta_tile_launch(a) : LASER_ERR_UNSUPPORTED;
@@ -169,7 +175,7 @@ static laser_status run_gsta_views(GstaArgs& ga, MultiresArgs& ma) {
     ga.r = ma.r;
     return run_gsta(ga, variant);
   }
-  const laser_status s = run_gsta(ga, variant);
+  const laser_status s = run_gsta(ga, LASER_GSTA_AUTO);
   if (s != LASER_OK) return s;
   return multires_launch(ma);
 }

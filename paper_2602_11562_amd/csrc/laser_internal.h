@@ -191,7 +191,7 @@ laser_status fused_stream_launch(const FusedArgs& a);
 // Each launcher returns LASER_ERR_UNSUPPORTED (launching nothing) when the shape is outside its range.
 bool sta_generic_supports(const StaArgs& a);
 laser_status sta_generic_launch(const StaArgs& a);
-bool sta_f32_supports(const StaArgs& a);   // fp32 storage at the usual widths: the generic variant's matrix-core form
+bool sta_f32_supports(const StaArgs& a);   // fp32 storage at the usual widths, on the matrix cores
 laser_status sta_f32_launch(const StaArgs& a);
 bool sta_mfma_supports(const StaArgs& a);
 laser_status sta_mfma_launch(const StaArgs& a);
@@ -204,7 +204,7 @@ laser_status sta_few_folded_launch(const StaArgs& a, const ProjHeadsArgs& p);
 
 bool gsta_generic_supports(const GstaArgs& a);
 laser_status gsta_generic_launch(const GstaArgs& a);
-// d in {64, 128}: tiles of 1 to 16 pairs, any number of layers (the tiled variant; the generic one for fp32 storage)
+// d in {64, 128}: tiles of 1 to 16 pairs, any number of layers (the tiled variant, and what AUTO runs for fp32 storage)
 bool gsta_tile_supports(const GstaArgs& a);
 laser_status gsta_tile_launch(const GstaArgs& a);
 bool gsta_tile_preferred(const GstaArgs& a);   // one layer, bf16: a batch too small for the forms that fill the machine

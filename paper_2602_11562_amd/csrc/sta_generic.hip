@@ -148,7 +148,6 @@ bool sta_generic_supports(const StaArgs& a) {
 
 laser_status sta_generic_launch(const StaArgs& a) {
   if (!sta_generic_supports(a)) return LASER_ERR_UNSUPPORTED;
-  if (sta_f32_supports(a)) return sta_f32_launch(a);
   const int TI = gen_pick_ti(a.d_q, a.d, a.heads);
   const size_t lds = gen_lds_bytes(TI, a.d_q, a.d, a.heads);
   const unsigned blocks = (unsigned)((long long)a.U * ((a.C + GEN_WAVES - 1) / GEN_WAVES) * a.S);

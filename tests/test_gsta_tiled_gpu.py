@@ -44,7 +44,7 @@ def test_gsta_tiled(name):
     for u, n in enumerate(lens):      # rows of segments without a valid item are never read
         Hs[u, :, -(-int(n) // w):] = np.nan if dtype == "f32" else 0x7fc0
     z = laser.laser_gsta_forward(to_device(Hs), to_device(ts), to_device(wqs), to_device(wks), to_device(wvs),
-                                 to_device(lens), L, w, variant=laser.GSTA_GENERIC if dtype == "f32" else laser.GSTA_TILED)
+                                 to_device(lens), L, w, variant=laser.GSTA_AUTO if dtype == "f32" else laser.GSTA_TILED)
     torch.cuda.synchronize()
     pick = slice(None) if C <= 8 else [0, 1, 2, 3, 5, 8, C // 2, C - 2, C - 1]
     ref = oracle.gsta_forward(Hv[:, pick], tv[:, pick], wqv, wkv, wvv, cnt)
@@ -131,3 +131,21 @@ def test_pooled_columns_of_minus_infinity(P, S):
     for p, n in ((0, S), (1, 2)):
         assert torch.equal(pool[p, 0], seg[p, 0, :n].max(dim=0).values)
     assert not pool[2].any()
+
+
+@pytest.mark.parametrize("U,C,S,d,M", [(2, 3, 11, 64, 2), (3, 100, 20, 128, 1)])
+def test_generic_by_name_in_fp32(U, C, S, d, M):
+    """The generic kernel stays an independent check of the tiled one in single precision: asked for by name it runs."""
+    import torch
+    rng = np.random.default_rng(6700 + C)
+    lens = np.array(([S, S // 3, 0] * U)[:U], dtype=np.int32)
+    seg, t0 = rng.normal(size=(U, C, S, d)).astype(np.float32), rng.normal(size=(U, C, d)).astype(np.float32)
+    W = [(rng.normal(size=(M, d, d)) / math.sqrt(d)).astype(np.float32) for _ in range(3)]
+    args = [to_device(x) for x in (seg, t0, *W, lens)]
+    print(f"U {U} C {C} S {S} d {d} M {M}", flush=True)
+    auto, generic = (laser.laser_gsta_forward(*args, S, 1, variant=v) for v in (laser.GSTA_AUTO, laser.GSTA_GENERIC))
+    torch.cuda.synchronize()
+    assert not torch.equal(auto, generic)          # (sums in another order)
+    ref = oracle.gsta_forward(seg[:, :3], t0[:, :3], *W, oracle.segment_counts(lens, S, 1))
+    for z in (auto, generic):
+        assert vec_rel_err(to_host_f64(z)[:, :3], ref) <= TOL["f32"]

@@ -75,3 +75,22 @@ def test_not_finite_items_stay_in_their_segment(name, x):
     assert np.array_equal(got[0, :, 0, 3], np.full(C, x), equal_nan=True)
     ref, _ = oracle.sta_forward(q[:2].astype(np.float64), k[:2].astype(np.float64), v[:2].astype(np.float64), lens[:2], w, gamma)
     assert vec_rel_err(np.where(bad[:2], 0.0, got[:2]), np.where(bad[:2], 0.0, ref)) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("name", ["17_candidates_two_tiles", "33_candidates_three_tiles"])
+def test_generic_by_name_in_fp32(name):
+    """The generic kernel stays an independent check of the matrix-core one: asked for by name it runs."""
+    import torch
+    C, L, dq, d, w, lens = STA_CASES[name]
+    U, gamma = len(lens), math.sqrt(dq)
+    rng = np.random.default_rng(5300 + sum(map(ord, name)))
+    q, k, v = (rng.normal(size=s).astype(np.float32) for s in ((U, C, dq), (U, L, dq), (U, L, d)))
+    lens = np.array(lens, dtype=np.int32)
+    print(f"case {name}", flush=True)
+    args = [to_device(x) for x in (q, k, v, lens)]
+    auto, generic = (laser.laser_sta_forward(*args, w, gamma, variant=x)[0] for x in (laser.STA_AUTO, laser.STA_GENERIC))
+    torch.cuda.synchronize()
+    assert not torch.equal(auto, generic)          # (sums in another order)
+    ref, _ = oracle.sta_forward(q, k, v, lens, w, gamma)
+    for seg in (auto, generic):
+        assert vec_rel_err(to_host_f64(seg), ref) <= TOL["f32"]
