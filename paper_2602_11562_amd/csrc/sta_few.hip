@@ -432,10 +432,29 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
 //   256, 4, 1000, 50         19 -> 16           21 -> 15         32 -> 23        21 -> 18
 //   1000, 8, 2048, 256      252 -> 93          145 -> 65        236 -> 140      349 -> 114
 //   256, 8, 8000, 512       266 -> 91          157 -> 60        286 -> 135      382 -> 106
+// The table's calls fill the machine. In one that does not, the time is the chain of tiles of one run (two at least, and a
+// segment is one run however long it is), and up to six rows the vector-ALU kernels, whose four waves share a long segment
+// and which start faster, are the better ones: 1 user x 2, L = 2000, w = 512, 64 / 64 6.6 us there, 14.7 here; 16 x 3,
+// L = 2048, w = 256, 32 / 64 6.0 and 8.5; 64 x 3, L = 200, w = 5, 128 / 128 6.0 and 7.0; 4 x 2, L = 2000, w = 2, 64 / 64 5.1 and
+// 7.4. The lines lie where the times of 3000 such calls (1 to 1500 users, 2 to 8 rows, every width, w = 1 to 1000) cross: 35
+// of those left here are more than 5 % slower than there, by 16 % at most.
+static bool few_fills(const StaArgs& a) {
+  const long long items = (long long)a.U * a.L, segs = (long long)a.U * a.S;
+  const bool narrow = a.d == 64;
+  if (a.C >= 7 || (a.w > 32 && a.w <= 100)) return true;
+  if (a.w > 100) return a.C >= (a.w <= 128 ? 4 : 6) || segs >= (a.C == 2 ? 1024 : 512);
+  if (a.w <= 4 && narrow) return items >= (a.C <= 4 ? 65536 >> a.C : 0);
+  if (a.w <= 4) return items >= (a.C <= 4 ? 32768 : 524288 >> a.C);
+  if (a.C == 2) return items >= (a.w <= 10 ? 65536 : 131072);
+  if (narrow || a.C == 6) return true;
+  if (a.C == 3) return items >= 65536;
+  return a.w > 10 || items >= (a.C == 4 ? 32768 : 8192);
+}
+
 bool sta_few_supports(const StaArgs& a) {
   if (a.dt != LASER_BF16 || a.C > 8 || a.heads != 1 || a.softmax) return false;
   if (!(a.d_q == 32 || a.d_q == 64 || a.d_q == 128) || !(a.d == 64 || a.d == 128)) return false;
-  return a.C > 2 || (a.C == 2 && a.d_q == 64 && a.d == 64);
+  return (a.C > 2 || (a.C == 2 && a.d_q == 64 && a.d == 64)) && few_fills(a);
 }
 
 laser_status sta_few_launch(const StaArgs& a) {
@@ -454,9 +473,12 @@ laser_status sta_few_launch(const StaArgs& a) {
 // The folded form: a is STA over the raw items (C query rows per user, heads of each candidate next to each other), p the
 // projection of its sums
 // 2048 users x 1 candidate x 2 heads, L = 1000, w = 10, lengths uniform in [200, 1000]: 112 us; the vector-ALU kernel over
-// the raw items and the projection of its stored sums took 101 + 33 us. More than four query rows do not fit the ring.
+// the raw items and the projection of its stored sums took 101 + 33 us. More than four query rows do not fit the ring. With
+// one or two rows, long segments and few of them the separate launches are the better ones, as above (whole chain, L = 1000,
+// w = 1000: 16 users x 1 row 21 us, 35 here; 64 x 2 rows 32 and 36; 64 x 1, L = 4000, w = 500 the same time).
 bool sta_few_folded_supports(const StaArgs& a, const ProjHeadsArgs& p) {
   if (a.dt != LASER_BF16 || a.C > 4 || a.k != a.v || a.d_q != 128 || a.d != 128) return false;
+  if (a.C <= 2 && a.w > 128 * a.C && (long long)a.U * a.S < 512) return false;
   return (p.d == 64 || p.d == 128) && p.d % p.heads == 0 && (p.d / p.heads) % 32 == 0;
 }
 

@@ -1,5 +1,5 @@
-// STA for one or two candidates per user (up to eight with two heads, with softmax and in the fused form): an HBM
-// streaming kernel on the vector ALUs. More candidates: sta_few.hip.
+// STA for one or two candidates per user (up to eight with two heads, with softmax, in the fused form and in calls that do
+// not fill the machine): an HBM streaming kernel on the vector ALUs. More candidates: sta_few.hip.
 //
 // With one or a few candidates the STA equation of Sec. 3.4.2 does about one flop per byte of history read, so
 // the matrix cores have nothing to amortise and the only thing that matters is that K and V are read once, in
@@ -626,11 +626,12 @@ static void launch_c(const StaArgs& a, float nsl) {
 #define LASER_STREAM_LAUNCH(CM)                                                                                      \
   do {                                                                                                               \
     if (short_seg && a.softmax) LASER_STREAM_SHORT(CM, true, false);                                                 \
-    else if constexpr (HEADS == 2 || CM <= 2) {   /* (one head, more rows: sta_few_kernel) */                        \
-      if (short_seg && nt) LASER_STREAM_SHORT(CM, false, true);                                                      \
-      else if (short_seg) LASER_STREAM_SHORT(CM, false, false);                                                      \
-      else if (nt) LASER_STREAM_LONG(CM, true);                                                                      \
+    else if ((HEADS == 1 && CM > 2) || !nt) {     /* (one head, more rows, large: sta_few_kernel) */                 \
+      if (short_seg) LASER_STREAM_SHORT(CM, false, false);                                                           \
       else LASER_STREAM_LONG(CM, false);                                                                             \
+    } else if constexpr (HEADS == 2 || CM <= 2) {                                                                    \
+      if (short_seg) LASER_STREAM_SHORT(CM, false, true);                                                            \
+      else LASER_STREAM_LONG(CM, true);                                                                              \
     }                                                                                                                \
   } while (0)
   if (a.C <= 1) LASER_STREAM_LAUNCH(1);

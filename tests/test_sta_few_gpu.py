@@ -23,6 +23,12 @@ CASES = {
     "short_last_segment": (7, 129, 128, 64, 64, [129, 128, 65]),
     "one_segment_longer_than_the_history": (4, 77, 32, 128, 2000, [77, 76, 1]),
     "more_units_than_waves": (4, 40, 64, 64, 4, [(7 * i) % 41 for i in range(700)]),
+    # (one to six rows in calls too small to fill the machine run on the vector-ALU kernels; the same edges in larger ones)
+    "one_item_segments_of_many_users": (3, 70, 32, 64, 1, [70, 0, 33, 1, 70, 69] * 50),
+    "two_rows_of_many_users": (2, 100, 64, 64, 7, [100, 99, 8, 0] * 170),
+    "three_wide_rows_of_many_users": (3, 130, 128, 128, 9, [130, 129, 28, 9] * 130),
+    "long_segments_of_many_users": (4, 133, 32, 128, 131, [133, 132, 131, 1] * 130),
+    "two_rows_long_segments": (2, 134, 64, 64, 2000, [134, 33, 1, 0] * 1030),
 }
 
 
@@ -52,12 +58,12 @@ def test_sta_few(name):
     torch.cuda.synchronize()
     assert np.array_equal(cnt.cpu().numpy(), oracle.segment_counts(lens, L, w))
     got = to_host_f64(seg)
-    for u in (range(U) if U <= 8 else [0, 1, 5, 6, 40, 41, 350, U - 1]):
+    for u in (range(U) if U <= 8 else [0, 1, 2, 3, 5, 6, 40, 41, U // 2, U - 1]):
         ref, _ = oracle.sta_forward(q[1][u:u + 1], k[1][u:u + 1], v[1][u:u + 1], lens[u:u + 1], w, gamma)
         assert vec_rel_err(got[u:u + 1], ref) <= TOL["bf16"], u
 
 
-@pytest.mark.parametrize("name", ["two_rows", "block_ends_inside_tiles", "short_last_segment"])
+@pytest.mark.parametrize("name", ["two_rows", "block_ends_inside_tiles", "short_last_segment", "two_rows_of_many_users"])
 @pytest.mark.parametrize("bits", [0x7f80, 0xff80, 0x7fc0], ids=["inf", "-inf", "nan"])
 def test_not_finite_items_stay_in_their_segment(name, bits):
     import torch
@@ -68,7 +74,8 @@ def test_not_finite_items_stay_in_their_segment(name, bits):
     seg, _ = laser.laser_sta_forward(to_device(q[0]), to_device(kn), to_device(vn), to_device(lens), w, gamma)
     torch.cuda.synchronize()
     got = to_host_f64(seg)
-    ref, _ = oracle.sta_forward(q[1], k[1], v[1], lens, w, gamma)
+    got, lens = got[:8], lens[:8]
+    ref, _ = oracle.sta_forward(q[1][:8], k[1][:8], v[1][:8], lens, w, gamma)
     bad = np.zeros(ref.shape, dtype=bool)
     bad[0, :, 5 // w, 3] = True
     bad[1, :, (2 * w % lens[1]) // w] = True
@@ -98,6 +105,11 @@ FOLDED = {
     "two_candidates_two_heads": (2, 2, 64, 200, 33, [200, 66, 67]),
     "three_candidates": (3, 1, 128, 65, 64, [65, 64]),
     "one_row": (1, 1, 64, 50, 50, [50, 0]),
+    # three launches: more rows than the ring holds; one and two rows, long segments and few of them
+    "five_rows": (5, 1, 128, 130, 10, [130, 101]),
+    "eight_rows": (4, 2, 64, 200, 64, [200, 65, 64]),
+    "one_row_long_segments": (1, 1, 128, 300, 140, [300, 141, 0]),
+    "two_rows_long_segments": (1, 2, 128, 300, 260, [300, 259]),
 }
 
 
