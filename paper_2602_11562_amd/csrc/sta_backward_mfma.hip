@@ -418,8 +418,12 @@ static StaBwdMfmaShape sta_bwd_mfma_shape(const StaBwdArgs& a, int max_groups) {
 // faster one (2048 users x 4, L = 1000, w = 10, 32 / 128: 586 us against 819 us here; 512 x 4, L = 2000, w = 64, 128 / 128:
 // 356 against 470 us; 64 / 64 the other way round, 188 against 126 us); beyond four the alternative is one item per wave,
 // eight candidates a pass: 512 x 5, L = 1000, w = 10, 32 / 128: 260 against 168 us, 512 x 8, w = 64, 128 / 128: 475 against
-// 158 us.
+// 158 us. Not for segments so short that their tiles of 32 items x 32 candidates are nearly empty, where there are enough of
+// them to fill the machine (us, the other kernel / here; L = 300): 1024 users x 5, w = 1, 128 / 64 377 / 890, 512 x 8, w = 3,
+// 64 / 128 the same way by 1.46, 512 x 5, w = 5, 128 / 128 by 1.59, w = 6 even; the second pass that nine candidates cost there
+// moves the line to 18 products of a segment, and from 13 on this kernel is the better one for any segment.
 bool sta_bwd_mfma_supports(const StaBwdArgs& a) {
+  if ((long long)a.U * a.S >= 6144 && (long long)a.C * a.w <= (a.C <= 8 ? 25 : a.C <= 12 ? 18 : 0)) return false;
   return a.dt == LASER_BF16 && !a.grads_bf16 && a.C > 4 && (a.d_q == 32 || a.d_q == 64 || a.d_q == 128) &&
          (a.d == 64 || a.d == 128);
 }

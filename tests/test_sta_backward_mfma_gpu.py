@@ -58,6 +58,28 @@ def test_sta_backward_on_the_matrix_cores(name):
     assert all(torch.equal(x, y) for x, y in zip(got, again))      # fixed summation order
 
 
+@pytest.mark.parametrize("C,w", [(5, 5), (8, 3), (9, 2), (8, 4)])   # either side of the line: nearly empty tiles
+def test_many_short_segments(C, w):
+    import torch
+    L, dq, d, U = 60, 64, 64, 6144 * w // 60 + 1
+    S = -(-L // w)
+    rng = np.random.default_rng(4300 + C + w)
+    (qs, qv), (ks, kv), (vs, vv), (gs, gv) = (_store(rng.normal(size=s), "bf16")
+                                              for s in ((U, C, dq), (U, L, dq), (U, L, d), (U, C, S, d)))
+    lens = rng.integers(0, L + 1, U).astype(np.int32)
+    gamma = math.sqrt(dq)
+    print(f"C {C} w {w} users {U}", flush=True)
+    got = laser.laser_sta_backward(*(to_device(x) for x in (qs, ks, vs, lens, gs)), w, gamma)
+    torch.cuda.synchronize()
+    pick = [0, 1, 2, U // 2, U - 1]
+    ref = oracle.sta_backward(qv[pick], kv[pick], vv[pick], lens[pick], w, gamma, gv[pick])
+    for nm, a, b in zip(("dq", "dk", "dv"), got, ref):
+        a = to_host_f64(a)[pick]
+        if nm == "dk":
+            a, b = a.reshape(len(pick), -1), b.reshape(len(pick), -1)
+        assert vec_rel_err(a, b) <= BWD_TOL, nm
+
+
 def _classes(x):
     return np.where(np.isnan(x), 2, np.where(np.isposinf(x), 1, np.where(np.isneginf(x), -1, 0)))
 
