@@ -404,8 +404,10 @@ static bool sta_bwd_wide_supports(const StaBwdArgs& a);
 // length classes: worth their empty workgroups once the launch is several rounds of workgroups and lengths differ, but not
 // for short segments, whose runs are short whatever the history: in plain order the workgroups in flight sweep memory front
 // to back (2048 users x 100 segments of 10 items, lengths 200..1000: 240 us with four classes, 211 with one)
-static int sta_bwd_classes(const StaBwdArgs& a, unsigned blocks) {
-  int classes = (a.lens != nullptr && a.w > 32 && blocks >= 4096 && (unsigned long long)blocks * 4 <= 0x7fffffffULL) ? 4 : 1;
+// (360 of 363 other calls up to w = 32 the same way, 0.76 to 1.02 times the time). The one-item kernel with more than two
+// candidates works longer on a segment: its line is lower (2048 x 8, L = 300, w = 20, fp32: 454 us with classes, 481 without).
+static int sta_bwd_classes(const StaBwdArgs& a, unsigned blocks, int short_w) {
+  int classes = (a.lens != nullptr && a.w > short_w && blocks >= 4096 && (unsigned long long)blocks * 4 <= 0x7fffffffULL) ? 4 : 1;
   const int cls_forced = tuning_int("LASER_STREAM_CLASSES", 0);   // tuning builds only, shared with the forward kernel
   if (cls_forced >= 1 && cls_forced <= 8 && (unsigned long long)blocks * cls_forced <= 0x7fffffffULL) classes = cls_forced;
   return classes;
@@ -426,7 +428,7 @@ template <typename T, int TQ, int TV>
 static void sta_bwd_launch_c(const StaBwdArgs& a, unsigned blocks, size_t lds, int spg, int groups) {
   const float inv_gamma = 1.0f / a.gamma;
   const float nsl = -1.4426950408889634f * inv_gamma;
-  const int classes = sta_bwd_classes(a, blocks);
+  const int classes = sta_bwd_classes(a, blocks, a.C <= 2 ? 32 : 16);
   // more than SB_CMAX candidates per user: one launch per block of SB_CMAX, in order on the stream; the first
   // writes dk and dv (and the zeros of the padding rows), the others add to them
 #define LASER_BWD_LAUNCH(CM)                                                                                          \
@@ -468,7 +470,7 @@ template <int DQ, int D>
 static void sta_bwd_wide_launch(const StaBwdArgs& a, unsigned blocks, int spg, int groups) {
   const float inv_gamma = 1.0f / a.gamma;
   const float nsl = -1.4426950408889634f * inv_gamma;
-  const int classes = sta_bwd_classes(a, blocks);
+  const int classes = sta_bwd_classes(a, blocks, 32);
   // Histories and gradients that together are more than the last-level cache (256 MB) holds, with the non-temporal hint:
   // 2048 users x 1000 items of 320 bytes (1.05 GB) 211 -> 196 us; 256 such users (131 MB) 28 -> 34 us
   const bool nt = (double)a.U * a.L * (DQ + D) * (a.grads_bf16 ? 4 : 6) >= 600.0e6;
