@@ -1054,26 +1054,32 @@ static bool is_direct(const StaArgs& a) {
   return a.heads == 1 && !a.softmax && a.d_q == 128 && a.d == 128 && tuning_int("LASER_STA_NODMA", 0) == 0;
 }
 
-// Waves (32 candidates each) per workgroup. Segments shorter than a staged tile (64 items) keep the waves of a workgroup
-// waiting for each other once per segment: two workgroups of four waves on a compute unit are then better than one of eight,
-// and waste fewer candidate slots (64 users x 256 candidates x 100 segments of 10 items, d_q = 32, d = 128, two heads: 104 ->
-// 102 us; 64 x 320, w = 20: 74 -> 64; 10 x 400, w = 32, 64/64: 36 -> 25); from w = 64 on eight are (32 x 256, L = 4096,
-// w = 128, 64/64: 21 against 24 us; 8 x 512, w = 256: 21 against 25).
+// Waves (32 candidates each) per workgroup. Past 128 candidates one workgroup of eight on a compute unit, or two of four,
+// which wait less for each other where segments are shorter than a staged tile (64 items) and have no empty half where the
+// candidates fill an odd number of fours. Four for such segments if that number is odd (64 users x 320 candidates, w = 20:
+// 74 -> 64 us), if they are short (up to 20 items; 32 x 256, w = 10, 128 / 64: 37 -> 32; not with softmax or, past 256
+// candidates, several heads, whose state in registers makes eight the better ones: 20 x 512, four heads, softmax 74 against
+// 109), or if eight would leave compute units without work (8 x 256, w = 56: 11.9 -> 10.3). From w = 64 on eight (32 x 256,
+// L = 4096, w = 128, 64 / 64: 21 against 24 us).
 static int pick_nw(const StaArgs& a) {
   const int vv = tuning_int("LASER_STA_NW", 0);   // tuning builds
   if (vv == 1 || vv == 2 || vv == 4 || vv == 8) return vv;
-  if (a.C > 128 && (is_direct(a) || a.w >= TI)) return 8;
-  return a.C > 64 ? 4 : (a.C > 32 ? 2 : 1);
+  if (a.C <= 128) return a.C > 64 ? 4 : (a.C > 32 ? 2 : 1);
+  if (is_direct(a) || a.w >= TI) return 8;
+  const bool odd = ((a.C + 127) / 128) % 2 != 0;
+  const bool short_seg = a.w <= 20 && !a.softmax && (a.C <= 256 || a.heads == 1);
+  return odd || short_seg || (long long)a.U * ((a.C + 255) / 256) * a.S <= 256 ? 4 : 8;
 }
 
 // Consecutive segments per workgroup of the register-staged forms (they share the query registers and the prefetch
 // pipeline). One and two waves: as many as still leave a few workgroups per compute unit (64 users x 64 candidates x 16
 // segments, two waves: 15.1 us with 512 workgroups of two segments, 11.2 us with 1024 of one). Four waves, two workgroups on
 // a compute unit, and eight, one on it: the smallest estimate of rounds of workgroups times the length of one, in segments,
-// with half a segment for its start and half a round for the last one. It follows the measured times to within a tenth (two
-// heads, w = 10, four waves, 12800 segments in all, 1 / 2 / 4 / 6 / 8 / 12 / 16 per workgroup: 114, 102, 98, 96, 101, 105,
-// 119 us); 48 users x 512 candidates, w = 40: 58 -> 42 us, 40 x 130, w = 50: 28 -> 22 us against as many segments as filled
-// the chip once.
+// each with a constant for what starting costs. The constants are those that came closest to the best of 1 to 16 segments
+// over 292 calls (2 to 128 users, 65 to 512 candidates, w = 5 to 256, every width, up to four heads, both kinds of gate): 5 %
+// above it on average, where as many segments as still filled the chip once were 15 % above and cost up to 1.8 times the
+// best (two heads, w = 10, four waves, 12800 segments in all, 1 / 2 / 4 / 6 / 8 / 12 / 16 per workgroup: 114, 102, 98, 96, 101,
+// 105, 119 us).
 static int pick_spw(const StaArgs& a, int nw, int ctiles) {
   const long long per = (long long)a.U * ctiles;
   int best = 1;
@@ -1081,11 +1087,10 @@ static int pick_spw(const StaArgs& a, int nw, int ctiles) {
     while (best < 8 && per * ((a.S + 2 * best - 1) / (2 * best)) >= 2048 / nw) best *= 2;
     return best;
   }
-  const double slots = nw == 8 ? 256.0 : 512.0;
   double least = 0.0;
   for (int spw : {1, 2, 3, 4, 6, 8, 12, 16}) {
-    const double rounds = per * ((a.S + spw - 1) / spw) / slots;
-    const double cost = (nw == 8 && rounds <= 1.0 ? 1.0 : (rounds > 0.5 ? rounds : 0.5) + 0.5) * (spw + 0.5);
+    const double rounds = per * ((a.S + spw - 1) / spw) / (nw == 8 ? 256.0 : 512.0);
+    const double cost = nw == 4 ? (rounds + 0.7) * (spw + 0.75) : (rounds <= 1.0 ? 1.0 : rounds + 0.3) * (spw + 0.4);
     if (spw == 1 || cost < least) {
       best = spw;
       least = cost;

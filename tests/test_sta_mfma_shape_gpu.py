@@ -21,6 +21,12 @@ CASES = {
     "257_candidates_short_last_segment": (2, 257, 101, 32, 128, 20, 1),
     "two_heads_many_segments": (4, 140, 251, 32, 128, 2, 2),
     "65_candidates_runs_past_the_end": (30, 65, 190, 128, 64, 10, 1),
+    # eight waves below w = 64 (an even number of fours, enough segments), and four for an odd number or short segments
+    "200_candidates_w40": (45, 200, 240, 64, 64, 40, 1),
+    "300_candidates_w40": (45, 300, 240, 64, 64, 40, 1),
+    "256_candidates_w20": (45, 256, 240, 64, 64, 20, 1),
+    "384_candidates_two_heads_w21": (20, 384, 270, 32, 128, 21, 2),
+    "512_candidates_two_heads_w20": (20, 512, 270, 64, 64, 20, 2),
 }
 
 
