@@ -26,7 +26,7 @@ namespace laser {
 
 // PW: pairs per workgroup; R: row loads per lane and round; RES: one round holds every row (H' stays in registers)
 template <typename T, int D, int PW, int R, bool RES>
-__global__ __launch_bounds__(4 * D) void gsta_tiled_kernel(const T* __restrict__ seg, const T* __restrict__ t0,
+__global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kernel(const T* __restrict__ seg, const T* __restrict__ t0,
                                                           const T* __restrict__ wq, const T* __restrict__ wk,
                                                           const T* __restrict__ wv, const int32_t* __restrict__ lens,
                                                           const int32_t* __restrict__ cand_off, int U, int P, int C,
@@ -262,7 +262,14 @@ static void launch_pairs(const GstaArgs& a, int P) {
   // eight rows a lane fit the registers beside the matrices up to eight pairs (sixteen where a wave has two of them and
   // rows are bf16; otherwise they spill or leave one wave per SIMD), twelve for eight pairs of bf16 rows
   constexpr bool EIGHT = PW == 4 || PW == 8 || (PW == 16 && D == 128 && sizeof(T) == 2);
-  if (a.S <= 4 * HELD) LASER_TILED(4, true);
+  // Sixteen pairs of few rows, d = 128: with two or three rows a lane the registers suffice for two workgroups on a compute
+  // unit, which hide each other's chains (two layers, S = 4: 8192 pairs 25.3 -> 20.5 us, 65536 pairs 187 -> 125; S = 12: 25.2 ->
+  // 23.7 and 188 -> 149, but 13.4 -> 15.1 for 4096 pairs, one workgroup a compute unit; the form with 32-pair tiles that this
+  // kernel replaced took 20.4, 165, 23.1 and 191)
+  constexpr bool FEW = PW == 16 && D == 128 && sizeof(T) == 2;
+  if (FEW && a.S <= 2 * HELD) LASER_TILED((FEW ? 2 : 4), true);
+  else if (FEW && a.S <= 3 * HELD && P > 256 * PW) LASER_TILED((FEW ? 3 : 4), true);
+  else if (a.S <= 4 * HELD) LASER_TILED(4, true);
   else if constexpr (EIGHT) {
     if (a.S <= 8 * HELD) LASER_TILED(8, true);
     else if constexpr (PW == 8 && D == 128 && sizeof(T) == 2) {
