@@ -64,6 +64,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
   constexpr int RP = D + 4;
   constexpr int R = 16 / (int)sizeof(T) / 2;                      // rows of H' in flight per lane: 4 or 2
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  __shared__ int some_of[16];                                     // the pair has a valid segment
   typename X::Act& ba = *reinterpret_cast<typename X::Act*>(lds);
   typename X::Act& bb = *reinterpret_cast<typename X::Act*>(lds + sizeof(typename X::Act));
   unsigned char* at = lds + 2 * sizeof(typename X::Act);
@@ -86,13 +87,11 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
   typename X::Operand rk, rv, rq;
   X::load_cols(cq, wq, n0, lane);
   f32x4 t, g;                                                     // pair g4 + r, column col
-  bool some[4];                                                   // the pair has a valid segment
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int p = pbase + g4 + r < P ? pbase + g4 + r : P - 1;
     t[r] = g4 + r < PW ? load_as_f32(t0, (size_t)p * D + col) : 0.0f;
     g[r] = g4 + r < PW ? dz[(size_t)p * D + col] : 0.0f;
-    some[r] = valid_len(lens, p / C, L) > 0;
   }
   X::load_rows(rk, wk, n0, lane);
   int nv[PPW];
@@ -104,6 +103,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     const int pr = pbase + pj < P ? pbase + pj : P - 1;
     nv[i] = __builtin_amdgcn_readfirstlane((valid_len(lens, pr / C, L) + w - 1) / w);
     H[i] = seg + (size_t)pr * S * D + gl * 8;
+    if (lane == 0) some_of[pj] = nv[i] > 0;
   }
   auto load_h = [&](Row8<T> (&x)[R], int i, int k0) {             // rows at or past nv: the last valid one, weight zero
     const int last = nv[i] > 0 ? nv[i] - 1 : 0;
@@ -120,13 +120,10 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     for (int r = 0; r < 4; ++r)
       if (g4 + r < PW) X::put(b, g4 + r, col, x[r]);
   };
-  // one of the six vectors of a pair and layer: zeros without a valid segment, like p and dr there (products of a zero with
-  // a target or gradient that is not finite are NaN)
-  auto put_scratch = [&](int l, int slot, const f32x4& x) {
+  auto put_scratch = [&](int l, int slot, const f32x4& x) {       // one of the six vectors of a pair and layer
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (g4 + r < PW && pbase + g4 + r < P)
-        pv[(((size_t)(pbase + g4 + r) * M + l) * 6 + slot) * D + col] = some[r] ? x[r] : 0.0f;
+      if (g4 + r < PW && pbase + g4 + r < P) pv[(((size_t)(pbase + g4 + r) * M + l) * 6 + slot) * D + col] = x[r];
   };
   auto put_rows = [&](int l, int off, const f32x4& x, float f) {  // into the (pair, layer) block
 #pragma unroll
@@ -378,6 +375,10 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
 #pragma unroll
   for (int r = 0; r < 4; ++r)
     if (g4 + r < PW && pbase + g4 + r < P) dt0[(size_t)(pbase + g4 + r) * D + col] = g[r];
+  // A pair without a valid segment adds nothing to the weight gradients, whatever its target and dz hold: its vectors, of which p
+  // and dr are zeros already, are overwritten with zeros (zero times a value that is not finite is NaN).
+  for (unsigned long long m = __ballot(lane < PW && pbase + lane < P && some_of[lane & 15] == 0); m != 0; m &= m - 1)
+    for (int e = tid; e < M * 6 * D; e += 4 * D) pv[(size_t)(pbase + __builtin_ctzll(m)) * M * 6 * D + e] = 0.0f;
 }
 
 template <typename T, int D>
