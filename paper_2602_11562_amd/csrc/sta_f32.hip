@@ -22,6 +22,9 @@ namespace laser {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// the value row of items past a segment's end: an infinity in a valid row would make their zero gates NaN
+__device__ float sta_f32_zeros[128];
+
 // NCT: candidate tiles of 16 per wave
 template <int DQ, int D, int NCT>
 __global__ __launch_bounds__(256) void sta_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
@@ -75,15 +78,11 @@ __global__ __launch_bounds__(256) void sta_f32_kernel(const float* __restrict__ 
       for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kU + (size_t)krow * DQ + j * 16);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = t0 + g * 4 + r < hi ? t0 + g * 4 + r : hi - 1;
+        const int row = t0 + g * 4 + r;
+        const float* v_row = row < hi ? vU + (size_t)row * D : sta_f32_zeros + l16;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) vf[r][db] = vU[(size_t)row * D + db * 16];
+        for (int db = 0; db < DB; ++db) vf[r][db] = v_row[db * 16];
       }
-      if (t0 + 16 > hi)   // the rows past the end are zeros: the last one may hold an infinity, which a zero gate would make NaN
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int db = 0; db < DB; ++db) vf[r][db] = t0 + g * 4 + r < hi ? vf[r][db] : 0.0f;
 #pragma unroll
       for (int c = 0; c < NCT; ++c) {
         f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
