@@ -56,9 +56,11 @@ def test_gsta_tiled(name):
 
 
 # pairs, S, d, r: the views from the tiled form (waves that share a pair, one and several pairs a wave, streamed rows) and,
-# from 8193 pairs with 33 rows on, from the split form; equal to the two entry points apart, bit for bit
+# from larger batches on from the one-kernel form (with and without room for the recent rows) and the split form; equal to
+# the two entry points apart, bit for bit
 @pytest.mark.parametrize("P,S,d,r", [(3, 5, 128, 5), (300, 40, 128, 3), (1200, 9, 64, 1), (2500, 70, 128, 8),
-                                     (5000, 33, 64, 0), (8193, 33, 128, 2)])
+                                     (5000, 33, 64, 0), (8193, 33, 128, 2), (4097, 9, 128, 3), (4099, 30, 128, 30),
+                                     (8195, 20, 64, 2), (4097, 40, 64, 3), (16385, 70, 64, 5)])
 def test_views_of_every_form(P, S, d, r):
     import torch
     gen = torch.Generator(device="cuda").manual_seed(P)

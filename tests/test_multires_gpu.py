@@ -113,12 +113,13 @@ def test_whole_path_with_all_views(name, over, r):
 
 
 @pytest.mark.parametrize("name,over,r", [
-    ("cfg3_high_fanout", dict(U=2, L=1024 + 128), 3),      # one-kernel form: the views come out of the GSTA kernel
-    ("cfg3_high_fanout", dict(U=2, C=40, L=1000, w=10), 8),   # 100 segments: split form, views from its streaming kernel
-    ("cfg2_bf16", dict(U=5, C=9, L=2048, w=16), 128),      # split form, d = 64, r = S, ragged lengths (some rows invalid)
-    ("cfg3_high_fanout", dict(U=3, C=5, L=1000, w=10), 100),  # split form, r = S, few pairs
-    ("cfg5_lifelong", dict(U=1, L=2 * 256 + 16), 2),       # M = 2: the views take a launch of their own
-    ("cfg1_tiny_f32", dict(), 5),                          # fp32: the same
+    # bf16, M = 1, few pairs: the views come out of the tiled form (test_gsta_tiled_gpu.py has the forms of larger batches)
+    ("cfg3_high_fanout", dict(U=2, L=1024 + 128), 3),
+    ("cfg3_high_fanout", dict(U=2, C=40, L=1000, w=10), 8),   # 100 segments
+    ("cfg2_bf16", dict(U=5, C=9, L=2048, w=16), 128),      # d = 64, r = S, ragged lengths (some rows invalid)
+    ("cfg3_high_fanout", dict(U=3, C=5, L=1000, w=10), 100),  # r = S
+    ("cfg5_lifelong", dict(U=1, L=2 * 256 + 16), 2),       # M = 2: the tiled form
+    ("cfg1_tiny_f32", dict(), 5),                          # fp32: the views take a launch of their own
 ])
 def test_gsta_with_views_from_a_stored_h(name, over, r):
     """laser_gsta_forward_multires = laser_gsta_forward + laser_multires_forward on the same H', bit for bit, and the

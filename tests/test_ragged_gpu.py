@@ -1,6 +1,6 @@
 """GPU parity of the packed-pairs entry points (ragged candidate counts per user) against the fp64 checker, element by
-element, on shapes that reach every STA and GSTA kernel family; equal counts must reproduce the dense entry points
-bit for bit. Stored inputs on both sides; tolerances as everywhere (fp32 1e-5, bf16 2e-2 per output vector; GSTA reads
+element, on shapes that reach every STA kernel family and GSTA in tiles of a few pairs; the GSTA forms for large batches on
+batches of their size, on sampled pairs; equal counts must reproduce the dense entry points bit for bit. Stored inputs on both sides; tolerances as everywhere (fp32 1e-5, bf16 2e-2 per output vector; GSTA reads
 H' as stored)."""
 import math
 
@@ -27,6 +27,8 @@ CASES = {
     "streaming_short_segments": ("bf16", 1000, 32, 128, 10, 1, 2, [2, 0, 1, 2, 1], [1000, 1000, 404, 7, 0]),
     "many_segments_split_gsta": ("bf16", 2560, 128, 128, 64, 1, 40, [40, 7], [2560, 1000]),
     "generic_f32": ("f32", 130, 24, 48, 16, 2, 5, [5, 0, 2, 4], [130, 130, 50, 17]),
+    "matrix_core_f32": ("f32", 130, 32, 64, 20, 2, 40, [5, 0, 40, 17, 16], [130, 130, 50, 17, 81]),
+    "matrix_core_f32_wide": ("f32", 200, 128, 128, 64, 1, 70, [70, 33, 0, 1], [200, 65, 9, 0]),
 }
 
 
@@ -107,6 +109,42 @@ def test_equal_counts_reproduce_the_dense_entry_points(shape):
     torch.cuda.synchronize()
     assert torch.equal(seg_d.view(torch.int16).view(U * C, -1, d), seg_r.view(torch.int16))
     assert torch.equal(cnt_d, cnt_r) and torch.equal(z_d.view(U * C, d), z_r)
+
+
+# just past the sizes up to which tiles of a few pairs are taken: the one-kernel form and the split form
+@pytest.mark.parametrize("P,S,d", [(4100, 12, 128), (8200, 40, 128), (8200, 20, 64), (4100, 50, 64), (16400, 70, 64)])
+def test_gsta_of_many_packed_pairs(P, S, d):
+    import torch
+    U, cmax = 90, 400
+    rng = np.random.default_rng(P + S)
+    cuts = np.sort(rng.integers(0, P + 1, U - 1))
+    cuts[3], cuts[50] = cuts[2], cuts[49]                      # users without candidates
+    off = np.concatenate([[0], cuts, [P]])
+    while np.diff(off).max() > cmax:                           # (no user past the largest count)
+        u = int(np.argmax(np.diff(off)))
+        v = int(np.argmin(np.diff(off)[10:])) + 10
+        n = np.diff(off)
+        n[u], n[v] = n[u] - (n[u] - cmax), n[v] + (n[u] - cmax)
+        off = np.concatenate([[0], np.cumsum(n)])
+    off = off.astype(np.int32)
+    lens = rng.integers(0, S + 1, U).astype(np.int32)
+    lens[0], lens[1] = S, 0
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
+    seg, t0 = rnd(P, S, d), rnd(P, d)
+    W = [(rnd(1, d, d).float() / math.sqrt(d)).bfloat16() for _ in range(3)]
+    print(f"P {P} S {S} d {d}", flush=True)
+    _, _, z = laser.laser_forward_ragged(None, rnd(U, S, 8), rnd(U, S, d), t0, *W, to_device(lens), to_device(off), cmax, 1, 1.0,
+                                         seg_out=seg, stage="gsta")
+    of = np.repeat(np.arange(U), np.diff(off))
+    dense = laser.laser_gsta_forward(seg[:, None], t0[:, None], *W, to_device(lens[of]), S, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(z, dense[:, 0])
+    Wv = [to_host_f64(x) for x in W]
+    zh = to_host_f64(z)
+    for p in [0, 1, 31, 32, int(off[4]), int(off[50]), P // 2, P - 33, P - 1]:
+        ref = oracle.gsta_pair(to_host_f64(seg[p]), to_host_f64(t0[p]), *Wv, np.arange(S) < lens[of[p]])
+        assert vec_rel_err(zh[p], ref) <= TOL["bf16"], p
 
 
 def test_offsets_that_break_the_rules_stay_inside_the_buffers():

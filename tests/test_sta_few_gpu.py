@@ -137,3 +137,41 @@ def test_folded(name):
     assert vec_rel_err(to_host_f64(g), g_ref) <= TOL["bf16"]
     ref = oracle.project_heads(to_host_f64(g).reshape(U * C, heads, S, din), wv[1], heads).reshape(U, C, S, -1)
     assert vec_rel_err(to_host_f64(seg), ref) <= TOL["bf16"]
+
+
+# Histories past the last-level cache, which are read with the non-temporal hint. rows, L, d_q, d, w, users (lengths full)
+@pytest.mark.parametrize("rows,dq,d,w", [(3, 64, 64, 10), (1, 64, 64, 10), (1, 64, 64, 100), (3, 128, 128, 64)])
+def test_histories_past_the_cache(rows, dq, d, w):
+    import torch
+    L = 1000
+    U = 300_000_000 // (L * (dq + d) * 2) + 1
+    gen = torch.Generator(device="cuda").manual_seed(rows * w)
+    q, k, v = (torch.randn(*s, device="cuda", generator=gen).bfloat16() for s in ((U, rows, dq), (U, L, dq), (U, L, d)))
+    gamma = math.sqrt(dq)
+    print(f"rows {rows} {dq}/{d} w {w} users {U}", flush=True)
+    seg, _ = laser.laser_sta_forward(q, k, v, None, w, gamma)
+    torch.cuda.synchronize()
+    for u in (0, 1, U // 2, U - 1):
+        ref, _ = oracle.sta_forward(*(to_host_f64(x[u:u + 1]) for x in (q, k, v)), None, w, gamma)
+        assert vec_rel_err(to_host_f64(seg[u:u + 1]), ref) <= TOL["bf16"], u
+
+
+@pytest.mark.parametrize("rows", [1, 4])
+def test_folded_histories_past_the_cache(rows):
+    import torch
+    U, L, w, din = 1201, 1000, 10, 128
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
+    t, h = rnd(U, rows, din), rnd(U, L, din)
+    A, wv = rnd(din, din) / math.sqrt(din), rnd(din, din) / math.sqrt(din)
+    lens = torch.full((U,), L, device="cuda", dtype=torch.int32)
+    g = torch.empty((U, rows, L // w, din), dtype=torch.bfloat16, device="cuda")
+    qf = torch.empty((U, rows, din), dtype=torch.bfloat16, device="cuda")
+    print(f"rows {rows}", flush=True)
+    seg, _ = laser.laser_sta_folded_forward(t, h, A, wv, lens, w, 4.0, 1, qf_work=qf, g_work=g)
+    torch.cuda.synchronize()
+    for u in (0, 1, U // 2, U - 1):
+        ref, _ = oracle.sta_forward(*(to_host_f64(x[u:u + 1]) for x in (qf, h, h)), None, w, 4.0)
+        assert vec_rel_err(to_host_f64(g[u:u + 1]), ref) <= TOL["bf16"], u
+        ref = to_host_f64(g[u]) @ to_host_f64(wv)
+        assert vec_rel_err(to_host_f64(seg[u]), ref) <= TOL["bf16"], u
