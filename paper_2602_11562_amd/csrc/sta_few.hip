@@ -168,7 +168,7 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
   auto dma_nt = [&](unsigned dst, unsigned off, const void* src) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt\n" ::"s"(dst), "v"(off), "s"(src) : "memory");
   };
-  const bool nt = __builtin_amdgcn_readfirstlane(past_cache(lens, (int)(units / runs), L, FOLD ? D * 2 : (DQ + D) * 2, lane));
+  const bool nt = __builtin_amdgcn_readfirstlane(past_cache(lens, (int)(units / runs), L, FOLD || k == v ? D * 2 : (DQ + D) * 2, lane));
   // requests tile t of a unit into ring buffer b (with the unit's queries when it is the first) and returns how many
   // fetches that were. Rows past the end repeat the last valid one (their gates are zero).
   auto fetch = [&](const Unit& x, int t, int b) {
