@@ -86,13 +86,12 @@ __device__ __forceinline__ void stage_rows(unsigned char* t, const unsigned shor
   }
 }
 
-// Whether a wave's sums hold a value that is not finite (zero times it is NaN)
-template <int N>
-__device__ __forceinline__ bool any_not_finite(const f32x16 (&x)[N], float zero = 0.0f) {
+// Whether any score gradient of a wave was not finite, from one of its column blocks of dK or dQ: every column of an item's
+// or a query's row is a sum over all of its score gradients, and not finite if one of them is (zero times it is NaN).
+__device__ __forceinline__ bool any_not_finite(const f32x16& x) {
+  float zero = 0.0f;
 #pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) zero = fmaf(x[i][r], 0.0f, zero);
+  for (int r = 0; r < 16; ++r) zero = fmaf(x[r], 0.0f, zero);
   return __any(!(zero == 0.0f));
 }
 
@@ -232,9 +231,9 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
         }
       }
     }
-    // Sums that are not finite once more without the tiles: there a zero row that pads the candidates meets an infinite key
-    // or value, and the zero parts of a split gate an infinite dH', and give NaN where the sum has none.
-    const bool plain = work_here && (any_not_finite(dka) || any_not_finite(dva));
+    // Sums over score gradients that are not finite once more without the tiles: there a zero row that pads the candidates
+    // meets an infinite key or value, and the zero parts of a split gate an infinite dH', and give NaN where the sum has none.
+    const bool plain = work_here && any_not_finite(dka[0]);
     if (__builtin_expect(plain, 0)) {
       for (int row = 0; row < rows; ++row) {
         const size_t j = (size_t)u * L + lo + row;
@@ -358,7 +357,7 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
           for (int r = 0; r < 16; ++r) dqa[db][r] += src[(db * 16 + r) * 64];
       }
     }
-    if (__builtin_expect(any_not_finite(dqa), 0)) {   // as for the items: padding rows of a tile meet an infinite dH'
+    if (__builtin_expect(any_not_finite(dqa[0]), 0)) {   // as for the items: padding rows of a tile meet an infinite dH'
       for (int c = cbase; c < C && c < cbase + 32; ++c) {
         PlainRow<DQ> qr, kr, dqr;
         PlainRow<D> hr, vr;
