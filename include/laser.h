@@ -471,8 +471,9 @@ laser_status laser_gsta_backward(const void* seg, const void* t0, const void* wq
                                  laser_dtype dt, void* dseg_out, float* dt0_out, float* dwq_out, float* dwk_out,
                                  float* dwv_out, void* work, size_t work_bytes, void* stream);
 
-/* Name of the STA / GSTA kernel AUTO would pick for a shape in a batch that fills the machine (smaller ones may take
- * another form; static strings; host only, no GPU needed). */
+/* Name of the family of STA / GSTA kernels AUTO would pick from for a shape in a batch that fills the machine (smaller ones
+ * may take another form; "sta_generic" and "gsta_generic" include the matrix-core kernels that AUTO runs for fp32 at the
+ * usual widths, "sta_stream_bf16" the one for a few candidates per user; static strings; host only, no GPU needed). */
 const char* laser_sta_kernel_name(int C, int d_q, int d, int w, laser_dtype dt);
 const char* laser_gsta_kernel_name(int C, int S, int d, laser_dtype dt);               /* one layer (M = 1) */
 const char* laser_gsta_kernel_name_layers(int C, int S, int d, int M, laser_dtype dt);

@@ -21,8 +21,8 @@
 // are zeros in LDS, so they add nothing to any finite sum (padding of the history is never read); a wave whose sums come out
 // not finite forms them again over the valid rows alone.
 //
-// What bounds it: LDS reads and MFMA issue share the time (two workgroups of four waves per compute unit: 256
-// registers a wave); at 64 users x 64 candidates, L = 2048, w = 128, d = d_q = 64 (lengths 410 .. 2048) the launch takes
+// What bounds it: waiting, 47 % of the waves' cycles (a block of rows is fetched between two barriers, with only the other
+// workgroup of a compute unit to overlap: 256 registers a wave), the matrix pipe is busy 14 %; at 64 users x 64 candidates, L = 2048, w = 128, d = d_q = 64 (lengths 410 .. 2048) the launch takes
 // 30 us for the 92 MB it cannot do without, eight passes of the one-item-per-wave kernel took 1840 us.
 #include "laser_internal.h"
 #include "sta_mfma_tile.h"
@@ -413,9 +413,9 @@ static StaBwdMfmaShape sta_bwd_mfma_shape(const StaBwdArgs& a, int max_groups) {
   return s;
 }
 
-// From five candidates on. Up to four the several-items-per-wave kernel streams the history once and is mostly the
-// faster one (2048 users x 4, L = 1000, w = 10, 32 / 128: 586 us against 819 us here; 512 x 4, L = 2000, w = 64, 128 / 128:
-// 356 against 470 us; 64 / 64 the other way round, 188 against 126 us); beyond four the alternative is one item per wave,
+// From five candidates on. Up to four the several-items-per-wave kernel streams the history once and is the faster one
+// (2048 users x 4, L = 1000, w = 10, 32 / 128: 586 us against 819 us here; 512 x 4, L = 2000, w = 64, 128 / 128: 356 against
+// 470 us) but at 64 / 64 (188 against 126 us), which is left on the one line for all widths; beyond four the alternative is one item per wave,
 // eight candidates a pass: 512 x 5, L = 1000, w = 10, 32 / 128: 260 against 168 us, 512 x 8, w = 64, 128 / 128: 475 against
 // 158 us. Not for segments so short that their tiles of 32 items x 32 candidates are nearly empty, where there are enough of
 // them to fill the machine (us, the other kernel / here; L = 300): 1024 users x 5, w = 1, 128 / 64 377 / 890, 512 x 8, w = 3,

@@ -13,8 +13,8 @@
 // take alternate item tiles of a segment, so that a single request still spreads over the chip, and their sums meet in LDS
 // in a fixed order. Items past the end of a segment have a gate of exactly zero and zeros for values.
 //
-// Bound: the fp32 matrix rate, 157 TFLOP/s (one 16 x 16 tile with d = d_q = 64 is 1024 cycles of one SIMD), and for small
-// calls the load - score - gate - sum chain of one tile. Against the generic kernel (one candidate a wave, a score per
+// Bound by the load - score - gate - sum chain of a tile, whose loads are not ahead of it (24 users x 50 candidates: waves wait
+// 45 % of their cycles, the matrix pipe is busy 21 %; a 16 x 16 tile with d = d_q = 64 is 1024 cycles of it). Against the generic kernel (one candidate a wave, a score per
 // lane): 24 users x 50 candidates, L = 1500, w = 100, 64 / 64: 217 -> 13.8 us; 1 x 16, L = 1024, w = 64: 23.7 -> 4.8 us.
 #include "laser_internal.h"
 
