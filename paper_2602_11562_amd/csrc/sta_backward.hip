@@ -180,8 +180,7 @@ __device__ __forceinline__ void unpack8b(const u32x4b& r, float (&x)[8]) {
 }
 
 // GB16: dk and dv are written in bf16 (the storage type of k and v: half the bytes of the two largest outputs) instead
-// of fp32; the sums are fp32 either way and rounded once. NT: items and bf16 gradients with the non-temporal hint (fp32 ones
-// leave as two 16-byte halves of every 32, which the hint keeps from meeting in the cache: up to 1.22 times the time).
+// of fp32; the sums are fp32 either way and rounded once. NT: items and gradients with the non-temporal hint.
 template <int DQ, int D, int CMAX, bool GB16, bool NT>
 __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short* __restrict__ q,
                                                            const unsigned short* __restrict__ k,
@@ -224,7 +223,7 @@ __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short*
   G* dkU = static_cast<G*>(dk) + (size_t)u * L * DQ;
   G* dvU = static_cast<G*>(dv) + (size_t)u * L * D;
   auto put = [](auto* dst, const auto& x) {
-    if constexpr (NT && GB16) __builtin_nontemporal_store(x, dst);
+    if constexpr (NT) __builtin_nontemporal_store(x, dst);
     else *dst = x;
   };
   auto store8 = [&](G* dst, const float (&x)[8]) {   // eight consecutive gradient values: 16 or 32 bytes
