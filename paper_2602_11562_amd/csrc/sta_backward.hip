@@ -471,7 +471,10 @@ static void sta_bwd_wide_launch(const StaBwdArgs& a, unsigned blocks, int spg, i
   const float nsl = -1.4426950408889634f * inv_gamma;
   const int classes = sta_bwd_classes(a, blocks, 32);
   // Histories and gradients that together are more than the last-level cache (256 MB) holds, with the non-temporal hint:
-  // 2048 users x 1000 items of 320 bytes (1.05 GB) 211 -> 196 us; 256 such users (131 MB) 28 -> 34 us
+  // 2048 users x 1000 items of 320 bytes (1.05 GB) 211 -> 196 us; 256 such users (131 MB) 28 -> 34 us. With fp32 gradients, which
+  // leave as two 16-byte halves of every 32, the launch by itself is up to 1.2 times slower for it from about 14 items a segment
+  // on, but in a training pass (110 of them, 0.6 to 2.2 GB, two batches in turn) what it leaves in the cache for the launches
+  // around it is worth more: 0.90 to 1.03 times the time of a pass without the hint on the stores, by size and segment length
   const bool nt = (double)a.U * a.L * (DQ + D) * (a.grads_bf16 ? 4 : 6) >= 600.0e6;
 #define LASER_BWD_WIDE_AS(CM, GB, NT)                                                                                \
   hipLaunchKernelGGL((sta_bwd_wide_kernel<DQ, D, CM, GB, NT>), dim3(blocks * classes), dim3(256), 0, a.stream,      \
