@@ -1059,8 +1059,9 @@ static bool is_direct(const StaArgs& a) {
 // candidates fill an odd number of fours. Four for such segments if that number is odd (64 users x 320 candidates, w = 20:
 // 74 -> 64 us), if they are short (up to 20 items; 32 x 256, w = 10, 128 / 64: 37 -> 32; not with softmax or, past 256
 // candidates, several heads, whose state in registers makes eight the better ones: 20 x 512, four heads, softmax 74 against
-// 109), or if eight would leave compute units without work (8 x 256, w = 56: 11.9 -> 10.3). From w = 64 on eight (32 x 256,
-// L = 4096, w = 128, 64 / 64: 21 against 24 us).
+// 109), or if eight would leave compute units without work for most of the time (8 x 256, L = 2000, w = 56: 11.9 -> 10.3).
+// Between 21 and 63 items either is up to 9 % better than the other by widths, lengths and w in no pattern found, eight by 3 %
+// on average; from w = 64 on eight (32 x 256, L = 4096, w = 128, 64 / 64: 21 against 24 us).
 static int pick_nw(const StaArgs& a) {
   const int vv = tuning_int("LASER_STA_NW", 0);   // tuning builds
   if (vv == 1 || vv == 2 || vv == 4 || vv == 8) return vv;
@@ -1068,7 +1069,7 @@ static int pick_nw(const StaArgs& a) {
   if (is_direct(a) || a.w >= TI) return 8;
   const bool odd = ((a.C + 127) / 128) % 2 != 0;
   const bool short_seg = a.w <= 20 && !a.softmax && (a.C <= 256 || a.heads == 1);
-  return odd || short_seg || (long long)a.U * ((a.C + 255) / 256) * a.S <= 256 ? 4 : 8;
+  return odd || short_seg || (long long)a.U * ((a.C + 255) / 256) * a.S <= 384 ? 4 : 8;
 }
 
 // Consecutive segments per workgroup of the register-staged forms (they share the query registers and the prefetch
