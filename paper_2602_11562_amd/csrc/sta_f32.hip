@@ -22,9 +22,6 @@ namespace laser {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// the value row of items past a segment's end: an infinity in a valid row would make their zero gates NaN
-__device__ float sta_f32_zeros[128];
-
 // NCT: candidate tiles of 16 per wave
 template <int DQ, int D, int NCT>
 __global__ __launch_bounds__(256) void sta_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
@@ -69,20 +66,24 @@ __global__ __launch_bounds__(256) void sta_f32_kernel(const float* __restrict__ 
         qf[c][j] = *reinterpret_cast<const f32x4*>(q + ((size_t)cr.first + cand) * DQ + j * 16 + g * 4);
     }
     const float* kU = k + (size_t)u * L * DQ + g * 4;
-    const float* vU = v + (size_t)u * L * D + l16;
+    // Values through a buffer descriptor of the tile's valid rows: rows past them read zeros (an infinity in a repeated valid row
+    // would make their zero gates NaN), and one offset serves every load.
+    const float* vU = v + (size_t)u * L * D;
+    int v_off = (g * 4 * D + l16) * 4;
     for (int t0 = lo + part * 16; t0 < hi; t0 += wi * 16) {
       f32x4 kf[KJ];
       float vf[4][DB];
+      const __amdgpu_buffer_rsrc_t v_rows = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(vU + (size_t)t0 * D), 0, (hi - t0 < 16 ? hi - t0 : 16) * D * 4, 0x00027000);   // (32-bit elements)
+      asm volatile("" : "+v"(v_off));   // (keeps the sums with constants here, where they are the loads' immediate offsets)
       const int krow = t0 + l16 < hi ? t0 + l16 : hi - 1;
 #pragma unroll
       for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kU + (size_t)krow * DQ + j * 16);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = t0 + g * 4 + r;
-        const float* v_row = row < hi ? vU + (size_t)row * D : sta_f32_zeros + l16;
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int db = 0; db < DB; ++db) vf[r][db] = v_row[db * 16];
-      }
+        for (int db = 0; db < DB; ++db)
+          vf[r][db] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(v_rows, v_off + (r * D + db * 16) * 4, 0, 0));
 #pragma unroll
       for (int c = 0; c < NCT; ++c) {
         f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
