@@ -13,7 +13,7 @@
 //
 // Bound by the chain of five products and two passes per workgroup (one round of workgroups) and by H' read twice and dH'
 // written: 2048 pairs, S = 100, d = 128 (132 MB at most, 84 MB valid) 33 us, one workgroup per pair with its rows in LDS
-// 131 us; 4096 pairs, S = 16, d = 64 18 us, 55 us before.
+// 131 us; 4096 pairs, S = 16, d = 64 15 us (18 us before the vectors of the tile crossed LDS and memory four columns at a time).
 #include "gsta_tile.h"
 #include "laser_internal.h"
 
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
   typename X::Act& ba = *reinterpret_cast<typename X::Act*>(lds);
   typename X::Act& bb = *reinterpret_cast<typename X::Act*>(lds + sizeof(typename X::Act));
   unsigned char* at = lds + 2 * sizeof(typename X::Act);
-  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = (lane >> 4) * 4;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned char* patch = at + wave * X::PATCH;
   at += NW * X::PATCH;
@@ -79,30 +79,34 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
   float* pl = pml + NW * 4;
   auto rr_of = [&](int j, int l) { return pl + (j * M + l) * stride; };   // r / sqrt(d), in the units of X::ex
   // dp_of = rr_of + RP, p_of = rr_of + 2 RP, statistics (maximum, 1 / denominator) = rr_of + 3 RP, then e (later a), de
-  const int pbase = blockIdx.x * PW, n0 = wave * 16, col = n0 + l16;
+  const int pbase = blockIdx.x * PW, n0 = wave * 16, c4 = n0 + 4 * (lane >> 4);
   const int gl = lane % LPR, grp = lane / LPR, wp = PW < NW ? wave % WPP : 0;
   const float scale = 1.0f / sqrtf((float)D);
 
   typename X::Cols cq, cx;                                        // columns of W_q; of W_v (forward) and W_k (backward)
   typename X::Operand rk, rv, rq;
   X::load_cols(cq, wq, n0, lane);
-  f32x4 t, g;                                                     // pair g4 + r, column col
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int p = pbase + g4 + r < P ? pbase + g4 + r : P - 1;
-    t[r] = g4 + r < PW ? load_as_f32(t0, (size_t)p * D + col) : 0.0f;
-    g[r] = g4 + r < PW ? dz[(size_t)p * D + col] : 0.0f;
-  }
+  auto at4 = [&] { return (size_t)(pbase + l16 < P ? pbase + l16 : P - 1) * D + c4; };   // pair l16, columns c4 ..
+  const bool mine4 = l16 < PW && pbase + l16 < P;
+  const typename X::Raw4 traw = *reinterpret_cast<const typename X::Raw4*>(t0 + at4());
+  f32x4 g = *reinterpret_cast<const f32x4*>(dz + at4());
   X::load_rows(rk, wk, n0, lane);
+  // (lengths without a branch on `lens`, in which one load would wait for the other)
+  auto pair_of = [&](int i) {
+    const int pr = pbase + (PW < NW ? wave / WPP : wave * PPW + i);
+    return pr < P ? pr : P - 1;
+  };
+  int nl[PPW];
+#pragma unroll
+  for (int i = 0; i < PPW; ++i) nl[i] = *(lens != nullptr ? lens + pair_of(i) / C : reinterpret_cast<const int32_t*>(wq));
   int nv[PPW];
   const T* H[PPW];
   Row8<T> h[R];
 #pragma unroll
   for (int i = 0; i < PPW; ++i) {
     const int pj = PW < NW ? wave / WPP : wave * PPW + i;
-    const int pr = pbase + pj < P ? pbase + pj : P - 1;
-    nv[i] = __builtin_amdgcn_readfirstlane((valid_len(lens, pr / C, L) + w - 1) / w);
-    H[i] = seg + (size_t)pr * S * D + gl * 8;
+    nv[i] = __builtin_amdgcn_readfirstlane(((lens == nullptr || nl[i] > L ? L : (nl[i] < 0 ? 0 : nl[i])) + w - 1) / w);
+    H[i] = seg + (size_t)pair_of(i) * S * D;
     if (lane == 0) some_of[pj] = nv[i] > 0;
   }
   auto load_h = [&](Row8<T> (&x)[R], int i, int k0) {             // rows at or past nv: the last valid one, weight zero
@@ -111,35 +115,30 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     for (int k = 0; k < R; ++k) {
       int row = ((k0 + k) * WPP + wp) * RPW + grp;
       row = row < last ? row : last;
-      x[k].load(H[i] + (size_t)row * D);
+      x[k].load(H[i] + (unsigned)(row * D + gl * 8));
     }
   };
   load_h(h, 0, 0);                                                // (the first rows of the first pass, ahead of the products)
-  auto put_tile = [&](typename X::Act& b, const f32x4& x) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (g4 + r < PW) X::put(b, g4 + r, col, x[r]);
-  };
+  __builtin_assume(M > 0);                                        // (or the loads move behind a branch on it)
+  __builtin_amdgcn_sched_barrier(0);                              // (widened any earlier, t waits for its load ahead of the others)
+  f32x4 t = X::wide4(traw);
+  auto put_tile = [&](typename X::Act& b, const f32x4& x) { X::put4(b, l16, c4, x); };
   auto put_scratch = [&](int l, int slot, const f32x4& x) {       // one of the six vectors of a pair and layer
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (g4 + r < PW && pbase + g4 + r < P) pv[(((size_t)(pbase + g4 + r) * M + l) * 6 + slot) * D + col] = x[r];
+    if (mine4) *reinterpret_cast<f32x4*>(pv + (((size_t)(pbase + l16) * M + l) * 6 + slot) * D + c4) = x;
   };
   auto put_rows = [&](int l, int off, const f32x4& x, float f) {  // into the (pair, layer) block
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (g4 + r < PW) rr_of(g4 + r, l)[off + col] = x[r] * f;
+    if (l16 < PW) *reinterpret_cast<f32x4*>(rr_of(l16, l) + off + c4) = x * f;
   };
-  // A vector that the waves of a pair have summed over their rows (`acc`, over the lane groups already): handed to
-  // `take(pair, element, value)` by one thread per element. Ends with a barrier.
-  auto gather = [&](int i, const float (&acc)[8], float f, auto take) {
+  // A vector summed over a wave's rows, `acc` still apart by lane group: handed to `take(pair, element, value)` by one lane per
+  // element, or left for over_waves() where several waves share the pair.
+  auto gather = [&](int i, float (&acc)[8], float f, auto take) {
     const int pj = PW < NW ? wave / WPP : wave * PPW + i;
-    if constexpr (WPP == 1) {
-      if (grp == 0)
+    scatter_over_groups<LPR>(acc, lane);
+    const int y0 = gl * 8 + group_first<LPR>(lane);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) take(pj, gl * 8 + e, acc[e] * f);
-    } else {
-      if (grp == 0) store_row8<float>(part + wave * RP + gl * 8, acc);
+    for (int e = 0; e < LPR / 8; ++e) {
+      if constexpr (WPP == 1) take(pj, y0 + e, acc[e] * f);
+      else part[wave * RP + y0 + e] = acc[e];
     }
   };
   auto over_waves = [&](float f, auto take) {
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
       const float mw = over_groups<LPR, true>(m), f = X::ex(m - softmax_ref(mw));
       den = over_groups<LPR, false>(den * f);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = over_groups<LPR, false>(acc[e] * f);
+      for (int e = 0; e < 8; ++e) acc[e] *= f;
       // no valid segment: p = 0 (by their number, as in the forward kernel)
       const float inv = nv[i] > 0 ? 1.0f / den : 0.0f;
       if (WPP == 1) {
@@ -350,8 +349,6 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
 #pragma unroll
           for (int k = 0; k < R; ++k) h[k] = ahead[k];
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = over_groups<LPR, false>(acc[e]);
       gather(i, acc, scale, [&](int j, int y, float x) {
         X::put(bb, j, y, x);
         if (pbase + j < P) pv[(((size_t)(pbase + j) * M + l) * 6 + 2) * D + y] = x;
@@ -372,9 +369,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     g += X::product(ba, rq, lane);                                // g += dq' W_q^T (the residual path keeps g)
     __syncthreads();
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-    if (g4 + r < PW && pbase + g4 + r < P) dt0[(size_t)(pbase + g4 + r) * D + col] = g[r];
+  if (mine4) *reinterpret_cast<f32x4*>(dt0 + at4()) = g;
   // A pair without a valid segment adds nothing to the weight gradients, whatever its target and dz hold: its vectors, of which p
   // and dr are zeros already, are overwritten with zeros (zero times a value that is not finite is NaN).
   for (unsigned long long m = __ballot(lane < PW && pbase + lane < P && some_of[lane & 15] == 0); m != 0; m &= m - 1)

@@ -9,6 +9,7 @@
 namespace laser {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 template <typename T> struct Row8;
 template <> struct Row8<unsigned short> {
@@ -42,12 +43,41 @@ __device__ __forceinline__ float over_groups(float x) {
   return both(__uint_as_float(s[0]), __uint_as_float(s[1]));
 }
 
+// Sums of eight values over the 64 / LPR lane groups of a wave, dealt out over the groups: lane group `grp` ends with x[0 ..
+// 8 LPR / 64 - 1] = the sums of elements group_first(lane) .. (7 exchanges where every lane getting every sum takes 24)
+template <int LPR>
+__device__ __forceinline__ int group_first(int lane) {
+  return LPR == 16 ? ((lane >> 5) * 4 + ((lane >> 4) & 1) * 2) : ((lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1));
+}
+template <int LPR>
+__device__ __forceinline__ void scatter_over_groups(float (&x)[8], int lane) {
+  static_assert(LPR == 8 || LPR == 16, "8 elements a lane, d = 64 or 128");
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {   // the lower half of the wave keeps element e, the upper e + 4
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 4]), false, false);
+    x[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {   // rows of 16 lanes in pairs
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 2]), false, false);
+    x[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  if (LPR == 8) {
+    const bool odd = lane & 8;
+    const float keep = odd ? x[1] : x[0], send = odd ? x[0] : x[1];
+    x[0] = keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0x128, 0xf, 0xf, false));  // row_ror:8
+  }
+}
+
 // What an online softmax subtracts from its scores when the largest so far is m: scores of -inf alone (or none) then have
 // weight zero without a difference of infinities, and one of NaN or +inf gives NaN.
 __device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 0.0f : m; }
 
-// Per storage type: the left operand's tile in LDS (16 pairs x D values of fp32 meaning), a wave's share of a matrix, and
-// the product of the two.
+// Per storage type: the tile's vectors in LDS (16 pairs x D values of fp32 meaning), a wave's share of a matrix (16 columns),
+// and the product of the two, with the matrix as the left operand: lane (l16, g) gets columns n0 + 4 g .. + 3 of pair l16,
+// which go to LDS, and to and from memory, as one piece (matrices and rows are addressed by a uniform base and an unsigned
+// 32-bit lane offset: 64-bit lane addresses, kept over the layers, spilled at d = 128 in fp32) (the other way round, four pairs of one column, every vector took
+// twelve two-byte writes where three of eight bytes do).
 template <typename T, int D> struct Prod;
 
 template <int D> struct Prod<float, D> {
@@ -60,15 +90,20 @@ template <int D> struct Prod<float, D> {
   static __device__ __forceinline__ float ex(float x) { return expf(x); }
   static constexpr float LOG = 1.0f;                        // scores enter ex() in this base's units
   static __device__ __forceinline__ void put(Act& a, int pair, int col, float x) { a.v[pair * PITCH + col] = x; }
+  static __device__ __forceinline__ void put4(Act& a, int pair, int col, const f32x4& x) {
+    *reinterpret_cast<f32x4*>(a.v + pair * PITCH + col) = x;
+  }
+  typedef f32x4 Raw4;                                       // four stored values
+  static __device__ __forceinline__ f32x4 wide4(const Raw4& x) { return x; }
   static __device__ __forceinline__ void load_cols(Cols& c, const float* W, int n0, int lane) {
 #pragma unroll
     for (int it = 0; it < NCOL; ++it)
-      c.x[it] = *reinterpret_cast<const f32x4*>(W + (size_t)(it * 16 + (lane >> 2)) * D + n0 + (lane & 3) * 4);
+      c.x[it] = *reinterpret_cast<const f32x4*>(W + it * 16 * D + n0 + (unsigned)((lane >> 2) * D + (lane & 3) * 4));
   }
   static __device__ __forceinline__ void load_rows(Operand& r, const float* W, int n0, int lane) {
 #pragma unroll
     for (int j = 0; j < D / 16; ++j)
-      r.x[j] = *reinterpret_cast<const f32x4*>(W + (size_t)(n0 + (lane & 15)) * D + j * 16 + (lane >> 4) * 4);
+      r.x[j] = *reinterpret_cast<const f32x4*>(W + n0 * D + j * 16 + (unsigned)((lane & 15) * D + (lane >> 4) * 4));
   }
   static __device__ __forceinline__ Operand transposed(const Cols& c, unsigned char* patch, int lane) {
     float* p = reinterpret_cast<float*>(patch);             // [D][16]
@@ -91,7 +126,7 @@ template <int D> struct Prod<float, D> {
     for (int j = 0; j < D / 16; ++j) {
       const f32x4 x = *reinterpret_cast<const f32x4*>(a.v + (lane & 15) * PITCH + j * 16 + (lane >> 4) * 4);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) s[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[m], w.x[j][m], s[m], 0, 0, 0);
+      for (int m = 0; m < 4; ++m) s[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x[j][m], x[m], s[m], 0, 0, 0);
     }
     return (s[0] + s[1]) + (s[2] + s[3]);
   }
@@ -114,15 +149,29 @@ template <int D> struct Prod<unsigned short, D> {
     a.v[1][pair * PITCH + col] = h1;
     a.v[2][pair * PITCH + col] = f32_to_bf16_bits(r1 - bf16_bits_to_f32(h1));
   }
+  static __device__ __forceinline__ void put4(Act& a, int pair, int col, f32x4 x) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const bf16x4 b = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
+      *reinterpret_cast<bf16x4*>(a.v[p] + pair * PITCH + col) = b;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] -= (float)b[e];
+    }
+  }
+  typedef u32x2 Raw4;                                       // four stored values
+  static __device__ __forceinline__ f32x4 wide4(const Raw4& x) {
+    const bf16x4 b = __builtin_bit_cast(bf16x4, x);
+    return f32x4{(float)b[0], (float)b[1], (float)b[2], (float)b[3]};
+  }
   static __device__ __forceinline__ void load_cols(Cols& c, const unsigned short* W, int n0, int lane) {
 #pragma unroll
     for (int it = 0; it < NCOL; ++it)
-      c.x[it] = *reinterpret_cast<const u32x4*>(W + (size_t)(it * 32 + (lane >> 1)) * D + n0 + (lane & 1) * 8);
+      c.x[it] = *reinterpret_cast<const u32x4*>(W + it * 32 * D + n0 + (unsigned)((lane >> 1) * D + (lane & 1) * 8));
   }
   static __device__ __forceinline__ void load_rows(Operand& r, const unsigned short* W, int n0, int lane) {
 #pragma unroll
     for (int s = 0; s < D / 32; ++s)
-      r.x[s] = *reinterpret_cast<const bf16x8*>(W + (size_t)(n0 + (lane & 15)) * D + s * 32 + (lane >> 4) * 8);
+      r.x[s] = *reinterpret_cast<const bf16x8*>(W + n0 * D + s * 32 + (unsigned)((lane & 15) * D + (lane >> 4) * 8));
   }
   static __device__ __forceinline__ Operand transposed(const Cols& c, unsigned char* patch, int lane) {
 #pragma unroll
@@ -150,7 +199,7 @@ template <int D> struct Prod<unsigned short, D> {
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
         const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v[p] + (lane & 15) * PITCH + k * 32 + (lane >> 4) * 8);
-        s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w.x[k], s[p], 0, 0, 0);
+        s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], x, s[p], 0, 0, 0);
       }
     return (s[2] + s[1]) + s[0];
   }

@@ -26,7 +26,7 @@ namespace laser {
 
 // PW: pairs per workgroup; R: row loads per lane and round; RES: one round holds every row (H' stays in registers)
 template <typename T, int D, int PW, int R, bool RES>
-__global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kernel(const T* __restrict__ seg, const T* __restrict__ t0,
+__global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) void gsta_tiled_kernel(const T* __restrict__ seg, const T* __restrict__ t0,
                                                           const T* __restrict__ wq, const T* __restrict__ wk,
                                                           const T* __restrict__ wv, const int32_t* __restrict__ lens,
                                                           const int32_t* __restrict__ cand_off, int U, int P, int C,
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
   __shared__ float pml[NW][2];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pbase = blockIdx.x * PW, n0 = wave * 16, col = n0 + l16;
+  const int pbase = blockIdx.x * PW, n0 = wave * 16, c4 = n0 + 4 * g;
   unsigned char* patch = patches[wave];
   // rows of H': lane group `grp` of the wave, elements 8 gl ..
   const int gl = lane % LPR, grp = lane / LPR, wp = PW < NW ? wave % WPP : 0;
@@ -52,14 +52,19 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
   typename X::Cols cq, cv;
   typename X::Operand rk;
   X::load_cols(cq, wq, n0, lane);
-  f32x4 t;                                                        // pair 4 g + r, column col
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int p = pbase + 4 * g + r;
-    t[r] = 4 * g + r < PW ? load_as_f32(t0, (size_t)(p < P ? p : P - 1) * D + col) : 0.0f;
-  }
+  const int pt = pbase + l16 < P ? pbase + l16 : P - 1;           // (rows of the tile past its pairs are not read back)
+  const typename X::Raw4 traw = *reinterpret_cast<const typename X::Raw4*>(t0 + (size_t)pt * D + c4);
   X::load_rows(rk, wk, n0, lane);
-  // the pairs whose H' this wave works on (a pair past the last one is worked on again, and not stored)
+  // the pairs whose H' this wave works on (a pair past the last one is worked on again, and not stored); their lengths without a
+  // branch on `lens`, in which one load would wait for the other
+  auto pair_of = [&](int i) {
+    const int pr = pbase + (PW < NW ? wave / WPP : wave * PPW + i);
+    return pr < P ? pr : P - 1;
+  };
+  int nl[PPW];
+#pragma unroll
+  for (int i = 0; i < PPW; ++i)
+    nl[i] = *(lens != nullptr ? lens + pair_user(cand_off, U, C, pair_of(i)) : reinterpret_cast<const int32_t*>(wq));
   int nv[PPW];
   const T* H[PPW];
   Row8<T> h[RES ? PPW : 1][R];
@@ -69,40 +74,39 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
     for (int k = 0; k < R; ++k) {
       int row = ((k0 + k) * WPP + wp) * RPW + grp;
       row = row < last ? row : last;
-      x[k].load(H[i] + (size_t)row * D);
+      x[k].load(H[i] + (unsigned)(row * D + gl * 8));
     }
   };
 #pragma unroll
   for (int i = 0; i < PPW; ++i) {
-    const int pj = PW < NW ? wave / WPP : wave * PPW + i;
-    const int pr = pbase + pj < P ? pbase + pj : P - 1;
-    nv[i] = __builtin_amdgcn_readfirstlane((valid_len(lens, pair_user(cand_off, U, C, pr), L) + w - 1) / w);
-    H[i] = seg + (size_t)pr * S * D + gl * 8;
+    nv[i] = __builtin_amdgcn_readfirstlane(((lens == nullptr || nl[i] > L ? L : (nl[i] < 0 ? 0 : nl[i])) + w - 1) / w);
+    H[i] = seg + (size_t)pair_of(i) * S * D;
     // (without a valid segment row 0 is requested and not used: a branch here makes the compiler wait for the loads)
-    if constexpr (RES) load_h(h[i], i, 0);
+    if (RES || i == 0) load_h(h[RES ? i : 0], i, 0);              // (streamed: the first rows of the first pass)
   }
-  X::load_cols(cv, wv, n0, lane);
+  // (a share of a matrix takes 32 registers in fp32 at d = 128: beside eight rows a lane there is room for two)
+  constexpr bool LATE = sizeof(T) == 4 && D == 128 && R == 8;
+  if (!LATE) X::load_cols(cv, wv, n0, lane);
   const float scale = X::LOG / sqrtf((float)D);
+  // (with M = 0 thinkable the compiler moves every load that only the loop wants behind a branch, and the wait for t before it)
+  __builtin_assume(M > 0);
+  if (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);          // (widened any earlier, t waits for its load ahead of the others)
+  f32x4 t = X::wide4(traw);                                       // pair l16, columns c4 ..
 
   for (int l = 0; l < M; ++l) {
     const bool more_layers = l + 1 < M;
     const size_t next = (size_t)(l + 1) * D * D;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (4 * g + r < PW) X::put(bt, 4 * g + r, col, t[r]);
+    X::put4(bt, l16, c4, t);
     const typename X::Operand oq = X::transposed(cq, patch, lane);
     __syncthreads();
     const f32x4 q = X::product(bt, oq, lane);                     // q' = t W_q
     if (more_layers) X::load_cols(cq, wq + next, n0, lane);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (4 * g + r < PW) X::put(bq, 4 * g + r, col, q[r]);
+    X::put4(bq, l16, c4, q);
     __syncthreads();
     const f32x4 rv = X::product(bq, rk, lane);                    // r = W_k q'
+    if (LATE) X::load_cols(cv, wv + next - D * D, n0, lane);
     if (more_layers) X::load_rows(rk, wk + next, n0, lane);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (4 * g + r < PW) rr[(4 * g + r) * RP + col] = rv[r] * scale;
+    if (l16 < PW) *reinterpret_cast<f32x4*>(rr + l16 * RP + c4) = rv * scale;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {                               // one pass over the rows of H'
@@ -119,7 +123,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
       }
       Row8<T> (&hi)[R] = h[RES ? i : 0];
       Row8<T> ahead[R];
-      if (!RES && nv[i] > 0) load_h(hi, i, 0);
+      if (!RES && i > 0) load_h(hi, i, 0);
       for (int k0 = 0; k0 * WPP * RPW < nv[i]; k0 += R) {
 #pragma unroll
         for (int k = 0; k < R; ++k) hi[k].pin();
@@ -158,25 +162,25 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
       const float mw = over_groups<LPR, true>(m), f = X::ex(m - softmax_ref(mw));
       den = over_groups<LPR, false>(den * f);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = over_groups<LPR, false>(acc[e] * f);
+      for (int e = 0; e < 8; ++e) acc[e] *= f;
+      scatter_over_groups<LPR>(acc, lane);
+      const int y0 = gl * 8 + group_first<LPR>(lane);             // the elements this lane hands on
       // p, zero without a valid segment (by their number: a denominator of NaN, or of zero where every score is -inf, has to
       // reach the result)
       if constexpr (WPP == 1) {
         const float inv = nv[i] > 0 ? 1.0f / den : 0.0f;
-        if (grp == 0)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) X::put(bq, pj, gl * 8 + e, acc[e] * inv);
+        for (int e = 0; e < LPR / 8; ++e) X::put(bq, pj, y0 + e, acc[e] * inv);
       } else {
-        if (grp == 0) {
-          *reinterpret_cast<f32x4*>(&part[wave][gl * 8]) = f32x4{acc[0], acc[1], acc[2], acc[3]};
-          *reinterpret_cast<f32x4*>(&part[wave][gl * 8 + 4]) = f32x4{acc[4], acc[5], acc[6], acc[7]};
-        }
+        if constexpr (LPR == 16) *reinterpret_cast<f32x2*>(&part[wave][y0]) = f32x2{acc[0], acc[1]};
+        else part[wave][y0] = acc[0];
         if (lane == 0) {
           pml[wave][0] = nv[i] > 0 ? mw : 0.0f;
           pml[wave][1] = nv[i] > 0 ? den : 1.0f;
         }
       }
     }
+    if (!RES && more_layers) load_h(h[0], 0, 0);                  // the first rows of the next layer's pass
     const typename X::Operand ov = X::transposed(cv, patch, lane);
     __syncthreads();
     if constexpr (WPP > 1) {                                      // the waves of a pair
@@ -197,11 +201,9 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
       __syncthreads();
     }
     t += X::product(bq, ov, lane);                                // t += p W_v
-    if (more_layers) X::load_cols(cv, wv + next, n0, lane);
+    if (more_layers && !LATE) X::load_cols(cv, wv + next, n0, lane);
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-    if (4 * g + r < PW && pbase + 4 * g + r < P) z[(size_t)(pbase + 4 * g + r) * D + col] = t[r];
+  if (l16 < PW && pbase + l16 < P) *reinterpret_cast<f32x4*>(z + (size_t)(pbase + l16) * D + c4) = t;
 
   // the other two views (Sec. 3.4.4), bf16 only: the component-wise maximum over the valid rows and the first rows as
   // stored. The rows are read once more (they were last read a moment ago); maxima of stored values are exact.
@@ -214,14 +216,14 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 ? 4 : 1)) void gsta_tiled_kern
       if (recent != nullptr && pr < P)
         for (int row = wp * RPW + grp; row < recent_n; row += WPP * RPW)
           *reinterpret_cast<u32x4*>(recent + ((size_t)pr * recent_n + row) * D + gl * 8) =
-              *reinterpret_cast<const u32x4*>(H[i] + (size_t)row * D);
+              *reinterpret_cast<const u32x4*>(H[i] + (unsigned)(row * D + gl * 8));
       if (pool == nullptr) continue;
       float best[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) best[e] = -INFINITY;
       for (int row = wp * RPW + grp; row < nv[i]; row += WPP * RPW) {
         Row8<T> x;
-        x.load(H[i] + (size_t)row * D);
+        x.load(H[i] + (unsigned)(row * D + gl * 8));
 #pragma unroll
         for (int e = 0; e < 8; ++e) best[e] = fmaxf(best[e], x.get(e));
       }
@@ -258,16 +260,20 @@ static void launch_pairs(const GstaArgs& a, int P) {
                      a.stream, (const T*)a.seg, (const T*)a.t0, (const T*)a.wq, (const T*)a.wk, (const T*)a.wv,    \
                      a.lens, a.cand_off, a.U, P, a.C, a.L, a.w < a.L ? a.w : a.L, a.S, a.M, a.z_out,               \
                      (T*)a.pool_out, (T*)a.recent_out, a.r)
-  constexpr int STREAM = 8 / (int)sizeof(T);                      // rows in flight when the block does not stay
+  // rows in flight when the block does not stay
+  constexpr int STREAM = 8 / (int)sizeof(T);
   // eight rows a lane fit the registers beside the matrices up to eight pairs (sixteen where a wave has two of them and
   // rows are bf16; otherwise they spill or leave one wave per SIMD), twelve for eight pairs of bf16 rows
-  constexpr bool EIGHT = PW == 4 || PW == 8 || (PW == 16 && D == 128 && sizeof(T) == 2);
+  constexpr bool EIGHT = PW == 4 || PW == 8 || (sizeof(T) == 2 && (PW <= 2 || (PW == 16 && D == 128)));
   // Sixteen pairs of few rows, d = 128: with two or three rows a lane the registers suffice for two workgroups on a compute
   // unit, which hide each other's chains (two layers, S = 4: 8192 pairs 25.3 -> 20.5 us, 65536 pairs 187 -> 125; S = 12: 25.2 ->
   // 23.7 and 188 -> 149, but 13.4 -> 15.1 for 4096 pairs, one workgroup a compute unit; the form with 32-pair tiles that this
   // kernel replaced took 20.4, 165, 23.1 and 191)
   constexpr bool FEW = PW == 16 && D == 128 && sizeof(T) == 2;
-  if (FEW && a.S <= 2 * HELD) LASER_TILED((FEW ? 2 : 4), true);
+  // One or two rows a lane where that is all there is: with four, the rows past the last one are worked on too (4096 pairs,
+  // S = 16, d = 64, bf16: the pass 3700 -> 1900 cycles of a workgroup's 14000)
+  if (a.S <= HELD) LASER_TILED(1, true);
+  else if (a.S <= 2 * HELD) LASER_TILED(2, true);
   else if (FEW && a.S <= 3 * HELD && P > 256 * PW) LASER_TILED((FEW ? 3 : 4), true);
   else if (a.S <= 4 * HELD) LASER_TILED(4, true);
   else if constexpr (EIGHT) {

@@ -29,6 +29,13 @@ GSTA_CASES = {
     "sixteen_pairs_of_one_row": ("bf16", 3, 700, 1, 1, 128, 2),        # two and three rows a lane
     "sixteen_pairs_of_eight_rows": ("bf16", 3, 700, 8, 1, 128, 3),
     "sixteen_pairs_of_twelve_rows": ("bf16", 3, 1400, 12, 1, 128, 2),
+    "one_row_a_lane_f32": ("f32", 3, 5, 32, 1, 64, 2),                 # one and two rows a lane, and eight of few pairs
+    "two_rows_a_lane": ("bf16", 3, 1367, 16, 1, 64, 2),
+    "two_rows_a_lane_f32": ("f32", 3, 700, 15, 1, 64, 1),
+    "two_rows_a_lane_and_one_more": ("bf16", 3, 1367, 17, 1, 64, 1),
+    "one_pair_a_workgroup_eight_rows": ("bf16", 1, 7, 200, 1, 128, 2),
+    "two_pairs_a_workgroup_eight_rows": ("bf16", 3, 110, 100, 1, 128, 2),
+    "four_pairs_a_workgroup_eight_rows_f32": ("f32", 3, 229, 60, 1, 128, 3),
 }
 
 
