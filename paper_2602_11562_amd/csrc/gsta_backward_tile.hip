@@ -162,7 +162,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     put_scratch(l, 4, t);
     const typename X::Operand oq = X::transposed(cq, patch, lane);
     __syncthreads();
-    const f32x4 q = X::product(ba, oq, lane);                     // q' = t W_q
+    const f32x4 q = X::template product<PW>(ba, oq, lane);                     // q' = t W_q
     if (more) {
       X::load_cols(cq, wq + next, n0, lane);
       X::load_cols(cx, wv + here, n0, lane);
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     put_tile(bb, q);
     put_scratch(l, 3, q);
     __syncthreads();
-    const f32x4 r = X::product(bb, rk, lane);                     // r = W_k q'
+    const f32x4 r = X::template product<PW>(bb, rk, lane);                     // r = W_k q'
     if (more) X::load_rows(rk, wk + next, n0, lane);
     put_rows(l, 0, r, scale * X::LOG);
     __syncthreads();
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     if (more) {
       const typename X::Operand ov = X::transposed(cx, patch, lane);
       __syncthreads();
-      t += X::product(ba, ov, lane);                              // t += p W_v
+      t += X::template product<PW>(ba, ov, lane);                              // t += p W_v
       __syncthreads();
     }
   }
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     put_tile(ba, g);
     put_scratch(l, 1, g);
     __syncthreads();
-    const f32x4 dp = X::product(ba, rv, lane);                    // dp = do W_v^T, do = g
+    const f32x4 dp = X::template product<PW>(ba, rv, lane);                    // dp = do W_v^T, do = g
     X::load_cols(cx, wk + here, n0, lane);
     put_rows(l, RP, dp, 1.0f);
     __syncthreads();
@@ -362,11 +362,11 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
       X::put(bb, j, y, x);
       if (pbase + j < P) pv[(((size_t)(pbase + j) * M + l) * 6 + 2) * D + y] = x;
     });
-    const f32x4 dq = X::product(bb, ok_, lane);                   // dq' = dr W_k
+    const f32x4 dq = X::template product<PW>(bb, ok_, lane);                   // dq' = dr W_k
     put_tile(ba, dq);
     put_scratch(l, 5, dq);
     __syncthreads();
-    g += X::product(ba, rq, lane);                                // g += dq' W_q^T (the residual path keeps g)
+    g += X::template product<PW>(ba, rq, lane);                                // g += dq' W_q^T (the residual path keeps g)
     __syncthreads();
   }
   if (mine4) *reinterpret_cast<f32x4*>(dt0 + at4()) = g;

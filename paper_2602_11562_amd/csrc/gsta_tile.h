@@ -3,6 +3,8 @@
 // columns of a matrix.
 #pragma once
 
+#include <type_traits>
+
 #include "laser_internal.h"
 #include "sta_mfma_tile.h"
 
@@ -118,6 +120,7 @@ template <int D> struct Prod<float, D> {
     __builtin_amdgcn_wave_barrier();
     return o;
   }
+  template <int PW>
   static __device__ __forceinline__ f32x4 product(const Act& a, const Operand& w, int lane) {
     f32x4 s[4];                                             // independent sums: the chain is a fourth as long
 #pragma unroll
@@ -190,7 +193,32 @@ template <int D> struct Prod<unsigned short, D> {
     __builtin_amdgcn_wave_barrier();
     return o;
   }
+  // With few pairs their parts share an operand's 16 columns: up to four pairs column 4 part + pair of one operand instead of three,
+  // up to eight the first two parts at 8 part + pair. Every wave of the workgroup reads the whole tile, at d = 128 a product is
+  // bound by these LDS reads (12, 8 or 4 of 16 bytes a lane; PW = 1 6.6 -> 5.9 us a layer). The parts meet by lane rotations;
+  // lanes of pairs past PW hold no result.
+  template <int PW>
   static __device__ __forceinline__ f32x4 product(const Act& a, const Operand& w, int lane) {
+    auto from = [](float v, auto ctrl) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    typedef std::integral_constant<int, 0x12C> From4;       // row_ror:12: lane + 4
+    typedef std::integral_constant<int, 0x128> From8;       // row_ror:8
+    if constexpr (PW <= 8) {
+      constexpr int N = PW <= 4 ? 4 : 8;
+      const int part = (lane & 15) / N;
+      f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, s2 = s;
+#pragma unroll
+      for (int k = 0; k < D / 32; ++k) {
+        const int at = (lane & (N - 1)) * PITCH + k * 32 + (lane >> 4) * 8;
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(a.v[part < 2 ? part : 2] + at), s, 0, 0, 0);
+        if (N == 8) s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(a.v[2] + at), s2, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        s[r] += N == 4 ? from(s[r], From4{}) + from(s[r], From8{}) : from(s[r], From8{}) + s2[r];
+      return s;
+    }
     f32x4 s[3];                                             // independent sums: the chain is a third as long
 #pragma unroll
     for (int p = 0; p < 3; ++p) s[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};

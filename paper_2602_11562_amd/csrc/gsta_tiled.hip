@@ -99,11 +99,11 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
     X::put4(bt, l16, c4, t);
     const typename X::Operand oq = X::transposed(cq, patch, lane);
     __syncthreads();
-    const f32x4 q = X::product(bt, oq, lane);                     // q' = t W_q
+    const f32x4 q = X::template product<PW>(bt, oq, lane);                     // q' = t W_q
     if (more_layers) X::load_cols(cq, wq + next, n0, lane);
     X::put4(bq, l16, c4, q);
     __syncthreads();
-    const f32x4 rv = X::product(bq, rk, lane);                    // r = W_k q'
+    const f32x4 rv = X::template product<PW>(bq, rk, lane);                    // r = W_k q'
     if (LATE) X::load_cols(cv, wv + next - D * D, n0, lane);
     if (more_layers) X::load_rows(rk, wk + next, n0, lane);
     if (l16 < PW) *reinterpret_cast<f32x4*>(rr + l16 * RP + c4) = rv * scale;
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
       }
       __syncthreads();
     }
-    t += X::product(bq, ov, lane);                                // t += p W_v
+    t += X::template product<PW>(bq, ov, lane);                                // t += p W_v
     if (more_layers && !LATE) X::load_cols(cv, wv + next, n0, lane);
   }
   if (l16 < PW && pbase + l16 < P) *reinterpret_cast<f32x4*>(z + (size_t)(pbase + l16) * D + c4) = t;
