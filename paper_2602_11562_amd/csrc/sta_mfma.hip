@@ -603,14 +603,32 @@ __device__ __forceinline__ void gate_steps6(f32x16& sc, bf16x8& p0, bf16x8& p1, 
 // (they are awaited where their registers are used) nor moves memory operations across it.
 __device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// 4 bytes per lane, as dma16
+__device__ __forceinline__ void dma4(const void* gbase, unsigned voff, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2\n" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
+}
+// sum over the lanes up to this one
+__device__ __forceinline__ int wave_prefix_sum(int x) {
+#define LASER_DPP_SUM(ctrl, rows) x += __builtin_amdgcn_update_dpp(0, x, ctrl, rows, 0xf, false)
+  LASER_DPP_SUM(0x111, 0xf);   // row_shr:1
+  LASER_DPP_SUM(0x112, 0xf);
+  LASER_DPP_SUM(0x114, 0xf);
+  LASER_DPP_SUM(0x118, 0xf);
+  LASER_DPP_SUM(0x142, 0xa);   // row_bcast:15 into the odd rows
+  LASER_DPP_SUM(0x143, 0xc);   // row_bcast:31 into the upper half
+#undef LASER_DPP_SUM
+  return x;
+}
+
 // NT: H' rows leave with the non-temporal hint (nobody reads them soon) or cacheable (the whole path: the next
 // launch streams them back)
-template <int NW, bool NTS>
+// dealt: workgroups by the users' lengths and counts (below) instead of S segments of C candidates for every user
+template <int NW, bool NTS, bool dealt>
 __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned short* __restrict__ q,
                                                                const unsigned short* __restrict__ k,
                                                                const unsigned short* __restrict__ v,
                                                                const int32_t* __restrict__ lens,
-                                                           const int32_t* __restrict__ cand_off, int P, int C_all,
+                                                           const int32_t* __restrict__ cand_off, int U, int P, int C_all,
                                                            int L, int w,
                                                                int S, int spw, int ctiles, int sruns,
                                                                float neg_scale_log2e,
@@ -625,49 +643,57 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   constexpr int OP = OPitch<D>::v, OBYTES = CW * OP;
   constexpr int IPW = 8 / NW;        // 1 KB fetch groups per wave per matrix per tile (a tile has 8 of each)
   constexpr int OPT = 2 * IPW;       // fetch instructions per wave per tile
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[DT_NBUF * TB + NW * OBYTES];
+  constexpr int DEALB = 3 * 256;     // a wave's copies of the lengths and offsets of 64 users
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DT_NBUF * TB + NW * OBYTES + (dealt ? NW * DEALB : 0)];
 
   // Workgroups are dealt to the eight XCDs round-robin by index; renumber them so that each XCD gets a contiguous
   // range: the workgroups that share a user's queries then share an L2 as well
   int bid = blockIdx.x;
   if (gridDim.x % 8 == 0) bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
-  const int srun = bid % sruns;
-  bid /= sruns;
-  const int ct = bid % ctiles;
-  const int u = bid / ctiles;
-  const CandRange crange = cand_range(cand_off, u, C_all, P);
-  const int C = crange.count;               // this user's candidates
-  const size_t pb = (size_t)crange.first;   // and the index of their first pair
-  if (ct * (CW * NW) >= C) {   // a candidate tile past this user's count: nothing to do (the first still writes the counts)
-    if (srun == 0 && ct == 0) write_seg_cnt(seg_cnt, u, valid_len(lens, u, L), L, w, S, threadIdx.x, 64 * NW);
-    return;
-  }
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: fetch addresses and cursors stay scalar
   const int l32 = lane & 31, h = lane >> 5;
-  const int cbase = ct * (CW * NW) + wave * CW;
   unsigned char* opatch = smem + DT_NBUF * TB + wave * OBYTES;
   const unsigned lds_base = __builtin_amdgcn_readfirstlane(
       (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem);
+  const int frow = lane >> 4, fpos = lane & 15;
+  const unsigned qlds = lds_base + DT_NBUF * TB + wave * OBYTES;
+
+  // What this workgroup works on: `span` segments from seg_lo of candidate tile ct of user u, by the launch's own division
+  // (every user S segments) or dealt out by the segments that hold items (below; with lengths, at most 64 users).
+  int u = bid / sruns, srun = bid % sruns, ct = u % ctiles, span = spw;
+  u /= ctiles;
+  CandRange crange = {0, 0};
+  if (!dealt || u < U) crange = cand_range(cand_off, u, C_all, P);
+  const bool early = ct * (CW * NW) < crange.count;   // (the launch may have more workgroups than the division needs)
+  if (!dealt && !early) {   // a candidate tile past this user's count: nothing to do (the first still writes the counts)
+    if (srun == 0 && ct == 0) write_seg_cnt(seg_cnt, u, valid_len(lens, u, L), L, w, S, threadIdx.x, 64 * NW);
+    return;
+  }
+  unsigned char* deal = smem + DT_NBUF * TB + NW * OBYTES + wave * DEALB;   // this wave's copies of the users' lengths and offsets
+  if (dealt) {
+    const unsigned at = lds_base + DT_NBUF * TB + NW * OBYTES + wave * DEALB;
+    dma4(lens, (lane < U ? lane : U - 1) * 4, at);
+    if (cand_off) {
+      dma4(cand_off, (lane < U ? lane : U) * 4, at + 256);
+      dma4(cand_off, (lane < U ? lane + 1 : U) * 4, at + 512);
+    }
+  }
 
   // Queries first, before anything that depends on the valid length: the wave's 32 rows (8 KB, K swizzle) are
   // fetched into its output patch, which is idle until the first segment ends, and read into registers once.
   // Rows past the last candidate repeat it (never stored).
-  const int frow = lane >> 4, fpos = lane & 15;
-  const unsigned qlds = lds_base + DT_NBUF * TB + wave * OBYTES;
-  {
-    const unsigned char* qU = reinterpret_cast<const unsigned char*>(q + pb * DQ);
+  auto fetch_queries = [&]() {
+    const unsigned char* qU = reinterpret_cast<const unsigned char*>(q + (size_t)crange.first * DQ);
 #pragma unroll
     for (int j = 0; j < CW / 4; ++j) {
       const int row = j * 4 + frow;
-      const int c = cbase + row < C ? cbase + row : C - 1;
+      int c = ct * (CW * NW) + wave * CW + row;
+      c = c < crange.count ? c : crange.count - 1;
       dma16(qU, (unsigned)c * ROWB + ((fpos ^ (row & 15)) << 4), qlds + j * 1024);
     }
-  }
-  const unsigned char* kU = reinterpret_cast<const unsigned char*>(k + (size_t)u * L * DQ);
-  const unsigned char* vU = reinterpret_cast<const unsigned char*>(v + (size_t)u * L * D);
-  const int seg_lo = srun * spw;
+  };
+  if (early) fetch_queries();
 
   // ---- fetch side: this wave moves rows 4 g .. 4 g + 3 of every tile, g = wave * IPW + j
   unsigned fk[IPW], fv[IPW];   // per-lane byte offsets inside a full tile (row and swizzled chunk)
@@ -681,7 +707,10 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   // to memory, and nothing can be computed before this tile has landed): its 32 rows exist whenever they lie
   // inside the history, whatever they hold. If the length then says the tile is not a full one, the request is
   // simply made again the regular way, into the same buffer; it lands after this one (loads retire in order).
-  const bool spec = seg_lo < S && w >= DT_TI && seg_lo * w + DT_TI <= L;
+  const unsigned char* kU = reinterpret_cast<const unsigned char*>(k + (size_t)u * L * DQ);
+  const unsigned char* vU = reinterpret_cast<const unsigned char*>(v + (size_t)u * L * D);
+  int seg_lo = srun * spw;
+  bool spec = early && seg_lo < S && w >= DT_TI && seg_lo * w + DT_TI <= L;
   if (spec) {
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
@@ -690,11 +719,98 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
       dma16(vU + (size_t)seg_lo * w * ROWB, fv[j], lds_base + KB + g * 1024);
     }
   }
-  const int n = __builtin_amdgcn_readfirstlane(valid_len(lens, u, L));
 
-  const int seg_hi = (seg_lo + spw) < S ? (seg_lo + spw) : S;
+  // Dealt out: histories differ in length, and with S segments to every user the longest one's workgroup sets the time while
+  // others have nothing. Every wave takes the lengths of all users and the smallest number of segments per workgroup, s, with
+  // which the runs of s valid segments of all users are no more than the launch has workgroups; run number `bid` is its own. A
+  // user's empty segments are shared by its runs. With full histories that is the launch's own division, so its early
+  // requests stand; otherwise they are made again (into the same places: loads retire in order). 29 users x up to 201
+  // candidates, 31 segments, lengths uniform in [L / 5, L]: the launch 27.8 -> 21 us
+  int n, zero_lo, zero_hi;   // the user's valid items; the segments this workgroup writes as zeros
+  if (dealt) {
+    wait_vm((early ? CW / 4 : 0) + (spec ? OPT : 0));   // the copies have landed (they are older than the rest)
+    asm volatile("" ::: "memory");
+    auto copy = [&](int i) { return *reinterpret_cast<const int*>(deal + i * 256 + lane * 4); };
+    int len = copy(0);
+    len = len < 0 ? 0 : (len > L ? L : len);
+    n = L;
+    zero_lo = zero_hi = 0;
+    if (cand_off == nullptr && __builtin_amdgcn_ballot_w64(lane < U && len != L) == 0) {   // full histories: nothing to divide anew
+      if (!early) return;
+    } else {
+      const int nv = (len + w - 1) / w;
+      int count = C_all;
+      if (cand_off) {   // as cand_range()
+        const int at = copy(1), room = P - (at < 0 ? 0 : (at > P ? P : at));
+        count = copy(2) - at;
+        count = count < 0 ? 0 : (count > room ? room : count);
+        count = count > C_all ? C_all : count;
+      }
+      int tiles = (count + CW * NW - 1) / (CW * NW);
+      tiles = lane < U ? (tiles > 1 ? tiles : 1) : 0;
+      // half the waves idle, a step takes 0.95 us instead of 1.7: runs of such users are longer by as much
+      const bool light = NW == 8 && count <= CW * NW / 2;
+      int own, runs, upto, total;
+      auto divide = [&](int s) {   // runs of each user's tiles, and their sum up to each user (the quotient is exact below 2^20)
+        own = light ? s * 7 / 4 : s;
+        runs = nv > 0 && count > 0 ? (int)(((float)(nv + own - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)own)) : 1;
+        upto = wave_prefix_sum(runs * tiles);
+        total = __builtin_amdgcn_readlane(upto, 63);
+      };
+      int s = 1;
+      divide(1);
+      if (total > (int)gridDim.x) {
+        s = total * 4 / (7 * (int)gridDim.x);
+        do divide(++s);
+        while (total > (int)gridDim.x);
+      }
+      if (bid >= total) {   // nothing left (what is under way into this workgroup's LDS has to land first)
+        wait_vm(0);
+        return;
+      }
+      const int to = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > bid));
+      const int to_runs = __builtin_amdgcn_readlane(runs, to);
+      int r = bid - __builtin_amdgcn_readlane(upto - runs * tiles, to), to_ct = 0;
+      while (r >= to_runs) {
+        r -= to_runs;
+        ++to_ct;
+      }
+      n = __builtin_amdgcn_readlane(len, to);
+      const int valid = __builtin_amdgcn_readlane(nv, to);
+      zero_lo = valid + (S - valid) * r / to_runs;
+      zero_hi = valid + (S - valid) * (r + 1) / to_runs;
+      span = __builtin_amdgcn_readlane(own, to);
+      if (to != u || to_ct != ct || r * span != seg_lo) {
+        u = to;
+        ct = to_ct;
+        crange = cand_range(cand_off, u, C_all, P);
+        kU = reinterpret_cast<const unsigned char*>(k + (size_t)u * L * DQ);
+        vU = reinterpret_cast<const unsigned char*>(v + (size_t)u * L * D);
+        spec = false;
+        if (crange.count > 0) fetch_queries();
+      }
+      srun = r;
+      seg_lo = r * span;
+      if (crange.count == 0) {
+        wait_vm(0);
+        if (srun == 0) write_seg_cnt(seg_cnt, u, n, L, w, S, tid, NT);
+        return;
+      }
+    }
+  } else {
+    n = __builtin_amdgcn_readfirstlane(valid_len(lens, u, L));
+  }
+  const int C = crange.count;               // this user's candidates
+  const size_t pb = (size_t)crange.first;   // and the index of their first pair
+  const int cbase = ct * (CW * NW) + wave * CW;
+
+  const int seg_hi = (seg_lo + span) < S ? (seg_lo + span) : S;
   int seg_ne = seg_lo;
   while (seg_ne < seg_hi && seg_ne * w < n) ++seg_ne;
+  if (!dealt) {
+    zero_lo = seg_ne;
+    zero_hi = seg_hi;
+  }
   const int item_end = n < L ? n : L;   // one past the user's last valid item
   auto seg_end = [&](int i) {
     const int e = i * w + w;
@@ -847,6 +963,15 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   }
   __syncthreads();
 
+  if (dealt && cbase >= C) {   // no candidate for this wave: its share of the fetches, step by step, is all it does
+    for (; cur.seg < seg_ne; cur = advance(cur)) {
+      if (fetched - done >= 4) __builtin_amdgcn_s_waitcnt(vmcnt_imm(OPT));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      bare_barrier();
+      issue_next();
+      ++done;
+    }
+  } else {
   bf16x8 qreg[KSTEPS], ka[KSTEPS], va[2][DB];
   auto read_k = [&](int buf) {
     const unsigned tb = lds_base + buf * TB;
@@ -1034,14 +1159,21 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
     step(scB, scA);
   }
   if (out_seg >= 0) flush_units(FU - out_units);
+  }
 
-  if (seg_ne < seg_hi) {   // empty segments of the run: exact zeros
+  if (zero_lo < zero_hi) {   // empty segments: exact zeros
     const int ncand = (C - ct * (CW * NW)) < CW * NW ? (C - ct * (CW * NW)) : CW * NW;
-    const int per_row = D / 8;
-    const int rows = ncand * (seg_hi - seg_ne);
-    for (int e = tid; e < rows * per_row; e += NT) {
+    if constexpr (dealt) {   // a few of every candidate: row groups, one segment after the other (no division per piece)
+      for (int cc = wave * RPI + lane / LPR; cc < ncand; cc += NW * RPI) {
+        unsigned short* row = seg_out + ((pb + ct * (CW * NW) + cc) * S + zero_lo) * D + (lane % LPR) * 8;
+        for (int ii = zero_lo; ii < zero_hi; ++ii, row += D) *reinterpret_cast<u32x4*>(row) = u32x4{0u, 0u, 0u, 0u};
+      }
+      return;
+    }
+    const int per_row = D / 8, each = zero_hi - zero_lo;
+    for (int e = tid; e < ncand * each * per_row; e += NT) {
       const int row = e / per_row, ch = e - row * per_row;
-      const int cc = row / (seg_hi - seg_ne), ii = seg_ne + row % (seg_hi - seg_ne);
+      const int cc = row / each, ii = zero_lo + row % each;
       *reinterpret_cast<u32x4*>(seg_out + ((pb + ct * (CW * NW) + cc) * S + ii) * D + ch * 8) =
           u32x4{0u, 0u, 0u, 0u};
     }
@@ -1100,6 +1232,21 @@ static int pick_spw(const StaArgs& a, int nw, int ctiles) {
   return best;
 }
 
+// Segments per workgroup with which one round of 256 workgroups of the direct-to-LDS form covers full histories and counts, where
+// its workgroups are dealt out by the lengths and counts, or 0: up to 64 users, one per lane, and 16 segments. Where nothing is
+// full the queries and the first tile come two trips to memory later (4 us with the requests made in vain), so it has to
+// save a good part of a round: own counts (29 users x up to 201 candidates, 31 segments of 100 items: 27.8 -> 21 us), or more
+// segments than one round of eight holds (40 x 300, 25 segments of 200 items: 130 -> 60 us; 16 x 200 of them, one round, 20.3
+// against 26 if dealt out), and steps enough; segments of one or two tiles leave the zeros of the empty ones, written at the
+// end, too large a part (64 x 200, 63 segments of 32: 40 against 45 us).
+static int deal_spw(const StaArgs& a, int ctiles) {
+  if (a.lens == nullptr || a.U > 64) return 0;
+  int spw = 1;
+  while (spw <= 16 && (long long)a.U * ctiles * ((a.S + spw - 1) / spw) > 256) ++spw;
+  const int tiles = (a.w + DT_TI - 1) / DT_TI;
+  return spw <= 16 && tiles >= 3 && spw * tiles >= 12 && spw >= (a.cand_off != nullptr ? 3 : 9) ? spw : 0;
+}
+
 bool sta_mfma_supports(const StaArgs& a) {
   if (a.dt != LASER_BF16) return false;
   if (!(a.d_q == 32 || a.d_q == 64 || a.d_q == 128)) return false;
@@ -1122,7 +1269,7 @@ static void launch_one(const StaArgs& a, int spw, int ctiles, int sruns, float n
 }
 
 template <int DQ, int D>
-static void launch_nw(const StaArgs& a, int nw, int spw, int ctiles, int sruns, float nsl) {
+static void launch_nw(const StaArgs& a, int nw, int spw, int ctiles, int sruns, int dealt, float nsl) {
   // eight waves fill a compute unit on their own and prefetch through LDS buffers of their own (direct-to-LDS
   // fetches for d_q = d = 128; a tuning build can select the register-staged form there too, for comparison);
   // smaller workgroups overlap memory and MFMA work across the several workgroups that share a compute unit
@@ -1145,34 +1292,27 @@ static void launch_nw(const StaArgs& a, int nw, int spw, int ctiles, int sruns, 
     else LASER_STA_STAGED(1, true);
   } else if (a.heads == 2) {
     LASER_STA_STAGED(2, false);
-  } else if (nw == 8 && DQ == 128 && D == 128 && tuning_int("LASER_STA_NODMA", 0) == 0) {
-    const unsigned blocks = (unsigned)((long long)a.U * ctiles * sruns);
-    if (a.reread)
-      hipLaunchKernelGGL((sta_mfma_dma_kernel<8, false>), dim3(blocks), dim3(512), 0, a.stream,
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,
-                         a.cand_off, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
-    else
-      hipLaunchKernelGGL((sta_mfma_dma_kernel<8, true>), dim3(blocks), dim3(512), 0, a.stream,
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,
-                         a.cand_off, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
+  } else if (nw >= 4 && DQ == 128 && D == 128 && tuning_int("LASER_STA_NODMA", 0) == 0) {
+    // (65 to 128 candidates: four waves, one workgroup per compute unit (LDS) and one wave per SIMD; its deep prefetch needs
+    // several segments per workgroup to pay, see sta_mfma_launch)
+    const unsigned blocks = dealt ? 256u : (unsigned)((long long)a.U * ctiles * sruns);
+#define LASER_STA_DMA(N, NTS, DEALT)                                                                                   \
+  hipLaunchKernelGGL((sta_mfma_dma_kernel<N, NTS, DEALT>), dim3(blocks), dim3(64 * N), 0, a.stream,                     \
+                     (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,        \
+                     a.cand_off, a.U, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt)
+    if (nw == 8) {
+      if (dealt) { if (a.reread) LASER_STA_DMA(8, false, true); else LASER_STA_DMA(8, true, true); }
+      else { if (a.reread) LASER_STA_DMA(8, false, false); else LASER_STA_DMA(8, true, false); }
+    } else {
+      if (dealt) { if (a.reread) LASER_STA_DMA(4, false, true); else LASER_STA_DMA(4, true, true); }
+      else { if (a.reread) LASER_STA_DMA(4, false, false); else LASER_STA_DMA(4, true, false); }
+    }
+#undef LASER_STA_DMA
   } else if (nw == 8) {
     const unsigned blocks = (unsigned)((long long)a.U * ctiles * sruns);
     hipLaunchKernelGGL((sta_mfma_pipe_kernel<DQ, D, 8>), dim3(blocks), dim3(512), 0, a.stream,
                        (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,
                        a.cand_off, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
-  }
-  else if (nw == 4 && DQ == 128 && D == 128 && tuning_int("LASER_STA_NODMA", 0) == 0) {
-    // 65 to 128 candidates: the same kernel with four waves, one workgroup per compute unit (LDS) and one wave per
-    // SIMD; its deep prefetch needs several segments per workgroup to pay (see sta_mfma_launch)
-    const unsigned blocks = (unsigned)((long long)a.U * ctiles * sruns);
-    if (a.reread)
-      hipLaunchKernelGGL((sta_mfma_dma_kernel<4, false>), dim3(blocks), dim3(256), 0, a.stream,
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,
-                         a.cand_off, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
-    else
-      hipLaunchKernelGGL((sta_mfma_dma_kernel<4, true>), dim3(blocks), dim3(256), 0, a.stream,
-                         (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,
-                         a.cand_off, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
   }
   else if (nw == 4) launch_one<DQ, D, 4, 1>(a, spw, ctiles, sruns, nsl);
   else if (nw == 2) launch_one<DQ, D, 2, 1>(a, spw, ctiles, sruns, nsl);
@@ -1183,7 +1323,7 @@ laser_status sta_mfma_launch(const StaArgs& a) {
   if (!sta_mfma_supports(a)) return LASER_ERR_UNSUPPORTED;
   const int nw = pick_nw(a);
   const int ctiles = (a.C + CW * nw - 1) / (CW * nw);
-  int spw = pick_spw(a, nw, ctiles);
+  int spw = pick_spw(a, nw, ctiles), dealt = 0;
   // the direct-to-LDS kernels take a compute unit's LDS per workgroup: as many segments per workgroup as bring the
   // launch down to one round of 256 workgroups, eight at most (16 users x 128 candidates x 40 segments: 640
   // workgroups of one segment 32.9 us in the register-staged form, 224 of three segments 26.8 us in this one)
@@ -1191,6 +1331,8 @@ laser_status sta_mfma_launch(const StaArgs& a) {
     const long long per_seg = (long long)a.U * ctiles * a.S;
     spw = (int)((per_seg + 255) / 256 < 8 ? (per_seg + 255) / 256 : 8);
     if (spw < 1) spw = 1;
+    dealt = deal_spw(a, ctiles);
+    if (dealt) spw = dealt;
   }
   const int spw_forced = tuning_int("LASER_STA_SPW", 0);   // tuning builds only
   if (spw_forced >= 1 && spw_forced <= 64) spw = spw_forced;
@@ -1198,12 +1340,12 @@ laser_status sta_mfma_launch(const StaArgs& a) {
   const float nsl = -1.4426950408889634f / a.gamma;
   const int key = a.d_q * 1000 + a.d;
   switch (key) {
-    case 32064: launch_nw<32, 64>(a, nw, spw, ctiles, sruns, nsl); break;
-    case 32128: launch_nw<32, 128>(a, nw, spw, ctiles, sruns, nsl); break;
-    case 64064: launch_nw<64, 64>(a, nw, spw, ctiles, sruns, nsl); break;
-    case 64128: launch_nw<64, 128>(a, nw, spw, ctiles, sruns, nsl); break;
-    case 128064: launch_nw<128, 64>(a, nw, spw, ctiles, sruns, nsl); break;
-    case 128128: launch_nw<128, 128>(a, nw, spw, ctiles, sruns, nsl); break;
+    case 32064: launch_nw<32, 64>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
+    case 32128: launch_nw<32, 128>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
+    case 64064: launch_nw<64, 64>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
+    case 64128: launch_nw<64, 128>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
+    case 128064: launch_nw<128, 64>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
+    case 128128: launch_nw<128, 128>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
     default: return LASER_ERR_UNSUPPORTED;
   }
   return launch_status();
