@@ -21,9 +21,11 @@
 // are zeros in LDS, so they add nothing to any finite sum (padding of the history is never read); a wave whose sums come out
 // not finite forms them again over the valid rows alone.
 //
-// What bounds it: waiting, 47 % of the waves' cycles (a block of rows is fetched between two barriers, with only the other
-// workgroup of a compute unit to overlap: 256 registers a wave), the matrix pipe is busy 14 %; at 64 users x 64 candidates, L = 2048, w = 128, d = d_q = 64 (lengths 410 .. 2048) the launch takes
-// 30 us for the 92 MB it cannot do without, eight passes of the one-item-per-wave kernel took 1840 us.
+// What bounds it: waiting (47 % of the waves' cycles before the rows of the next block were requested while the current one is
+// worked on; the matrix pipe is busy 14 %). The rows go to LDS directly, two sets of them where the workgroups that registers
+// allow on a compute unit still fit: 16 users x 64 candidates, L = 2000, w = 256, 128 / 128 41.6 -> 28 us, 1024 x 16, w = 10, 64 / 128
+// 553 -> 398 us, 64 users x 64 candidates, L = 2048, w = 128, 64 / 64 (lengths 410 .. 2048, 92 MB it cannot do without) 32 -> 31 us:
+// there the items have two blocks of candidates, and their 75 MB of gradients are most of the launch.
 #include "laser_internal.h"
 #include "sta_mfma_tile.h"
 
@@ -33,11 +35,11 @@ namespace laser {
 // stay free of bank conflicts: 16 consecutive rows at one chunk (operand reads, 16 bytes a lane) and four consecutive
 // rows at four neighbouring chunks (transpose loads, 8 bytes a lane).
 template <int D>
-__device__ __forceinline__ int swz(int r, int c) {
-  if constexpr (D == 128) return r * 256 + ((c ^ (((r & 3) << 2) | ((r >> 2) & 3))) << 4);
-  else if constexpr (D == 64) return r * 128 + ((c ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3))) << 4);
-  else return r * 64 + ((c ^ ((r >> 2) & 3)) << 4);
+__device__ __forceinline__ int swz_key(int r) {
+  return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (D == 64 ? (((r >> 1) & 1) << 2) | ((r >> 2) & 3) : (r >> 2) & 3);
 }
+template <int D>
+__device__ __forceinline__ int swz(int r, int c) { return r * (D * 2) + ((c ^ swz_key<D>(r)) << 4); }
 
 // operand whose lanes are the rows of a tile: row l32, k-slots 16 ks + 8 h ..
 template <int D>
@@ -73,18 +75,20 @@ __device__ __forceinline__ Split3 split3(const f32x16& x, int s) {
   return o;
 }
 
-// rows [0, rows) of a matrix with row pitch `pitch` elements into a 32-row tile, zeros after them; nt threads share it
+// rows [0, rows) of a matrix with row pitch `pitch` elements (uniform, 32 rows below 4 GB) into a 32-row tile, zeros after them;
+// `waves` waves share it. The rows go to LDS directly and are awaited by the caller.
 template <int D>
-__device__ __forceinline__ void stage_rows(unsigned char* t, const unsigned short* src, size_t pitch, int rows, int tid,
-                                           int nt) {
+__device__ __forceinline__ void stage_rows(unsigned char* t, const unsigned short* src, size_t pitch, int rows, int wave,
+                                           int waves, int lane) {
   constexpr int CH = D / 8;
-  for (int e = tid; e < 32 * CH; e += nt) {
-    const int r = e / CH, c = e % CH;
-    u32x4 x = {0u, 0u, 0u, 0u};
-    if (r < rows) x = *reinterpret_cast<const u32x4*>(src + (size_t)r * pitch + c * 8);
-    *reinterpret_cast<u32x4*>(t + swz<D>(r, c)) = x;
+  const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)t);
+  for (int g = wave; g < 32 * CH / 64; g += waves) {
+    const int e = g * 64 + lane, r = e / CH, c = (e % CH) ^ swz_key<D>(r);
+    if (r < rows) dma16(src, (unsigned)r * (unsigned)(pitch * 2) + c * 16, at + g * 1024);
+    else *reinterpret_cast<u32x4*>(t + e * 16) = u32x4{0u, 0u, 0u, 0u};
   }
 }
+__device__ __forceinline__ void staged() { __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); }
 
 // Whether any score gradient of a wave was not finite, from one of its column blocks of dK or dQ: every column of an item's
 // or a query's row is a sum over all of its score gradients, and not finite if one of them is (zero times it is NaN).
@@ -132,13 +136,15 @@ struct StaBwdMfmaShape {
   int nct, groups, spg;
 };
 
-template <int DQ, int D>
-__global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned short* __restrict__ q,
+// PRE: two sets of tiles, the next block's rows on their way into one while the other is worked on (one barrier a block);
+// half_lds: bytes of a set
+template <int DQ, int D, bool PRE>
+__global__ __launch_bounds__(256, DQ + D <= 128 ? 3 : 2) void sta_bwd_mfma_kernel(const unsigned short* __restrict__ q,
                                                               const unsigned short* __restrict__ k,
                                                               const unsigned short* __restrict__ v,
                                                               const unsigned short* __restrict__ dhp,
                                                               const int32_t* __restrict__ lens, int C, int L, int w,
-                                                              int S, StaBwdMfmaShape sh, int query_blocks,
+                                                              int S, StaBwdMfmaShape sh, int query_blocks, int half_lds,
                                                               float neg_scale_log2e, float inv_gamma,
                                                               float* __restrict__ dk, float* __restrict__ dv,
                                                               float* __restrict__ dq_part) {
@@ -193,15 +199,27 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
 #pragma unroll
         for (int ks = 0; ks < KV; ++ks) vf[ks] = *reinterpret_cast<const bf16x8*>(v + row * D + ks * 16 + h * 8);
       }
-      unsigned char* Qs = lds;
-      unsigned char* Hs = lds + QBYTES + si * VBYTES;
       const int hseg = seg < S ? seg : S - 1;
-      for (int c0 = 0; c0 < C; c0 += 32) {
+      auto stage = [&](int c0, int buf) {
         const int nc = C - c0 < 32 ? C - c0 : 32;
-        __syncthreads();
-        stage_rows<DQ>(Qs, q + ((size_t)u * C + c0) * DQ, DQ, nc, tid, 256);
-        stage_rows<D>(Hs, dhp + (((size_t)u * C + c0) * S + hseg) * D, (size_t)S * D, nc, tid % (64 * sh.wi), 64 * sh.wi);
-        __syncthreads();
+        unsigned char* set = lds + (PRE ? buf * half_lds : 0);
+        stage_rows<DQ>(set, q + ((size_t)u * C + c0) * DQ, DQ, nc, wave, 4, lane);
+        stage_rows<D>(set + QBYTES + si * VBYTES, dhp + (((size_t)u * C + c0) * S + hseg) * D, (size_t)S * D, nc, wave % sh.wi, sh.wi, lane);
+      };
+      if (PRE) stage(0, 0);
+      for (int c0 = 0, buf = 0; c0 < C; c0 += 32, buf ^= 1) {
+        if (PRE) {
+          staged();
+          __syncthreads();
+          if (c0 + 32 < C) stage(c0 + 32, buf ^ 1);
+        } else {
+          __syncthreads();
+          stage(c0, 0);
+          staged();
+          __syncthreads();
+        }
+        const unsigned char* Qs = lds + (PRE ? buf * half_lds : 0);
+        const unsigned char* Hs = Qs + QBYTES + si * VBYTES;
         if (work_here) {
           f32x16 s = zero16, dd = zero16;
 #pragma unroll
@@ -283,8 +301,6 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
     const int valid_segs = (n + w - 1) / w;
     if (i_end > valid_segs) i_end = valid_segs;
     const int tiles = (w + 31) / 32;                                   // (w <= L)
-    unsigned char* Ks = lds + sq * (QBYTES + VBYTES);
-    unsigned char* Vs = Ks + QBYTES;
     const int crow = cbase + l32 < C ? cbase + l32 : C - 1;            // (rows past the last candidate are not stored)
 
     bf16x8 qf[KQ], hf[KV];
@@ -294,26 +310,44 @@ __global__ __launch_bounds__(256, 2) void sta_bwd_mfma_kernel(const unsigned sho
 #pragma unroll
     for (int ks = 0; ks < KQ; ++ks)
       qf[ks] = *reinterpret_cast<const bf16x8*>(q + ((size_t)u * C + crow) * DQ + ks * 16 + h * 8);
-    for (int i0 = i_beg; i0 < i_end; i0 += sh.ws_q) {
-      const int i = i0 + sq;
-      const bool live = i < i_end;
-      const int lo = live ? i * w : 0;
-      int hi = live ? (i * w + w < L ? i * w + w : L) : 0;
-      if (hi > n) hi = n;
-      if (live) {
+    // item tile t of segment i0 + sq, for every wave at once; with one segment in work the history's end ends the walk
+    struct At { int i0, t; };
+    auto more = [&](const At& a) { return a.i0 < i_end && !(sh.ws_q == 1 && a.i0 * w + a.t * 32 >= n); };
+    auto after = [&](const At& a) { return a.t + 1 < tiles ? At{a.i0, a.t + 1} : At{a.i0 + sh.ws_q, 0}; };
+    auto items_of = [&](const At& a) {                                 // valid items of the tile (0: none)
+      const int i = a.i0 + sq, end = i * w + w < n ? i * w + w : n, left = end - (i * w + a.t * 32);
+      return i < i_end ? (left < 0 ? 0 : (left < 32 ? left : 32)) : 0;
+    };
+    auto stage = [&](const At& a, int buf) {
+      const int rows = items_of(a);
+      const size_t r0 = (size_t)u * L + (rows > 0 ? (a.i0 + sq) * w + a.t * 32 : 0);
+      unsigned char* set = lds + (PRE ? buf * half_lds : 0) + sq * (QBYTES + VBYTES);
+      stage_rows<DQ>(set, k + r0 * DQ, DQ, rows, wave % sh.wc, sh.wc, lane);
+      stage_rows<D>(set + QBYTES, v + r0 * D, D, rows, wave % sh.wc, sh.wc, lane);
+    };
+    At cur = {i_beg, 0};
+    if (PRE && more(cur)) stage(cur, 0);
+    for (int buf = 0; more(cur); cur = after(cur), buf ^= 1) {
+      {
+        const int i = cur.i0 + sq, rows = items_of(cur);
+        if (cur.t == 0 && i < i_end) {
 #pragma unroll
-        for (int ks = 0; ks < KV; ++ks)
-          hf[ks] = *reinterpret_cast<const bf16x8*>(dhp + (((size_t)u * C + crow) * S + i) * D + ks * 16 + h * 8);
-      }
-      for (int t = 0; t < tiles; ++t) {
-        const int left = hi - lo - t * 32;
-        const int rows = left < 0 ? 0 : (left < 32 ? left : 32);
-        if (i0 * w + t * 32 >= n && sh.ws_q == 1) break;               // workgroup-uniform: the history ends here
-        const size_t r0 = (size_t)u * L + lo + (rows > 0 ? t * 32 : 0);
-        __syncthreads();
-        stage_rows<DQ>(Ks, k + r0 * DQ, DQ, rows, tid % (64 * sh.wc), 64 * sh.wc);
-        stage_rows<D>(Vs, v + r0 * D, D, rows, tid % (64 * sh.wc), 64 * sh.wc);
-        __syncthreads();
+          for (int ks = 0; ks < KV; ++ks)
+            hf[ks] = *reinterpret_cast<const bf16x8*>(dhp + (((size_t)u * C + crow) * S + i) * D + ks * 16 + h * 8);
+        }
+        if (PRE) {
+          staged();
+          __syncthreads();
+          const At nxt = after(cur);
+          if (more(nxt)) stage(nxt, buf ^ 1);
+        } else {
+          __syncthreads();
+          stage(cur, 0);
+          staged();
+          __syncthreads();
+        }
+        const unsigned char* Ks = lds + (PRE ? buf * half_lds : 0) + sq * (QBYTES + VBYTES);
+        const unsigned char* Vs = Ks + QBYTES;
         if (rows > 0 && mine) {
           f32x16 s = zero16, dd = zero16;
 #pragma unroll
@@ -433,12 +467,19 @@ static laser_status launch_shape(const StaBwdArgs& a, const StaBwdMfmaShape& s, 
   if (qb + ib > 0x7fffffffLL) return LASER_ERR_SHAPE;
   const int items = 32 * DQ * 2 + s.ws_i * 32 * D * 2, queries = s.ws_q * (32 * DQ * 2 + 32 * D * 2);
   const int reduce = (s.ws_q - 1) * s.wc * DQ * 32 * 4;
-  int lds = items > queries ? items : queries;
+  const int set = items > queries ? items : queries;
+  // two sets of tiles while as many workgroups as registers allow still fit a compute unit, and more than one block to walk
+  const bool pre = 2 * (DQ + D <= 128 ? 3 : 2) * set <= 160 * 1024 && (a.C > 32 || s.spg > s.ws_q || a.w > 32);
+  int lds = pre ? 2 * set : set;
   if (reduce > lds) lds = reduce;
   const float inv_gamma = 1.0f / a.gamma;
-  hipLaunchKernelGGL((sta_bwd_mfma_kernel<DQ, D>), dim3((unsigned)(qb + ib)), dim3(256), lds, a.stream,
+  auto kern = pre ? sta_bwd_mfma_kernel<DQ, D, true> : sta_bwd_mfma_kernel<DQ, D, false>;
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+    return LASER_ERR_LAUNCH;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(qb + ib)), dim3(256), lds, a.stream,
                      (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,
-                     (const unsigned short*)a.dhp, a.lens, a.C, a.L, a.w < a.L ? a.w : a.L, a.S, s, (int)qb,
+                     (const unsigned short*)a.dhp, a.lens, a.C, a.L, a.w < a.L ? a.w : a.L, a.S, s, (int)qb, set,
                      -1.4426950408889634f * inv_gamma, inv_gamma, static_cast<float*>(a.dk), static_cast<float*>(a.dv),
                      part);
   return launch_status();

@@ -533,13 +533,7 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_pipe_kernel(const unsigned s
 //    whole path, whose next launch streams them back (measured: about 3 us of the step).
 constexpr int DT_TI = 32, DT_NBUF = 5, DT_AHEAD = 4;
 
-// 16 bytes per lane from global (uniform base + per-lane byte offset) to LDS (uniform address + 16 * lane)
-__device__ __forceinline__ void dma16(const void* gbase, unsigned voff, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n" ::"s"(lds_addr), "v"(voff), "s"(gbase)
-               : "memory");
-}
 
-constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
 // waits until at most n (rounded down to even, at most 30) of this wave's vector-memory operations are outstanding
 __device__ __forceinline__ void wait_vm(int n) {

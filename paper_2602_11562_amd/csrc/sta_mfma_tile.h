@@ -30,6 +30,15 @@ __device__ __forceinline__ float gate(float score, float neg_scale_log2e) {
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(score * neg_scale_log2e));
 }
 
+// 16 bytes per lane from global (uniform base + per-lane byte offset) to LDS (uniform address + 16 * lane)
+__device__ __forceinline__ void dma16(const void* gbase, unsigned voff, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n" ::"s"(lds_addr), "v"(voff), "s"(gbase)
+               : "memory");
+}
+
+// (gfx9 encoding of a wait that leaves every other counter alone)
+constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+
 template <int DQ, int D, int NT>
 struct Stage {
   static constexpr int KCH = DQ / 8, VCH = D / 8;   // 16-byte chunks per row
