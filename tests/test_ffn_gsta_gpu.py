@@ -80,6 +80,8 @@ FUSED = {
     # first of the next (S = 5: two whole pairs; S = 20: 20 + 12, 8 + 20, ...; S = 100: 96 + 4 | 28 + ...)
     "packed_tiles_5": ("bf16", 6, 800, 60, 12, 128, 128, 1, [60, 13, 60, 0, 35, 59], 1.0),
     "packed_tiles_20": ("bf16", 5, 1000, 200, 10, 128, 64, 1, [200, 200, 95, 0, 151], 1.0),
+    # a pair that ends inside its tile after 1 .. 24 rows: at the edges of the weighted sum's groups of eight and beside them
+    "packed_tiles_ends": ("bf16", 16, 260, 31, 1, 128, 128, 1, [1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 12, 0, 30, 2, 31], 1.0),
     "packed_tiles_100": ("bf16", 3, 750, 1000, 10, 128, 128, 1, [1000, 1000, 637], 1.0),
 }
 UNFUSED = {
