@@ -533,8 +533,6 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_pipe_kernel(const unsigned s
 //    whole path, whose next launch streams them back (measured: about 3 us of the step).
 constexpr int DT_TI = 32, DT_NBUF = 5, DT_AHEAD = 4;
 
-
-
 // waits until at most n (rounded down to even, at most 30) of this wave's vector-memory operations are outstanding
 __device__ __forceinline__ void wait_vm(int n) {
   switch (n >> 1) {
