@@ -21,8 +21,8 @@
 // are zeros in LDS, so they add nothing to any finite sum (padding of the history is never read); a wave whose sums come out
 // not finite forms them again over the valid rows alone.
 //
-// What bounds it: waiting (47 % of the waves' cycles before the rows of the next block were requested while the current one is
-// worked on; the matrix pipe is busy 14 %). The rows go to LDS directly, two sets of them where the workgroups that registers
+// What bounds it: waiting (47 % of the waves' cycles, and the matrix pipe busy 14 %, counted before the rows of the next block were
+// requested while the current one is worked on). The rows go to LDS directly, two sets of them where the workgroups that registers
 // allow on a compute unit still fit: 16 users x 64 candidates, L = 2000, w = 256, 128 / 128 41.6 -> 28 us, 1024 x 16, w = 10, 64 / 128
 // 553 -> 398 us, 64 users x 64 candidates, L = 2048, w = 128, 64 / 64 (lengths 410 .. 2048, 92 MB it cannot do without) 32 -> 31 us:
 // there the items have two blocks of candidates, and their 75 MB of gradients are most of the launch.
@@ -474,8 +474,9 @@ static laser_status launch_shape(const StaBwdArgs& a, const StaBwdMfmaShape& s, 
   if (reduce > lds) lds = reduce;
   const float inv_gamma = 1.0f / a.gamma;
   auto kern = pre ? sta_bwd_mfma_kernel<DQ, D, true> : sta_bwd_mfma_kernel<DQ, D, false>;
+  // (the same limit whatever the call, half a compute unit's LDS at most is asked for: threads do not lower each other's)
   if (lds > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024) != hipSuccess)
     return LASER_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3((unsigned)(qb + ib)), dim3(256), lds, a.stream,
                      (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v,
