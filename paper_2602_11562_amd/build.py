@@ -93,6 +93,35 @@ def build_host_check(out: str) -> str:
     return out
 
 
+def build_launch_recorder(out: str) -> str:
+    """Build a library of the same entry points whose launches are recorded instead of made (tests/launch_recorder.cpp): the
+    host halves of the sources, with the overrides of a tuning build. No GPU needed to build or use it."""
+    os.makedirs(OBJDIR, exist_ok=True)
+    no_kernels = os.path.join(OBJDIR, "no_kernels.bin")      # what stands in the place of the device code
+    with open(no_kernels, "wb") as f:
+        f.write(b"none")
+    flags = [f for f in HIPCC_FLAGS if not f.startswith("--offload-arch")] + [
+        "-O1", "-DLASER_TUNING", "-Xclang", "-fcuda-include-gpubinary", "-Xclang", no_kernels]
+
+    def compile_one(src: str) -> str:
+        obj = os.path.join(OBJDIR, "launches_" + os.path.basename(src).rsplit(".", 1)[0] + ".o")
+        cmd = [_hipcc(), "-x", "hip", "--offload-host-only", *flags, "-c", src, "-o", obj]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"host half of {src}:\n" + r.stderr[-4000:])
+        return obj
+
+    srcs = [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(ROOT, "tests", "launch_recorder.cpp")]
+    with ThreadPoolExecutor(max_workers=6) as ex:
+        objs = list(ex.map(compile_one, srcs))
+    # (bound to its own functions, whatever runtime the process has loaded)
+    r = subprocess.run(["/opt/rocm/lib/llvm/bin/clang++", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-o", out, *objs, "-ldl"],
+                       capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("launch recorder link failed:\n" + r.stderr[-4000:])
+    return out
+
+
 if __name__ == "__main__":
     if len(sys.argv) > 2 and sys.argv[1] == "--tuning":      # python -m paper_2602_11562_amd.build --tuning OUT.so
         print(build_library(tuning=True, out=os.path.abspath(sys.argv[2])))

@@ -1327,7 +1327,10 @@ laser_status sta_mfma_launch(const StaArgs& a) {
     if (dealt) spw = dealt;
   }
   const int spw_forced = tuning_int("LASER_STA_SPW", 0);   // tuning builds only
-  if (spw_forced >= 1 && spw_forced <= 64) spw = spw_forced;
+  if (spw_forced >= 1 && spw_forced <= 64) {   // the launch's own division, as many workgroups as it takes
+    spw = spw_forced;
+    dealt = 0;
+  }
   const int sruns = (a.S + spw - 1) / spw;
   const float nsl = -1.4426950408889634f / a.gamma;
   const int key = a.d_q * 1000 + a.d;
