@@ -308,7 +308,7 @@ static size_t gsta_bwd_lds(const GstaBwdArgs& a) {
 }
 
 bool gsta_backward_supports(const GstaBwdArgs& a) {
-  return a.d <= GB_MAXD && a.M <= GB_MAXM && gsta_bwd_lds(a) <= 150 * 1024;
+  return a.d <= GB_MAXD && a.M <= GB_MAXM && gsta_bwd_lds(a) <= DYNAMIC_LDS_MOST;
 }
 
 static int gsta_bwd_workgroups(int d, int M) { return M * 3 * ((d + 15) / 16) * ((d + 15) / 16); }
@@ -336,7 +336,7 @@ laser_status gsta_backward_launch(const GstaBwdArgs& a) {
   } else if (a.dt == LASER_BF16) {
     auto kern = gsta_bwd_kernel<unsigned short>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)P), dim3(GB_THREADS), lds, a.stream, (const unsigned short*)a.seg,
                        (const unsigned short*)a.t0, (const unsigned short*)a.wq, (const unsigned short*)a.wk,
@@ -345,7 +345,7 @@ laser_status gsta_backward_launch(const GstaBwdArgs& a) {
   } else {
     auto kern = gsta_bwd_kernel<float>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)P), dim3(GB_THREADS), lds, a.stream, (const float*)a.seg,
                        (const float*)a.t0, (const float*)a.wq, (const float*)a.wk, (const float*)a.wv, a.lens, a.dz, a.C,

@@ -386,7 +386,7 @@ static laser_status launch_pairs(const GstaBwdArgs& a, int P) {
   auto kern = gsta_bwd_tile_kernel<T, D, PW>;
   const size_t lds = lds_for<T, D>(a, PW);
   if (lds > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
     return LASER_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3((unsigned)((P + PW - 1) / PW)), dim3(4 * D), lds, a.stream, (const T*)a.seg,
                      (const T*)a.t0, (const T*)a.wq, (const T*)a.wk, (const T*)a.wv, a.lens, a.dz, P, a.C, a.L,
@@ -394,14 +394,12 @@ static laser_status launch_pairs(const GstaBwdArgs& a, int P) {
   return launch_status();
 }
 
-constexpr size_t GSTA_BWD_TILE_LDS = 150 * 1024;
-
 template <typename T, int D>
 static laser_status launch_t(const GstaBwdArgs& a) {
   const int P = a.U * a.C, per = D == 128 || sizeof(T) == 4 ? P : (P + 1) / 2;
   // pairs per workgroup: as in the forward kernel (gsta_tiled.hip), halved while their rows' scores do not fit in LDS
   int pw = per <= 256 ? 1 : per <= 512 ? 2 : per <= 1024 ? 4 : per <= 2048 ? 8 : 16;
-  while (pw > 1 && lds_for<T, D>(a, pw) > GSTA_BWD_TILE_LDS) pw /= 2;
+  while (pw > 1 && lds_for<T, D>(a, pw) > DYNAMIC_LDS_MOST) pw /= 2;
   switch (pw) {
     case 1: return launch_pairs<T, D, 1>(a, P);
     case 2: return launch_pairs<T, D, 2>(a, P);
@@ -415,7 +413,7 @@ bool gsta_bwd_tile_supports(const GstaBwdArgs& a) {
   if (a.d != 64 && a.d != 128) return false;
   const size_t lds = a.dt == LASER_BF16 ? (a.d == 64 ? lds_for<unsigned short, 64>(a, 1) : lds_for<unsigned short, 128>(a, 1))
                                         : (a.d == 64 ? lds_for<float, 64>(a, 1) : lds_for<float, 128>(a, 1));
-  return lds <= GSTA_BWD_TILE_LDS;
+  return lds <= DYNAMIC_LDS_MOST;
 }
 
 laser_status gsta_bwd_tile_launch(const GstaBwdArgs& a) {

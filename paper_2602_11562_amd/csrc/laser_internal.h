@@ -231,6 +231,11 @@ inline int tuning_int(const char* name, int unset) {
   return unset;
 }
 
+// Dynamic LDS that kernels with sizes of the call's own ask for at most, and the limit they set where they need more than the
+// default. A kernel's limit belongs to the process: set to each call's need, a thread with a smaller one would lower it
+// between another's setting and launch.
+constexpr int DYNAMIC_LDS_MOST = 150 * 1024;
+
 inline laser_status launch_status() { return hipGetLastError() == hipSuccess ? LASER_OK : LASER_ERR_LAUNCH; }
 
 // ---------------------------------------------------------------- device helpers

@@ -49,14 +49,14 @@ __global__ __launch_bounds__(PG_THREADS) void project_generic_kernel(const T* __
 
 laser_status project_generic_launch(const ProjArgs& a) {
   const size_t lds = (size_t)PG_ROWS * a.d_in * sizeof(float);
-  if (lds > 150 * 1024) return LASER_ERR_UNSUPPORTED;
+  if (lds > DYNAMIC_LDS_MOST) return LASER_ERR_UNSUPPORTED;
   const long long blocks = (a.rows + PG_ROWS - 1) / PG_ROWS;
   if (blocks > 0x7fffffffLL) return LASER_ERR_SHAPE;
   if (blocks == 0) return LASER_OK;
   if (a.dt == LASER_BF16) {
     auto kern = project_generic_kernel<unsigned short>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PG_THREADS), lds, a.stream, (const unsigned short*)a.x,
                        (const unsigned short*)a.w[0], (const unsigned short*)a.w[1], a.rows, a.d_in, a.n[0], a.n[1],
@@ -65,7 +65,7 @@ laser_status project_generic_launch(const ProjArgs& a) {
   } else {
     auto kern = project_generic_kernel<float>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PG_THREADS), lds, a.stream, (const float*)a.x,
                        (const float*)a.w[0], (const float*)a.w[1], a.rows, a.d_in, a.n[0], a.n[1], a.wpitch[0],
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(PG_THREADS) void project_heads_generic_kernel(const
 
 laser_status project_heads_generic_launch(const ProjHeadsArgs& a) {
   const size_t lds = (size_t)PG_ROWS * a.heads * a.d_in * sizeof(float);
-  if (lds > 150 * 1024) return LASER_ERR_UNSUPPORTED;
+  if (lds > DYNAMIC_LDS_MOST) return LASER_ERR_UNSUPPORTED;
   const long long rows = a.P * a.S;
   const long long blocks = (rows + PG_ROWS - 1) / PG_ROWS;
   if (blocks > 0x7fffffffLL) return LASER_ERR_SHAPE;
@@ -295,14 +295,14 @@ laser_status project_heads_generic_launch(const ProjHeadsArgs& a) {
   if (a.dt == LASER_BF16) {
     auto kern = project_heads_generic_kernel<unsigned short>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PG_THREADS), lds, a.stream, (const unsigned short*)a.x,
                        (const unsigned short*)a.wv, rows, a.S, a.d_in, a.d, a.heads, (unsigned short*)a.y);
   } else {
     auto kern = project_heads_generic_kernel<float>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PG_THREADS), lds, a.stream, (const float*)a.x,
                        (const float*)a.wv, rows, a.S, a.d_in, a.d, a.heads, (float*)a.y);

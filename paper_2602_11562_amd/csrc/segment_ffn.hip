@@ -103,7 +103,7 @@ __global__ __launch_bounds__(FG_THREADS) void segment_ffn_generic_kernel(
 
 bool segment_ffn_generic_supports(const FfnArgs& a) {
   const size_t lds = (size_t)FG_ROWS * (2 * a.d + a.d_ff + 2) * sizeof(float);
-  return lds <= 150 * 1024;
+  return lds <= DYNAMIC_LDS_MOST;
 }
 
 laser_status segment_ffn_generic_launch(const FfnArgs& a) {
@@ -115,7 +115,7 @@ laser_status segment_ffn_generic_launch(const FfnArgs& a) {
   if (a.dt == LASER_BF16) {
     auto kern = segment_ffn_generic_kernel<unsigned short>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(FG_THREADS), lds, a.stream, (const unsigned short*)a.seg,
                        a.lens, (const unsigned short*)a.w1, a.b1, (const unsigned short*)a.w2, a.b2, a.ln_g, a.ln_b,
@@ -123,7 +123,7 @@ laser_status segment_ffn_generic_launch(const FfnArgs& a) {
   } else {
     auto kern = segment_ffn_generic_kernel<float>;
     if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, DYNAMIC_LDS_MOST) != hipSuccess)
       return LASER_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(FG_THREADS), lds, a.stream, (const float*)a.seg, a.lens,
                        (const float*)a.w1, a.b1, (const float*)a.w2, a.b2, a.ln_g, a.ln_b, a.cand_off, a.U, rows, a.C, a.L, a.d,

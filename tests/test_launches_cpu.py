@@ -53,3 +53,46 @@ def test_forced_segments_per_workgroup_launch_the_whole_division(recorder, monke
     print(own.kernel, own.grid, forced.kernel, forced.grid)
     assert forced.block == own.block == 64 * waves
     assert forced.grid == U * tiles * -(-S // spw)
+
+
+def gsta_backward(U, d, S, M, dt):
+    return lambda lib: lib.laser_gsta_backward(A, A, A, A, A, A, A, U, 128, S * 8, d, 8, M, dt, A, A, A, A, A, A, 1 << 40, None)
+
+
+def project(d_in, dt):
+    return lambda lib: lib.laser_project_q_forward_variant(A, A, 2, 3, d_in, 128, dt, A, None, binding.PROJECT_GENERIC)
+
+
+def project_heads(heads, d_in, dt):
+    return lambda lib: lib.laser_project_heads_forward(A, A, 3, 5, d_in, 128, heads, dt, A, None, binding.PROJECT_GENERIC)
+
+
+def ffn(d_ff, dt):
+    return lambda lib: lib.laser_segment_ffn_forward_variant(A, A, A, A, A, A, A, A, 2, 3, 64, 256, d_ff, 8, 1e-5, dt, A, None,
+                                                             binding.FFN_GENERIC)
+
+
+# A kernel's limit of dynamic LDS belongs to the process: if every call sets its own need, a second thread with a smaller one
+# lowers it between another's setting and launch. Calls of one kernel with different needs past 64 KB, the largest first.
+LIMITS = {
+    "gsta_bwd_tile_kernel": [gsta_backward(32, d, S, M, dt) for d in (64, 128) for dt in (F32, BF16) for M, S in ((2, 120), (2, 60), (1, 140), (1, 30))],
+    "gsta_bwd_kernel": [gsta_backward(2, 256, S, M, dt) for dt in (F32, BF16) for M, S in ((2, 65), (2, 45), (1, 130), (1, 90))],
+    "project_generic_kernel": [project(d_in, dt) for d_in in (4096, 3072, 2304) for dt in (F32, BF16)],
+    "project_heads_generic_kernel": [project_heads(heads, d_in, dt) for heads, d_in in ((8, 512), (4, 768)) for dt in (F32, BF16)],
+    "segment_ffn_generic_kernel": [ffn(d_ff, dt) for d_ff in (4096, 3072, 2048) for dt in (F32, BF16)],
+}
+
+
+@pytest.mark.parametrize("kernel", list(LIMITS))
+def test_a_kernel_has_one_lds_limit(recorder, kernel):
+    seen = {}
+    for call in LIMITS[kernel]:
+        for r in launches(recorder, call):
+            name = r.kernel.decode()
+            if f"{len(kernel)}{kernel}I" in name and r.lds > 64 * 1024:
+                assert r.limit >= r.lds
+                seen.setdefault(name, set()).add((r.lds, r.limit))
+    print({k: sorted(v) for k, v in seen.items()})
+    assert any(len({lds for lds, _ in v}) > 1 for v in seen.values())      # (the calls are what they are meant to be)
+    for name, v in seen.items():
+        assert len({limit for _, limit in v}) == 1, name
