@@ -195,7 +195,10 @@ def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream.cuda_stream or None
     core = _torch()._C     # handle of the current device's current stream
-    return core._cuda_getCurrentRawStream(core._cuda_getDevice()) or None
+    try:
+        return core._cuda_getCurrentRawStream(core._cuda_getDevice()) or None
+    except AttributeError:     # a torch without these two, which are not of its documented interface
+        return _torch().cuda.current_stream().cuda_stream or None
 
 
 def _check(code: int, where: str) -> None:

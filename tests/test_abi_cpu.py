@@ -136,6 +136,19 @@ def test_binding_refuses_host_tensors():
                                 seg_out=torch.zeros(1, 2, 2, 8), want_cnt=False)
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_the_current_stream_without_torchs_undocumented_functions(monkeypatch, missing):
+    import types
+
+    import torch
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1000 + device)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x2000))
+    assert binding._stream(None) == 0x1003
+    monkeypatch.delattr(torch._C, missing)
+    assert binding._stream(None) == 0x2000
+
+
 def _multires(lib, seg=A, lens=None, U=2, C=3, L=64, d=16, w=8, r=2, dt=1, pool=A, recent=A):
     return lib.laser_multires_forward(seg, lens, U, C, L, d, w, r, dt, pool, recent, None)
 
