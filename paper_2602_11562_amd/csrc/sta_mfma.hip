@@ -714,11 +714,10 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
 
   // Dealt out: histories differ in length, and with S segments to every user the longest one's workgroup sets the time while
   // others have nothing. Every wave takes the lengths of all users and the smallest number of segments per workgroup, s, with
-  // which the runs of s valid segments of all users are no more than the launch has workgroups; run number `bid` is its own. A
-  // user's empty segments are shared by its runs. With full histories that is the launch's own division, so its early
-  // requests stand; otherwise they are made again (into the same places: loads retire in order). 29 users x up to 201
-  // candidates, 31 segments, lengths uniform in [L / 5, L]: the launch 27.8 -> 21 us
-  int n, zero_lo, zero_hi;   // the user's valid items; the segments this workgroup writes as zeros
+  // which the runs of s valid segments of all users are no more than the launch has workgroups; run number `bid` is its own. The
+  // early requests are made again (into the same places: loads retire in order). Empty segments are shared by all workgroups,
+  // at the end. 29 users x up to 201 candidates, 31 segments, lengths uniform in [L / 5, L]: the launch 27.8 -> 21 us
+  int n, zero_lo = 0, zero_hi = 0;   // the user's valid items; the segments this workgroup writes as zeros (not dealt out)
   if (dealt) {
     wait_vm((early ? CW / 4 : 0) + (spec ? OPT : 0));   // the copies have landed (they are older than the rest)
     asm volatile("" ::: "memory");
@@ -726,7 +725,6 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
     int len = copy(0);
     len = len < 0 ? 0 : (len > L ? L : len);
     n = L;
-    zero_lo = zero_hi = 0;
     if (cand_off == nullptr && __builtin_amdgcn_ballot_w64(lane < U && len != L) == 0) {   // full histories: nothing to divide anew
       if (!early) return;
     } else {
@@ -756,38 +754,33 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
         do divide(++s);
         while (total > (int)gridDim.x);
       }
-      if (bid >= total) {   // nothing left (what is under way into this workgroup's LDS has to land first)
-        wait_vm(0);
-        return;
+      if (bid >= total) {   // no run left: a share of the zeros is all this workgroup does
+        crange = {0, 0};
+        srun = 1;
+        n = 0;
+      } else {
+        const int to = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > bid));
+        const int to_runs = __builtin_amdgcn_readlane(runs, to);
+        int r = bid - __builtin_amdgcn_readlane(upto - runs * tiles, to), to_ct = 0;
+        while (r >= to_runs) {
+          r -= to_runs;
+          ++to_ct;
+        }
+        n = __builtin_amdgcn_readlane(len, to);
+        span = __builtin_amdgcn_readlane(own, to);
+        if (to != u || to_ct != ct || r * span != seg_lo) {
+          u = to;
+          ct = to_ct;
+          crange = cand_range(cand_off, u, C_all, P);
+          kU = reinterpret_cast<const unsigned char*>(k + (size_t)u * L * DQ);
+          vU = reinterpret_cast<const unsigned char*>(v + (size_t)u * L * D);
+          spec = false;
+          if (crange.count > 0) fetch_queries();
+        }
+        srun = r;
+        seg_lo = r * span;
       }
-      const int to = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > bid));
-      const int to_runs = __builtin_amdgcn_readlane(runs, to);
-      int r = bid - __builtin_amdgcn_readlane(upto - runs * tiles, to), to_ct = 0;
-      while (r >= to_runs) {
-        r -= to_runs;
-        ++to_ct;
-      }
-      n = __builtin_amdgcn_readlane(len, to);
-      const int valid = __builtin_amdgcn_readlane(nv, to);
-      zero_lo = valid + (S - valid) * r / to_runs;
-      zero_hi = valid + (S - valid) * (r + 1) / to_runs;
-      span = __builtin_amdgcn_readlane(own, to);
-      if (to != u || to_ct != ct || r * span != seg_lo) {
-        u = to;
-        ct = to_ct;
-        crange = cand_range(cand_off, u, C_all, P);
-        kU = reinterpret_cast<const unsigned char*>(k + (size_t)u * L * DQ);
-        vU = reinterpret_cast<const unsigned char*>(v + (size_t)u * L * D);
-        spec = false;
-        if (crange.count > 0) fetch_queries();
-      }
-      srun = r;
-      seg_lo = r * span;
-      if (crange.count == 0) {
-        wait_vm(0);
-        if (srun == 0) write_seg_cnt(seg_cnt, u, n, L, w, S, tid, NT);
-        return;
-      }
+      if (crange.count == 0) span = 0;   // (its counts are written below)
     }
   } else {
     n = __builtin_amdgcn_readfirstlane(valid_len(lens, u, L));
@@ -1153,15 +1146,39 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   if (out_seg >= 0) flush_units(FU - out_units);
   }
 
-  if (zero_lo < zero_hi) {   // empty segments: exact zeros
-    const int ncand = (C - ct * (CW * NW)) < CW * NW ? (C - ct * (CW * NW)) : CW * NW;
-    if constexpr (dealt) {   // a few of every candidate: row groups, one segment after the other (no division per piece)
-      for (int cc = wave * RPI + lane / LPR; cc < ncand; cc += NW * RPI) {
-        unsigned short* row = seg_out + ((pb + ct * (CW * NW) + cc) * S + zero_lo) * D + (lane % LPR) * 8;
-        for (int ii = zero_lo; ii < zero_hi; ++ii, row += D) *reinterpret_cast<u32x4*>(row) = u32x4{0u, 0u, 0u, 0u};
-      }
-      return;
+  // Empty segments: exact zeros. Dealt out, every wave of the launch takes an equal share of all users' (a user with few valid
+  // segments has few runs: left to those, 6 users x 277 candidates, 82 segments, two of them nearly empty, took 51 us)
+  if constexpr (dealt) {
+    asm volatile("" ::: "memory");
+    const int at = cand_off ? *reinterpret_cast<const int*>(deal + 256 + lane * 4) : 0;
+    int len = *reinterpret_cast<const int*>(deal + lane * 4), count = C_all, first = lane * C_all;
+    len = len < 0 ? 0 : (len > L ? L : len);
+    if (cand_off) {   // as cand_range()
+      first = at < 0 ? 0 : (at > P ? P : at);
+      count = *reinterpret_cast<const int*>(deal + 512 + lane * 4) - at;
+      count = count < 0 ? 0 : (count > P - first ? P - first : count);
+      count = count > C_all ? C_all : count;
     }
+    const int nv = (len + w - 1) / w, rows = lane < U ? count * (S - nv) : 0, upto = wave_prefix_sum(rows);
+    const long long total = __builtin_amdgcn_readlane(upto, 63);
+    const int me = bid * NW + wave, waves = (int)gridDim.x * NW;
+    int lo = (int)(total * me / waves);
+    const int hi = (int)(total * (me + 1) / waves);
+    while (lo < hi) {   // one user after the other, its rows candidate by candidate
+      const int of = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto > lo));
+      const int end = __builtin_amdgcn_readlane(upto, of), valid = __builtin_amdgcn_readlane(nv, of), each = S - valid;
+      const int start = end - __builtin_amdgcn_readlane(rows, of), stop = end < hi ? end : hi;
+      const unsigned i0 = (unsigned)(lo - start) + lane / LPR;
+      unsigned c = i0 / (unsigned)each, seg = i0 - c * each;
+      unsigned short* out = seg_out + (size_t)__builtin_amdgcn_readlane(first, of) * S * D + (lane % LPR) * 8;
+      for (int i = lo + lane / LPR; i < stop; i += RPI) {
+        *reinterpret_cast<u32x4*>(out + ((size_t)c * S + valid + seg) * D) = u32x4{0u, 0u, 0u, 0u};
+        for (seg += RPI; seg >= (unsigned)each; seg -= each) ++c;
+      }
+      lo = stop;
+    }
+  } else if (zero_lo < zero_hi) {
+    const int ncand = (C - ct * (CW * NW)) < CW * NW ? (C - ct * (CW * NW)) : CW * NW;
     const int per_row = D / 8, each = zero_hi - zero_lo;
     for (int e = tid; e < ncand * each * per_row; e += NT) {
       const int row = e / per_row, ch = e - row * per_row;

@@ -62,3 +62,32 @@ def test_every_row_is_written(U, C, L, w, lens, own):
     assert torch.isfinite(out).all()
     top = ref.abs().amax(-1)
     assert ((out - ref).abs().amax(-1) <= TOL["bf16"] * top).all()      # rows of empty segments are zeros exactly
+
+
+@pytest.mark.parametrize("U,C,L,w,valid", [(6, 277, 6781, 83, [1, 1, 12, 1, 0, 3]), (13, 452, 7755, 67, [1, 116] + [2] * 11),
+                                           (16, 106, 9845, 68, [145, 145] + [3] * 14)])
+def test_short_histories_take_no_longer_than_full_ones(U, C, L, w, valid):
+    """The rows of empty segments are everybody's work: left to the few workgroups of a short history they took up to 2.3 times the
+    time of the whole launch."""
+    import torch
+    d, S = 128, -(-L // w)
+    k, v, q = (torch.randn(*s, device="cuda").bfloat16() for s in ((U, L, d), (U, L, d), (U * C, d)))
+    off = torch.arange(0, U * C + 1, C, dtype=torch.int32, device="cuda")
+    out, cnt = torch.empty(U * C, S, d, device="cuda", dtype=torch.bfloat16), torch.empty(U, S, device="cuda", dtype=torch.int32)
+
+    def us(lens):
+        best = math.inf
+        for _ in range(20):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                laser.laser_forward_ragged(q, k, v, None, None, None, None, lens, off, C, w, math.sqrt(d), seg_out=out, seg_cnt=cnt,
+                                           stage="sta")
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        return best
+
+    full, short = (us(torch.tensor(x, dtype=torch.int32, device="cuda").clamp(max=S) * w) for x in ([S] * U, valid))
+    print(f"U {U} C {C} L {L} w {w}: {full:.1f} us with full histories, {short:.1f} with short ones", flush=True)
+    assert short <= 1.15 * full
