@@ -715,9 +715,13 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   // Dealt out: histories differ in length, and with S segments to every user the longest one's workgroup sets the time while
   // others have nothing. Every wave takes the lengths of all users and the smallest number of segments per workgroup, s, with
   // which the runs of s valid segments of all users are no more than the launch has workgroups; run number `bid` is its own. The
-  // early requests are made again (into the same places: loads retire in order). Empty segments are shared by all workgroups,
-  // at the end. 29 users x up to 201 candidates, 31 segments, lengths uniform in [L / 5, L]: the launch 27.8 -> 21 us
-  int n, zero_lo = 0, zero_hi = 0;   // the user's valid items; the segments this workgroup writes as zeros (not dealt out)
+  // early requests are made again (into the same places: loads retire in order), unless the launch's own division is as good.
+  // Empty segments are shared by all workgroups, at the end. 29 users x up to 201 candidates, 31 segments, lengths uniform in
+  // [L / 5, L]: the launch 26.2 -> 19.7 us; 800 calls of 2 to 64 users (lengths full to log-uniform in [L / 64, L], counts equal,
+  // nearly equal or uniform) take 0.76 of the time without it on average, four of them more than 5 % more (8 % at most: the
+  // division itself is up to a microsecond)
+  int n;                 // the user's valid items
+  bool again = false;    // divided anew
   if (dealt) {
     wait_vm((early ? CW / 4 : 0) + (spec ? OPT : 0));   // the copies have landed (they are older than the rest)
     asm volatile("" ::: "memory");
@@ -738,23 +742,33 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
       }
       int tiles = (count + CW * NW - 1) / (CW * NW);
       tiles = lane < U ? (tiles > 1 ? tiles : 1) : 0;
-      // half the waves idle, a step takes 0.95 us instead of 1.7: runs of such users are longer by as much
+      // half the waves idle, a step takes 0.95 us instead of 1.4: runs of such users are longer by as much (by 7 / 4, with the 1.7 us
+      // that a step takes where stores are on their way too, their workgroups came last: 48 users x up to 228, 15 segments of 260
+      // items 43 against 38 us without dealing)
       const bool light = NW == 8 && count <= CW * NW / 2;
       int own, runs, upto, total;
       auto divide = [&](int s) {   // runs of each user's tiles, and their sum up to each user (the quotient is exact below 2^20)
-        own = light ? s * 7 / 4 : s;
+        own = light ? s * 3 / 2 : s;
         runs = nv > 0 && count > 0 ? (int)(((float)(nv + own - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)own)) : 1;
         upto = wave_prefix_sum(runs * tiles);
         total = __builtin_amdgcn_readlane(upto, 63);
       };
-      int s = 1;
-      divide(1);
-      if (total > (int)gridDim.x) {
-        s = total * 4 / (7 * (int)gridDim.x);
-        do divide(++s);
-        while (total > (int)gridDim.x);
+      // no s is smaller than all runs' lengths together over the workgroups (3 segments of a light user count as 2)
+      const int per = 3 * (int)gridDim.x;
+      int s = (__builtin_amdgcn_readlane(wave_prefix_sum((count > 0 ? nv : 0) * tiles * (light ? 2 : 3)), 63) + per - 1) / per;
+      const int most = spw - (w > 3 * DT_TI ? 1 : 2);   // (the requests made again cost as much as three steps)
+      for (s = s > 1 ? s : 1; s <= most; ++s) {
+        divide(s);
+        if (total <= (int)gridDim.x) break;
       }
-      if (bid >= total) {   // no run left: a share of the zeros is all this workgroup does
+      again = s <= most;
+      if (!again) {   // no shorter runs than the launch's own, or hardly: its division and requests stand
+        if (!early) {
+          if (u < U && ct == 0 && srun == 0) write_seg_cnt(seg_cnt, u, __builtin_amdgcn_readlane(len, u), L, w, S, tid, NT);
+          return;
+        }
+        n = __builtin_amdgcn_readlane(len, u);
+      } else if (bid >= total) {   // no run left: a share of the zeros is all this workgroup does
         crange = {0, 0};
         srun = 1;
         n = 0;
@@ -792,10 +806,6 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   const int seg_hi = (seg_lo + span) < S ? (seg_lo + span) : S;
   int seg_ne = seg_lo;
   while (seg_ne < seg_hi && seg_ne * w < n) ++seg_ne;
-  if (!dealt) {
-    zero_lo = seg_ne;
-    zero_hi = seg_hi;
-  }
   const int item_end = n < L ? n : L;   // one past the user's last valid item
   auto seg_end = [&](int i) {
     const int e = i * w + w;
@@ -1146,9 +1156,10 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
   if (out_seg >= 0) flush_units(FU - out_units);
   }
 
-  // Empty segments: exact zeros. Dealt out, every wave of the launch takes an equal share of all users' (a user with few valid
-  // segments has few runs: left to those, 6 users x 277 candidates, 82 segments, two of them nearly empty, took 51 us)
-  if constexpr (dealt) {
+  // Empty segments: exact zeros. Divided anew, every wave of the launch takes an equal share of all users' (a user with few valid
+  // segments has few runs: left to those, 6 users x 277 candidates, 82 segments of 83 items, lengths log-uniform in [L / 64, L],
+  // took 34 to 51 us, now 18)
+  if (again) {
     asm volatile("" ::: "memory");
     const int at = cand_off ? *reinterpret_cast<const int*>(deal + 256 + lane * 4) : 0;
     int len = *reinterpret_cast<const int*>(deal + lane * 4), count = C_all, first = lane * C_all;
@@ -1177,12 +1188,12 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
       }
       lo = stop;
     }
-  } else if (zero_lo < zero_hi) {
+  } else if (seg_ne < seg_hi) {
     const int ncand = (C - ct * (CW * NW)) < CW * NW ? (C - ct * (CW * NW)) : CW * NW;
-    const int per_row = D / 8, each = zero_hi - zero_lo;
+    const int per_row = D / 8, each = seg_hi - seg_ne;
     for (int e = tid; e < ncand * each * per_row; e += NT) {
       const int row = e / per_row, ch = e - row * per_row;
-      const int cc = row / each, ii = zero_lo + row % each;
+      const int cc = row / each, ii = seg_ne + row % each;
       *reinterpret_cast<u32x4*>(seg_out + ((pb + ct * (CW * NW) + cc) * S + ii) * D + ch * 8) =
           u32x4{0u, 0u, 0u, 0u};
     }
@@ -1244,10 +1255,11 @@ static int pick_spw(const StaArgs& a, int nw, int ctiles) {
 // Segments per workgroup with which one round of 256 workgroups of the direct-to-LDS form covers full histories and counts, where
 // its workgroups are dealt out by the lengths and counts, or 0: up to 64 users, one per lane, and 16 segments. Where nothing is
 // full the queries and the first tile come two trips to memory later (4 us with the requests made in vain), so it has to
-// save a good part of a round: own counts (29 users x up to 201 candidates, 31 segments of 100 items: 27.8 -> 21 us), or more
-// segments than one round of eight holds (40 x 300, 25 segments of 200 items: 130 -> 60 us; 16 x 200 of them, one round, 20.3
-// against 26 if dealt out), and steps enough; segments of one or two tiles leave the zeros of the empty ones, written at the
-// end, too large a part (64 x 200, 63 segments of 32: 40 against 45 us).
+// save a good part of a round: own counts (29 users x up to 201 candidates, 31 segments of 100 items: 26.2 -> 19.7 us), or more
+// segments than one round of eight holds (40 x 300, 25 segments of 200 items: 130 -> 64 us), and steps enough. Short of these
+// lines the two are about even with lengths uniform in [L / 5, L] (dense, own division / dealt out: 16 x 200, 25 segments of 200
+// 21.2 / 21.8 us, of 128 15.5 / 13.1; 64 x 200, 63 segments of 32 41.4 / 40.8); the lines were drawn when the zeros of the empty
+// segments were left to their user's workgroups (20.3 / 26 and 40 / 45), and could be wider since.
 static int deal_spw(const StaArgs& a, int ctiles) {
   if (a.lens == nullptr || a.U > 64) return 0;
   int spw = 1;
