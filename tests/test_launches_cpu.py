@@ -6,6 +6,8 @@ import math
 import pytest
 
 from paper_2602_11562_amd import binding
+from test_sta_backward_mfma_gpu import SETS
+from test_sta_dealt_gpu import CASES as DEALT
 
 
 class Launch(ctypes.Structure):
@@ -53,6 +55,33 @@ def test_forced_segments_per_workgroup_launch_the_whole_division(recorder, monke
     print(own.kernel, own.grid, forced.kernel, forced.grid)
     assert forced.block == own.block == 64 * waves
     assert forced.grid == U * tiles * -(-S // spw)
+
+
+@pytest.mark.parametrize("whole", [False, True], ids=["sta", "whole_path"])
+@pytest.mark.parametrize("U,C,L,w,lens,own,dealt", DEALT)
+def test_calls_with_workgroups_dealt_out(recorder, U, C, L, w, lens, own, dealt, whole):
+    head, sizes, P = (A, A, A), (L, 128, 128, w, math.sqrt(128)), U * C // 2
+    if own and whole:
+        call = lambda lib: lib.laser_forward_ragged(*head, A, A, A, A, A, A, U, C, P, *sizes, 1, BF16, A, A, A, None)
+    elif own:
+        call = lambda lib: lib.laser_sta_forward_ragged(*head, A, A, U, C, P, *sizes, BF16, A, A, None)
+    elif whole:
+        call = lambda lib: lib.laser_forward(*head, A, A, A, A, A, U, C, *sizes, 1, BF16, A, A, A, None)
+    else:
+        call = sta(U, C, L, w)
+    first = launches(recorder, call)[0]
+    waves = 4 if C <= 128 else 8
+    assert f"19sta_mfma_dma_kernelILi{waves}ELb{int(not whole)}ELb{int(dealt)}EE" in first.kernel.decode()
+    assert not dealt or first.grid == 256
+
+
+@pytest.mark.parametrize("name", list(SETS))
+def test_backward_calls_with_two_sets_of_tiles(recorder, name):
+    U, C, L, dq, d, w, grid, lds = SETS[name]
+    first = launches(recorder, lambda lib: lib.laser_sta_backward(A, A, A, A, A, U, C, L, dq, d, w, 1.0, BF16, A, A, A, A, 1 << 40, None))[0]
+    print(first.kernel, first.grid, first.lds)
+    assert f"19sta_bwd_mfma_kernelILi{dq}ELi{d}ELb1EE" in first.kernel.decode()
+    assert (first.grid, first.lds) == (grid, lds)
 
 
 def gsta_backward(U, d, S, M, dt):

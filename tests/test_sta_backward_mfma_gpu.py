@@ -80,6 +80,56 @@ def test_many_short_segments(C, w):
         assert vec_rel_err(a, b) <= BWD_TOL, nm
 
 
+# The form with two sets of tiles on both sides. Users, C, L, d_q, d, w, workgroups and LDS of the launch (shown by
+# test_launches_cpu.py): workgroups = users x (runs of segments x blocks of four candidate tiles + blocks of segments x blocks of item
+# tiles). With 130 users a run is four of 13 segments: two steps of two segments with 33 to 64 candidates, four of one past them; 80 KB
+# is the most that a call asks for
+SETS = {
+    "two_segments_in_work_64_64": (130, 40, 128, 64, 64, 10, 130 * 4 + 130 * 4, 40960),
+    "two_segments_in_work_64_128": (130, 64, 121, 64, 128, 10, 130 * 4 + 130 * 4, 73728),
+    "two_segments_in_work_128_128": (130, 33, 130, 128, 128, 10, 130 * 4 + 130 * 4, 81920),
+    "two_tiles_a_segment_32_64": (130, 50, 500, 32, 64, 40, 130 * 4 + 130 * 7, 24576),
+    "three_candidate_blocks_128_128": (130, 75, 400, 128, 128, 31, 130 * 4 + 130 * 4, 81920),
+    "four_candidate_blocks_64_64": (17, 128, 200, 64, 64, 20, 17 * 10 + 17 * 3, 40960),
+}
+
+
+@pytest.mark.parametrize("name", list(SETS))
+def test_two_sets_of_tiles(name):
+    """Several steps of a workgroup on either side: every second block comes from the other set, and a step to the next segments
+    takes their dH'. Lengths end inside tiles, runs and segments; what lies past them may hold anything."""
+    import torch
+    U, C, L, dq, d, w = SETS[name][:6]
+    S = -(-L // w)
+    rng = np.random.default_rng(4400 + sum(map(ord, name)))
+    (qs, qv), (ks, kv), (vs, vv), (gs, gv) = (_store(rng.normal(size=s), "bf16")
+                                              for s in ((U, C, dq), (U, L, dq), (U, L, d), (U, C, S, d)))
+    lens = rng.integers(0, L + 1, U).astype(np.int32)
+    lens[:4] = L, 4 * w + 1, 0, L - 1
+    for u, n in enumerate(lens):
+        ks[u, n:] = 0x7fc0
+        vs[u, n:] = 0x7fc0
+    gamma = math.sqrt(dq)
+    print(f"case {name}", flush=True)
+    args = (to_device(qs), to_device(ks), to_device(vs), to_device(lens), to_device(gs), w, gamma)
+    got = laser.laser_sta_backward(*args)
+    again = laser.laser_sta_backward(*args)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(got, again))
+    pick = [0, 1, 2, 3, U // 2, U - 2, U - 1]
+    ref = oracle.sta_backward(qv[pick], kv[pick], vv[pick], lens[pick], w, gamma, gv[pick])
+    for nm, a, b in zip(("dq", "dk", "dv"), got, ref):
+        a = to_host_f64(a)
+        assert np.isfinite(a).all(), nm
+        a = a[pick]
+        assert not a[b == 0].any(), nm
+        if nm == "dk":
+            a, b = a.reshape(len(pick), -1), b.reshape(len(pick), -1)
+        err = vec_rel_err(a, b)
+        print(f"  {nm}: max relative error {err:.3e}", flush=True)
+        assert err <= BWD_TOL, nm
+
+
 def _classes(x):
     return np.where(np.isnan(x), 2, np.where(np.isposinf(x), 1, np.where(np.isneginf(x), -1, 0)))
 

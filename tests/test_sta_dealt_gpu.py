@@ -1,6 +1,7 @@
 """The direct-to-LDS STA kernel (d_q = d = 128) with its workgroups dealt out by the users' lengths: every row of H' and every
-count is written, once, whatever the lengths and the candidates' counts, against the generic kernel (bf16 results: the two differ
-by the gates' rounding, 2e-2 as everywhere)."""
+count is written, whatever the lengths and the candidates' counts, and nothing beside them, alone and in the whole path, against
+the generic kernel (bf16 results: the two differ by the gates' rounding, 2e-2 as everywhere). test_launches_cpu.py shows that
+these calls launch the dealt form, or do not, as listed."""
 import math
 
 import pytest
@@ -11,17 +12,22 @@ pytestmark = pytest.mark.gpu
 
 laser = pytest.importorskip("paper_2602_11562_amd")
 
-# users, candidates, items, w, lengths, own counts per user. Dealt out: own counts from three segments of a workgroup on, dense
-# calls past eight, up to 64 users, both workgroup sizes, the last tile of a segment of one item, users without candidates or
-# items, full and empty histories. Not: one round of the launch's own division, 65 users, segments of a tile or less
-CASES = [(29, 201, 3001, 100, "mixed", True), (40, 300, 2500, 100, "mixed", False), (40, 300, 2500, 100, "full", False),
-         (64, 70, 2910, 97, "mixed", True), (64, 128, 2800, 70, "mixed", False), (13, 500, 3500, 65, "mixed", True),
-         (64, 300, 640, 80, "empty", True), (33, 257, 1500, 129, "full", True),
-         (7, 129, 3001, 100, "mixed", False), (65, 70, 900, 40, "mixed", True), (5, 257, 1000, 64, "mixed", True)]
+# users, candidates, items, w, lengths, own counts per user, whether workgroups are dealt out: with own counts from three
+# segments of a workgroup on, dense calls past eight, up to 64 users, both workgroup sizes. Among them the last tile of a segment of
+# one item, users without candidates or items, full and empty histories, and histories that divided anew have runs no shorter.
+# Not dealt out: one round of the launch's own division, 65 users, segments of a tile or less
+CASES = [(29, 201, 3001, 100, "mixed", True, True), (40, 300, 2500, 100, "mixed", False, True),
+         (40, 300, 2500, 100, "full", False, True), (64, 70, 2910, 97, "mixed", True, True),
+         (64, 128, 2800, 70, "mixed", False, True), (13, 500, 3500, 65, "mixed", True, True),
+         (64, 300, 640, 80, "empty", True, True), (33, 257, 1500, 129, "full", True, True),
+         (9, 480, 6000, 80, "one_short", True, True), (64, 128, 2800, 70, "one_short", False, True),
+         (12, 128, 6400, 100, "last_only", True, True),
+         (7, 129, 3001, 100, "mixed", False, False), (65, 70, 900, 40, "mixed", True, False), (5, 257, 1000, 64, "mixed", True, False)]
 
 
-@pytest.mark.parametrize("U,C,L,w,lens,own", CASES)
-def test_every_row_is_written(U, C, L, w, lens, own):
+@pytest.mark.parametrize("whole", [False, True], ids=["sta", "whole_path"])
+@pytest.mark.parametrize("U,C,L,w,lens,own,dealt", CASES)
+def test_every_row_is_written(U, C, L, w, lens, own, dealt, whole):
     import torch
     d = 128
     S = -(-L // w)
@@ -33,35 +39,57 @@ def test_every_row_is_written(U, C, L, w, lens, own):
         n[:] = L
     elif lens == "empty":
         n[:] = 0
+    elif lens == "one_short":
+        n[:] = L
+        n[U // 2] = L - 1
+    elif lens == "last_only":
+        n[:] = 0
+        n[-2] = L
     else:
         n[0] = L
         n[U // 2:U // 2 + 1] = 0 if U > 1 else L
-    print(f"U {U} C {C} L {L} w {w} {lens} {own}", flush=True)
+    print(f"U {U} C {C} L {L} w {w} {lens} {own} {whole}", flush=True)
+    counts = torch.full((U,), C)
     if own:
         counts = torch.randint(0, C + 1, (U,), generator=torch.Generator().manual_seed(U))
         counts[0], counts[-1] = C, 0
-        off = torch.cat([torch.zeros(1, dtype=torch.int64), counts.cumsum(0)]).to(torch.int32).cuda()
-        user = torch.repeat_interleave(torch.arange(U), counts)
-        P = int(counts.sum())
-        q = rnd(P, d)
-        out, cnt = torch.full((P, S, d), math.nan, device="cuda").bfloat16(), torch.full((U, S), -7, device="cuda", dtype=torch.int32)
-        laser.laser_forward_ragged(q, k, v, None, None, None, None, n, off, C, w, math.sqrt(d), seg_out=out, seg_cnt=cnt, stage="sta")
-        qd = torch.zeros(U, C, d, device="cuda").bfloat16()
-        place = torch.cat([torch.arange(int(c)) for c in counts])
-        qd[user, place] = q
-        ref, ref_cnt = laser.laser_sta_forward(qd, k, v, n, w, math.sqrt(d), variant=laser.STA_GENERIC)
-        ref = ref[user, place]
+        if lens == "last_only":
+            counts[-2] = C
+    off = torch.cat([torch.zeros(1, dtype=torch.int64), counts.cumsum(0)]).to(torch.int32).cuda()
+    P = int(counts.sum())
+    q, t0, weights = rnd(P, d), rnd(P, d), [rnd(1, d, d) for _ in range(3)]
+    # a row more before and after each output
+    outs = [torch.full((P + 2, S, d), math.nan, device="cuda").bfloat16(), torch.full((U + 2, S), -7, device="cuda", dtype=torch.int32),
+            torch.full((P + 2, d), math.nan, device="cuda")]
+    out, cnt, z = (x[1:-1] for x in outs)
+    g = math.sqrt(d)
+    if own:
+        laser.laser_forward_ragged(q, k, v, t0, *weights, n, off, C, w, g, seg_out=out, seg_cnt=cnt, z_out=z,
+                                   stage="both" if whole else "sta")
+        _, _, z_ref = laser.laser_forward_ragged(None, k, v, t0, *weights, n, off, C, w, g, seg_out=out, stage="gsta")
     else:
-        q = rnd(U, C, d)
-        out, cnt = torch.full((U, C, S, d), math.nan, device="cuda").bfloat16(), torch.full((U, S), -7, device="cuda", dtype=torch.int32)
-        laser.laser_sta_forward(q, k, v, n, w, math.sqrt(d), seg_out=out, seg_cnt=cnt, variant=laser.STA_MFMA)
-        ref, ref_cnt = laser.laser_sta_forward(q, k, v, n, w, math.sqrt(d), variant=laser.STA_GENERIC)
+        q4, t4, o4, z4 = q.view(U, C, d), t0.view(U, C, d), out.view(U, C, S, d), z.view(U, C, d)
+        if whole:
+            laser.laser_forward(q4, k, v, t4, *weights, n, w, g, seg_out=o4, seg_cnt=cnt, z_out=z4)
+        else:
+            laser.laser_sta_forward(q4, k, v, n, w, g, seg_out=o4, seg_cnt=cnt, variant=laser.STA_MFMA)
+        z_ref = laser.laser_gsta_forward(o4, t4, *weights, n, L, w).view(P, d)
+    user = torch.repeat_interleave(torch.arange(U), counts)
+    place = torch.cat([torch.arange(int(c)) for c in counts])
+    qd = torch.zeros(U, C, d, device="cuda").bfloat16()
+    qd[user, place] = q
+    ref, ref_cnt = laser.laser_sta_forward(qd, k, v, n, w, g, variant=laser.STA_GENERIC)
+    ref = ref[user, place].float()
     torch.cuda.synchronize()
     assert torch.equal(cnt, ref_cnt)
-    out, ref = out.float(), ref.float()
     assert torch.isfinite(out).all()
     top = ref.abs().amax(-1)
-    assert ((out - ref).abs().amax(-1) <= TOL["bf16"] * top).all()      # rows of empty segments are zeros exactly
+    assert ((out.float() - ref).abs().amax(-1) <= TOL["bf16"] * top).all()      # rows of empty segments are zeros exactly
+    if whole:
+        assert torch.equal(z, z_ref)
+    for x in outs:
+        edge = x[[0, -1]]
+        assert (edge == -7).all() if x.dtype == torch.int32 else edge.isnan().all()
 
 
 @pytest.mark.parametrize("U,C,L,w,valid", [(6, 277, 6781, 83, [1, 1, 12, 1, 0, 3]), (13, 452, 7755, 67, [1, 116] + [2] * 11),
