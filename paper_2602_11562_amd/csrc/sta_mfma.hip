@@ -566,31 +566,6 @@ __device__ __forceinline__ bf16x8 lds_read_tr(lds_bytes p) {
   return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// Instruction J (0..71) of the 16 gates of a lane, in dependency order per half of 8: scale (8), exp2 (8), 1 + (8),
-// reciprocal (8), round pairs to bf16 (4). The scores are transformed in place.
-template <int J>
-__device__ __forceinline__ void gate_step(f32x16& sc, bf16x8& p0, bf16x8& p1, float nsl) {
-  constexpr int half = J / 36, r = J % 36, stage = r / 8, e = r % 8, i = half * 8 + e;
-  if constexpr (stage == 0) sc[i] *= nsl;
-  else if constexpr (stage == 1) sc[i] = __builtin_amdgcn_exp2f(sc[i]);
-  else if constexpr (stage == 2) sc[i] += 1.0f;
-  else if constexpr (stage == 3) sc[i] = __builtin_amdgcn_rcpf(sc[i]);
-  else {
-    constexpr int a0 = half * 8 + 2 * e;
-    if constexpr (half == 0) { p0[2 * e] = (__bf16)sc[a0]; p0[2 * e + 1] = (__bf16)sc[a0 + 1]; }
-    else { p1[2 * e] = (__bf16)sc[a0]; p1[2 * e + 1] = (__bf16)sc[a0 + 1]; }
-  }
-}
-template <int J0>
-__device__ __forceinline__ void gate_steps6(f32x16& sc, bf16x8& p0, bf16x8& p1, float nsl) {
-  gate_step<J0>(sc, p0, p1, nsl);
-  gate_step<J0 + 1>(sc, p0, p1, nsl);
-  gate_step<J0 + 2>(sc, p0, p1, nsl);
-  gate_step<J0 + 3>(sc, p0, p1, nsl);
-  gate_step<J0 + 4>(sc, p0, p1, nsl);
-  gate_step<J0 + 5>(sc, p0, p1, nsl);
-}
-
 // Barrier without the fence of __syncthreads(): the compiler neither waits for the wave's outstanding LDS reads
 // (they are awaited where their registers are used) nor moves memory operations across it.
 __device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
