@@ -77,9 +77,9 @@ __device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 
 
 // Per storage type: the tile's vectors in LDS (16 pairs x D values of fp32 meaning), a wave's share of a matrix (16 columns),
 // and the product of the two, with the matrix as the left operand: lane (l16, g) gets columns n0 + 4 g .. + 3 of pair l16,
-// which go to LDS, and to and from memory, as one piece (matrices and rows are addressed by a uniform base and an unsigned
-// 32-bit lane offset: 64-bit lane addresses, kept over the layers, spilled at d = 128 in fp32) (the other way round, four pairs of one column, every vector took
-// twelve two-byte writes where three of eight bytes do).
+// which go to LDS, and to and from memory, as one piece (the other way round, four pairs of one column, every vector took twelve
+// two-byte writes where three of eight bytes do). Matrices and rows are addressed by a uniform base and an unsigned 32-bit lane
+// offset: 64-bit lane addresses, kept over the layers, spilled at d = 128 in fp32.
 template <typename T, int D> struct Prod;
 
 template <int D> struct Prod<float, D> {

@@ -16,9 +16,9 @@
 //
 // Bound by the chain of a layer (three products, the pass over H', four or five barriers: 3 us for d = 128, 1.7 us for
 // d = 64) until the machine is full, by the stream of H' and of the matrices (96 KB a workgroup at d = 128) beyond. bf16, two
-// layers, d = 128: 100 pairs, S = 100 9.9 us (77 us on one workgroup per pair that walked the matrices row by row); 2048
-// pairs, S = 40 14.3 us, 4096 pairs, S = 32 16.7 us (16.3 and 31.2 us in the form with 32-pair tiles this one replaced);
-// fp32, 1200 pairs, S = 15, d = 64, two layers 9 us (34 us).
+// layers, d = 128: 100 pairs, S = 100 10.1 us (77 us on one workgroup per pair that walked the matrices row by row); 2048
+// pairs, S = 40 13.5 us, 4096 pairs, S = 32 17.8 us (16.3 and 31.2 us in the form with 32-pair tiles this one replaced);
+// fp32, 1200 pairs, S = 15, d = 64, two layers 8.2 us (34 us).
 #include "gsta_tile.h"
 #include "laser_internal.h"
 
@@ -265,13 +265,12 @@ static void launch_pairs(const GstaArgs& a, int P) {
   // eight rows a lane fit the registers beside the matrices up to eight pairs (sixteen where a wave has two of them and
   // rows are bf16; otherwise they spill or leave one wave per SIMD), twelve for eight pairs of bf16 rows
   constexpr bool EIGHT = PW == 4 || PW == 8 || (sizeof(T) == 2 && (PW <= 2 || (PW == 16 && D == 128)));
-  // Sixteen pairs of few rows, d = 128: with two or three rows a lane the registers suffice for two workgroups on a compute
-  // unit, which hide each other's chains (two layers, S = 4: 8192 pairs 25.3 -> 20.5 us, 65536 pairs 187 -> 125; S = 12: 25.2 ->
-  // 23.7 and 188 -> 149, but 13.4 -> 15.1 for 4096 pairs, one workgroup a compute unit; the form with 32-pair tiles that this
-  // kernel replaced took 20.4, 165, 23.1 and 191)
+  // Sixteen pairs of few rows, d = 128: with up to three rows a lane the registers suffice for two workgroups on a compute
+  // unit, which hide each other's chains (two layers, four rows a lane -> the fewest: S = 4 8192 pairs 23.2 -> 17.1 us, 65536 pairs
+  // 165 -> 102; S = 12 23.4 -> 19.8 and 169 -> 119; three rows for 4096 pairs, one workgroup a compute unit, were slower: 13.4 -> 15.1)
   constexpr bool FEW = PW == 16 && D == 128 && sizeof(T) == 2;
   // One or two rows a lane where that is all there is: with four, the rows past the last one are worked on too (4096 pairs,
-  // S = 16, d = 64, bf16: the pass 3700 -> 1900 cycles of a workgroup's 14000)
+  // S = 16, d = 64, bf16: 6.5 -> 5.8 us, the pass 3700 -> 1900 cycles of a workgroup's 14000)
   if (a.S <= HELD) LASER_TILED(1, true);
   else if (a.S <= 2 * HELD) LASER_TILED(2, true);
   else if (FEW && a.S <= 3 * HELD && P > 256 * PW) LASER_TILED((FEW ? 3 : 4), true);
@@ -289,15 +288,16 @@ static void launch_pairs(const GstaArgs& a, int P) {
 // Pairs per workgroup: the fewest that leave the launch one round of workgroups (256 of eight waves for d = 128 and for
 // fp32, whose products fill the matrix pipe; twice as many of four waves for d = 64 in bf16), since a layer's chain costs
 // about the same for 1 and for 16 pairs. Two layers, bf16,
-// d = 128, S = 32, PW = 1 / 2 / 4 / 8 / 16: 100 pairs 9.9 / 9.7 / 11 / 12 / 14 us, 512 pairs 16 / 10.4 / 11.0 / 12.1, 2048
-// pairs 53 / 30 / 21 / 13.4 / 15.7, 8192 pairs - / - / 83 / 50 / 35.
+// d = 128, S = 32, PW = 1 / 2 / 4 / 8 / 16: 100 pairs 9.2 / 9.1 / 9.8 / 11.0 / 14.8 us, 512 pairs 14.8 / 9.6 / 10.0 / 11.0 / 15.0,
+// 2048 pairs 45 / 26 / 16 / 11.8 / 15.5, 8192 pairs 157 / 82 / 48 / 41 / 34.
 template <typename T, int D>
 static void launch_t(const GstaArgs& a) {
   const int P = gsta_pairs(a), per = D == 128 || sizeof(T) == 4 ? P : (P + 1) / 2;
   if (per <= 256) launch_pairs<T, D, 1>(a, P);
   else if (per <= 512) launch_pairs<T, D, 2>(a, P);
   else if (per <= 1024) launch_pairs<T, D, 4>(a, P);
-  // (d = 64 with 33 to 64 rows: eight rows a lane, for which sixteen pairs have no room: 8192 pairs 21 against 24 us)
+  // (d = 64 with 33 to 64 rows: eight rows a lane, for which sixteen pairs have no room: 8192 pairs, S = 50, two layers 21.9
+  // against 23.7 us; one layer either way 17.5)
   else if (per <= 2048 || (D == 64 && a.S > 32 && a.S <= 64)) launch_pairs<T, D, 8>(a, P);
   else launch_pairs<T, D, 16>(a, P);
 }
@@ -318,11 +318,11 @@ laser_status gsta_tile_launch(const GstaArgs& a) {
 bool gsta_tile_supports(const GstaArgs& a) { return a.d == 64 || a.d == 128; }
 
 // Whether a one-layer bf16 batch is small enough for this kernel to beat the forms written for full machines (us, this
-// kernel / the other). Against the one-kernel form, d = 128: one round of sixteen pairs, 4096 pairs, S = 32 11.4 / 15.5,
-// S = 8 9.0 / 11.5; 6000 pairs 21.2 / 20.1 and 16.3 / 11.7. d = 64: 8192 pairs, S = 16 10.3 / 10.8, S = 32 10.8 / 12.3; 16384
-// pairs, S = 16 19.2 / 15.5; S = 64 4096 pairs 9.9 / 13.2, 8192 pairs 21 / 17.5. Against the split form (longer
-// blocks): d = 128, S = 100 2048 pairs 16 / 26, 8192 pairs 44 / 50, 16384 pairs 103 / 99; d = 64, S = 100 16384 pairs
-// 43 / 47, 24576 pairs 75 / 70.
+// kernel / the other). Against the one-kernel form, d = 128, S = 32: one round of sixteen pairs, 4096 pairs 13.2 / 16.3, 6000 pairs
+// 19.9 / 16.9, 8192 23.4 / 19.1. Against the split form (longer blocks): d = 128, S = 100 2048 pairs 14.3 / 26.7, 8192 41.4 / 49.6,
+// 16384 97 / 101; d = 64, S = 100 16384 pairs 39 / 48, 24576 72 / 71. The lines for short blocks and for d = 64 were drawn before
+// this kernel's steps became shorter, and it is the faster one past them too: d = 128, S = 8 6000 pairs 11.7 / 12.4, 16384 20.3 / 24.6;
+// d = 64, S = 16 8192 pairs 7.6 / 11.6, 32768 18.5 / 27.7, S = 32 16384 pairs 16.8 / 23.5, S = 64 8192 pairs 15.5 / 18.7.
 bool gsta_tile_preferred(const GstaArgs& a) {
   const int P = gsta_pairs(a);
   if (gsta_one_supports(a)) return a.d == 128 ? P <= 4096 : P <= (a.S <= 32 ? 8192 : 4096);

@@ -21,11 +21,12 @@
 // are zeros in LDS, so they add nothing to any finite sum (padding of the history is never read); a wave whose sums come out
 // not finite forms them again over the valid rows alone.
 //
-// What bounds it: waiting (47 % of the waves' cycles, and the matrix pipe busy 14 %, counted before the rows of the next block were
-// requested while the current one is worked on). The rows go to LDS directly, two sets of them where the workgroups that registers
-// allow on a compute unit still fit: 16 users x 64 candidates, L = 2000, w = 256, 128 / 128 41.6 -> 28 us, 1024 x 16, w = 10, 64 / 128
-// 553 -> 398 us, 64 users x 64 candidates, L = 2048, w = 128, 64 / 64 (lengths 410 .. 2048, 92 MB it cannot do without) 32 -> 31 us:
-// there the items have two blocks of candidates, and their 75 MB of gradients are most of the launch.
+// What bounds it: waiting (36 % of the waves' cycles, 47 % before the rows of the next block were requested while the current one is
+// worked on) and issue (29 %); the matrix pipe is busy 15 %. The rows go to LDS directly, two sets of them where the workgroups that
+// registers allow on a compute unit still fit: 16 users x 64 candidates, L = 2000, w = 256, 128 / 128 41.6 -> 30 us, 1024 x 16, w = 10,
+// 64 / 128 553 -> 398 us, 64 users x 64 candidates, L = 2048, w = 128, 64 / 64 (lengths 410 .. 2048) 32 -> 30 us for 128 MB, 20 us at
+// the card's rate. The second set costs registers: 2 spill at 64 / 64 (none before), 3 at 64 / 128 (none), 43 at 128 / 128 (33), and
+// loads return in order, so a reload in the block loop waits for the rows that were to overlap the products.
 #include "laser_internal.h"
 #include "sta_mfma_tile.h"
 
@@ -434,8 +435,8 @@ static StaBwdMfmaShape sta_bwd_mfma_shape(const StaBwdArgs& a, int max_groups) {
   s.wc = waves_for(ct);
   s.ws_q = 4 / s.wc;
   s.nct = (ct + s.wc - 1) / s.wc;
-  // runs of segments: two workgroups per compute unit (as many as fit at once), each run a multiple of the segments in
-  // work; every further run costs a partial sum of dQ in memory
+  // runs of segments: two workgroups per compute unit (as many as fit at once, three at d_q + d <= 128), each run a multiple of the
+  // segments in work; every further run costs a partial sum of dQ in memory
   const long long users = (long long)a.U * s.nct;
   long long g = (512 + users - 1) / users;
   if (g > max_groups) g = max_groups;
@@ -447,14 +448,15 @@ static StaBwdMfmaShape sta_bwd_mfma_shape(const StaBwdArgs& a, int max_groups) {
   return s;
 }
 
-// From five candidates on. Up to four the several-items-per-wave kernel streams the history once and is the faster one
-// (2048 users x 4, L = 1000, w = 10, 32 / 128: 586 us against 819 us here; 512 x 4, L = 2000, w = 64, 128 / 128: 356 against
-// 470 us) but at 64 / 64 (188 against 126 us), which is left on the one line for all widths; beyond four the alternative is one item per wave,
-// eight candidates a pass: 512 x 5, L = 1000, w = 10, 32 / 128: 260 against 168 us, 512 x 8, w = 64, 128 / 128: 475 against
-// 158 us. Not for segments so short that their tiles of 32 items x 32 candidates are nearly empty, where there are enough of
-// them to fill the machine (us, the other kernel / here; L = 300): 1024 users x 5, w = 1, 128 / 64 377 / 890, 512 x 8, w = 3,
-// 64 / 128 the same way by 1.46, 512 x 5, w = 5, 128 / 128 by 1.59, w = 6 even; the second pass that nine candidates cost there
-// moves the line to 18 products of a segment, and from 13 on this kernel is the better one for any segment.
+// From five candidates on (us, the other kernel / here, full histories). Up to four the several-items-per-wave kernel streams the
+// history once and is the faster one for short segments (2048 users x 4, L = 1000, w = 10: 32 / 128 561 / 860, 64 / 64 399 / 579); for
+// long ones the two are about even (512 x 4, L = 2000, w = 64: 128 / 128 398 / 397, 64 / 64 195 / 178), which is left on the one line.
+// Beyond four the alternative is one item per wave, eight candidates a pass: 512 x 5, L = 1000, w = 10, 32 / 128 318 / 200, 512 x 8,
+// L = 2000, w = 64, 128 / 128 918 / 405. Not for segments so short that their tiles of 32 items x 32 candidates are nearly empty,
+// where there are enough of them to fill the machine (L = 300): 1024 users x 5, w = 1, 128 / 64 453 / 1111, 512 x 8, w = 3, 64 / 128
+// 172 / 197, 512 x 5, w = 5, 128 / 128 142 / 188 (w = 6, on this side of the line: 147 / 166); the second pass that nine candidates
+// cost there moves the line to 18 products of a segment (512 x 9, w = 2, 64 / 128, on this side of 18: 312 / 284), and from 13 on this kernel
+// is the better one for any segment (12, w = 1: 567 / 569).
 bool sta_bwd_mfma_supports(const StaBwdArgs& a) {
   if ((long long)a.U * a.S >= 6144 && (long long)a.C * a.w <= (a.C <= 8 ? 25 : a.C <= 12 ? 18 : 0)) return false;
   return a.dt == LASER_BF16 && !a.grads_bf16 && a.C > 4 && (a.d_q == 32 || a.d_q == 64 || a.d_q == 128) &&
