@@ -264,7 +264,8 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
       const int abits = __float_as_int(a);
       // Eight rows at a time: a group of one pair's rows takes that pair's sums alone, the group in which A ends both. The tile is
       // bound by vector issue, and both pairs' sums and maxima for every row were a quarter of its instructions (the
-      // complete head, 16384 pairs, S = 100, lengths uniform in [200, 1000]: 262.0 -> 259.2 us).
+      // complete head with the views, 16384 pairs, S = 100, lengths uniform in [200, 1000], 25 runs in turn: 293.2 -> 289.2 us, quartiles
+      // 292.5 .. 294.9 and 288.0 .. 290.1; without the views, whose maxima cost most, the same either way).
       unsigned wd[FM_ROWS];
 #pragma unroll
       for (int row = 0; row < FM_ROWS; ++row) wd[row] = *reinterpret_cast<const unsigned*>(pcol + row * OP);
