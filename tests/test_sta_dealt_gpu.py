@@ -92,6 +92,28 @@ def test_every_row_is_written(U, C, L, w, lens, own, dealt, whole):
         assert (edge == -7).all() if x.dtype == torch.int32 else edge.isnan().all()
 
 
+@pytest.mark.parametrize("kind", ["above_the_count", "past_the_pairs", "decreasing", "huge"])
+def test_offsets_that_break_the_rules_stay_inside_the_buffers(kind):
+    """The kernel clamps every user's range for itself, also where it shares the empty rows of all users."""
+    import torch
+    U, C, P, L, w, d = 13, 500, 900, 3500, 65, 128
+    S = -(-L // w)
+    off = {"above_the_count": [0, 600, 620] + [700] * 10 + [P], "past_the_pairs": [P + 50, P + 60] + [3] * 11 + [P],
+           "decreasing": [0, 400, 401, 90, 300, 10, 500, 20, 600, 30, 700, 40, 800, P], "huge": [0] * 12 + [1 << 30, -(1 << 30)]}[kind]
+    rnd = lambda *s: torch.randn(*s, device="cuda").bfloat16()
+    lens = (torch.arange(U, device="cuda", dtype=torch.int32) * 271) % (L + 1)
+    out, cnt = torch.full((P + 2, S, d), 3.0, device="cuda").bfloat16(), torch.full((U + 2, S), -7, device="cuda", dtype=torch.int32)
+    print(kind, flush=True)
+    laser.laser_forward_ragged(rnd(P, d), rnd(U, L, d), rnd(U, L, d), None, None, None, None, lens,
+                               torch.tensor(off, dtype=torch.int32, device="cuda"), C, w, math.sqrt(d), seg_out=out[1:-1],
+                               seg_cnt=cnt[1:-1], stage="sta")
+    torch.cuda.synchronize()
+    assert (out[[0, -1]] == 3.0).all() and (cnt[[0, -1]] == -7).all() and out.isfinite().all()
+    items = (lens[:, None] - torch.arange(S, device="cuda")[None, :] * w).clamp(0, w)
+    items[:, -1] = items[:, -1].clamp(max=L - (S - 1) * w)
+    assert torch.equal(cnt[1:-1], items.to(torch.int32))
+
+
 @pytest.mark.parametrize("U,C,L,w,valid", [(6, 277, 6781, 83, [1, 1, 12, 1, 0, 3]), (13, 452, 7755, 67, [1, 116] + [2] * 11),
                                            (16, 106, 9845, 68, [145, 145] + [3] * 14)])
 def test_short_histories_take_no_longer_than_full_ones(U, C, L, w, valid):
