@@ -195,6 +195,7 @@ bool sta_f32_supports(const StaArgs& a);   // fp32 storage at the usual widths, 
 laser_status sta_f32_launch(const StaArgs& a);
 bool sta_mfma_supports(const StaArgs& a);
 laser_status sta_mfma_launch(const StaArgs& a);
+laser_status sta_ring_launch(const StaArgs& a);   // sigmoid gates, a wave of its own for the fetches (sta_mfma_launch picks)
 bool sta_stream_supports(const StaArgs& a);
 laser_status sta_stream_launch(const StaArgs& a);
 bool sta_few_supports(const StaArgs& a);   // at most eight query rows per user: the stream variant's matrix-core form
@@ -237,6 +238,19 @@ inline int tuning_int(const char* name, int unset) {
 constexpr int DYNAMIC_LDS_MOST = 150 * 1024;
 
 inline laser_status launch_status() { return hipGetLastError() == hipSuccess ? LASER_OK : LASER_ERR_LAUNCH; }
+
+// x / n for x < 2^31 + 2^16 by a multiplication (round-up method: 2^s >= n, 33-bit multiplier m + 2^32)
+struct MulDiv {
+  unsigned m;
+  int s;
+  __device__ __forceinline__ unsigned div(unsigned x) const { return (unsigned)((((unsigned long long)x * m >> 32) + x) >> s); }
+};
+inline MulDiv mul_div(unsigned n) {
+  MulDiv d{0, 0};
+  while ((1ull << d.s) < n) ++d.s;
+  d.m = (unsigned)((((1ull << d.s) - n) << 32) / n + 1);
+  return d;
+}
 
 // ---------------------------------------------------------------- device helpers
 __device__ __forceinline__ float bf16_bits_to_f32(unsigned short b) { return __uint_as_float(((unsigned int)b) << 16); }

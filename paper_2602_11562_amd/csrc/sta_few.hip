@@ -49,12 +49,6 @@ struct FewShape {
   static constexpr int NT = 64 * NW, LDS = WVB + NW * WAVE;
 };
 
-// x / n for x < 2^31 + 2^16 by a multiplication (round-up method: 2^s >= n, 33-bit multiplier m + 2^32)
-struct FewDiv {
-  unsigned m;
-  int s;
-  __device__ __forceinline__ unsigned div(unsigned x) const { return (unsigned)((((unsigned long long)x * m >> 32) + x) >> s); }
-};
 struct FewFold {
   const unsigned short* wv;    // [D, FE]
   unsigned short* y;           // [pairs, S, FE]: H'
@@ -65,7 +59,7 @@ template <int DQ, int D, int FE>
 __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
     const unsigned short* __restrict__ q, const unsigned short* __restrict__ k, const unsigned short* __restrict__ v,
     const int32_t* __restrict__ lens, const int32_t* __restrict__ cand_off, int P, int C_all, int L, int w, int S,
-    int cps, int run_segs, unsigned runs, unsigned units, FewDiv dv, float neg_scale_log2e, unsigned short* __restrict__ seg_out,
+    int cps, int run_segs, unsigned runs, unsigned units, MulDiv dv, float neg_scale_log2e, unsigned short* __restrict__ seg_out,
     int32_t* __restrict__ seg_cnt, FewFold fold) {
   using Sh = FewShape<DQ, D, FE>;
   constexpr bool FOLD = Sh::FOLD;
@@ -411,9 +405,7 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
   const unsigned runs = (unsigned)((a.S + run - 1) / run);
   const unsigned units = (unsigned)a.U * runs;   // <= U S, which fits an int
   const unsigned blocks = units < 256 ? units : 256u;
-  FewDiv dv{0, 0};
-  while ((1ull << dv.s) < runs) ++dv.s;
-  dv.m = (unsigned)((((1ull << dv.s) - runs) << 32) / runs + 1);
+  const MulDiv dv = mul_div(runs);
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(Sh::NT), Sh::LDS, a.stream, (const unsigned short*)a.q,
                      (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens, a.cand_off, a.P, a.C, a.L, w, a.S, cps,
                      (int)run, runs, units, dv, -1.4426950408889634f / a.gamma, (unsigned short*)a.seg_out, a.seg_cnt, fold);

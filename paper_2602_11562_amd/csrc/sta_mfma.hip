@@ -1,4 +1,6 @@
-// STA on the bf16 matrix cores (many candidates per user).
+// STA on the bf16 matrix cores (many candidates per user): the form for d_q = d = 128 whose workgroups fill a compute unit (the
+// direct-to-LDS form, below), and the softmax variant. All other calls with sigmoid gates run in sta_ring.hip, which shares the
+// mapping of the products.
 //
 // Operation (Sec. 3.4.2 STA equation, global-score form of Sec. 3.5.1): for a user, the scores of all
 // candidates against all history items are one [C x d_q].[d_q x L] contraction, the gated aggregation is a
@@ -14,7 +16,7 @@
 //
 // Both products are computed transposed so that nothing has to be shuffled between them:
 //   Sc^T[item, cand] = K_tile . Q^T            v_mfma_f32_32x32x16_bf16, A = K rows from LDS (16 B per lane)
-//   P^T = bf16(sigmoid(Sc^T / gamma))          in the accumulator registers
+//   P^T = bf16(gates)                          in the accumulator registers
 //   acc^T[dcol, cand] += V_tile^T . P^T        A = V^T via the LDS transpose load, B = P^T as it already sits
 // The accumulator layout of the first product (lane = candidate, registers = items 8(r/4)+4(lane/32)+r%4) is,
 // per 16-item step, exactly a B operand whose k-slots are the items {4h..4h+3, 8+4h..8+4h+3}; V^T is fetched
@@ -33,11 +35,11 @@ namespace laser {
 // HEADS > 1 (Sec. 4.1.2): head h owns the h-th run of d_q / HEADS columns of q and k, a whole number of 16-wide
 // k-steps, and of d / HEADS columns of v and H', a whole number of 32-column blocks; one score block and one gate
 // per head, and every column block is aggregated with its own head's gates.
-// SOFTMAX (the ablation of Sec. 4.4.1): the gates of a segment are a softmax over its valid items, per candidate and
+// The softmax variant (the ablation of Sec. 4.4.1): the gates of a segment are a softmax over its valid items, per candidate and
 // head, taken online: a running maximum and denominator per lane (the two lanes of a candidate agree on the maximum
 // after every block and add their denominators at the end of the segment), the sums rescaled when the maximum
 // moves. Zero-filled padding rows would count in the denominator, so their scores are masked in a partial block.
-template <int DQ, int D, int NW, int NBUF, int HEADS = 1, bool SOFTMAX = false>
+template <int DQ, int D, int NW, int NBUF, int HEADS>
 __global__ __launch_bounds__(64 * NW) void sta_mfma_kernel(const unsigned short* __restrict__ q,
                                                            const unsigned short* __restrict__ k,
                                                            const unsigned short* __restrict__ v,
@@ -185,40 +187,33 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_kernel(const unsigned short*
 #pragma unroll
           for (int ks = hd * KH; ks < (hd + 1) * KH; ++ks)
             sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qreg[ks], sc, 0, 0, 0);
-          if constexpr (SOFTMAX) {
-            const float sl = -neg_scale_log2e;            // log2(e) / gamma
-            const int left = chi - ct0 - ib * 32;         // valid items from the start of this block (>= 1)
-            float x[16], bm = SM_NEG;
+          const float sl = -neg_scale_log2e;            // log2(e) / gamma
+          const int left = chi - ct0 - ib * 32;         // valid items from the start of this block (>= 1)
+          float x[16], bm = SM_NEG;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              x[r] = sc[r] * sl;
-              if (left < 32 && 8 * (r >> 2) + 4 * h + (r & 3) >= left) x[r] = SM_NEG;
-              bm = fmaxf(bm, x[r]);
-            }
-            bm = both_halves(bm, true);
-            const float m_new = fmaxf(sm_m[hd], bm);
-            const float corr = __builtin_amdgcn_exp2f(sm_m[hd] - m_new);   // 0 at the first block of a segment
-            float ps = 0.0f;
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const float pe = __builtin_amdgcn_exp2f(x[s * 8 + e] - m_new);
-                ps += pe;
-                p[hd][s][e] = (__bf16)pe;
-              }
-            sm_l[hd] = fmaf(sm_l[hd], corr, ps);
-            sm_m[hd] = m_new;
-#pragma unroll
-            for (int db = hd * DBH; db < (hd + 1) * DBH; ++db)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) acc[db][r] *= corr;
-          } else {
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-              for (int e = 0; e < 8; ++e) p[hd][s][e] = (__bf16)gate(sc[s * 8 + e], neg_scale_log2e);
+          for (int r = 0; r < 16; ++r) {
+            x[r] = sc[r] * sl;
+            if (left < 32 && 8 * (r >> 2) + 4 * h + (r & 3) >= left) x[r] = SM_NEG;
+            bm = fmaxf(bm, x[r]);
           }
+          bm = both_halves(bm, true);
+          const float m_new = fmaxf(sm_m[hd], bm);
+          const float corr = __builtin_amdgcn_exp2f(sm_m[hd] - m_new);   // 0 at the first block of a segment
+          float ps = 0.0f;
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float pe = __builtin_amdgcn_exp2f(x[s * 8 + e] - m_new);
+              ps += pe;
+              p[hd][s][e] = (__bf16)pe;
+            }
+          sm_l[hd] = fmaf(sm_l[hd], corr, ps);
+          sm_m[hd] = m_new;
+#pragma unroll
+          for (int db = hd * DBH; db < (hd + 1) * DBH; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[db][r] *= corr;
         }
         // ---- acc^T += V^T . P^T
 #pragma unroll
@@ -249,17 +244,16 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_kernel(const unsigned short*
       // ---- segment finished: H'[u, c, ci, :] is parked in the wave-private patch as bf16 rows; it is written
       // to global memory at the top of the next step, behind that step's prefetch loads, so that waiting for
       // the prefetch never has to wait for these stores first
-      if constexpr (SOFTMAX) {   // divide by the denominator (the segment holds a valid item: it is positive)
+      // divided by the denominator (the segment holds a valid item: it is positive)
 #pragma unroll
-        for (int hd = 0; hd < HEADS; ++hd) {
-          const float inv = 1.0f / both_halves(sm_l[hd], false);
+      for (int hd = 0; hd < HEADS; ++hd) {
+        const float inv = 1.0f / both_halves(sm_l[hd], false);
 #pragma unroll
-          for (int db = hd * DBH; db < (hd + 1) * DBH; ++db)
+        for (int db = hd * DBH; db < (hd + 1) * DBH; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[db][r] *= inv;
-          sm_m[hd] = SM_NEG;
-          sm_l[hd] = 0.0f;
-        }
+          for (int r = 0; r < 16; ++r) acc[db][r] *= inv;
+        sm_m[hd] = SM_NEG;
+        sm_l[hd] = 0.0f;
       }
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -309,209 +303,9 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_kernel(const unsigned short*
   }
 }
 
-// ------------------------------------------------------------------------------------------ pipelined form
-// Same mapping and arithmetic as above, with the two 32-item blocks of a tile software-pipelined inside each
-// wave so that the sigmoid work (VALU, transcendental unit) of one block runs in the shadow of the MFMAs of
-// another:
-//   phase A   Sc(b1) = K.Q^T            ||  P(b0) = sigmoid(Sc(b0))
-//   phase B   acc += V^T(b0).P(b0)      ||  P(b1) = sigmoid(Sc(b1))
-//   phase C   acc += V^T(b1).P(b1)          then the prefetched tile goes to the other LDS buffer
-//   barrier
-//   phase D   Sc(b0 of the next tile) = K.Q^T
-// Every tile is computed in full (its padding rows are zeros in LDS), so the phases are straight-line code.
-template <int DQ, int D, int NW>
-__global__ __launch_bounds__(64 * NW) void sta_mfma_pipe_kernel(const unsigned short* __restrict__ q,
-                                                                const unsigned short* __restrict__ k,
-                                                                const unsigned short* __restrict__ v,
-                                                                const int32_t* __restrict__ lens,
-                                                                const int32_t* __restrict__ cand_off, int P, int C_all,
-                                                                int L,
-                                                                int w, int S, int spw, int ctiles, int sruns,
-                                                                float neg_scale_log2e,
-                                                                unsigned short* __restrict__ seg_out,
-                                                                int32_t* __restrict__ seg_cnt) {
-  constexpr int KP = KPitch<DQ>::v, VP = VPitch<D>::v;
-  constexpr int NT = 64 * NW;
-  constexpr int KSTEPS = DQ / 16, DB = D / 32;
-  constexpr int OP = OPitch<D>::v;
-  constexpr int KBYTES = TI * KP, VBYTES = TI * VP, OBYTES = CW * OP;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * (KBYTES + VBYTES) + NW * OBYTES];
-
-  int bid = blockIdx.x;
-  const int srun = bid % sruns;
-  bid /= sruns;
-  const int ct = bid % ctiles;
-  const int u = bid / ctiles;
-  const CandRange crange = cand_range(cand_off, u, C_all, P);
-  const int C = crange.count;               // this user's candidates
-  const size_t pb = (size_t)crange.first;   // and the index of their first pair
-  if (ct * (CW * NW) >= C) {   // a candidate tile past this user's count: nothing to do (the first still writes the counts)
-    if (srun == 0 && ct == 0) write_seg_cnt(seg_cnt, u, valid_len(lens, u, L), L, w, S, threadIdx.x, 64 * NW);
-    return;
-  }
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int l32 = lane & 31, h = lane >> 5;
-  const int cbase = ct * (CW * NW) + wave * CW;
-  const int n = valid_len(lens, u, L);
-  if (srun == 0 && ct == 0) write_seg_cnt(seg_cnt, u, n, L, w, S, tid, NT);
-  unsigned char* opatch = smem + 2 * (KBYTES + VBYTES) + wave * OBYTES;
-
-  bf16x8 qreg[KSTEPS];
-  {
-    const int c = cbase + l32;
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      u32x4 raw = {0u, 0u, 0u, 0u};
-      if (c < C) raw = *reinterpret_cast<const u32x4*>(q + (pb + c) * DQ + ks * 16 + h * 8);
-      qreg[ks] = __builtin_bit_cast(bf16x8, raw);
-    }
-  }
-
-  const unsigned short* kU = k + (size_t)u * L * DQ;
-  const unsigned short* vU = v + (size_t)u * L * D;
-
-  const int seg_lo = srun * spw;
-  const int seg_hi = (seg_lo + spw) < S ? (seg_lo + spw) : S;
-  int seg_ne = seg_lo;
-  while (seg_ne < seg_hi && seg_ne * w < n) ++seg_ne;
-  auto seg_end = [&](int i) {
-    int e = i * w + w;
-    if (e > L) e = L;
-    if (e > n) e = n;
-    return e;
-  };
-
-  // per-lane LDS offsets that do not change: K operand row (block 0) and the transpose-load source
-  const int koff = l32 * KP + h * 16;
-  const int voff = (h * 4 + ((lane & 15) >> 2)) * VP + ((l32 & 16) + 4 * (lane & 3)) * 2;
-
-  auto score = [&](const unsigned char* Ks, int ib) {   // Sc^T of block ib: 32 items x 32 candidates
-    f32x16 sc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(Ks + ib * 32 * KP + koff + ks * 32);
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[ks], sc, 0, 0, 0);
-    }
-    return sc;
-  };
-  f32x16 acc[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
-  auto aggregate = [&](const unsigned char* Vs, int ib, const bf16x8 (&p)[2]) {   // acc^T += V^T . P^T
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const unsigned char* src = Vs + (ib * 32 + s * 16) * VP + voff + db * 64;
-        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
-        const s16x4 hi4 =
-            __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + 8 * VP));
-        const s16x8 both = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), p[s], acc[db], 0, 0, 0);
-      }
-  };
-  auto gates = [&](const f32x16& sc, bf16x8 (&p)[2]) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) p[s][e] = (__bf16)gate(sc[s * 8 + e], neg_scale_log2e);
-  };
-
-  constexpr int LPR = D / 8, RPI = 64 / LPR;
-  auto flush = [&](int seg) {
-#pragma unroll
-    for (int it = 0; it < CW / RPI; ++it) {
-      const int row = it * RPI + lane / LPR;
-      const u32x4 val = *reinterpret_cast<const u32x4*>(opatch + row * OP + (lane % LPR) * 16);
-      const int cr = cbase + row;
-      if (cr < C)
-        *reinterpret_cast<u32x4*>(seg_out + ((pb + cr) * S + seg) * D + (lane % LPR) * 8) = val;
-    }
-  };
-
-  Stage<DQ, D, NT> st;
-  int ci = seg_lo, ct0 = seg_lo * w, chi = seg_ne > seg_lo ? seg_end(seg_lo) : 0;
-  int buf = 0, out_seg = -1;
-  f32x16 sc0;
-  if (seg_ne > seg_lo) {
-    st.load(kU, vU, ct0, chi, tid);
-    st.store(smem, smem + KBYTES, tid);
-  }
-  __syncthreads();
-  if (seg_ne > seg_lo) sc0 = score(smem, 0);
-
-  while (ci < seg_ne) {
-    int ni = ci, nt0 = ct0 + TI, nhi = chi;
-    if (nt0 >= chi) {
-      ni = ci + 1;
-      nt0 = ni * w;
-      nhi = ni < seg_ne ? seg_end(ni) : 0;
-    }
-    const bool has_next = ni < seg_ne;
-    const unsigned char* Ks = smem + buf * (KBYTES + VBYTES);
-    const unsigned char* Vs = Ks + KBYTES;
-    unsigned char* nKs = smem + (buf ^ 1) * (KBYTES + VBYTES);
-
-    st.load(kU, vU, has_next ? nt0 : ct0, has_next ? nhi : chi, tid);   // lands during phases A-C
-    if (out_seg >= 0) {
-      flush(out_seg);
-      out_seg = -1;
-    }
-
-    bf16x8 p0[2], p1[2];
-    const f32x16 sc1 = score(Ks, 1);   // phase A
-    gates(sc0, p0);
-    aggregate(Vs, 0, p0);              // phase B
-    gates(sc1, p1);
-    aggregate(Vs, 1, p1);              // phase C
-    if (has_next) st.store(nKs, nKs + KBYTES, tid);
-
-    if (ni != ci) {   // segment finished: park H' rows in the patch, stored to global at the top of the next step
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          bf16x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[db][g * 4 + e];
-          *reinterpret_cast<u32x2*>(opatch + l32 * OP + (db * 32 + g * 8 + h * 4) * 2) = __builtin_bit_cast(u32x2, o);
-        }
-      out_seg = ci;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
-    }
-    __syncthreads();
-    buf ^= 1;
-    if (has_next) sc0 = score(nKs, 0);   // phase D
-    ci = ni;
-    ct0 = nt0;
-    chi = nhi;
-  }
-  if (out_seg >= 0) flush(out_seg);
-
-  if (seg_ne < seg_hi) {   // empty segments of the run: exact zeros
-    const int ncand = (C - ct * (CW * NW)) < CW * NW ? (C - ct * (CW * NW)) : CW * NW;
-    const int per_row = D / 8;
-    const int rows = ncand * (seg_hi - seg_ne);
-    for (int e = tid; e < rows * per_row; e += NT) {
-      const int row = e / per_row, ch = e - row * per_row;
-      const int cc = row / (seg_hi - seg_ne), ii = seg_ne + row % (seg_hi - seg_ne);
-      *reinterpret_cast<u32x4*>(seg_out + ((pb + ct * (CW * NW) + cc) * S + ii) * D + ch * 8) =
-          u32x4{0u, 0u, 0u, 0u};
-    }
-  }
-}
-
 // ------------------------------------------------------------------------------------------ direct-to-LDS form
-// d_q = d = 128 and more than 128 candidates per user (the benchmark shape). Same arithmetic and wave mapping as
-// the pipelined form; what changes is how history reaches LDS and how little vector-ALU work surrounds the matrix
+// d_q = d = 128, many candidates and long segments (the benchmark shape; is_direct() has the line). Same arithmetic and wave
+// mapping as above, with sigmoid gates; what changes is how history reaches LDS and how little vector-ALU work surrounds the matrix
 // instructions (a MFMA blocks VALU issue of its SIMD for about half of its own duration, and the gates already
 // need more VALU slots than the MFMAs leave free, so every address computation removed from the loop counts):
 //  * tiles of 32 items are fetched with global_load_lds_dwordx4 (each lane names a 16-byte global chunk, the 64
@@ -533,42 +327,12 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_pipe_kernel(const unsigned s
 //    whole path, whose next launch streams them back (measured: about 3 us of the step).
 constexpr int DT_TI = 32, DT_NBUF = 5, DT_AHEAD = 4;
 
-// waits until at most n (rounded down to even, at most 30) of this wave's vector-memory operations are outstanding
-__device__ __forceinline__ void wait_vm(int n) {
-  switch (n >> 1) {
-#define LASER_VM_CASE(i) case i: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * i)); break;
-    LASER_VM_CASE(1) LASER_VM_CASE(2) LASER_VM_CASE(3) LASER_VM_CASE(4) LASER_VM_CASE(5) LASER_VM_CASE(6)
-    LASER_VM_CASE(7) LASER_VM_CASE(8) LASER_VM_CASE(9) LASER_VM_CASE(10) LASER_VM_CASE(11) LASER_VM_CASE(12)
-    LASER_VM_CASE(13) LASER_VM_CASE(14)
-#undef LASER_VM_CASE
-    default:
-      if (n >= 30) __builtin_amdgcn_s_waitcnt(vmcnt_imm(30));
-      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  }
-}
-
-typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
-// The compiler re-associates "lane offset + buffer offset + constant" into one three-operand add per read; hiding
-// the sum of the first two behind an empty asm leaves it "register + constant", which becomes the read's
-// immediate offset.
-__device__ __forceinline__ lds_bytes lds_at(unsigned addr) { return (lds_bytes)(size_t)addr; }
-__device__ __forceinline__ lds_bytes lds_opaque(unsigned addr) {
-  asm volatile("" : "+v"(addr));
-  return lds_at(addr);
-}
-__device__ __forceinline__ bf16x8 lds_read16(lds_bytes p) {
-  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(p);
-}
 // items k0..k0+3 and k0+8..k0+11 of one value column per lane (see the file header); p addresses row k0
 __device__ __forceinline__ bf16x8 lds_read_tr(lds_bytes p) {
   const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
   const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 2048));
   return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
 }
-
-// Barrier without the fence of __syncthreads(): the compiler neither waits for the wave's outstanding LDS reads
-// (they are awaited where their registers are used) nor moves memory operations across it.
-__device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // 4 bytes per lane, as dma16
 __device__ __forceinline__ void dma4(const void* gbase, unsigned voff, unsigned lds_addr) {
@@ -1176,30 +940,36 @@ __global__ __launch_bounds__(64 * NW) void sta_mfma_dma_kernel(const unsigned sh
 }
 
 // ------------------------------------------------------------------------------------------ host side
-// the direct-to-LDS form's shapes
-static bool is_direct(const StaArgs& a) {
-  return a.heads == 1 && !a.softmax && a.d_q == 128 && a.d == 128 && tuning_int("LASER_STA_NODMA", 0) == 0;
-}
-
-// Waves (32 candidates each) per workgroup. Past 128 candidates one workgroup of eight on a compute unit, or two of four,
-// which wait less for each other where segments are shorter than a staged tile (64 items) and have no empty half where the
-// candidates fill an odd number of fours. Four for such segments if that number is odd (64 users x 320 candidates, w = 20:
-// 74 -> 64 us), if they are short (up to 20 items; 32 x 256, w = 10, 128 / 64: 37 -> 32; not with softmax or, past 256
-// candidates, several heads, whose state in registers makes eight the better ones: 20 x 512, four heads, softmax 74 against
-// 109), or if eight would leave compute units without work for most of the time (8 x 256, L = 2000, w = 56: 11.9 -> 10.3).
-// Between 21 and 63 items either is up to 9 % better than the other by widths, lengths and w in no pattern found, eight by 3 %
-// on average; from w = 64 on eight (32 x 256, L = 4096, w = 128, 64 / 64: 21 against 24 us).
+// Waves (32 candidates each) per workgroup
 static int pick_nw(const StaArgs& a) {
   const int vv = tuning_int("LASER_STA_NW", 0);   // tuning builds
   if (vv == 1 || vv == 2 || vv == 4 || vv == 8) return vv;
   if (a.C <= 128) return a.C > 64 ? 4 : (a.C > 32 ? 2 : 1);
-  if (is_direct(a) || a.w >= TI) return 8;
+  if (!a.softmax || a.w >= TI) return 8;
+  // softmax with segments shorter than a staged tile: two workgroups of four on a compute unit wait less for each other and have
+  // no empty half where the candidates fill an odd number of fours, or where eight would leave compute units without work
   const bool odd = ((a.C + 127) / 128) % 2 != 0;
-  const bool short_seg = a.w <= 20 && !a.softmax && (a.C <= 256 || a.heads == 1);
-  return odd || short_seg || (long long)a.U * ((a.C + 255) / 256) * a.S <= 384 ? 4 : 8;
+  return odd || (long long)a.U * ((a.C + 255) / 256) * a.S <= 384 ? 4 : 8;
 }
 
-// Consecutive segments per workgroup of the register-staged forms (they share the query registers and the prefetch
+// The direct-to-LDS form's calls. One workgroup of eight waves (four up to 128 candidates) on a compute unit shares every fetched
+// item with 256 candidates, so it is the better form where the fetches count: long segments, workgroups whose candidates fill
+// them, and steps enough behind the prologue of 4 us. Below these lines a ring per 64 candidates (sta_ring.hip) starts sooner, fills the
+// machine and stages no tile for two items. 160 dense calls (1 to 256 users, 65 to 512 candidates, w = 1 to 700; the better of a
+// few settings of the ring, in times of the direct form): w < 48 0.72 (0.41 to 1.03; 90 x 74, L = 263, w = 2: 108 -> 55 us). Longer
+// segments, less than 2400 tiles: 0.83 with up to 30 segments (0.58 to 1.1; 43 x 229, L = w = 395: 17.0 -> 10.9 us), 0.94 with more
+// (0.85 to 1.13; 3 x 198, L = 6210, w = 114: 11.0 -> 12.4). From 2400 tiles on, 0.94 (0.49 to 1.3; 112 x 197, L = 3045, w = 81:
+// 94 -> 115), but 0.82 where a user's last workgroup is nearly empty (up to 0.58 of the candidates' places taken; 183 x 263,
+// w = 202: 57 -> 38). With own counts per user, whose workgroups are dealt out, the line was not drawn anew.
+static bool is_direct(const StaArgs& a, int nw) {
+  if (a.heads != 1 || a.softmax || a.d_q != 128 || a.d != 128 || a.C <= 64) return false;
+  if (a.cand_off != nullptr) return true;
+  const long long tiles = (a.C + CW * nw - 1) / (CW * nw), steps = (a.w + DT_TI - 1) / DT_TI;
+  if (a.w < 48) return false;
+  return a.U * tiles * a.S * steps >= 2400 ? a.C * 100LL > tiles * CW * nw * 58 : a.S > 30;
+}
+
+// Consecutive segments per workgroup of the register-staged form (they share the query registers and the prefetch
 // pipeline). One and two waves: as many as still leave a few workgroups per compute unit (64 users x 64 candidates x 16
 // segments, two waves: 15.1 us with 512 workgroups of two segments, 11.2 us with 1024 of one). Four waves, two workgroups on
 // a compute unit, and eight, one on it: the smallest estimate of rounds of workgroups times the length of one, in segments,
@@ -1251,79 +1021,61 @@ bool sta_mfma_supports(const StaArgs& a) {
   if (a.heads != 1 && a.heads != 2 && a.heads != 4) return false;
   if (a.heads == 4 && (a.d_q < 64 || a.d != 128)) return false;
   if (a.C < 9) return false;   // fewer candidates than that: the streaming kernel's range
-  const int nw = pick_nw(a);
-  const long long ctiles = (a.C + CW * nw - 1) / (CW * nw);
+  const long long ctiles = (a.C + CW - 1) / CW;
   return (long long)a.U * ctiles * a.S <= 0x7fffffffLL;
 }
 
-template <int DQ, int D, int NW, int NBUF, int HEADS = 1, bool SOFTMAX = false>
+template <int DQ, int D, int NW, int NBUF, int HEADS>
 static void launch_one(const StaArgs& a, int spw, int ctiles, int sruns, float nsl) {
   const unsigned blocks = (unsigned)((long long)a.U * ctiles * sruns);
-  hipLaunchKernelGGL((sta_mfma_kernel<DQ, D, NW, NBUF, HEADS, SOFTMAX>), dim3(blocks), dim3(64 * NW), 0, a.stream,
+  hipLaunchKernelGGL((sta_mfma_kernel<DQ, D, NW, NBUF, HEADS>), dim3(blocks), dim3(64 * NW), 0, a.stream,
                      (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens, a.cand_off, a.P, a.C,
                      a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
 }
 
+// (eight waves fill a compute unit on their own and prefetch into a second tile; smaller workgroups overlap memory and matrix work
+// across the several that share a compute unit)
+template <int DQ, int D, int HEADS>
+static void launch_softmax(const StaArgs& a, int nw, int spw, int ctiles, int sruns, float nsl) {
+  if (nw == 8) launch_one<DQ, D, 8, 2, HEADS>(a, spw, ctiles, sruns, nsl);
+  else if (nw == 4) launch_one<DQ, D, 4, 1, HEADS>(a, spw, ctiles, sruns, nsl);
+  else if (nw == 2) launch_one<DQ, D, 2, 1, HEADS>(a, spw, ctiles, sruns, nsl);
+  else launch_one<DQ, D, 1, 1, HEADS>(a, spw, ctiles, sruns, nsl);
+}
+
 template <int DQ, int D>
-static void launch_nw(const StaArgs& a, int nw, int spw, int ctiles, int sruns, int dealt, float nsl) {
-  // eight waves fill a compute unit on their own and prefetch through LDS buffers of their own (direct-to-LDS
-  // fetches for d_q = d = 128; a tuning build can select the register-staged form there too, for comparison);
-  // smaller workgroups overlap memory and MFMA work across the several workgroups that share a compute unit
-  // two heads, the softmax variant: the register-staged form for every workgroup size (two tile buffers with
-  // eight waves)
-#define LASER_STA_STAGED(H, SM)                                                      \
-  do {                                                                               \
-    if (nw == 8) launch_one<DQ, D, 8, 2, H, SM>(a, spw, ctiles, sruns, nsl);         \
-    else if (nw == 4) launch_one<DQ, D, 4, 1, H, SM>(a, spw, ctiles, sruns, nsl);    \
-    else if (nw == 2) launch_one<DQ, D, 2, 1, H, SM>(a, spw, ctiles, sruns, nsl);    \
-    else launch_one<DQ, D, 1, 1, H, SM>(a, spw, ctiles, sruns, nsl);                 \
-  } while (0)
-  if (a.heads == 4) {
-    if constexpr ((DQ / 16) % 4 == 0 && (D / 32) % 4 == 0) {
-      if (a.softmax) LASER_STA_STAGED(4, true);
-      else LASER_STA_STAGED(4, false);
-    }
-  } else if (a.softmax) {
-    if (a.heads == 2) LASER_STA_STAGED(2, true);
-    else LASER_STA_STAGED(1, true);
-  } else if (a.heads == 2) {
-    LASER_STA_STAGED(2, false);
-  } else if (nw >= 4 && DQ == 128 && D == 128 && tuning_int("LASER_STA_NODMA", 0) == 0) {
-    // (65 to 128 candidates: four waves, one workgroup per compute unit (LDS) and one wave per SIMD; its deep prefetch needs
-    // several segments per workgroup to pay, see sta_mfma_launch)
-    const unsigned blocks = dealt ? 256u : (unsigned)((long long)a.U * ctiles * sruns);
+static void launch_heads(const StaArgs& a, int nw, int spw, int ctiles, int sruns, float nsl) {
+  if (a.heads == 1) launch_softmax<DQ, D, 1>(a, nw, spw, ctiles, sruns, nsl);
+  else if (a.heads == 2) launch_softmax<DQ, D, 2>(a, nw, spw, ctiles, sruns, nsl);
+  else if constexpr (DQ >= 64 && D == 128) launch_softmax<DQ, D, 4>(a, nw, spw, ctiles, sruns, nsl);
+}
+
+static void launch_direct(const StaArgs& a, int nw, int spw, int ctiles, int sruns, int dealt, float nsl) {
+  const unsigned blocks = dealt ? 256u : (unsigned)((long long)a.U * ctiles * sruns);
 #define LASER_STA_DMA(N, NTS, DEALT)                                                                                   \
   hipLaunchKernelGGL((sta_mfma_dma_kernel<N, NTS, DEALT>), dim3(blocks), dim3(64 * N), 0, a.stream,                     \
                      (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,        \
                      a.cand_off, a.U, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt)
-    if (nw == 8) {
-      if (dealt) { if (a.reread) LASER_STA_DMA(8, false, true); else LASER_STA_DMA(8, true, true); }
-      else { if (a.reread) LASER_STA_DMA(8, false, false); else LASER_STA_DMA(8, true, false); }
-    } else {
-      if (dealt) { if (a.reread) LASER_STA_DMA(4, false, true); else LASER_STA_DMA(4, true, true); }
-      else { if (a.reread) LASER_STA_DMA(4, false, false); else LASER_STA_DMA(4, true, false); }
-    }
-#undef LASER_STA_DMA
-  } else if (nw == 8) {
-    const unsigned blocks = (unsigned)((long long)a.U * ctiles * sruns);
-    hipLaunchKernelGGL((sta_mfma_pipe_kernel<DQ, D, 8>), dim3(blocks), dim3(512), 0, a.stream,
-                       (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens,
-                       a.cand_off, a.P, a.C, a.L, a.w, a.S, spw, ctiles, sruns, nsl, (unsigned short*)a.seg_out, a.seg_cnt);
+  if (nw == 8) {
+    if (dealt) { if (a.reread) LASER_STA_DMA(8, false, true); else LASER_STA_DMA(8, true, true); }
+    else { if (a.reread) LASER_STA_DMA(8, false, false); else LASER_STA_DMA(8, true, false); }
+  } else {   // 65 to 128 candidates: one workgroup per compute unit (LDS) and one wave per SIMD
+    if (dealt) { if (a.reread) LASER_STA_DMA(4, false, true); else LASER_STA_DMA(4, true, true); }
+    else { if (a.reread) LASER_STA_DMA(4, false, false); else LASER_STA_DMA(4, true, false); }
   }
-  else if (nw == 4) launch_one<DQ, D, 4, 1>(a, spw, ctiles, sruns, nsl);
-  else if (nw == 2) launch_one<DQ, D, 2, 1>(a, spw, ctiles, sruns, nsl);
-  else launch_one<DQ, D, 1, 1>(a, spw, ctiles, sruns, nsl);
+#undef LASER_STA_DMA
 }
 
 laser_status sta_mfma_launch(const StaArgs& a) {
   if (!sta_mfma_supports(a)) return LASER_ERR_UNSUPPORTED;
   const int nw = pick_nw(a);
+  const bool direct = is_direct(a, nw);
+  if (!direct && !a.softmax) return sta_ring_launch(a);
   const int ctiles = (a.C + CW * nw - 1) / (CW * nw);
   int spw = pick_spw(a, nw, ctiles), dealt = 0;
   // the direct-to-LDS kernels take a compute unit's LDS per workgroup: as many segments per workgroup as bring the
-  // launch down to one round of 256 workgroups, eight at most (16 users x 128 candidates x 40 segments: 640
-  // workgroups of one segment 32.9 us in the register-staged form, 224 of three segments 26.8 us in this one)
-  if (is_direct(a) && (nw == 8 || nw == 4)) {
+  // launch down to one round of 256 workgroups, eight at most
+  if (direct) {
     const long long per_seg = (long long)a.U * ctiles * a.S;
     spw = (int)((per_seg + 255) / 256 < 8 ? (per_seg + 255) / 256 : 8);
     if (spw < 1) spw = 1;
@@ -1337,15 +1089,17 @@ laser_status sta_mfma_launch(const StaArgs& a) {
   }
   const int sruns = (a.S + spw - 1) / spw;
   const float nsl = -1.4426950408889634f / a.gamma;
-  const int key = a.d_q * 1000 + a.d;
-  switch (key) {
-    case 32064: launch_nw<32, 64>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
-    case 32128: launch_nw<32, 128>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
-    case 64064: launch_nw<64, 64>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
-    case 64128: launch_nw<64, 128>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
-    case 128064: launch_nw<128, 64>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
-    case 128128: launch_nw<128, 128>(a, nw, spw, ctiles, sruns, dealt, nsl); break;
-    default: return LASER_ERR_UNSUPPORTED;
+  if (direct) {
+    launch_direct(a, nw, spw, ctiles, sruns, dealt, nsl);
+    return launch_status();
+  }
+  switch (a.d_q * 1000 + a.d) {
+    case 32064: launch_heads<32, 64>(a, nw, spw, ctiles, sruns, nsl); break;
+    case 32128: launch_heads<32, 128>(a, nw, spw, ctiles, sruns, nsl); break;
+    case 64064: launch_heads<64, 64>(a, nw, spw, ctiles, sruns, nsl); break;
+    case 64128: launch_heads<64, 128>(a, nw, spw, ctiles, sruns, nsl); break;
+    case 128064: launch_heads<128, 64>(a, nw, spw, ctiles, sruns, nsl); break;
+    default: launch_heads<128, 128>(a, nw, spw, ctiles, sruns, nsl); break;
   }
   return launch_status();
 }

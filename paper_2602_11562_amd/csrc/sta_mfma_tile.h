@@ -39,6 +39,38 @@ __device__ __forceinline__ void dma16(const void* gbase, unsigned voff, unsigned
 // (gfx9 encoding of a wait that leaves every other counter alone)
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
+// waits until at most n (rounded down to even, at most 30) of this wave's vector-memory operations are outstanding
+__device__ __forceinline__ void wait_vm(int n) {
+  switch (n >> 1) {
+#define LASER_VM_CASE(i) case i: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * i)); break;
+    LASER_VM_CASE(1) LASER_VM_CASE(2) LASER_VM_CASE(3) LASER_VM_CASE(4) LASER_VM_CASE(5) LASER_VM_CASE(6)
+    LASER_VM_CASE(7) LASER_VM_CASE(8) LASER_VM_CASE(9) LASER_VM_CASE(10) LASER_VM_CASE(11) LASER_VM_CASE(12)
+    LASER_VM_CASE(13) LASER_VM_CASE(14)
+#undef LASER_VM_CASE
+    default:
+      if (n >= 30) __builtin_amdgcn_s_waitcnt(vmcnt_imm(30));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  }
+}
+
+typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
+// The compiler re-associates "lane offset + buffer offset + constant" into one three-operand add per read; hiding
+// the sum of the first two behind an empty asm leaves it "register + constant", which becomes the read's
+// immediate offset.
+__device__ __forceinline__ lds_bytes lds_at(unsigned addr) { return (lds_bytes)(size_t)addr; }
+__device__ __forceinline__ lds_bytes lds_opaque(unsigned addr) {
+  asm volatile("" : "+v"(addr));
+  return lds_at(addr);
+}
+__device__ __forceinline__ bf16x8 lds_read16(lds_bytes p) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(p);
+}
+// Barrier without the fence of __syncthreads(): the compiler neither waits for the wave's outstanding LDS reads
+// (they are awaited where their registers are used) nor moves memory operations across it.
+__device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
+// The same, with this wave's LDS operations done: what the others may overwrite after it has been read, what it wrote is there
+__device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int DQ, int D, int NT>
 struct Stage {
   static constexpr int KCH = DQ / 8, VCH = D / 8;   // 16-byte chunks per row
