@@ -71,6 +71,19 @@ __device__ __forceinline__ void scatter_over_groups(float (&x)[8], int lane) {
   }
 }
 
+// sum (or maximum) over the lanes l, l + PW, l + 2 PW .. below N (4 or 8) of 16, for l below PW; what other lanes hold is not read
+template <int PW, int N, bool MAX>
+__device__ __forceinline__ float over_waves(float x) {
+  auto step = [](float v, auto ctrl) {
+    const float o = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, false));
+    return MAX ? fmaxf(v, o) : v + o;
+  };
+  if (PW <= 1) x = step(x, std::integral_constant<int, 0xB1>{});              // quad_perm [1,0,3,2]
+  if (PW <= 2) x = step(x, std::integral_constant<int, 0x4E>{});              // quad_perm [2,3,0,1]
+  if (PW <= 4 && N == 8) x = step(x, std::integral_constant<int, 0x12C>{});   // row_ror:12: lane + 4
+  return x;
+}
+
 // What an online softmax subtracts from its scores when the largest so far is m: scores of -inf alone (or none) then have
 // weight zero without a difference of infinities, and one of NaN or +inf gives NaN.
 __device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 0.0f : m; }
@@ -108,15 +121,18 @@ template <int D> struct Prod<float, D> {
       r.x[j] = *reinterpret_cast<const f32x4*>(W + n0 * D + j * 16 + (unsigned)((lane & 15) * D + (lane >> 4) * 4));
   }
   static __device__ __forceinline__ Operand transposed(const Cols& c, unsigned char* patch, int lane) {
-    float* p = reinterpret_cast<float*>(patch);             // [D][16]
+    // [D][16], row r of 64 bytes at place (r + r / 4) % 4 of its four rows: the four rows of a piece written at once, and the rows r,
+    // r + 4, r + 8, r + 12 read at once, are in different banks
+    float* p = reinterpret_cast<float*>(patch);
+    const int place = ((lane >> 4) * 4 + (((lane >> 2) + (lane >> 4)) & 3)) * 16 + (lane & 3) * 4;
 #pragma unroll
-    for (int it = 0; it < NCOL; ++it) *reinterpret_cast<f32x4*>(p + it * 256 + lane * 4) = c.x[it];
+    for (int it = 0; it < NCOL; ++it) *reinterpret_cast<f32x4*>(p + it * 256 + place) = c.x[it];
     __builtin_amdgcn_wave_barrier();                        // (LDS operations of a wave execute in order)
     Operand o;
 #pragma unroll
     for (int j = 0; j < D / 16; ++j)
 #pragma unroll
-      for (int m = 0; m < 4; ++m) o.x[j][m] = p[(j * 16 + (lane >> 4) * 4 + m) * 16 + (lane & 15)];
+      for (int m = 0; m < 4; ++m) o.x[j][m] = p[j * 256 + ((lane >> 4) * 4 + ((m + (lane >> 4)) & 3)) * 16 + (lane & 15)];
     __builtin_amdgcn_wave_barrier();
     return o;
   }
@@ -137,7 +153,10 @@ template <int D> struct Prod<float, D> {
 
 template <int D> struct Prod<unsigned short, D> {
   static constexpr int PITCH = D + 8;
-  struct Act { unsigned short v[3][16 * PITCH]; };          // head, remainder, remainder of that
+  // head, remainder, remainder of that. 128 and 320 bytes past a multiple of 256 from each other: four, or eight, rows of two or three
+  // parts read at once are in different banks
+  static constexpr int PART[3] = {0, 16 * PITCH + 64, 32 * PITCH + 160};
+  struct Act { unsigned short v[48 * PITCH + 160]; };
   static constexpr int NCOL = D / 32;
   struct Cols { u32x4 x[NCOL]; };                           // rows 32 it + lane / 2, columns n0 + 8 (lane % 2) ..
   struct Operand { bf16x8 x[D / 32]; };                     // column n of the product, k = 32 s + 8 g ..
@@ -148,15 +167,15 @@ template <int D> struct Prod<unsigned short, D> {
     const unsigned short h0 = f32_to_bf16_bits(x);
     const float r1 = x - bf16_bits_to_f32(h0);
     const unsigned short h1 = f32_to_bf16_bits(r1);
-    a.v[0][pair * PITCH + col] = h0;
-    a.v[1][pair * PITCH + col] = h1;
-    a.v[2][pair * PITCH + col] = f32_to_bf16_bits(r1 - bf16_bits_to_f32(h1));
+    a.v[PART[0] + pair * PITCH + col] = h0;
+    a.v[PART[1] + pair * PITCH + col] = h1;
+    a.v[PART[2] + pair * PITCH + col] = f32_to_bf16_bits(r1 - bf16_bits_to_f32(h1));
   }
   static __device__ __forceinline__ void put4(Act& a, int pair, int col, f32x4 x) {
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const bf16x4 b = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
-      *reinterpret_cast<bf16x4*>(a.v[p] + pair * PITCH + col) = b;
+      *reinterpret_cast<bf16x4*>(a.v + PART[p] + pair * PITCH + col) = b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) x[e] -= (float)b[e];
     }
@@ -177,8 +196,9 @@ template <int D> struct Prod<unsigned short, D> {
       r.x[s] = *reinterpret_cast<const bf16x8*>(W + n0 * D + s * 32 + (unsigned)((lane & 15) * D + (lane >> 4) * 8));
   }
   static __device__ __forceinline__ Operand transposed(const Cols& c, unsigned char* patch, int lane) {
+    // [D][16], the halves of every second eight rows swapped: lane groups 0 and 1, and 2 and 3, read from different banks
 #pragma unroll
-    for (int it = 0; it < NCOL; ++it) *reinterpret_cast<u32x4*>(patch + it * 1024 + lane * 16) = c.x[it];   // [D][16]
+    for (int it = 0; it < NCOL; ++it) *reinterpret_cast<u32x4*>(patch + it * 1024 + ((lane * 16) ^ ((lane & 16) << 3))) = c.x[it];
     __builtin_amdgcn_wave_barrier();
     Operand o;
 #pragma unroll
@@ -186,8 +206,9 @@ template <int D> struct Prod<unsigned short, D> {
       // transpose load: lane i of a 16-lane group supplies the address of row i / 4, columns 4 (i % 4) .. and receives
       // column i of four rows
       const unsigned char* src = patch + (k * 32 + (lane >> 4) * 8 + ((lane & 15) >> 2)) * 32 + (lane & 3) * 8;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + 128));
+      const int swap = (lane & 16) << 3;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + swap));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + (128 ^ swap)));
       o.x[k] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     }
     __builtin_amdgcn_wave_barrier();
@@ -207,12 +228,13 @@ template <int D> struct Prod<unsigned short, D> {
     if constexpr (PW <= 8) {
       constexpr int N = PW <= 4 ? 4 : 8;
       const int part = (lane & 15) / N;
+      const unsigned short* own = a.v + (part == 0 ? PART[0] : (part == 1 ? PART[1] : PART[2]));
       f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, s2 = s;
 #pragma unroll
       for (int k = 0; k < D / 32; ++k) {
         const int at = (lane & (N - 1)) * PITCH + k * 32 + (lane >> 4) * 8;
-        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(a.v[part < 2 ? part : 2] + at), s, 0, 0, 0);
-        if (N == 8) s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(a.v[2] + at), s2, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(own + at), s, 0, 0, 0);
+        if (N == 8) s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(a.v + PART[2] + at), s2, 0, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -226,7 +248,7 @@ template <int D> struct Prod<unsigned short, D> {
     for (int k = 0; k < D / 32; ++k)
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v[p] + (lane & 15) * PITCH + k * 32 + (lane >> 4) * 8);
+        const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v + PART[p] + (lane & 15) * PITCH + k * 32 + (lane >> 4) * 8);
         s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], x, s[p], 0, 0, 0);
       }
     return (s[2] + s[1]) + s[0];

@@ -18,7 +18,9 @@
 // d = 64) until the machine is full, by the stream of H' and of the matrices (96 KB a workgroup at d = 128) beyond. bf16, two
 // layers, d = 128: 100 pairs, S = 100 10.1 us (77 us on one workgroup per pair that walked the matrices row by row); 2048
 // pairs, S = 40 13.5 us, 4096 pairs, S = 32 17.8 us (16.3 and 31.2 us in the form with 32-pair tiles this one replaced);
-// fp32, 1200 pairs, S = 15, d = 64, two layers 8.2 us (34 us).
+// fp32, 1200 pairs, S = 15, d = 64, two layers 8.2 us (34 us). Parts and patches laid out so that what is read at once is in
+// different banks, the next layer's W_q across its patch behind the pass, and the waves of a pair met behind the last product: another
+// layer of 100 pairs, d = 128, S = 8 2.65 -> 2.45 us (fp32 6.3 -> 5.95); 120 drawn calls 0.979 of the time.
 #include "gsta_tile.h"
 #include "laser_internal.h"
 
@@ -40,8 +42,8 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   __shared__ __attribute__((aligned(16))) typename X::Act bt, bq; // t; q', then p
   __shared__ __attribute__((aligned(16))) float rr[PW * RP];      // r / sqrt(d)
   __shared__ __attribute__((aligned(16))) unsigned char patches[NW][X::PATCH];
-  __shared__ __attribute__((aligned(16))) float part[WPP > 1 ? NW : 1][D];
-  __shared__ float pml[NW][2];
+  __shared__ __attribute__((aligned(16))) float part[WPP > 1 ? NW : 1][D];   // (the views)
+  __shared__ __attribute__((aligned(8))) f32x2 pml[NW];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pbase = blockIdx.x * PW, n0 = wave * 16, c4 = n0 + 4 * g;
@@ -86,18 +88,22 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   }
   // (a share of a matrix takes 32 registers in fp32 at d = 128: beside eight rows a lane there is room for two)
   constexpr bool LATE = sizeof(T) == 4 && D == 128 && R == 8;
+  // the next layer's share of W_q crosses the patch in the shadow of the barrier behind the pass, not when it is wanted (unless that
+  // takes registers which are not there)
+  constexpr bool EAGER = sizeof(T) == 2 && !(PW == 16 && D == 128 && RES && R < 4);
   if (!LATE) X::load_cols(cv, wv, n0, lane);
   const float scale = X::LOG / sqrtf((float)D);
   // (with M = 0 thinkable the compiler moves every load that only the loop wants behind a branch, and the wait for t before it)
   __builtin_assume(M > 0);
   if (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);          // (widened any earlier, t waits for its load ahead of the others)
   f32x4 t = X::wide4(traw);                                       // pair l16, columns c4 ..
+  typename X::Operand oq;
 
   for (int l = 0; l < M; ++l) {
     const bool more_layers = l + 1 < M;
     const size_t next = (size_t)(l + 1) * D * D;
     X::put4(bt, l16, c4, t);
-    const typename X::Operand oq = X::transposed(cq, patch, lane);
+    if (EAGER ? l == 0 : true) oq = X::transposed(cq, patch, lane);
     __syncthreads();
     const f32x4 q = X::template product<PW>(bt, oq, lane);                     // q' = t W_q
     if (more_layers) X::load_cols(cq, wq + next, n0, lane);
@@ -167,40 +173,28 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
       const int y0 = gl * 8 + group_first<LPR>(lane);             // the elements this lane hands on
       // p, zero without a valid segment (by their number: a denominator of NaN, or of zero where every score is -inf, has to
       // reach the result)
-      if constexpr (WPP == 1) {
-        const float inv = nv[i] > 0 ? 1.0f / den : 0.0f;
+      const float inv = WPP > 1 ? 1.0f : (nv[i] > 0 ? 1.0f / den : 0.0f);
 #pragma unroll
-        for (int e = 0; e < LPR / 8; ++e) X::put(bq, pj, y0 + e, acc[e] * inv);
-      } else {
-        if constexpr (LPR == 16) *reinterpret_cast<f32x2*>(&part[wave][y0]) = f32x2{acc[0], acc[1]};
-        else part[wave][y0] = acc[0];
-        if (lane == 0) {
-          pml[wave][0] = nv[i] > 0 ? mw : 0.0f;
-          pml[wave][1] = nv[i] > 0 ? den : 1.0f;
-        }
-      }
+      for (int e = 0; e < LPR / 8; ++e) X::put(bq, WPP > 1 ? wp * PW + pj : pj, y0 + e, acc[e] * inv);
+      if (WPP > 1 && lane == 0) pml[wp * PW + pj] = nv[i] > 0 ? f32x2{mw, den} : f32x2{0.0f, 1.0f};
     }
     if (!RES && more_layers) load_h(h[0], 0, 0);                  // the first rows of the next layer's pass
     const typename X::Operand ov = X::transposed(cv, patch, lane);
+    if (EAGER && more_layers) oq = X::transposed(cq, patch, lane);
     __syncthreads();
-    if constexpr (WPP > 1) {                                      // the waves of a pair
-      for (int e = tid; e < PW * D; e += 4 * D) {
-        const int j = e / D, y = e % D;
-        float m = pml[j * WPP][0], num = 0.0f, den = 0.0f;
+    if constexpr (WPP == 1) {
+      t += X::template product<PW>(bq, ov, lane);                              // t += p W_v
+    } else {
+      // The waves of a pair meet behind the product: column o PW + pair is the sum of wave o, relative to its own maximum (merged
+      // before the product they took a barrier more, and an exponential per wave and element)
+      const f32x2 ml = pml[lane & (NW - 1)];
+      f32x4 y = X::template product<NW>(bq, ov, lane);
+      const float f = X::ex(ml[0] - softmax_ref(over_waves<PW, NW, true>(ml[0])));
+      const float scale = f / over_waves<PW, NW, false>(ml[1] * f);
 #pragma unroll
-        for (int o = 1; o < WPP; ++o) m = fmaxf(m, pml[j * WPP + o][0]);
-        m = softmax_ref(m);
-#pragma unroll
-        for (int o = 0; o < WPP; ++o) {
-          const float f = X::ex(pml[j * WPP + o][0] - m);
-          den = fmaf(pml[j * WPP + o][1], f, den);
-          num = fmaf(part[j * WPP + o][y], f, num);
-        }
-        X::put(bq, j, y, num / den);
-      }
-      __syncthreads();
+      for (int r = 0; r < 4; ++r) y[r] = over_waves<PW, NW, false>(y[r] * scale);
+      t += y;
     }
-    t += X::template product<PW>(bq, ov, lane);                                // t += p W_v
     if (more_layers && !LATE) X::load_cols(cv, wv + next, n0, lane);
   }
   if (l16 < PW && pbase + l16 < P) *reinterpret_cast<f32x4*>(z + (size_t)(pbase + l16) * D + c4) = t;
