@@ -17,12 +17,18 @@
 // are never read (whatever H' holds there is not trusted): they, and the results of a pair without any valid
 // segment, are written by a pass of their own before the first tile. The rows of the wave's next tile and r of the
 // pairs that start in it are in flight while it multiplies. After LayerNorm a lane holds, in the accumulator layout,
-// 64 of the 128 components of row l32: the rounded values (what a stored s would hold) are multiplied with the same
-// components of its pair's r, read from a wave-private LDS copy, and one exchange with lane ^ 32 gives the row's
-// score. Maximum and sum over the rows of a pair in the tile are wave reductions; tiles of a pair are merged with the
-// running maximum (online softmax). The weighted sum over rows is taken from the LDS patch the rounded rows are
-// parked in: lane l owns components 2 l and 2 l + 1 and reads one word per row, with the row's weight from
-// v_readlane. p / sum of weights replaces r in the pair's z row.
+// 64 of the 128 components of row l32, rounded (what a stored s would hold): per 16 components a valid B operand, so
+// the scores are one more product, r times the rows, and p = sum_i a_i s_i is another over the rows parked in the
+// wave's LDS patch (transpose loads). r and the weights a are fp32 and stay so: both enter as three bf16 parts, which
+// hold all 24 bits, in three rows of the A operand that are added afterwards. A tile holds rows of at most two pairs;
+// they have a slot each, by the parity of their number: half h of the wave owns slot h, its scores, running maximum
+// and sum (online softmax over a pair's tiles) and running p, and a row's weight is zero in the other slot.
+//
+// Vector issue and the matrix pipe of the two waves per SIMD bound the tile: 12.2 thousand cycles (the products 4.8, the
+// normalised rows and their scores 3.1, softmax and sum 1.6, addresses and requests 1.4). Scores as four vector
+// operations per word and the weighted sum row by row (a word, a weight from v_readlane, five to seven operations) were 350
+// of 1100 vector instructions, another hundred where two pairs met; the two products take 16 MFMAs. With the launches before
+// and behind it, 16384 pairs of 60 valid rows: 132.0 -> 125.4 us, with the views 144.6 -> 140.8.
 #include "segment_ffn_tile.h"
 
 namespace laser {
@@ -44,10 +50,39 @@ __device__ __forceinline__ void ffn_fetch_rows_two(const unsigned short* rowsA, 
   }
 }
 
+// x as three bf16 parts in the upper halves of hi, mid and lo (24 bits by truncation: the sum is x)
+__device__ __forceinline__ void ffn_three_parts(float x, unsigned& hi, unsigned& mid, unsigned& lo) {
+  hi = __float_as_uint(x) & 0xffff0000u;
+  const float r1 = x - __uint_as_float(hi);
+  mid = __float_as_uint(r1) & 0xffff0000u;
+  lo = __float_as_uint(r1 - __uint_as_float(mid));
+}
+
+// Component-wise maximum of two words of bf16 values below 2^120: below 2^121 their bits are ordered as fp16's are. NaN
+// words lose, as in fmaxf; -infinity (0xff80) is a NaN here, so it is a start value that every value replaces.
+__device__ __forceinline__ unsigned ffn_word_max(unsigned a, unsigned b) {
+  unsigned m;
+  asm("v_pk_max_f16 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+  return m;
+}
+constexpr unsigned FG_NONE = 0xff80ff80u;   // a word of bf16 -infinities
+
+// Sum and maximum over the 32 lanes of a half of the wave, in all of them (lane permutations, no LDS)
+__device__ __forceinline__ float ffn_half_sum(float v) {
+  const unsigned x = __float_as_uint(row_sum<16>(v));
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float ffn_half_max(float v) {
+  const unsigned x = __float_as_uint(ffn_row_max(v));
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // MR: also the two other views of Sec. 3.4.4 of the transformed rows: pool [P, D] bf16, the component-wise maximum
-// over the segments that hold a valid item (zeros when there is none), taken in the weighted-sum loop from the same
-// words (tile rows past the last one are copies of it, so they leave the maximum alone); recent [P, r, D] bf16,
-// the first r rows as they would be stored. Either may be null.
+// over the segments that hold a valid item (zeros when there is none), taken from the parked rows (tile rows past the
+// last one are copies of it, so they leave the maximum alone); recent [P, r, D] bf16, the first r rows as they would
+// be stored. Either may be null.
 template <int DFF, bool MR>
 __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     const unsigned short* seg, const int32_t* __restrict__ lens, const unsigned short* __restrict__ w1,
@@ -58,18 +93,23 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     float* z,              // [P, D]: r on entry, p on exit
     unsigned* pool, unsigned short* recent, int r) {
   constexpr int D = FM_D, KSTEPS = D / 16, DB = D / 32, OP = FM_OP;
-  constexpr int RVB = 512, RSLOTS = 4;   // copies of r per wave: the pairs of the tile in work and of the next one
+  // per wave: r of the pairs that start in the next tile, by slot (fp32, as it lands), and the three parts of r of the pairs in
+  // work, rows 3 slot + part of pitch RPP (16 rows read at once start in different banks)
+  constexpr int RVB = 512, RPP = D * 2 + 16, RPB = 6 * RPP;
+  constexpr int WPO = FM_ROWS * OP;        // the weights' parts: six rows of 64 bytes behind the patch's rows
+  static_assert(WPO + 6 * 64 <= FM_PATCH, "the weights' parts fit behind the patch's rows");
   __shared__ __attribute__((aligned(1024))) unsigned char W1L[FM_W1B];
   __shared__ __attribute__((aligned(1024))) unsigned char W2L[DFF * FM_ROWB];
   __shared__ __attribute__((aligned(1024))) unsigned char patch[FM_WAVES * FM_PATCH];
-  __shared__ __attribute__((aligned(1024))) unsigned char rvec[FM_WAVES * RSLOTS * RVB];
+  __shared__ __attribute__((aligned(1024))) unsigned char rvec[FM_WAVES * 2 * RVB];
+  __shared__ __attribute__((aligned(16))) unsigned char rparts[FM_WAVES * RPB];
   __shared__ __attribute__((aligned(16))) float vecs[DFF + 3 * D];                    // b1, b2, ln_g, ln_b
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned char* opatch = patch + wave * FM_PATCH;
   const unsigned land = __builtin_amdgcn_readfirstlane(ffn_lds_addr(opatch));
-  unsigned char* rmine = rvec + wave * RSLOTS * RVB;
+  unsigned char* rmine = rvec + wave * 2 * RVB;
   const unsigned rland = __builtin_amdgcn_readfirstlane(ffn_lds_addr(rmine));
   const int stride = gridDim.x * FM_WAVES;
   const int pr0 = blockIdx.x * FM_WAVES + wave;   // the wave's k-th pair is pr0 + k * stride
@@ -131,7 +171,32 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     return make_tile(kn, nvn, 0, t.ord + 2);
   };
   auto fetch_r = [&](int p, int slot) {   // 512 bytes: 16 per lane of the lower half of the wave
-    if (lane < 32) ffn_dma16(z + (size_t)p * D, (unsigned)(lane << 4), rland + (slot & (RSLOTS - 1)) * RVB);
+    if (lane < 32) ffn_dma16(z + (size_t)p * D, (unsigned)(lane << 4), rland + (slot & 1) * RVB);
+  };
+  // r of the pairs that start in tile t (landed) in its parts, behind the last use of the parts before. The product wants a
+  // 16-group's components in the order 0..3, 8..11, 4..7, 12..15: word w (components 2 w, 2 w + 1) at 4 (w / 2 & 1) + 2 (w / 4) + w % 2.
+  unsigned char* rpmine = rparts + wave * RPB;
+  // (Offsets of lanes that are used once per tile are worked out where they are used, from a lane number the compiler cannot tell
+  // from a fresh value: kept across the products they are spilled, and a reload waits for the fetches before it.)
+  auto lane_again = [&]() {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  auto park_r = [&](const Tile& t) {
+    const int l = lane_again();
+    unsigned char* rpword = rpmine + (l >> 3) * 32 + (4 * ((l >> 1) & 1) + 2 * ((l >> 2) & 1) + (l & 1)) * 4;
+    auto park = [&](int slot) {
+      const f32x2 rv = *reinterpret_cast<const f32x2*>(rmine + slot * RVB + l * 8);
+      unsigned a[3], b[3];
+      ffn_three_parts(rv[0], a[0], a[1], a[2]);
+      ffn_three_parts(rv[1], b[0], b[1], b[2]);
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+        *reinterpret_cast<unsigned*>(rpword + (3 * slot + part) * RPP) = (a[part] >> 16) | (b[part] & 0xffff0000u);
+    };
+    if (t.a0 == 0) park(t.ord & 1);
+    if (t.nb > 0) park((t.ord + 1) & 1);
   };
   // the rows of tile t into the landing area, and r of the pairs that start in it
   auto fetch_tile = [&](const Tile& t) {
@@ -165,147 +230,169 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   const unsigned char* opr = opatch + (lane / LPR) * OP + (lane % LPR) * 16;
   const unsigned char* pcol = opatch + lane * 4;   // components 2 lane, 2 lane + 1 of row 0
 
-  // maximum over the wave's rows (the value of a row sits in its 16-lane group's lanes l32 and l32 + 32)
-  auto rows_max = [&](float v) {
-    const int b = __float_as_int(ffn_row_max(v));
-    return fmaxf(__int_as_float(__builtin_amdgcn_readlane(b, 0)), __int_as_float(__builtin_amdgcn_readlane(b, 16)));
-  };
-  auto rows_sum = [&](float v) {
-    const int b = __float_as_int(row_sum<16>(v));
-    return __int_as_float(__builtin_amdgcn_readlane(b, 0)) + __int_as_float(__builtin_amdgcn_readlane(b, 16));
-  };
-  // a finished pair: its pooled maximum (bits of stored values pass through) and p / sum of weights in place of r
-  auto finish_pair = [&](int p, float den, float p0, float p1, float mx0, float mx1) {
-    if (MR && pool) pool[(size_t)p * (D / 2) + lane] = (__float_as_uint(mx0) >> 16) | (__float_as_uint(mx1) & 0xffff0000u);
-    const float inv = 1.0f / den;
-    *reinterpret_cast<f32x2*>(z + (size_t)p * D + 2 * lane) = f32x2{p0 * inv, p1 * inv};
-  };
+  // gamma and beta are of a size that keeps rows plain (see below)
+  bool gb_ok;
+  {
+    const f32x2 g2 = *reinterpret_cast<const f32x2*>(gs + 2 * lane), b2v = *reinterpret_cast<const f32x2*>(bs + 2 * lane);
+    const float lim = 0x1p60f;
+    gb_ok = __all(fabsf(g2[0]) < lim && fabsf(g2[1]) < lim && fabsf(b2v[0]) < lim && fabsf(b2v[1]) < lim);
+  }
 
   bf16x8 xreg[KSTEPS];
   if (cur.some) ffn_read_rows(opatch, l32, h, xreg);
-  // running sums of pair A (online softmax over its tiles)
-  float m = -INFINITY, den = 0.0f, p0 = 0.0f, p1 = 0.0f, mx0 = -INFINITY, mx1 = -INFINITY;
+  if (cur.some) park_r(cur);
+  // of the half's slot, over the pair's tiles: running maximum, sum of weights and p (components 16 b + i16, in both groups of 16)
+  float m = -INFINITY, den = 0.0f, psum[D / 16];
+#pragma unroll
+  for (int b = 0; b < D / 16; ++b) psum[b] = 0.0f;
+  unsigned mx = FG_NONE;       // pooled maximum of pair A, components 2 lane and 2 lane + 1
+  bool rough = !gb_ok;         // a row's values may be large or not finite (from the tile where that was seen on)
   while (cur.some) {
     const Tile nxt = tile_after(cur);
     if (nxt.some) fetch_tile(nxt);
     const int na = cur.na, nb = cur.nb, ntot = na + nb;
     const int pA = pr0 + cur.kA * stride, pB = pr0 + cur.kB * stride;
-    const bool ok = l32 < ntot;
-    const bool isB = nb > 0 && l32 >= na;
-    const float* rw = reinterpret_cast<const float*>(rmine + ((cur.ord + (isB ? 1 : 0)) & (RSLOTS - 1)) * RVB);
+    const bool slotA = h == (cur.ord & 1);                      // this half owns pair A's slot
+    const bool mine = l32 < ntot && (l32 >= na) != slotA;       // row l32 belongs to this half's pair
+    const bool fresh = !slotA || cur.a0 == 0;                   // ... which starts in this tile
     f32x16 acc[DB];
+    __builtin_amdgcn_s_setprio(2);   // the other wave of the SIMD has vector work for the matrix instructions' shadow: 1.5 % of the pass
     ffn_tile_products<DFF>(xreg, ln, W1L, W2L, b1s, b2s, l32, h, acc);
+    __builtin_amdgcn_s_setprio(0);
     if (nxt.some) {   // the next tile's rows move into the registers of this one's before the patch is written
       ffn_wait_fetches();
       ffn_read_rows(opatch, l32, h, xreg);
     }
     float rstd, nmr;
     ffn_row_stats(acc, eps, rstd, nmr);
-    // normalise, round (the value a stored s holds), park; the row's score against its pair's r from the rounded
+    // The fast forms below add rows of two pairs with weights of zero and compare bits as fp16. A row is plain when its mean is
+    // finite and moderate (nmr = -mean rstd): its normalised values are then below 12 (1 + |nmr|) < 2^45, and with gamma and beta
+    // below 2^60 all of them below 2^106.
+    rough = rough || !__all(fabsf(nmr) <= 0x1p40f * fminf(1.0f, rstd));
+    // normalise, round (the value a stored s holds), park; the rows' scores against r of both slots from the rounded
     // values. Tile rows past the last one hold copies of it: finite like it, with weight zero below.
-    float sdot = 0.0f;
+    // A operands: rows 0..2 of the scores' (32 rows) and 0..2 of the sums' (16) are the parts of slot 0, rows 4..6 and 8..10
+    // those of slot 1; the others repeat some part, and what they give is not looked at. A row of the scores' result is thus
+    // in half `slot` of the wave, and so is one of the sums'.
+    f32x16 sacc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sacc[e] = 0.0f;
+    const int la = lane_again();
+    const unsigned char* rop = rpmine + (3 * ((la >> 2) & 1) + ((la & 3) < 2 ? (la & 3) : 2)) * RPP + (la >> 5) * 16;
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
       __builtin_amdgcn_sched_barrier(0);   // a column block at a time: hoisted together, the LDS reads of all four spill
+      u32x4 ops[2];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int c0 = db * 32 + 8 * g + 4 * h;
         const f32x4 gg = *reinterpret_cast<const f32x4*>(gs + c0);
         const f32x4 bb = *reinterpret_cast<const f32x4*>(bs + c0);
-        const f32x4 rr = *reinterpret_cast<const f32x4*>(rw + c0);
         u32x2 bits;
 #pragma unroll
         for (int e2 = 0; e2 < 2; ++e2) {
           const bf16x2 o = {(__bf16)fmaf(fmaf(acc[db][4 * g + 2 * e2], rstd, nmr), gg[2 * e2], bb[2 * e2]),
                             (__bf16)fmaf(fmaf(acc[db][4 * g + 2 * e2 + 1], rstd, nmr), gg[2 * e2 + 1], bb[2 * e2 + 1])};
-          const unsigned wd = __builtin_bit_cast(unsigned, o);
-          bits[e2] = wd;
-          sdot = fmaf(__uint_as_float(wd << 16), rr[2 * e2], sdot);
-          sdot = fmaf(__uint_as_float(wd & 0xffff0000u), rr[2 * e2 + 1], sdot);
+          bits[e2] = __builtin_bit_cast(unsigned, o);
+          ops[g >> 1][2 * (g & 1) + e2] = bits[e2];
         }
         *reinterpret_cast<u32x2*>(opatch + l32 * OP + c0 * 2) = bits;
       }
-    }
-    sdot = ffn_both_halves_sum(sdot);
-    // softmax over the tile's rows, merged into the pair's running sums. Row reductions by lane permutations; the
-    // two rows of a half meet through scalar registers. The weighted sum over rows is taken from the parked words
-    // (LDS operations of a wave execute in order: no barrier needed), a row's weight from v_readlane.
-    if (nb == 0) {   // one pair in the tile
-      const float m_new = fmaxf(m, rows_max(ok ? sdot : -INFINITY));
-      const float sc = __expf(m - m_new);   // 0 for the pair's first tile (m = -inf)
-      const float a = ok ? __expf(sdot - m_new) : 0.0f;
-      den = fmaf(den, sc, rows_sum(a));
-      p0 *= sc;
-      p1 *= sc;
-      m = m_new;
-      const int abits = __float_as_int(a);
 #pragma unroll
-      for (int row = 0; row < FM_ROWS; ++row) {
-        const float ar = __int_as_float(__builtin_amdgcn_readlane(abits, row));
-        const unsigned wd = *reinterpret_cast<const unsigned*>(pcol + row * OP);
-        p0 = fmaf(ar, __uint_as_float(wd << 16), p0);
-        p1 = fmaf(ar, __uint_as_float(wd & 0xffff0000u), p1);
-        if (MR) {
-          mx0 = fmaxf(mx0, __uint_as_float(wd << 16));
-          mx1 = fmaxf(mx1, __uint_as_float(wd & 0xffff0000u));
-        }
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const bf16x8 ra = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(rop + (2 * db + s2) * 32));
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ra, __builtin_bit_cast(bf16x8, ops[s2]), sacc, 0, 0, 0);
       }
     }
-    float q0 = 0.0f, q1 = 0.0f, nx0 = -INFINITY, nx1 = -INFINITY, mB = -INFINITY, denB = 0.0f;   // pair B's sums
-    if (nb > 0) {    // A's last rows, then B's first
-      const float m_new = fmaxf(m, rows_max(isB ? -INFINITY : sdot));
-      mB = rows_max(isB && ok ? sdot : -INFINITY);
-      const float sc = __expf(m - m_new);
-      const float a = ok ? __expf(sdot - (isB ? mB : m_new)) : 0.0f;
-      den = fmaf(den, sc, rows_sum(isB ? 0.0f : a));
-      denB = rows_sum(isB ? a : 0.0f);
-      p0 *= sc;
-      p1 *= sc;
-      const int abits = __float_as_int(a);
-      // Eight rows at a time: a group of one pair's rows takes that pair's sums alone, the group in which A ends both. The tile is
-      // bound by vector issue, and both pairs' sums and maxima for every row were a quarter of its instructions (the
-      // complete head with the views, 16384 pairs, S = 100, lengths uniform in [200, 1000], 25 runs in turn: 293.2 -> 289.2 us, quartiles
-      // 292.5 .. 294.9 and 288.0 .. 290.1; without the views, whose maxima cost most, the same either way).
-      unsigned wd[FM_ROWS];
+    // softmax over the tile's rows, merged into the running sums of the half's pair; the weights' parts go to LDS as the A
+    // operand of the sum (operations of a wave on LDS execute in order: no barrier needed)
+    // Contraction index 8 kg + 4 s + j of the sums is row 8 kg + 2 j + s: sixteen rows that one transpose load reads, all even or
+    // all odd, start eight banks apart (row pitch 68 words).
+    const int lb = lane_again(), kg = lb >> 4;
+    const unsigned char* wop = opatch + WPO + (3 * ((lb >> 3) & 1) + ((lb & 3) < 2 ? (lb & 3) : 2)) * 64 + kg * 16;
+    const unsigned char* sop = opatch + (8 * kg + 2 * ((lb >> 2) & 3)) * OP + (lb & 3) * 8;
+    float scale;   // of what has been added up so far
+    {
+      unsigned char* wput = opatch + WPO + 3 * 64 * (lb >> 5) + ((lb >> 3) & 3) * 16 + (4 * (lb & 1) + ((lb >> 1) & 3)) * 2;
+      const float sdot = sacc[0] + (sacc[1] + sacc[2]);
+      const float m_old = fresh ? -INFINITY : m;
+      m = fmaxf(m_old, ffn_half_max(mine ? sdot : -INFINITY));
+      scale = __expf(m_old - m);   // 0 for the pair's first tile
+      const float a = mine ? __expf(sdot - m) : 0.0f;
+      unsigned part[3];
+      ffn_three_parts(a, part[0], part[1], part[2]);
 #pragma unroll
-      for (int row = 0; row < FM_ROWS; ++row) wd[row] = *reinterpret_cast<const unsigned*>(pcol + row * OP);
-      auto add_row = [&](int row, float& s0, float& s1, float& x0, float& x1) {
-        const float ar = __int_as_float(__builtin_amdgcn_readlane(abits, row));
-        const float lo = __uint_as_float(wd[row] << 16), hi = __uint_as_float(wd[row] & 0xffff0000u);
-        s0 = fmaf(ar, lo, s0);
-        s1 = fmaf(ar, hi, s1);
-        if (MR) {
-          x0 = fmaxf(x0, lo);
-          x1 = fmaxf(x1, hi);
-        }
-      };
+      for (int e = 0; e < 3; ++e) *reinterpret_cast<unsigned short*>(wput + e * 64) = (unsigned short)(part[e] >> 16);
+      den = fmaf(fresh ? 0.0f : den, scale, ffn_half_sum(a));
+    }
+    asm volatile("" ::: "memory");
+    const bf16x8 wa = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wop));
+    auto row_words = [&](int b) {   // 16 components of the 32 rows
+      const s16x4 e4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ffn_lds4(sop + b * 32));
+      const s16x4 o4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ffn_lds4(sop + b * 32 + OP));
+      return __builtin_bit_cast(u32x4, (s16x8)__builtin_shufflevector(e4, o4, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    const f32x4 none = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (!(rough && nb > 0)) {
 #pragma unroll
-      for (int r0 = 0; r0 < FM_ROWS; r0 += 8) {
-        if (na >= r0 + 8) {
+      for (int b = 0; b < D / 16; ++b) {
+        const f32x4 t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, __builtin_bit_cast(bf16x8, row_words(b)), none, 0, 0, 0);
+        psum[b] = fmaf(fresh ? 0.0f : psum[b], scale, t[0] + (t[1] + t[2]));
+      }
+    } else {   // zero times a value of the other pair that is not finite would be NaN: each pair's rows alone
+      u32x4 inA;
 #pragma unroll
-          for (int row = r0; row < r0 + 8; ++row) add_row(row, p0, p1, mx0, mx1);
-        } else if (na <= r0) {
+      for (int e = 0; e < 4; ++e) {
+        const int row = 8 * kg + 4 * (e & 1) + (e >> 1);        // of the word's lower half, the upper one's is row + 2
+        inA[e] = (row < na ? 0xffffu : 0u) | (row + 2 < na ? 0xffff0000u : 0u);
+      }
 #pragma unroll
-          for (int row = r0; row < r0 + 8; ++row) add_row(row, q0, q1, nx0, nx1);
-        } else {
+      for (int b = 0; b < D / 16; ++b) {
+        const u32x4 rows = row_words(b);
+        const f32x4 tA = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, __builtin_bit_cast(bf16x8, rows & inA), none, 0, 0, 0);
+        const f32x4 tB = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, __builtin_bit_cast(bf16x8, rows & ~inA), none, 0, 0, 0);
+        psum[b] = fmaf(fresh ? 0.0f : psum[b], scale, slotA ? tA[0] + (tA[1] + tA[2]) : tB[0] + (tB[1] + tB[2]));
+      }
+    }
+    // the pooled maxima, a word of two components per row: eight rows at a time where a group is one pair's
+    unsigned mxB = FG_NONE;
+    if (MR && pool) {
+      if (!rough) {
 #pragma unroll
-          for (int row = r0; row < r0 + 8; ++row) {
-            const bool rowA = row < na;   // uniform: the selects of the weights are scalar
-            const float ar = __int_as_float(__builtin_amdgcn_readlane(abits, row));
-            const float arA = rowA ? ar : 0.0f, arB = rowA ? 0.0f : ar;
-            const float lo = __uint_as_float(wd[row] << 16), hi = __uint_as_float(wd[row] & 0xffff0000u);
-            p0 = fmaf(arA, lo, p0);
-            p1 = fmaf(arA, hi, p1);
-            q0 = fmaf(arB, lo, q0);
-            q1 = fmaf(arB, hi, q1);
-            if (MR) {
-              mx0 = fmaxf(mx0, rowA ? lo : -INFINITY);
-              mx1 = fmaxf(mx1, rowA ? hi : -INFINITY);
-              nx0 = fmaxf(nx0, rowA ? -INFINITY : lo);
-              nx1 = fmaxf(nx1, rowA ? -INFINITY : hi);
+        for (int r0 = 0; r0 < FM_ROWS; r0 += 8) {
+          unsigned wd[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) wd[j] = *reinterpret_cast<const unsigned*>(pcol + (r0 + j) * OP);
+          if (nb == 0 || na >= r0 + 8) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) mx = ffn_word_max(mx, wd[j]);
+          } else if (na <= r0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) mxB = ffn_word_max(mxB, wd[j]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              mx = ffn_word_max(mx, r0 + j < na ? wd[j] : FG_NONE);
+              mxB = ffn_word_max(mxB, r0 + j < na ? FG_NONE : wd[j]);
             }
           }
         }
+      } else {
+        float lo[2], hi[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          lo[e] = __uint_as_float((e ? mxB : mx) << 16);
+          hi[e] = __uint_as_float((e ? mxB : mx) & 0xffff0000u);
+        }
+#pragma unroll 1
+        for (int row = 0; row < ntot; ++row) {
+          const unsigned wd = *reinterpret_cast<const unsigned*>(pcol + row * OP);
+          const float vl = __uint_as_float(wd << 16), vh = __uint_as_float(wd & 0xffff0000u);
+          if (row < na) { lo[0] = fmaxf(lo[0], vl); hi[0] = fmaxf(hi[0], vh); }
+          else { lo[1] = fmaxf(lo[1], vl); hi[1] = fmaxf(hi[1], vh); }
+        }
+        mx = (__float_as_uint(lo[0]) >> 16) | (__float_as_uint(hi[0]) & 0xffff0000u);
+        mxB = (__float_as_uint(lo[1]) >> 16) | (__float_as_uint(hi[1]) & 0xffff0000u);
       }
     }
     // rows on their way out, as whole 256-byte rows: tile row j is row a0 + j of A or row j - na of B. Without the
@@ -335,18 +422,24 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
         for (int b = 0; b * RPI < jr; ++b) rows_out(b);
       }
     }
-    if (nb > 0) {   // A ended; B's sums become the running ones, unless B ended here too
-      finish_pair(pA, den, p0, p1, mx0, mx1);
-      if (nb == cur.nvB) {
-        finish_pair(pB, denB, q0, q1, nx0, nx1);
-        m = -INFINITY; den = 0.0f; p0 = 0.0f; p1 = 0.0f; mx0 = -INFINITY; mx1 = -INFINITY;
-      } else {
-        m = mB; den = denB; p0 = q0; p1 = q1; mx0 = nx0; mx1 = nx1;
+    if (cur.a0 + na == cur.nvA) {   // A ended, and B too where it has no more rows: p / sum of weights in place of r
+      const bool endB = nb > 0 && nb == cur.nvB;
+      if (slotA || endB) {
+        const float inv = 1.0f / den;
+        float* zo = z + (size_t)(slotA ? pA : pB) * D + (kg & 1) * (D / 2) + (lb & 15);
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b) {
+          const float p_lo = psum[b], p_hi = psum[b + D / 32];   // (values: a choice of array elements would go through memory)
+          zo[16 * b] = ((kg & 1) ? p_hi : p_lo) * inv;
+        }
       }
-    } else if (cur.a0 + na == cur.nvA) {
-      finish_pair(pA, den, p0, p1, mx0, mx1);
-      m = -INFINITY; den = 0.0f; p0 = 0.0f; p1 = 0.0f; mx0 = -INFINITY; mx1 = -INFINITY;
+      if (MR && pool) {
+        pool[(size_t)pA * (D / 2) + lane] = mx;
+        if (endB) pool[(size_t)pB * (D / 2) + lane] = mxB;
+      }
+      mx = endB ? FG_NONE : mxB;
     }
+    if (nxt.some) park_r(nxt);
     cur = nxt;
   }
 }

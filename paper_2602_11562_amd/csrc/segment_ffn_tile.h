@@ -94,10 +94,13 @@ __device__ __forceinline__ const unsigned char* ffn_opaque(const unsigned char* 
   return (const unsigned char*)(__attribute__((address_space(3))) const unsigned char*)(size_t)a;
 }
 
+typedef __attribute__((address_space(3))) s16x4* ffn_lds4_t;
+__device__ __forceinline__ ffn_lds4_t ffn_lds4(const unsigned char* p) {
+  return (ffn_lds4_t)(size_t)(unsigned)(size_t)(__attribute__((address_space(3))) const unsigned char*)p;
+}
 __device__ __forceinline__ bf16x8 ffn_lds_tr(const unsigned char* p) {   // see lds_read_tr in sta_mfma.hip
-  typedef __attribute__((address_space(3))) s16x4* lds4;
-  const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(size_t)(unsigned)(size_t)(__attribute__((address_space(3))) const unsigned char*)p);
-  const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(size_t)(unsigned)(size_t)(__attribute__((address_space(3))) const unsigned char*)(p + 2048));
+  const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ffn_lds4(p));
+  const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ffn_lds4(p + 2048));
   return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 

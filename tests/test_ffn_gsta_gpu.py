@@ -325,3 +325,51 @@ def test_ffn_gsta_seeded_random_shapes_many_pairs():
             assert np.array_equal(to_host_f64(out[2]), pool_ref), case
             if r > 0:
                 assert np.array_equal(to_host_f64(out[3]), recent_ref), case
+
+
+def test_ffn_gsta_rows_that_are_not_finite_stay_in_their_pair():
+    """Tiles hold rows of two pairs (S = 20, 2500 pairs): a pair with an infinite or NaN row of H' gets a z of NaN and the
+    maximum of its other rows, every other pair keeps its bits."""
+    import torch
+    U, C, S = 5, 500, 20
+    cs = _case("bf16", U, C, S * 10, 10, 128, 128, 1, [200, 200, 150, 190, 200], seed=41)
+    dev = {k: to_device(cs[k]) for k in ("Hs", "lens", "W1s", "b1", "W2s", "b2", "g", "b", "t0s", "wqs", "wks", "wvs")}
+    call = lambda seg: laser.laser_ffn_gsta_forward(seg, dev["t0s"], dev["wqs"], dev["wks"], dev["wvs"], dev["lens"], dev["W1s"],
+                                                    dev["b1"], dev["W2s"], dev["b2"], dev["g"], dev["b"], S * 10, 10, 1e-5, r=2)
+    s0, z0, pool0, _ = call(dev["Hs"])
+    bad = dev["Hs"].clone()
+    hit = [(0, 0, 0, float("inf")), (0, 499, 19, float("nan")), (1, 7, 3, float("-inf")), (2, 100, 14, float("inf")), (4, 499, 9, float("nan"))]
+    for u, c, i, x in hit:
+        bad[u, c, i, 5] = x
+    s1, z1, pool1, _ = call(bad)
+    torch.cuda.synchronize()
+    keep = torch.ones(U, C, dtype=torch.bool)
+    nv = [20, 20, 15, 19, 20]
+    for u, c, i, _ in hit:
+        keep[u, c] = False
+        assert torch.isnan(z1[u, c]).all()
+        rows = to_host_f64(s1[u, c])[:nv[u]]
+        assert np.isnan(rows[i]).all()
+        assert np.array_equal(to_host_f64(pool1[u, c]), np.fmax.reduce(rows, axis=0))
+    keep = keep.cuda()
+    assert torch.equal(z1[keep].view(torch.int32), z0[keep].view(torch.int32))
+    assert torch.equal(pool1[keep].view(torch.int16), pool0[keep].view(torch.int16))
+
+
+def test_ffn_gsta_rows_of_the_largest_values():
+    """LayerNorm weights that take rows past 2^121: maxima of the stored rows, z as from the two calls in a row."""
+    import torch
+    U, C, S = 3, 800, 20
+    cs = _case("bf16", U, C, S * 10, 10, 128, 64, 1, [200, 150, 200], seed=43)
+    dev = {k: to_device(cs[k]) for k in ("Hs", "lens", "W1s", "b1", "W2s", "b2", "g", "b", "t0s", "wqs", "wks", "wvs")}
+    g, t0 = dev["g"] * 2.0 ** 122, dev["t0s"] * 1e-3
+    s, z, pool, _ = laser.laser_ffn_gsta_forward(dev["Hs"], t0, dev["wqs"], dev["wks"], dev["wvs"], dev["lens"], dev["W1s"],
+                                                 dev["b1"], dev["W2s"], dev["b2"], g, dev["b"], S * 10, 10, 1e-5, r=2)
+    z2 = laser.laser_gsta_forward(s, t0, dev["wqs"], dev["wks"], dev["wvs"], dev["lens"], S * 10, 10)
+    torch.cuda.synchronize()
+    sh = to_host_f64(s)
+    assert np.isfinite(sh).all() and np.abs(sh).max() > 2.0 ** 122
+    for u, nv in enumerate((20, 15, 20)):
+        assert np.array_equal(to_host_f64(pool)[u], sh[u, :, :nv].max(axis=1))
+    # one row carries all the weight; its score decides which, and ties of 24 bits do not occur
+    assert vec_rel_err(to_host_f64(z), to_host_f64(z2)) <= 1e-4
