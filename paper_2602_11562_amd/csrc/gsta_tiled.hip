@@ -311,16 +311,18 @@ laser_status gsta_tile_launch(const GstaArgs& a) {
 
 bool gsta_tile_supports(const GstaArgs& a) { return a.d == 64 || a.d == 128; }
 
-// Whether a one-layer bf16 batch is small enough for this kernel to beat the forms written for full machines (us, this
-// kernel / the other). Against the one-kernel form, d = 128, S = 32: one round of sixteen pairs, 4096 pairs 13.2 / 16.3, 6000 pairs
-// 19.9 / 16.9, 8192 23.4 / 19.1. Against the split form (longer blocks): d = 128, S = 100 2048 pairs 14.3 / 26.7, 8192 41.4 / 49.6,
-// 16384 97 / 101; d = 64, S = 100 16384 pairs 39 / 48, 24576 72 / 71. The lines for short blocks and for d = 64 were drawn before
-// this kernel's steps became shorter, and it is the faster one past them too: d = 128, S = 8 6000 pairs 11.7 / 12.4, 16384 20.3 / 24.6;
-// d = 64, S = 16 8192 pairs 7.6 / 11.6, 32768 18.5 / 27.7, S = 32 16384 pairs 16.8 / 23.5, S = 64 8192 pairs 15.5 / 18.7.
+// Whether a one-layer bf16 batch runs on this kernel and not on the forms written for full machines (us, this kernel / the other,
+// lengths full). At d = 64 it does: S = 2 65536 pairs 0.54 of the time, S = 16 8192 pairs 7.7 / 11.0, 32768 0.67, S = 32 65536
+// 0.66, S = 64 8192 0.86, 65536 0.76; against the split form (longer blocks) S = 100 32768 pairs 1.00, 8192 0.73, S = 160 0.58 .. 0.91. At
+// d = 128 it does for blocks of up to three rows a lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Against the split form S = 100
+// 2048 pairs 14.3 / 26.7, S = 48 8192 0.74, S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views. Between,
+// the one-kernel form is the better one once it fills a round of 256 workgroups of 32 pairs with more than half: S = 32 4096 pairs
+// 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24.
 bool gsta_tile_preferred(const GstaArgs& a) {
   const int P = gsta_pairs(a);
-  if (gsta_one_supports(a)) return a.d == 128 ? P <= 4096 : P <= (a.S <= 32 ? 8192 : 4096);
-  return a.d == 128 ? P <= 8192 : P <= 16384;
+  if (a.d == 64 || a.S <= 12) return true;
+  if (!gsta_one_supports(a)) return P <= 8192;
+  return P <= 4096 || (P > 8192 && P <= 11264);
 }
 
 }  // namespace laser

@@ -161,3 +161,29 @@ def test_generic_by_name_in_fp32(U, C, S, d, M):
     ref = oracle.gsta_forward(seg[:, :3], t0[:, :3], *W, oracle.segment_counts(lens, S, 1))
     for z in (auto, generic):
         assert vec_rel_err(to_host_f64(z)[:, :3], ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("d,P,S", [(64, 8193, 1), (64, 9000, 33), (64, 8200, 64), (64, 16500, 5), (128, 4097, 12), (128, 16390, 3), (128, 8193, 32)])
+def test_one_layer_of_many_pairs(d, P, S):
+    """Sizes at which the form is chosen for batches that fill the machine: against fp64 of the same inputs (fp32 sums, the factors
+    of H' in three bf16 parts: 1e-5 of a vector's largest component) and the other forms (two parts there: 1e-4)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    w, C = 4, 1
+    seg = torch.randn(P, C, S, d, device="cuda", generator=gen).to(torch.bfloat16)
+    t0 = (torch.randn(P, C, d, device="cuda", generator=gen) * 0.3).to(torch.bfloat16)
+    ws = [(torch.randn(1, d, d, device="cuda", generator=gen) * d ** -0.5).to(torch.bfloat16) for _ in range(3)]
+    lens = torch.randint(0, 4 * S + 1, (P,), device="cuda", generator=gen, dtype=torch.int32)
+    z = laser.laser_gsta_forward(seg, t0, *ws, lens, 4 * S, w)
+    one = laser.laser_gsta_forward(seg, t0, *ws, lens, 4 * S, w, variant=laser.binding.GSTA_ONE)
+    torch.cuda.synchronize()
+    H, t = seg[:, 0].cpu().double(), t0[:, 0].cpu().double()
+    wq, wk, wv = (x[0].cpu().double() for x in ws)
+    r = (t @ wq) @ wk.T / math.sqrt(d)
+    nv = (lens.cpu() + w - 1) // w
+    scores = (H * r[:, None]).sum(-1).masked_fill(torch.arange(S)[None] >= nv[:, None], float("-inf"))
+    a = torch.softmax(scores, 1).nan_to_num(0.0)
+    ref = t + (a[:, :, None] * H).sum(1) @ wv
+    scale = ref.abs().amax(-1, keepdim=True)
+    assert ((z[:, 0].cpu().double() - ref).abs() / scale).max() <= 1e-5
+    assert ((one[:, 0].cpu().double() - ref).abs() / scale).max() <= 1e-4
