@@ -1001,16 +1001,17 @@ static int pick_spw(const StaArgs& a, int nw, int ctiles) {
 // its workgroups are dealt out by the lengths and counts, or 0: up to 64 users, one per lane, and 16 segments. Where nothing is
 // full the queries and the first tile come two trips to memory later (4 us with the requests made in vain), so it has to
 // save a good part of a round: own counts (29 users x up to 201 candidates, 31 segments of 100 items: 26.2 -> 19.7 us), or more
-// segments than one round of eight holds (40 x 300, 25 segments of 200 items: 130 -> 64 us), and steps enough. Short of these
-// lines the two are about even with lengths uniform in [L / 5, L] (dense, own division / dealt out: 16 x 200, 25 segments of 200
-// 21.2 / 21.8 us, of 128 15.5 / 13.1; 64 x 200, 63 segments of 32 41.4 / 40.8); the lines were drawn when the zeros of the empty
-// segments were left to their user's workgroups (20.3 / 26 and 40 / 45), and could be wider since.
+// segments than one round of eight holds (40 x 300, 25 segments of 200 items: 130 -> 64 us), and steps enough. With the
+// same count for all from four segments on: 80 calls with lengths uniform in [L / 5, L], four to eight segments and three tiles or
+// more 0.44 .. 1.06, 0.89 on average, of the time of the launch's own division (28 x 301, 30 segments of 212 items 62.1 / 41.1 us, 37 x 436, 10 of 117
+// 38.3 / 20.6, 45 x 85, 23 of 238 37.1 / 27.4), with full ones 0.85 .. 1.06. At three it is 0.85 .. 1.15 (12 x 453, 21 of 243 24.0 / 27.8),
+// and full histories lose a little (16 x 128, 40 of 256 38.3 / 39.2).
 static int deal_spw(const StaArgs& a, int ctiles) {
   if (a.lens == nullptr || a.U > 64) return 0;
   int spw = 1;
   while (spw <= 16 && (long long)a.U * ctiles * ((a.S + spw - 1) / spw) > 256) ++spw;
   const int tiles = (a.w + DT_TI - 1) / DT_TI;
-  return spw <= 16 && tiles >= 3 && spw * tiles >= 12 && spw >= (a.cand_off != nullptr ? 3 : 9) ? spw : 0;
+  return spw <= 16 && tiles >= 3 && spw * tiles >= 12 && spw >= (a.cand_off != nullptr ? 3 : 4) ? spw : 0;
 }
 
 bool sta_mfma_supports(const StaArgs& a) {

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 laser = pytest.importorskip("paper_2602_11562_amd")
 
 # users, candidates, items, w, lengths, own counts per user, whether workgroups are dealt out: with own counts from three
-# segments of a workgroup on, dense calls past eight, up to 64 users, both workgroup sizes. Among them the last tile of a segment of
+# segments of a workgroup on, dense calls from four, up to 64 users, both workgroup sizes. Among them the last tile of a segment of
 # one item, users without candidates or items, full and empty histories, and histories that divided anew have runs no shorter.
 # Not dealt out: one round of the launch's own division, 65 users, segments of a tile or less
 CASES = [(29, 201, 3001, 100, "mixed", True, True), (40, 300, 2500, 100, "mixed", False, True),
@@ -22,6 +22,7 @@ CASES = [(29, 201, 3001, 100, "mixed", True, True), (40, 300, 2500, 100, "mixed"
          (64, 300, 640, 80, "empty", True, True), (33, 257, 1500, 129, "full", True, True),
          (9, 480, 6000, 80, "one_short", True, True), (64, 128, 2800, 70, "one_short", False, True),
          (12, 128, 6400, 100, "last_only", True, True),
+         (37, 436, 1069, 117, "mixed", False, True), (45, 85, 5390, 238, "full", False, True), (12, 453, 4905, 243, "mixed", False, False),
          (7, 129, 3001, 100, "mixed", False, False), (65, 70, 900, 40, "mixed", True, False), (5, 257, 1000, 64, "mixed", True, False)]
 
 
