@@ -66,3 +66,29 @@ def test_values_that_are_not_finite_stay_in_their_segment(w, what):
     assert torch.equal(a[~bad], b[~bad])
     got = b[bad]
     assert (got.isnan() if math.isnan(what) else got == math.inf).all()
+
+
+@pytest.mark.parametrize("U,C,L,w", [(1, 70, 300, 9), (5, 130, 400, 3), (16, 90, 203, 40), (17, 90, 203, 40), (19, 200, 120, 11)])
+def test_counts_of_their_own(U, C, L, w):
+    """Up to 16 users the workgroups run in the order in which they are dealt, past them in ranges per XCD: either way every
+    user's rows are those of a call of its own, bit for bit, users without candidates among them."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(U)
+    counts = [C] + [int(x) for x in torch.randint(0, C + 1, (U - 1,), generator=torch.Generator().manual_seed(U))]
+    if U > 2:
+        counts[1] = 0
+    off = torch.tensor([0] + counts, device="cuda").cumsum(0).to(torch.int32)
+    P = sum(counts)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
+    q, k, v = rnd(P, 64), rnd(U, L, 64), rnd(U, L, 128)
+    n = torch.randint(0, L + 1, (U,), device="cuda", generator=gen, dtype=torch.int32)
+    n[0] = L
+    print(f"U {U} C {C} L {L} w {w}", flush=True)
+    out, cnt, _ = laser.laser_forward_ragged(q, k, v, None, None, None, None, n, off, C, w, 8.0, stage="sta")
+    for u in range(U):
+        lo, c = int(off[u]), counts[u]
+        if c < 9:      # (a dense call of so few runs another kernel)
+            continue
+        ref, ref_cnt = laser.laser_sta_forward(q[lo:lo + c].view(1, c, 64), k[u:u + 1], v[u:u + 1], n[u:u + 1], w, 8.0)
+        assert torch.equal(out[lo:lo + c].view(torch.int16), ref[0].view(torch.int16)), u
+        assert torch.equal(cnt[u], ref_cnt[0])
