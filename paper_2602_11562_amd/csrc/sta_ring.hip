@@ -17,9 +17,9 @@
 // block (reads, scores, gates, sums: 0.6 us) where they are long; several workgroups on a compute unit fill each other's gaps. Against
 // staging through registers, us: 64 users x 256 candidates, 100 segments of 10 items, two heads of 16 / 64, lengths uniform 99.7 -> 81
 // (450 MB: 5.6 TB/s); 64 x 64, 16 of 128, 64 / 64 11.3 -> 8.5; 1 x 100, 100 of 10, 32 / 128 4.8 -> 3.5; 505 x 16, 190 of 2, 64 / 64
-// 171 -> 60; 32 x 256, 32 of 128, 64 / 64 (there eight waves and a second tile) 20.8 -> 18.4. 200 drawn calls (1 to 512 users, 9 to 512
-// candidates, w = 1 to 1000, every width, up to four heads, full to log-uniform lengths, equal and own counts) 0.71 on average,
-// three more than 5 % above (14 x 46, L = 4057, w = 57, 128 / 128, four heads, log-uniform: 10.8 -> 12.9).
+// 171 -> 60; 32 x 256, 32 of 128, 64 / 64 (there eight waves and a second tile) 20.8 -> 18.4. 700 drawn calls (1 to 256 users, 9 to 512
+// candidates, w = 1 to 700, every width, up to four heads, full to log-uniform lengths, equal and own counts), direct-to-LDS ones of both
+// sides among them: 0.72 on average, six more than 3 % above, the worst 6 x 211, 48 segments of 64 items, 64 / 128, four heads 11.3 -> 12.9.
 #include <type_traits>
 
 #include "laser_internal.h"
@@ -29,14 +29,23 @@ namespace laser {
 
 constexpr int NB = 2;   // slots of the ring: with three or four, fewer workgroups fit a compute unit, and every call tried was slower
 
-template <int DQ, int D, int NW>
+// Waves that the registers of a form (as the compiler counts them) let a SIMD hold. The launch bounds ask for less: asked for these, forms
+// of one computing wave took accumulation registers beside and held fewer.
+template <int DQ, int D, int HEADS, bool SHORT, int NW>
+constexpr int ring_simd_waves() {
+  if (D == 64) return DQ == 128 ? 3 : (HEADS == 1 && (DQ == 32 || SHORT) ? 5 : 4);
+  if (DQ == 128) return SHORT && HEADS < 4 && NW == 2 ? 3 : 2;
+  return DQ == 64 && HEADS == 4 && !SHORT && NW < 3 ? 2 : 3;
+}
+
+template <int DQ, int D, int NW, int HEADS, bool SHORT>
 struct RingShape {
   static constexpr int KROW = DQ * 2, VROW = D * 2, KB = 32 * KROW, CB = KB + 32 * VROW;   // bytes of a row, a chunk's keys, a chunk
   static constexpr int ZERO = NB * CB, PATCH = ZERO + 256, OP = OPitch<D>::v;
   static constexpr int LDS = PATCH + NW * CW * OP;
   static constexpr int NT = 64 * (NW + 1);
-  static constexpr int BY_LDS = 160 * 1024 / LDS, BY_WAVES = 4 * (DQ == 128 ? 2 : (D == 128 ? 3 : 4)) / (NW + 1);
-  static constexpr int SIMD_WAVES = DQ == 128 || BY_LDS * (NW + 1) < 12 ? 2 : 3;   // at least, of a SIMD: what the LDS allows for
+  static constexpr int BY_LDS = 160 * 1024 / LDS, BY_WAVES = 4 * ring_simd_waves<DQ, D, HEADS, SHORT, NW>() / (NW + 1);
+  static constexpr int BOUND = DQ == 128 || BY_LDS * (NW + 1) < 12 ? 2 : 3;   // waves of a SIMD, at least: what the LDS allows for
   static constexpr int PER_CU = BY_WAVES < BY_LDS ? BY_WAVES : BY_LDS;   // workgroups of a compute unit
 };
 
@@ -46,12 +55,12 @@ template <int CH> __device__ __forceinline__ int ring_kswz(int r) { return ((r *
 template <int CH> __device__ __forceinline__ int ring_vswz(int r) { return ((r * CH) >> 4) & (CH / 4 - 1); }
 
 template <int DQ, int D, int NW, int HEADS, bool SHORT>
-__global__ __launch_bounds__(64 * (NW + 1), (RingShape<DQ, D, NW>::SIMD_WAVES)) void sta_ring_kernel(
+__global__ __launch_bounds__(64 * (NW + 1), (RingShape<DQ, D, NW, HEADS, SHORT>::BOUND)) void sta_ring_kernel(
     const unsigned short* __restrict__ q, const unsigned short* __restrict__ k, const unsigned short* __restrict__ v,
     const int32_t* __restrict__ lens, const int32_t* __restrict__ cand_off, int P, int C_all, int L, int w, int S, int spw,
     int chunk_segs, MulDiv by_runs, int sruns, MulDiv by_tiles, int ctiles, int xcd_ranges, float neg_scale_log2e,
     unsigned short* __restrict__ seg_out, int32_t* __restrict__ seg_cnt) {
-  using Sh = RingShape<DQ, D, NW>;
+  using Sh = RingShape<DQ, D, NW, HEADS, SHORT>;
   constexpr int KROW = Sh::KROW, VROW = Sh::VROW, KCH = DQ / 8, VCH = D / 8;
   constexpr int KSTEPS = DQ / 16, DB = D / 32, KH = KSTEPS / HEADS, DBH = DB / HEADS;
   static_assert(KSTEPS % HEADS == 0 && DB % HEADS == 0, "heads must own whole k-steps and whole column blocks");
@@ -336,26 +345,46 @@ __global__ __launch_bounds__(64 * (NW + 1), (RingShape<DQ, D, NW>::SIMD_WAVES)) 
 }
 
 // ------------------------------------------------------------------------------------------ host side
-// Segments per workgroup: the smallest estimate of rounds of workgroups times the length of one, from what fits a compute unit
-// (LDS, registers). A workgroup costs its start (1), its blocks of 32 rows and its stored rows (half a block each; 1.7 a segment of up
-// to 32 items, and 0.3 a chunk), 0.6 of it when it has the compute unit to itself. Fitted to 61 calls (1 to 512 users, 9 to 512
-// candidates, w = 1 to 1000, every width): 1.8 % above the best of up to 40 settings on average. Chunks of more than three segments
-// bring nothing (61 calls: three 1.8 %, four 2.6 %, six 2.1 % above the best).
-static int ring_segs(const StaArgs& a, int w, int fit, int ctiles, int per_cu) {
-  const int forced = tuning_int("LASER_STA_SPW", 0);   // tuning builds only
-  if (forced >= 1 && forced <= 64) return forced;
-  int best = 1;
-  double least = 0.0;
-  for (int n : {1, 2, 3, 4, 6, 8, 12}) {
-    if (n > 1 && n > a.S) break;
-    const double work = fit > 0 ? 1.7 * n + 0.3 * ((n + fit - 1) / fit) : n * ((w + 31) / 32 + 0.5);
-    const double rounds = (double)a.U * ctiles * ((a.S + n - 1) / n) / (256.0 * per_cu);
-    const double cost = (rounds <= 1.0 ? 1.0 : rounds + 0.25) * (1.0 + work * (0.6 + 0.4 * (rounds < 1.0 ? rounds : 1.0)));
-    if (n == 1 || cost < least) {
-      best = n;
-      least = cost;
+// Computing waves (32 candidates each) and segments per workgroup: the smallest estimate of rounds of workgroups times the length of one.
+// A workgroup costs its start (2), its blocks of 32 rows, which take as long as there are computing waves on a SIMD to issue them, per
+// segment its rows to store (0.7, and more in proportion to the waves) and per chunk 1. A launch of more than one round has a quarter of
+// one at its end, and takes one and a half at least; counts of their own leave even one round uneven. Three waves share an item among
+// half as many candidates again, so they are taken at 0.94 (between two and three the better one is up to a third faster, by how the
+// candidates fill 64 and 96 and by what fits a compute unit; four were the better ones nowhere by more than a few percent but at four
+// heads). Fitted to 1414 calls (1 to 256 users, 9 to 512 candidates, w = 1 to 700, every width, up to four heads, full to log-uniform
+// lengths, equal and own counts) at both and seven numbers of segments: 2.0 % above the best of the fourteen on average.
+// Chunks of more than three segments bring nothing (61 calls: three 1.8 %, four 2.6 %, six 2.1 % above the best).
+struct RingPlan {
+  int waves, segs;
+};
+static int ring_fit(int w) { return 32 / w < 3 ? 32 / w : 3; }   // segments of a chunk
+
+static RingPlan ring_plan(const StaArgs& a, int w, const int (&per_cu)[4]) {
+  const bool is_short = a.w <= 32, own = a.cand_off != nullptr;
+  RingPlan best{a.C <= CW ? 1 : 2, 1};
+  double least = -1.0;
+  const int nw_forced = tuning_int("LASER_STA_NW", 0), forced = tuning_int("LASER_STA_SPW", 0);   // tuning builds only
+  for (int nw = best.waves; nw <= (a.C <= 2 * CW ? best.waves : 3); ++nw) {
+    if (a.C > CW && (nw_forced == 2 || nw_forced == 3) && nw != nw_forced) continue;
+    // candidate tiles of a user (with counts of their own as the mean of them fills)
+    const double ctiles = own ? (double)a.P / a.U / (CW * nw) + 0.5 : (a.C + CW * nw - 1) / (CW * nw);
+    for (int n : {1, 2, 3, 4, 6, 8, 12}) {
+      if (n > 1 && n > a.S) break;
+      const double groups = a.U * ctiles * ((a.S + n - 1) / n), rounds = groups / (256.0 * per_cu[nw]);
+      // workgroups of a compute unit at a time; of four SIMDs
+      const double density = 0.25 * nw * (rounds >= 1.0 ? per_cu[nw] : (int)((groups + 255.0) / 256.0));
+      const int blocks = n * ((w + 31) / 32), chunks = is_short ? (n + ring_fit(w) - 1) / ring_fit(w) : blocks;
+      const double work = blocks * density + n * (0.7 + density * a.d / 128) + chunks;
+      const double late = rounds + 0.25;
+      const double turns = own ? (late > 1.0 ? late : 1.0) : (rounds <= 1.0 ? 1.0 : (late > 1.5 ? late : 1.5));
+      const double cost = turns * (2.0 + work) * (nw == 3 ? 0.94 : 1.0);
+      if (least < 0.0 || cost < least) {
+        best = RingPlan{nw, n};
+        least = cost;
+      }
     }
   }
+  if (forced >= 1 && forced <= 64) best.segs = forced;
   return best;
 }
 
@@ -365,37 +394,35 @@ static int ring_segs(const StaArgs& a, int w, int fit, int ctiles, int per_cu) {
 constexpr int RING_FEW_USERS = 16;
 
 template <int DQ, int D, int NW, int HEADS, bool SHORT>
-static void ring_launch(const StaArgs& a) {
-  using Sh = RingShape<DQ, D, NW>;
-  const int w = a.w < a.L ? a.w : a.L, ctiles = (a.C + CW * NW - 1) / (CW * NW);
-  const int fit = SHORT ? (32 / w < 3 ? 32 / w : 3) : 0;   // segments of a chunk
-  const int spw = ring_segs(a, w, fit, ctiles, Sh::PER_CU);
-  const int chunk_segs = SHORT ? (spw < fit ? spw : fit) : 1;
-  const int sruns = (a.S + spw - 1) / spw;
+static void ring_launch(const StaArgs& a, int w, int spw) {
+  using Sh = RingShape<DQ, D, NW, HEADS, SHORT>;
+  const int ctiles = (a.C + CW * NW - 1) / (CW * NW), sruns = (a.S + spw - 1) / spw;
+  const int chunk_segs = SHORT ? (spw < ring_fit(w) ? spw : ring_fit(w)) : 1;
   hipLaunchKernelGGL((sta_ring_kernel<DQ, D, NW, HEADS, SHORT>), dim3((unsigned)((long long)a.U * ctiles * sruns)), dim3(Sh::NT), 0,
                      a.stream, (const unsigned short*)a.q, (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens, a.cand_off,
                      a.P, a.C, a.L, w, a.S, spw, chunk_segs, mul_div(sruns), sruns, mul_div(ctiles), ctiles,
                      a.cand_off == nullptr || a.U > RING_FEW_USERS, -1.4426950408889634f / a.gamma, (unsigned short*)a.seg_out, a.seg_cnt);
 }
 
-// Two computing waves share a workgroup's items: four of them, with a barrier of five waves and half the workgroups, were up to a
-// tenth faster at 128 / 128 and up to a fifth slower elsewhere.
-template <int DQ, int D, int HEADS>
+template <int DQ, int D, int HEADS, bool SHORT>
 static void ring_form(const StaArgs& a) {
-  if (a.w <= 32) {
-    if (a.C <= CW) ring_launch<DQ, D, 1, HEADS, true>(a);
-    else ring_launch<DQ, D, 2, HEADS, true>(a);
-  } else {
-    if (a.C <= CW) ring_launch<DQ, D, 1, HEADS, false>(a);
-    else ring_launch<DQ, D, 2, HEADS, false>(a);
-  }
+  const int w = a.w < a.L ? a.w : a.L;
+  const RingPlan plan = ring_plan(a, w, {0, RingShape<DQ, D, 1, HEADS, SHORT>::PER_CU, RingShape<DQ, D, 2, HEADS, SHORT>::PER_CU,
+                                         RingShape<DQ, D, 3, HEADS, SHORT>::PER_CU});
+  if (plan.waves == 1) ring_launch<DQ, D, 1, HEADS, SHORT>(a, w, plan.segs);
+  else if (plan.waves == 2) ring_launch<DQ, D, 2, HEADS, SHORT>(a, w, plan.segs);
+  else ring_launch<DQ, D, 3, HEADS, SHORT>(a, w, plan.segs);
 }
 
 template <int DQ, int D>
 static void ring_heads(const StaArgs& a) {
-  if (a.heads == 1) ring_form<DQ, D, 1>(a);
-  else if (a.heads == 2) ring_form<DQ, D, 2>(a);
-  else if constexpr (DQ >= 64 && D == 128) ring_form<DQ, D, 4>(a);
+  auto form = [&](auto heads) {
+    if (a.w <= 32) ring_form<DQ, D, decltype(heads)::value, true>(a);
+    else ring_form<DQ, D, decltype(heads)::value, false>(a);
+  };
+  if (a.heads == 1) form(std::integral_constant<int, 1>{});
+  else if (a.heads == 2) form(std::integral_constant<int, 2>{});
+  else if constexpr (DQ >= 64 && D == 128) form(std::integral_constant<int, 4>{});
 }
 
 laser_status sta_ring_launch(const StaArgs& a) {

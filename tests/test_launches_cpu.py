@@ -2,12 +2,14 @@
 runtime (tests/launch_recorder.cpp), with made-up addresses that nothing reads."""
 import ctypes
 import math
+import re
 
 import pytest
 
 from paper_2602_11562_amd import binding
 from test_sta_backward_mfma_gpu import SETS
 from test_sta_dealt_gpu import CASES as DEALT
+from test_sta_ring_gpu import CASES as RING, THREE
 
 
 class Launch(ctypes.Structure):
@@ -73,6 +75,41 @@ def test_calls_with_workgroups_dealt_out(recorder, U, C, L, w, lens, own, dealt,
     waves = 4 if C <= 128 else 8
     assert f"19sta_mfma_dma_kernelILi{waves}ELb{int(not whole)}ELb{int(dealt)}EE" in first.kernel.decode()
     assert not dealt or first.grid == 256
+
+
+def sta_heads(U, C, L, dq, d, w, heads):
+    return lambda lib: lib.laser_sta_forward_heads(A, A, A, A, U, C, L, dq, d, w, math.sqrt(dq / heads), heads, BF16, A, A, None, binding.STA_AUTO)
+
+
+def ring(launch):
+    """(d_q, d, computing waves, heads, short segments) of a launch of the kernel with a wave of its own for the fetches."""
+    m = re.search(r"15sta_ring_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", launch.kernel.decode())
+    return m and tuple(int(x) for x in m.groups())
+
+
+@pytest.mark.parametrize("U,C,L,dq,d,w,heads", RING + THREE)
+def test_calls_with_a_wave_for_the_fetches(recorder, U, C, L, dq, d, w, heads):
+    launch, = launches(recorder, sta_heads(U, C, L, dq, d, w, heads))
+    got = ring(launch)
+    assert got and got[:2] == (dq, d) and got[3:] == (heads, int(w <= 32))
+    assert launch.block == 64 * (got[2] + 1) and (got[2] == 1) == (C <= 32) and (got[2] < 3 or C > 64)
+    assert got[2] == 3 or (U, C, L, dq, d, w, heads) not in THREE
+
+
+# (users, candidates, items, d_q, d, w, heads): computing waves, segments per workgroup. Long segments with lengths that differ, where a
+# second one per workgroup cost up to half the time; widths of which a compute unit holds more, or fewer, workgroups than its LDS
+# tells; candidates that fill 96 places and not 64, and the other way round; exactly one round and a little more than one
+PLANS = [(23, 487, 258, 128, 128, 81, 4, 2, 1), (32, 254, 517, 128, 128, 100, 4, 3, 1), (40, 78, 1631, 128, 64, 100, 2, 3, 1),
+         (9, 88, 5262, 64, 128, 17, 4, 3, 4), (34, 370, 1831, 64, 128, 55, 4, 3, 2), (64, 64, 2048, 64, 64, 128, 1, 2, 1),
+         (128, 64, 1280, 64, 128, 128, 1, 2, 2)]
+
+
+@pytest.mark.parametrize("U,C,L,dq,d,w,heads,waves,segs", PLANS)
+def test_waves_and_segments_of_a_workgroup(recorder, U, C, L, dq, d, w, heads, waves, segs):
+    launch, = launches(recorder, sta_heads(U, C, L, dq, d, w, heads))
+    print(launch.kernel, launch.grid)
+    assert ring(launch)[2] == waves
+    assert launch.grid == U * -(-C // (32 * waves)) * -(-(-(-L // w)) // segs)
 
 
 @pytest.mark.parametrize("name", list(SETS))

@@ -1,5 +1,5 @@
 """The matrix-core STA kernel with a wave of its own for the fetches, where its form or its edges change: segments around half a
-block, a block and several (1 .. 3 of them per chunk), candidates around 32 and 64, several heads, short last segments, lengths
+block, a block and several (1 .. 3 of them per chunk), candidates around 32, 64 and 96, several heads, short last segments, lengths
 that end inside a block; a history that is not finite past the valid length and in the next segment, and nothing written beside
 the outputs. Against the generic kernel (fp32 arithmetic; the gates are rounded to bf16 here and not there: 2e-2 as everywhere)."""
 import math
@@ -17,9 +17,13 @@ CASES = [(3, 9, 97, 32, 64, 1, 1), (4, 33, 203, 64, 64, 10, 1), (3, 32, 120, 64,
          (3, 64, 170, 128, 64, 17, 1), (4, 40, 310, 64, 128, 31, 4), (4, 31, 321, 128, 128, 32, 1), (2, 97, 331, 64, 64, 33, 2),
          (3, 50, 400, 128, 128, 63, 4), (2, 129, 700, 32, 64, 65, 1), (70, 70, 64, 64, 64, 7, 1), (1, 20, 25, 32, 128, 400, 1),
          (300, 200, 30, 32, 64, 3, 1), (6, 300, 900, 128, 128, 45, 1)]
+# ... and with three computing waves: candidates around 96 and its multiples
+THREE = [(60, 95, 300, 32, 64, 33, 1), (60, 96, 200, 64, 64, 15, 1), (40, 193, 203, 128, 64, 16, 1), (30, 193, 150, 64, 128, 31, 4),
+         (30, 280, 300, 64, 128, 70, 4), (60, 90, 260, 128, 128, 64, 2), (3, 96, 400, 32, 128, 9, 2), (50, 95, 210, 128, 64, 63, 2),
+         (70, 190, 96, 64, 128, 40, 1), (40, 258, 64, 128, 128, 33, 1), (7, 160, 260, 128, 128, 10, 4)]
 
 
-@pytest.mark.parametrize("U,C,L,dq,d,w,heads", CASES)
+@pytest.mark.parametrize("U,C,L,dq,d,w,heads", CASES + THREE)
 def test_edges(U, C, L, dq, d, w, heads):
     import torch
     S = -(-L // w)
