@@ -960,12 +960,14 @@ static int pick_nw(const StaArgs& a) {
 // segments, less than 2400 tiles: 0.83 with up to 30 segments (0.58 to 1.1; 43 x 229, L = w = 395: 17.0 -> 10.9 us), 0.94 with more
 // (0.85 to 1.13; 3 x 198, L = 6210, w = 114: 11.0 -> 12.4). From 2400 tiles on, 0.94 (0.49 to 1.3; 112 x 197, L = 3045, w = 81:
 // 94 -> 115), but 0.82 where a user's last workgroup is nearly empty (up to 0.58 of the candidates' places taken; 183 x 263,
-// w = 202: 57 -> 38). With own counts per user, whose workgroups are dealt out, the line was not drawn anew.
+// w = 202: 57 -> 38). Segments of more than half a tile are the direct form's too once eighteen of its workgroups of one segment come to a
+// compute unit and the candidates take 0.7 of their places: 54 calls in times of the ring 0.90 (0.69 to 1.18; 76 x 490, 36 of 28 items
+// 96.8 -> 66.4 us), with ten to eighteen 1.17 (0.83 to 1.95; 246 x 369, 9 of 18 items 35.5 / 69.4). With own counts per user, whose workgroups are dealt out, the line was not drawn anew.
 static bool is_direct(const StaArgs& a, int nw) {
   if (a.heads != 1 || a.softmax || a.d_q != 128 || a.d != 128 || a.C <= 64) return false;
   if (a.cand_off != nullptr) return true;
   const long long tiles = (a.C + CW * nw - 1) / (CW * nw), steps = (a.w + DT_TI - 1) / DT_TI;
-  if (a.w < 48) return false;
+  if (a.w < 48) return nw == 8 && a.w > 16 && a.U * tiles * a.S > 18 * 256 && a.C * 100LL > tiles * CW * nw * 70;
   return a.U * tiles * a.S * steps >= 2400 ? a.C * 100LL > tiles * CW * nw * 58 : a.S > 30;
 }
 

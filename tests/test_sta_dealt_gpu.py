@@ -93,6 +93,23 @@ def test_every_row_is_written(U, C, L, w, lens, own, dealt, whole):
         assert (edge == -7).all() if x.dtype == torch.int32 else edge.isnan().all()
 
 
+def test_many_segments_shorter_than_a_tile():
+    """Dense calls of enough segments of 17 items and more: the rows that each user's call of its own gives (another kernel with the
+    same arithmetic), bit for bit; test_launches_cpu.py shows which kernels these are."""
+    import torch
+    U, C, L, w, d = 64, 180, 1241, 17, 128
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(*s, device="cuda", generator=gen).bfloat16() for s in ((U, C, d), (U, L, d), (U, L, d)))
+    n = torch.randint(0, L + 1, (U,), device="cuda", generator=gen, dtype=torch.int32)
+    n[0], n[1], n[2] = L, 0, L - 1
+    for u in range(U):
+        v[u, int(n[u]):] = math.nan
+    out, cnt = laser.laser_sta_forward(q, k, v, n, w, math.sqrt(d))
+    for u in (0, 1, 2, 31, 63):
+        ref, ref_cnt = laser.laser_sta_forward(*(x[u:u + 1] for x in (q, k, v, n)), w, math.sqrt(d))
+        assert torch.equal(out[u].view(torch.int16), ref[0].view(torch.int16)) and torch.equal(cnt[u], ref_cnt[0]), u
+
+
 @pytest.mark.parametrize("kind", ["above_the_count", "past_the_pairs", "decreasing", "huge"])
 def test_offsets_that_break_the_rules_stay_inside_the_buffers(kind):
     """The kernel clamps every user's range for itself, also where it shares the empty rows of all users."""
