@@ -26,8 +26,9 @@
 
 namespace laser {
 
-// PW: pairs per workgroup; R: row loads per lane and round; RES: one round holds every row (H' stays in registers)
-template <typename T, int D, int PW, int R, bool RES>
+// PW: pairs per workgroup; R: row loads per lane and round; RES: one round holds every row (H' stays in registers); POOL: the maxima of
+// the pooled view from the pass over the rows (one layer, bf16, a wave's pairs its own)
+template <typename T, int D, int PW, int R, bool RES, bool POOL>
 __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) void gsta_tiled_kernel(const T* __restrict__ seg, const T* __restrict__ t0,
                                                           const T* __restrict__ wq, const T* __restrict__ wk,
                                                           const T* __restrict__ wv, const int32_t* __restrict__ lens,
@@ -86,6 +87,15 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
     // (without a valid segment row 0 is requested and not used: a branch here makes the compiler wait for the loads)
     if (RES || i == 0) load_h(h[RES ? i : 0], i, 0);              // (streamed: the first rows of the first pass)
   }
+  // the pooled maxima of pair i of a wave with pairs of its own, from the lane groups' (stored values: exact)
+  auto store_pool = [&](int i, float (&top)[8]) __attribute__((always_inline)) {
+    const int pr = pbase + wave * PPW + i;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) top[e] = over_groups<LPR, true>(top[e]);
+    if (grp == 0 && pr < P)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) store_from_f32(pool, (size_t)pr * D + gl * 8 + e, nv[i] > 0 ? top[e] : 0.0f);
+  };
   // (a share of a matrix takes 32 registers in fp32 at d = 128: beside eight rows a lane there is room for two)
   constexpr bool LATE = sizeof(T) == 4 && D == 128 && R == 8;
   // the next layer's share of W_q crosses the patch in the shadow of the barrier behind the pass, not when it is wanted (unless that
@@ -117,7 +127,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {                               // one pass over the rows of H'
       const int pj = PW < NW ? wave / WPP : wave * PPW + i;
-      float r8[8], acc[8], m = -INFINITY, den = 0.0f;
+      float r8[8], acc[8], top[8], m = -INFINITY, den = 0.0f;
       {
         const f32x4 a = *reinterpret_cast<const f32x4*>(rr + pj * RP + gl * 8);
         const f32x4 b = *reinterpret_cast<const f32x4*>(rr + pj * RP + gl * 8 + 4);
@@ -125,6 +135,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
         for (int e = 0; e < 8; ++e) {
           r8[e] = e < 4 ? a[e & 3] : b[e & 3];
           acc[e] = 0.0f;
+          top[e] = -INFINITY;
         }
       }
       Row8<T> (&hi)[R] = h[RES ? i : 0];
@@ -158,7 +169,10 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
           const float p = ((k0 + k) * WPP + wp) * RPW + grp < nv[i] ? X::ex(s[k] - ref) : 0.0f;
           den += p;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, hi[k].get(e), acc[e]);
+          for (int e = 0; e < 8; ++e) {
+            acc[e] = fmaf(p, hi[k].get(e), acc[e]);
+            if (POOL) top[e] = fmaxf(top[e], hi[k].get(e));       // (rows past the last valid one are copies of it)
+          }
         }
         if (RES) break;
         if (more)
@@ -177,6 +191,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
 #pragma unroll
       for (int e = 0; e < LPR / 8; ++e) X::put(bq, WPP > 1 ? wp * PW + pj : pj, y0 + e, acc[e] * inv);
       if (WPP > 1 && lane == 0) pml[wp * PW + pj] = nv[i] > 0 ? f32x2{mw, den} : f32x2{0.0f, 1.0f};
+      if constexpr (POOL) store_pool(i, top);
     }
     if (!RES && more_layers) load_h(h[0], 0, 0);                  // the first rows of the next layer's pass
     const typename X::Operand ov = X::transposed(cv, patch, lane);
@@ -202,8 +217,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   // the other two views (Sec. 3.4.4), bf16 only: the component-wise maximum over the valid rows and the first rows as
   // stored. The rows are read once more (they were last read a moment ago); maxima of stored values are exact.
   if constexpr (sizeof(T) == 2) {
-    if (pool == nullptr && recent == nullptr) return;
-    __syncthreads();                                              // part is free
+    if ((POOL || pool == nullptr) && recent == nullptr) return;
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
       const int pj = PW < NW ? wave / WPP : wave * PPW + i, pr = pbase + pj;
@@ -211,7 +225,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
         for (int row = wp * RPW + grp; row < recent_n; row += WPP * RPW)
           *reinterpret_cast<u32x4*>(recent + ((size_t)pr * recent_n + row) * D + gl * 8) =
               *reinterpret_cast<const u32x4*>(H[i] + (unsigned)(row * D + gl * 8));
-      if (pool == nullptr) continue;
+      if (POOL || pool == nullptr) continue;
       float best[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) best[e] = -INFINITY;
@@ -221,19 +235,18 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
 #pragma unroll
         for (int e = 0; e < 8; ++e) best[e] = fmaxf(best[e], x.get(e));
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) best[e] = over_groups<LPR, true>(best[e]);
       if constexpr (WPP == 1) {
-        if (grp == 0 && pr < P)
+        store_pool(i, best);
+      } else {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) store_from_f32(pool, (size_t)pr * D + gl * 8 + e, nv[i] > 0 ? best[e] : 0.0f);
-      } else if (grp == 0) {
+        for (int e = 0; e < 8; ++e) best[e] = over_groups<LPR, true>(best[e]);
+        if (grp == 0)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) part[wave][gl * 8 + e] = nv[i] > 0 ? best[e] : 0.0f;
+          for (int e = 0; e < 8; ++e) part[wave][gl * 8 + e] = nv[i] > 0 ? best[e] : 0.0f;
       }
     }
     if constexpr (WPP > 1) {
-      if (pool == nullptr) return;
+      if (POOL || pool == nullptr) return;
       __syncthreads();
       for (int e = tid; e < PW * D; e += 4 * D) {
         const int j = e / D, y = e % D;
@@ -249,11 +262,12 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
 template <typename T, int D, int PW>
 static void launch_pairs(const GstaArgs& a, int P) {
   constexpr int WPP = PW < D / 16 ? D / 16 / PW : 1, HELD = WPP * (512 / D);   // rows a pair's waves hold per row load
-#define LASER_TILED(R, RES)                                                                                         \
-  hipLaunchKernelGGL((gsta_tiled_kernel<T, D, PW, R, RES>), dim3((unsigned)((P + PW - 1) / PW)), dim3(4 * D), 0,   \
+#define LASER_TILED_FORM(R, RES, POOL)                                                                              \
+  hipLaunchKernelGGL((gsta_tiled_kernel<T, D, PW, R, RES, POOL>), dim3((unsigned)((P + PW - 1) / PW)), dim3(4 * D), 0,   \
                      a.stream, (const T*)a.seg, (const T*)a.t0, (const T*)a.wq, (const T*)a.wk, (const T*)a.wv,    \
                      a.lens, a.cand_off, a.U, P, a.C, a.L, a.w < a.L ? a.w : a.L, a.S, a.M, a.z_out,               \
                      (T*)a.pool_out, (T*)a.recent_out, a.r)
+#define LASER_TILED(R, RES) LASER_TILED_FORM(R, RES, false)
   // rows in flight when the block does not stay
   constexpr int STREAM = 8 / (int)sizeof(T);
   // eight rows a lane fit the registers beside the matrices up to eight pairs (sixteen where a wave has two of them and
@@ -275,8 +289,14 @@ static void launch_pairs(const GstaArgs& a, int P) {
       if (a.S <= 12 * HELD) LASER_TILED(12, true);
       else LASER_TILED(STREAM, false);
     } else LASER_TILED(STREAM, false);
+  } else if constexpr (PW == 16 && sizeof(T) == 2) {
+    // The pooled maxima from the pass itself: read once more, the rows of many pairs with long blocks come from memory again (lengths
+    // full: 35621 pairs x 229 473 -> 230 us, 17520 x 110 118 -> 67; without the views 0.92 .. 1.0 of the split form's times)
+    if (a.M == 1 && a.pool_out != nullptr) LASER_TILED_FORM(STREAM, false, true);
+    else LASER_TILED(STREAM, false);
   } else LASER_TILED(STREAM, false);
 #undef LASER_TILED
+#undef LASER_TILED_FORM
 }
 
 // Pairs per workgroup: the fewest that leave the launch one round of workgroups (256 of eight waves for d = 128 and for
@@ -313,11 +333,14 @@ bool gsta_tile_supports(const GstaArgs& a) { return a.d == 64 || a.d == 128; }
 
 // Whether a one-layer bf16 batch runs on this kernel and not on the forms written for full machines (us, this kernel / the other,
 // lengths full). At d = 64 it does: S = 2 65536 pairs 0.54 of the time, S = 16 8192 pairs 7.7 / 11.0, 32768 0.67, S = 32 65536
-// 0.66, S = 64 8192 0.86, 65536 0.76; against the split form (longer blocks) S = 100 32768 pairs 1.00, 8192 0.73, S = 160 0.58 .. 0.91. At
+// 0.66, S = 64 8192 0.86, 65536 0.76; against the split form (longer blocks, up to 256) 37 calls past 16384 pairs, most with the
+// views, lengths full 0.92 .. 1.05, uniform 0.83 .. 1.04, log-uniform 0.49 .. 0.88. At
 // d = 128 it does for blocks of up to three rows a lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Against the split form S = 100
-// 2048 pairs 14.3 / 26.7, S = 48 8192 0.74, S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views. Between,
+// 2048 pairs 14.3 / 26.7, S = 48 8192 0.74, S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views (which this
+// kernel reads the rows once more for at d = 128). Between,
 // the one-kernel form is the better one once it fills a round of 256 workgroups of 32 pairs with more than half: S = 32 4096 pairs
-// 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24.
+// 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24
+// (9 calls of 13 to 32 segments 0.87, 31 with the views 0.76 .. 1.07, 0.89; those above 1.0 with 28 segments and more).
 bool gsta_tile_preferred(const GstaArgs& a) {
   const int P = gsta_pairs(a);
   if (a.d == 64 || a.S <= 12) return true;

@@ -187,3 +187,30 @@ def test_one_layer_of_many_pairs(d, P, S):
     scale = ref.abs().amax(-1, keepdim=True)
     assert ((z[:, 0].cpu().double() - ref).abs() / scale).max() <= 1e-5
     assert ((one[:, 0].cpu().double() - ref).abs() / scale).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d,P,S,few", [(64, 4097, 65, 4000), (64, 16400, 33, 4000), (64, 16385, 130, 4000), (128, 8200, 30, 4096)])
+def test_views_of_many_pairs(d, P, S, few):
+    """Sixteen pairs of streamed rows at d = 64 take their maxima in the pass over the rows, a few pairs, and other forms, read them once
+    more: the same stored values, and z as close as the forms of one layer are to each other (1e-4 of a vector's largest component)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    seg = torch.randn(P, 1, S, d, device="cuda", generator=gen).to(torch.bfloat16)
+    t0 = (torch.randn(P, 1, d, device="cuda", generator=gen) * 0.3).to(torch.bfloat16)
+    ws = [(torch.randn(1, d, d, device="cuda", generator=gen) * d ** -0.5).to(torch.bfloat16) for _ in range(3)]
+    lens = torch.randint(0, S + 1, (P,), device="cuda", generator=gen, dtype=torch.int32)
+    lens[:3] = torch.tensor([0, 1, S])
+    seg[5, 0, 0] = float("-inf")      # a maximum of -inf, and NaN, as the rows read again give them
+    seg[6, 0, :, 3] = float("nan")
+    lens[5], lens[6] = 1, S
+    z, pool, recent = laser.laser_gsta_forward_multires(seg, t0, *ws, lens, S, 1, 3)
+    zf, poolf, recentf = laser.laser_gsta_forward_multires(seg[:few], t0[:few], *ws, lens[:few], S, 1, 3)
+    only, _ = laser.laser_multires_forward(seg, lens, S, 1, 0)
+    torch.cuda.synchronize()
+    bits = lambda x: x.view(torch.int16)
+    assert torch.equal(bits(pool[:few]), bits(poolf)) and torch.equal(bits(recent[:few]), bits(recentf))
+    assert torch.equal(bits(pool[7:]), bits(only[7:])) and torch.equal(bits(pool[:6]), bits(only[:6]))
+    ok = torch.ones(few, dtype=torch.bool, device="cuda")
+    ok[5:7] = False
+    assert ((z[:few] - zf).abs() / zf.abs().amax(-1, keepdim=True))[ok].max() <= 1e-4
+    assert z[5].isnan().all() and z[6].isnan().all()

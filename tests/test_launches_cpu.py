@@ -125,6 +125,37 @@ def test_direct_or_with_a_wave_for_the_fetches(recorder, U, C, L, w, direct):
     assert ("sta_mfma_dma_kernel" in launch.kernel.decode()) == direct and (ring(launch) is None) == direct
 
 
+def gsta(P, S, d, views, M=1):
+    if views:
+        return lambda lib: lib.laser_gsta_forward_multires(A, A, A, A, A, A, P, 1, S, d, 1, M, BF16, A, 1, A, A, None)
+    return lambda lib: lib.laser_gsta_forward(A, A, A, A, A, A, P, 1, S, d, 1, M, BF16, A, None)
+
+
+def gsta_form(lib, call):
+    """Which of the three bf16 forms a call of one layer runs."""
+    names = " ".join(r.kernel.decode() for r in launches(lib, call))
+    forms = [f for f, kernel in (("tiled", "gsta_tiled_kernel"), ("one", "gsta_one_kernel"), ("split", "gsta_pool_kernel")) if kernel in names]
+    assert len(forms) == 1, names
+    return forms[0]
+
+
+# pairs, segments, d: the form, on both sides of the lines
+@pytest.mark.parametrize("P,S,d,form", [
+    (65536, 64, 64, "tiled"), (16385, 65, 64, "tiled"), (65536, 257, 64, "tiled"), (65536, 12, 128, "tiled"), (4096, 13, 128, "tiled"),
+    (4097, 13, 128, "one"), (8192, 32, 128, "one"), (8193, 32, 128, "tiled"), (11264, 32, 128, "tiled"), (11265, 32, 128, "one"),
+    (8192, 33, 128, "tiled"), (8193, 33, 128, "split")])
+def test_forms_of_one_layer(recorder, P, S, d, form):
+    for views in (False, True):
+        assert gsta_form(recorder, gsta(P, S, d, views)) == form
+
+
+@pytest.mark.parametrize("P,S,d,M,views,pool", [(4097, 65, 64, 1, True, True), (65536, 229, 64, 1, True, True), (65536, 229, 64, 1, False, False),
+                                                (4097, 65, 64, 2, True, False), (4096, 65, 64, 1, True, False), (65536, 64, 64, 1, True, False)])
+def test_maxima_from_the_pass_over_the_rows(recorder, P, S, d, M, views, pool):
+    launch, = launches(recorder, gsta(P, S, d, views, M))
+    assert bool(re.search(r"gsta_tiled_kernelItLi64ELi16ELi4ELb0ELb1E", launch.kernel.decode())) == pool
+
+
 @pytest.mark.parametrize("name", list(SETS))
 def test_backward_calls_with_two_sets_of_tiles(recorder, name):
     U, C, L, dq, d, w, grid, lds = SETS[name]
