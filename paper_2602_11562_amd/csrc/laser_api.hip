@@ -105,16 +105,11 @@ static laser_sta_variant pick_sta(const StaArgs& a) {
   return LASER_STA_GENERIC;
 }
 
-// the form for a batch that fills the machine
-static laser_gsta_variant pick_gsta_full(const GstaArgs& a) {
+static laser_gsta_variant pick_gsta(const GstaArgs& a) {
+  if (gsta_tiled_supports(a) && a.M == 1 && gsta_tile_preferred(a)) return LASER_GSTA_TILED;
   if (gsta_one_supports(a)) return LASER_GSTA_ONE;
   if (gsta_split_supports(a)) return LASER_GSTA_SPLIT;
   return gsta_tiled_supports(a) ? LASER_GSTA_TILED : LASER_GSTA_GENERIC;
-}
-
-static laser_gsta_variant pick_gsta(const GstaArgs& a) {
-  if (gsta_tiled_supports(a) && a.M == 1 && gsta_tile_preferred(a)) return LASER_GSTA_TILED;
-  return pick_gsta_full(a);
 }
 
 static laser_status run_sta(const StaArgs& a, laser_sta_variant variant) {
@@ -763,10 +758,11 @@ const char* laser_gsta_kernel_name(int C, int S, int d, laser_dtype dt) {
 }
 
 const char* laser_gsta_kernel_name_layers(int C, int S, int d, int M, laser_dtype dt) {
-  GstaArgs a{};
-  a.U = 1; a.C = C; a.L = S; a.w = 1; a.S = S; a.d = d; a.M = M; a.dt = dt;
   if (C <= 0 || S <= 0 || d <= 0 || M <= 0 || (dt != LASER_F32 && dt != LASER_BF16)) return "invalid";
-  switch (pick_gsta_full(a)) {
+  GstaArgs a{};
+  a.U = C < 65536 ? 65536 / C + 1 : 1;   // a batch past every line of the rule
+  a.C = C; a.L = S; a.w = 1; a.S = S; a.d = d; a.M = M; a.dt = dt;
+  switch (pick_gsta(a)) {
     case LASER_GSTA_SPLIT: return "gsta_split_bf16";
     case LASER_GSTA_ONE: return "gsta_one_bf16";
     case LASER_GSTA_TILED: return "gsta_tiled_bf16";

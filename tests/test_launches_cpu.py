@@ -149,6 +149,14 @@ def test_forms_of_one_layer(recorder, P, S, d, form):
         assert gsta_form(recorder, gsta(P, S, d, views)) == form
 
 
+@pytest.mark.parametrize("S", [1, 8, 12, 13, 32, 33, 64, 65, 128, 129, 256, 257, 1000])
+@pytest.mark.parametrize("d", [64, 128])
+def test_kernel_name_is_what_a_large_batch_runs(recorder, d, S):
+    for C in (1, 7, 1000):
+        name = recorder.laser_gsta_kernel_name(C, S, d, BF16).decode()
+        assert name == f"gsta_{gsta_form(recorder, gsta(-(-12000 // C) * C, S, d, False))}_bf16", C
+
+
 @pytest.mark.parametrize("P,S,d,M,views,pool", [(4097, 65, 64, 1, True, True), (65536, 229, 64, 1, True, True), (65536, 229, 64, 1, False, False),
                                                 (4097, 65, 64, 2, True, False), (4096, 65, 64, 1, True, False), (65536, 64, 64, 1, True, False)])
 def test_maxima_from_the_pass_over_the_rows(recorder, P, S, d, M, views, pool):
