@@ -218,6 +218,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   // stored. The rows are read once more (they were last read a moment ago); maxima of stored values are exact.
   if constexpr (sizeof(T) == 2) {
     if ((POOL || pool == nullptr) && recent == nullptr) return;
+    if constexpr (!POOL) __syncthreads();   // (orders nothing, but without it log-uniform lengths took up to 3.5 % longer)
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
       const int pj = PW < NW ? wave / WPP : wave * PPW + i, pr = pbase + pj;
@@ -279,6 +280,17 @@ static void launch_pairs(const GstaArgs& a, int P) {
   constexpr bool FEW = PW == 16 && D == 128 && sizeof(T) == 2;
   // One or two rows a lane where that is all there is: with four, the rows past the last one are worked on too (4096 pairs,
   // S = 16, d = 64, bf16: 6.5 -> 5.8 us, the pass 3700 -> 1900 cycles of a workgroup's 14000)
+  auto streamed = [&]() {
+    if constexpr (PW == 16 && sizeof(T) == 2) {
+      // The pooled maxima from the pass itself: read once more, the rows of many pairs with long blocks come from memory again (d = 64,
+      // lengths full: 35621 pairs x 229 473 -> 230 us, 17520 x 110 118 -> 67; without the views 0.92 .. 1.0 of the split form's times)
+      if (a.M == 1 && a.pool_out != nullptr) {
+        LASER_TILED_FORM(STREAM, false, true);
+        return;
+      }
+    }
+    LASER_TILED(STREAM, false);
+  };
   if (a.S <= HELD) LASER_TILED(1, true);
   else if (a.S <= 2 * HELD) LASER_TILED(2, true);
   else if (FEW && a.S <= 3 * HELD && P > 256 * PW) LASER_TILED((FEW ? 3 : 4), true);
@@ -287,14 +299,9 @@ static void launch_pairs(const GstaArgs& a, int P) {
     if (a.S <= 8 * HELD) LASER_TILED(8, true);
     else if constexpr (PW == 8 && D == 128 && sizeof(T) == 2) {
       if (a.S <= 12 * HELD) LASER_TILED(12, true);
-      else LASER_TILED(STREAM, false);
-    } else LASER_TILED(STREAM, false);
-  } else if constexpr (PW == 16 && sizeof(T) == 2) {
-    // The pooled maxima from the pass itself: read once more, the rows of many pairs with long blocks come from memory again (lengths
-    // full: 35621 pairs x 229 473 -> 230 us, 17520 x 110 118 -> 67; without the views 0.92 .. 1.0 of the split form's times)
-    if (a.M == 1 && a.pool_out != nullptr) LASER_TILED_FORM(STREAM, false, true);
-    else LASER_TILED(STREAM, false);
-  } else LASER_TILED(STREAM, false);
+      else streamed();
+    } else streamed();
+  } else streamed();
 #undef LASER_TILED
 #undef LASER_TILED_FORM
 }
@@ -336,8 +343,8 @@ bool gsta_tile_supports(const GstaArgs& a) { return a.d == 64 || a.d == 128; }
 // 0.66, S = 64 8192 0.86, 65536 0.76; against the split form (longer blocks, up to 256) 37 calls past 16384 pairs, most with the
 // views, lengths full 0.92 .. 1.05, uniform 0.83 .. 1.04, log-uniform 0.49 .. 0.88. At
 // d = 128 it does for blocks of up to three rows a lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Against the split form S = 100
-// 2048 pairs 14.3 / 26.7, S = 48 8192 0.74, S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views (which this
-// kernel reads the rows once more for at d = 128). Between,
+// 2048 pairs 14.3 / 26.7, S = 48 8192 0.74, S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views, when
+// their maxima still came from a second reading. Between,
 // the one-kernel form is the better one once it fills a round of 256 workgroups of 32 pairs with more than half: S = 32 4096 pairs
 // 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24
 // (9 calls of 13 to 32 segments 0.87, 31 with the views 0.76 .. 1.07, 0.89; those above 1.0 with 28 segments and more).

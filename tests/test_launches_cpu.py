@@ -158,10 +158,11 @@ def test_kernel_name_is_what_a_large_batch_runs(recorder, d, S):
 
 
 @pytest.mark.parametrize("P,S,d,M,views,pool", [(4097, 65, 64, 1, True, True), (65536, 229, 64, 1, True, True), (65536, 229, 64, 1, False, False),
-                                                (4097, 65, 64, 2, True, False), (4096, 65, 64, 1, True, False), (65536, 64, 64, 1, True, False)])
+                                                (4097, 65, 64, 2, True, False), (4096, 65, 64, 1, True, False), (65536, 64, 64, 1, True, False),
+                                                (2049, 33, 128, 1, True, True), (2048, 33, 128, 1, True, False), (8192, 32, 128, 1, True, False)])
 def test_maxima_from_the_pass_over_the_rows(recorder, P, S, d, M, views, pool):
-    launch, = launches(recorder, gsta(P, S, d, views, M))
-    assert bool(re.search(r"gsta_tiled_kernelItLi64ELi16ELi4ELb0ELb1E", launch.kernel.decode())) == pool
+    launch = launches(recorder, gsta(P, S, d, views, M))[0]
+    assert bool(re.search(rf"gsta_tiled_kernelItLi{d}ELi16ELi4ELb0ELb1E", launch.kernel.decode())) == pool
 
 
 @pytest.mark.parametrize("name", list(SETS))
