@@ -9,6 +9,7 @@ import pytest
 from paper_2602_11562_amd import binding
 from test_sta_backward_mfma_gpu import SETS
 from test_sta_dealt_gpu import CASES as DEALT
+from test_sta_mfma_shape_gpu import CASES as SHAPES, eight_waves
 from test_sta_ring_gpu import CASES as RING, THREE
 
 
@@ -147,6 +148,18 @@ def gsta_form(lib, call):
 def test_forms_of_one_layer(recorder, P, S, d, form):
     for views in (False, True):
         assert gsta_form(recorder, gsta(P, S, d, views)) == form
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_kernels_of_the_shapes(recorder, name):
+    U, C, L, dq, d, w, heads = SHAPES[name]
+    launch, = launches(recorder, sta_heads(U, C, L, dq, d, w, heads))
+    assert ring(launch)
+    launch, = launches(recorder, lambda lib: lib.laser_sta_forward_softmax(A, A, A, A, U, C, L, dq, d, w, 1.0, heads, BF16, A, A, None, 0))
+    m = re.search(r"15sta_mfma_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", launch.kernel.decode())
+    got = tuple(int(x) for x in m.groups())
+    assert got[:2] == (dq, d) and got[4] == heads
+    assert got[2:4] == ((8, 2) if eight_waves(U, C, L, w) else ({1: 1, 2: 2}.get(-(-C // 32), 4), 1))
 
 
 @pytest.mark.parametrize("S", [1, 8, 12, 13, 32, 33, 64, 65, 128, 129, 256, 257, 1000])

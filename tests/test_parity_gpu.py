@@ -149,14 +149,14 @@ EDGE_SPECS = {
     "dq_differs_from_d": _spec("bf16", 2, 64, 512, 128, 64, 128, 1, 2007),
     "small_dims": _spec("f32", 2, 3, 50, 8, 8, 7, 3, 2008),
     "three_layers_long_tail": _spec("bf16", 3, 33, 1300, 64, 64, 256, 3, 2009),
-    # more than 128 candidates with d_q = d = 128: the direct-to-LDS STA kernel, on ragged histories
-    "many_candidates_ragged": _spec("bf16", 5, 200, 1000, 128, 128, 100, 1, 2011),   # w not a multiple of the tile
-    "many_candidates_small_w": _spec("bf16", 2, 130, 300, 128, 128, 10, 1, 2012),    # segments shorter than a tile
+    # more than 128 candidates with d_q = d = 128, on ragged histories (test_sta_dealt_gpu.py has the shapes of the direct-to-LDS kernel)
+    "many_candidates_ragged": _spec("bf16", 5, 200, 1000, 128, 128, 100, 1, 2011),   # w not a multiple of 32
+    "many_candidates_small_w": _spec("bf16", 2, 130, 300, 128, 128, 10, 1, 2012),    # segments shorter than a block
     "many_candidates_two_tiles": _spec("bf16", 3, 257, 512, 128, 128, 128, 1, 2013),  # two candidate tiles per user
-    # 65 to 128 candidates with d_q = d = 128: the same kernel with four waves
+    # 65 to 128 candidates with d_q = d = 128
     "four_waves_ragged": _spec("bf16", 5, 100, 1000, 128, 128, 100, 1, 2018),
     "four_waves_small_w": _spec("bf16", 2, 96, 300, 128, 128, 10, 1, 2019),
-    "four_waves_runs_of_segments": _spec("bf16", 8, 80, 2048, 128, 128, 32, 1, 2020),   # two segments per workgroup
+    "four_waves_runs_of_segments": _spec("bf16", 8, 80, 2048, 128, 128, 32, 1, 2020),   # segments of one block
     # short segments with few candidates per user: the wave-per-segment streaming form (C = 1 is how the paper's
     # own training batches look: one target per sample, Sec. 4.1.2)
     "paper_default_one_target": _spec("bf16", 6, 1, 1000, 128, 32, 10, 2, 2014),

@@ -23,7 +23,11 @@ CASES = [(29, 201, 3001, 100, "mixed", True, True), (40, 300, 2500, 100, "mixed"
          (9, 480, 6000, 80, "one_short", True, True), (64, 128, 2800, 70, "one_short", False, True),
          (12, 128, 6400, 100, "last_only", True, True),
          (37, 436, 1069, 117, "mixed", False, True), (45, 85, 5390, 238, "full", False, True), (12, 453, 4905, 243, "mixed", False, False),
-         (7, 129, 3001, 100, "mixed", False, False), (65, 70, 900, 40, "mixed", True, False), (5, 257, 1000, 64, "mixed", True, False)]
+         (7, 129, 3001, 100, "mixed", False, False), (65, 70, 900, 40, "mixed", True, False), (5, 257, 1000, 64, "mixed", True, False),
+         # segments shorter than the tile of 32 items and as long, both workgroup sizes: partial tiles alone, a segment done every step
+         (5, 130, 203, 1, "mixed", True, False), (9, 96, 301, 2, "mixed", True, False), (5, 200, 303, 10, "one_short", True, False),
+         (6, 100, 333, 10, "mixed", True, False), (3, 300, 500, 31, "mixed", True, False), (6, 257, 640, 32, "full", True, False),
+         (20, 70, 645, 31, "mixed", True, False), (4, 128, 641, 32, "mixed", True, False), (70, 90, 200, 33, "mixed", True, False)]
 
 
 @pytest.mark.parametrize("whole", [False, True], ids=["sta", "whole_path"])
