@@ -28,7 +28,7 @@
 // normalised rows and their scores 3.1, softmax and sum 1.6, addresses and requests 1.4). Scores as four vector
 // operations per word and the weighted sum row by row (a word, a weight from v_readlane, five to seven operations) were 350
 // of 1100 vector instructions, another hundred where two pairs met; the two products take 16 MFMAs. With the launches before
-// and behind it, 16384 pairs of 60 valid rows: 132.0 -> 125.4 us, with the views 144.6 -> 140.8.
+// and behind it, 16384 pairs of 60 valid rows, d_ff = 128, rows not stored: 137.3 -> 127.2 us, with the views 145.5 -> 142.0.
 #include "segment_ffn_tile.h"
 
 namespace laser {

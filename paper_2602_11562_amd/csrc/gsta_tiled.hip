@@ -43,7 +43,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   __shared__ __attribute__((aligned(16))) typename X::Act bt, bq; // t; q', then p
   __shared__ __attribute__((aligned(16))) float rr[PW * RP];      // r / sqrt(d)
   __shared__ __attribute__((aligned(16))) unsigned char patches[NW][X::PATCH];
-  __shared__ __attribute__((aligned(16))) float part[WPP > 1 ? NW : 1][D];   // (the views)
+  __shared__ __attribute__((aligned(16))) float part[WPP > 1 && sizeof(T) == 2 ? NW : 1][D];   // (the views)
   __shared__ __attribute__((aligned(8))) f32x2 pml[NW];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -208,7 +208,7 @@ laser_status gsta_generic_launch(const GstaArgs& a);
 // d in {64, 128}: tiles of 1 to 16 pairs, any number of layers (the tiled variant, and what AUTO runs for fp32 storage)
 bool gsta_tile_supports(const GstaArgs& a);
 laser_status gsta_tile_launch(const GstaArgs& a);
-bool gsta_tile_preferred(const GstaArgs& a);   // one layer, bf16: a batch too small for the forms that fill the machine
+bool gsta_tile_preferred(const GstaArgs& a);   // one layer, bf16: this form and not the one-kernel or the split form
 inline bool gsta_tiled_supports(const GstaArgs& a) { return a.dt == LASER_BF16 && gsta_tile_supports(a); }
 bool gsta_split_supports(const GstaArgs& a);
 laser_status gsta_split_launch(const GstaArgs& a);

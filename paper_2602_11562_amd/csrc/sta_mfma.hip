@@ -964,7 +964,7 @@ static int pick_nw(const StaArgs& a) {
 // compute unit and the candidates take 0.7 of their places: 54 calls in times of the ring 0.90 (0.69 to 1.18; 76 x 490, 36 of 28 items
 // 96.8 -> 66.4 us), with ten to eighteen 1.17 (0.83 to 1.95; 246 x 369, 9 of 18 items 35.5 / 69.4). With own counts per user, whose workgroups are dealt out, the line was not drawn anew.
 static bool is_direct(const StaArgs& a, int nw) {
-  if (a.heads != 1 || a.softmax || a.d_q != 128 || a.d != 128 || a.C <= 64) return false;
+  if (a.heads != 1 || a.softmax || a.d_q != 128 || a.d != 128 || nw < 4) return false;   // (65 candidates and more)
   if (a.cand_off != nullptr) return true;
   const long long tiles = (a.C + CW * nw - 1) / (CW * nw), steps = (a.w + DT_TI - 1) / DT_TI;
   if (a.w < 48) return nw == 8 && a.w > 16 && a.U * tiles * a.S > 18 * 256 && a.C * 100LL > tiles * CW * nw * 70;
@@ -972,8 +972,8 @@ static bool is_direct(const StaArgs& a, int nw) {
 }
 
 // Consecutive segments per workgroup of the register-staged form (they share the query registers and the prefetch
-// pipeline). One and two waves: as many as still leave a few workgroups per compute unit (64 users x 64 candidates x 16
-// segments, two waves: 15.1 us with 512 workgroups of two segments, 11.2 us with 1024 of one). Four waves, two workgroups on
+// pipeline). One and two waves: as many as still leave a few workgroups per compute unit (with sigmoid gates, whose calls
+// ran this form then, 64 users x 64 candidates x 16 segments: 15.1 us with 512 workgroups of two segments, 11.2 us with 1024 of one). Four waves, two workgroups on
 // a compute unit, and eight, one on it: the smallest estimate of rounds of workgroups times the length of one, in segments,
 // each with a constant for what starting costs. The constants are those that came closest to the best of 1 to 16 segments
 // over 292 calls (2 to 128 users, 65 to 512 candidates, w = 5 to 256, every width, up to four heads, both kinds of gate): 5 %
@@ -1020,7 +1020,7 @@ bool sta_mfma_supports(const StaArgs& a) {
   if (a.dt != LASER_BF16) return false;
   if (!(a.d_q == 32 || a.d_q == 64 || a.d_q == 128)) return false;
   if (!(a.d == 64 || a.d == 128)) return false;
-  // several heads: the register-staged form; a head owns whole 16-wide k-steps and whole 32-column blocks
+  // several heads: not the direct-to-LDS form; a head owns whole 16-wide k-steps and whole 32-column blocks
   if (a.heads != 1 && a.heads != 2 && a.heads != 4) return false;
   if (a.heads == 4 && (a.d_q < 64 || a.d != 128)) return false;
   if (a.C < 9) return false;   // fewer candidates than that: the streaming kernel's range

@@ -198,7 +198,8 @@ __global__ __launch_bounds__(64 * (NW + 1), (RingShape<DQ, D, NW, HEADS, SHORT>:
   }
 
   // patch -> global: 16 lanes x 16 B = one row; LDS operations of a wave execute in order, so the rows written by this wave are
-  // visible to its own reads without a barrier
+  // visible to its own reads without a barrier. Stored cacheable, whether H' is read again next or not: with the non-temporal hint
+  // outputs of up to 256 MB take as long, larger ones 4 % longer
   constexpr int LPR = D / 8, RPI = 64 / LPR;   // lanes per row, rows per instruction
   unsigned char* opatch = smem + Sh::PATCH + wave * (CW * Sh::OP);
   const unsigned row_out = (unsigned)S * VROW;
