@@ -341,12 +341,11 @@ bool gsta_tile_supports(const GstaArgs& a) { return a.d == 64 || a.d == 128; }
 // Whether a one-layer bf16 batch runs on this kernel and not on the forms written for full machines (us, this kernel / the other,
 // lengths full). At d = 64 it does: S = 2 65536 pairs 0.54 of the time, S = 16 8192 pairs 7.7 / 11.0, 32768 0.67, S = 32 65536
 // 0.66, S = 64 8192 0.86, 65536 0.76; against the split form (longer blocks, up to 256) 37 calls past 16384 pairs, most with the
-// views, lengths full 0.92 .. 1.05, uniform 0.83 .. 1.04, log-uniform 0.49 .. 0.88. At
-// d = 128 it does for blocks of up to three rows a lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Against the split form S = 100
-// 2048 pairs 14.3 / 26.7, S = 48 8192 0.74, S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views, when
-// their maxima still came from a second reading. Between,
-// the one-kernel form is the better one once it fills a round of 256 workgroups of 32 pairs with more than half: S = 32 4096 pairs
-// 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24
+// views, lengths full 0.92 .. 1.05, uniform 0.83 .. 1.04, log-uniform 0.49 .. 0.88. At d = 128 it does for blocks of up to three rows a
+// lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Against the split form S = 100 2048 pairs 14.3 / 26.7, S = 48 8192 0.74,
+// S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views, when their maxima still came from a second reading.
+// Between, the one-kernel form is the better one once it fills a round of 256 workgroups of 32 pairs with more than half: S = 32
+// 4096 pairs 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24
 // (9 calls of 13 to 32 segments 0.87, 31 with the views 0.76 .. 1.07, 0.89; those above 1.0 with 28 segments and more).
 bool gsta_tile_preferred(const GstaArgs& a) {
   const int P = gsta_pairs(a);

@@ -115,11 +115,13 @@ def test_waves_and_segments_of_a_workgroup(recorder, U, C, L, dq, d, w, heads, w
 
 # (users, candidates, items, w) at d_q = d = 128: whether the direct-to-LDS form takes the call, on both sides of each of its lines
 @pytest.mark.parametrize("U,C,L,w,direct", [
-    (16, 256, 4800, 64, True), (16, 256, 4544, 64, True), (4, 256, 2000, 64, True), (4, 256, 1920, 64, False),      # 2400 tiles; 30 segments
-    (183, 296, 2400, 200, False), (183, 300, 2400, 200, True),                                                       # 0.58 of the places
-    (16, 64, 4800, 64, False), (16, 75, 9600, 64, True), (16, 256, 4700, 47, False), (16, 256, 4800, 48, True),      # four waves; w = 48
-    (76, 490, 988, 28, True), (63, 490, 988, 28, False), (76, 490, 612, 17, True), (76, 490, 575, 16, False),        # half a tile; 18 a unit
-    (64, 180, 1241, 17, True), (1, 180, 1241, 17, False), (76, 350, 988, 28, False), (200, 128, 988, 28, False)])                                                          # 0.7 of them; 4 waves
+    # 2400 tiles; 30 segments; 0.58 of the places; four waves
+    (16, 256, 4800, 64, True), (16, 256, 4544, 64, True), (4, 256, 2000, 64, True), (4, 256, 1920, 64, False),
+    (183, 296, 2400, 200, False), (183, 300, 2400, 200, True), (16, 64, 4800, 64, False), (16, 75, 9600, 64, True),
+    # w = 48; below it half a tile, eighteen workgroups a compute unit, 0.7 of the places and eight waves
+    (16, 256, 4700, 47, False), (16, 256, 4800, 48, True), (76, 490, 988, 28, True), (63, 490, 988, 28, False),
+    (76, 490, 612, 17, True), (76, 490, 575, 16, False), (64, 180, 1241, 17, True), (1, 180, 1241, 17, False),
+    (76, 350, 988, 28, False), (200, 128, 988, 28, False)])
 def test_direct_or_with_a_wave_for_the_fetches(recorder, U, C, L, w, direct):
     launch, = launches(recorder, sta(U, C, L, w))
     print(launch.kernel, launch.grid)
