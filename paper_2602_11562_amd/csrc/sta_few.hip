@@ -31,12 +31,17 @@ constexpr int FEW_TI = 32;             // items per tile
 constexpr int FEW_LDS = 160 * 1024;    // of a compute unit
 
 // 16-byte chunk c of row r of a tile with CH chunks per row sits at chunk c ^ few_swz<CH>(r) of that row: 16 rows at one
-// chunk (operand reads) and four rows at every CH / 4-th chunk (transpose loads) both spread over all banks
+// chunk (operand reads, which the hardware serves for rows 0 - 3, 12 - 15 of one lane group with rows 4 - 11 of the next) and
+// four rows at four chunks in a row (transpose loads) both spread over all banks
 template <int CH>
-__device__ __forceinline__ int few_swz(int r) { return ((r * CH) >> 4) & (CH - 1); }
+__device__ __forceinline__ int few_swz(int r) {
+  const int lo = r & 3, hi = (r >> 2) & 3;
+  return (((lo * CH) >> 4) << 2) | (((hi ^ (hi >> 1)) & 1) << 1) | (hi >> 1);
+}
 
 // FE = 0: keys and values as given. FE > 0: the folded form, keys = values = raw items (DQ = D), FE output columns.
-template <int DQ, int D, int FE>
+// DEAL: a workgroup's waves take its units by ticket (see few_launch)
+template <int DQ, int D, int FE, bool DEAL>
 struct FewShape {
   static constexpr bool FOLD = FE > 0;
   static constexpr int CMAX = FOLD ? 4 : 8;                  // query rows per user
@@ -44,9 +49,9 @@ struct FewShape {
   static constexpr int KF = FOLD ? 0 : DQ / 16, VF = D / 16, F = KF + VF;         // and a tile's items
   static constexpr int KB = KF * 1024, QOFF = F * 1024, BUF = QOFF + QF * 1024;   // ring buffer: K, V, Q
   static constexpr int WVB = FOLD ? D * FE * 2 : 0;
-  static constexpr int WAVE = 2 * BUF, FIT = (FEW_LDS - WVB) / WAVE;
+  static constexpr int WAVE = 2 * BUF, FIT = (FEW_LDS - WVB - (DEAL ? 16 : 0)) / WAVE;
   static constexpr int NW = FIT < 8 ? FIT : 8;               // waves per workgroup, one workgroup per compute unit
-  static constexpr int NT = 64 * NW, LDS = WVB + NW * WAVE;
+  static constexpr int NT = 64 * NW, TICKET = WVB + NW * WAVE, LDS = TICKET + (DEAL ? 16 : 0);
 };
 
 struct FewFold {
@@ -55,26 +60,25 @@ struct FewFold {
   int hs;                      // log2 of the heads
 };
 
-template <int DQ, int D, int FE>
-__global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
+template <int DQ, int D, int FE, bool DEAL>
+__global__ __launch_bounds__((FewShape<DQ, D, FE, DEAL>::NT)) void sta_few_kernel(
     const unsigned short* __restrict__ q, const unsigned short* __restrict__ k, const unsigned short* __restrict__ v,
     const int32_t* __restrict__ lens, const int32_t* __restrict__ cand_off, int P, int C_all, int L, int w, int S,
     int cps, int run_segs, unsigned runs, unsigned units, MulDiv dv, float neg_scale_log2e, unsigned short* __restrict__ seg_out,
     int32_t* __restrict__ seg_cnt, FewFold fold) {
-  using Sh = FewShape<DQ, D, FE>;
+  using Sh = FewShape<DQ, D, FE, DEAL>;
   constexpr bool FOLD = Sh::FOLD;
   constexpr int KCH = DQ / 8, VCH = D / 8, KS = DQ / 32, VT = D / 16;
-  constexpr int LD = D / 4;                              // columns of a lane's (segment, query row)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hs = FOLD ? fold.hs : 0;
 
-  if constexpr (FOLD) {   // W_v in operand order: fragment (et, ks), lane (m, g), eight k = D/4 g + 8 ks + j of column
+  if constexpr (FOLD) {   // W_v in operand order: fragment (et, ks), lane (m, g), eight k = 32 ks + 8 g + j of column
     for (int e = tid; e < D * FE / 8; e += Sh::NT) {   // FE/4 (m / 4) + 4 et + m % 4
       const int kk = e / (FE / 8), n0 = (e % (FE / 8)) * 8;
       const u32x4 raw = *reinterpret_cast<const u32x4*>(fold.wv + (size_t)kk * FE + n0);
-      const int fg = kk / LD, fks = (kk % LD) / 8, fj = kk % 8;
+      const int fg = (kk >> 3) & 3, fks = kk >> 5, fj = kk & 7;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int col = n0 + j, m = (col / (FE / 4)) * 4 + (col & 3), et = (col % (FE / 4)) >> 2;
@@ -82,27 +86,33 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
             (unsigned short)((raw[j >> 1] >> ((j & 1) * 16)) & 0xffffu);
       }
     }
-    __syncthreads();
   }
+  if (DEAL && tid == 0) *reinterpret_cast<unsigned*>(smem + Sh::TICKET) = Sh::NW;
+  if (FOLD || DEAL) __syncthreads();
   const unsigned ring = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem + Sh::WVB +
                         (unsigned)wave * Sh::WAVE;
+  // the folded form's sums are not read back here: with the hint they leave the cache to H'
+  auto put_sums = [&](unsigned short* at, const u32x4& x) {
+    if constexpr (FOLD) __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(at));
+    else *reinterpret_cast<u32x4*>(at) = x;
+  };
   const unsigned char* ringp = smem + Sh::WVB + wave * Sh::WAVE;
 
   const int CP = 1 << cps, spb = 16 >> cps;   // query rows and segments of a block
   const int col_s = l16 >> cps, col_p = l16 & (CP - 1);
 
   // LDS offsets that do not change. Operand read of K: row l16, chunk 4 ks + g. Transpose load of V: rows 4 g + l16 / 4
-  // (and 16 further down), columns LD (l16 % 4) + 4 vt ..
+  // (and 16 further down), columns 32 (vt / 2) + 8 (l16 % 4) + 4 (vt % 2) ..
   const int krow = l16 * DQ * 2;
   const int vr = 4 * g + (l16 >> 2);
   auto koff = [&](int ks) { return krow + (((4 * ks + g) ^ few_swz<KCH>(l16)) << 4); };
   auto voff = [&](int vt) {
-    const int col = LD * (l16 & 3) + 4 * vt;
+    const int col = 32 * (vt >> 1) + 8 * (l16 & 3) + 4 * (vt & 1);
     return vr * D * 2 + (((col >> 3) ^ few_swz<VCH>(vr)) << 4) + (col & 4) * 2;
   };
 
-  // A unit of work is one run of a user's segments; a wave takes every (number of waves)-th one, so that the waves in flight
-  // sweep the arrays front to back, with the runs of a user rotated so that no wave meets one run only. The fetches are two
+  // A unit of work is one run of a user's segments; a workgroup takes every (number of workgroups)-th one and its waves share
+  // them, in turn or by ticket, so that the waves in flight sweep the arrays front to back, with the runs of a user rotated so that no wave meets one run only. The fetches are two
   // tiles ahead of the arithmetic across units, and every unit counts at least two tiles, so that this reaches into the
   // next unit and no further.
   struct Unit {
@@ -110,7 +120,6 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
     size_t pb;
     const unsigned short *k, *v;
   };
-  const unsigned nwaves = gridDim.x * Sh::NW;
   auto len_of = [&](unsigned it) { return it < units && lens != nullptr ? lens[dv.div(it)] : L; };
   // unit `it` of a user of (unclamped) length n: its counts, its empty segments; false: nothing to compute
   auto open_unit = [&](unsigned it, int n, Unit& x) {
@@ -131,7 +140,7 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
       const int len16 = (i_end - x.i_ne) * VCH;
       for (int c = 0; c < x.C; ++c)
         for (int e = lane; e < len16; e += 64)
-          *reinterpret_cast<u32x4*>(seg_out + ((x.pb + c) * S + x.i_ne) * D + e * 8) = z;
+          put_sums(seg_out + ((x.pb + c) * S + x.i_ne) * D + e * 8, z);
       if constexpr (FOLD) {
         const int ylen = (i_end - x.i_ne) * (FE / 8), pairs = x.C >> hs;
         for (int c = 0; c < pairs; ++c)
@@ -217,7 +226,13 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
     while (it < units) {
       const unsigned now = it;
       const int n = __builtin_amdgcn_readfirstlane(n_ahead);
-      it += nwaves;
+      if constexpr (DEAL) {
+        unsigned ticket = 0;
+        if (lane == 0) ticket = atomicAdd(reinterpret_cast<unsigned*>(smem + Sh::TICKET), 1u);
+        it = __builtin_amdgcn_readfirstlane(ticket) * gridDim.x + blockIdx.x;
+      } else {
+        it += gridDim.x * Sh::NW;
+      }
       n_ahead = len_of(it);
       if (open_unit(now, n, x)) return true;
     }
@@ -236,7 +251,7 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
   while (have) {
     const bool more = next_unit(nxt);
     const bool live = col_p < cur.C;   // this lane's query row exists
-    f32x4 acc[VT];   // rows: column LD g + 4 vt + i of the sums; columns: (segment, query row)
+    f32x4 acc[VT];   // rows: column 32 (vt / 2) + 8 g + 4 (vt % 2) + i of the sums; columns: (segment, query row)
 #pragma unroll
     for (int vt = 0; vt < VT; ++vt) acc[vt] = zero4;
     int blk = cur.i_beg;   // first segment of the block in work
@@ -270,7 +285,7 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
             for (int vt = 0; vt < VT; ++vt)
 #pragma unroll
               for (int i = 0; i < 4; ++i)
-                acc[vt][i] = fmaf(gt, bf16_bits_to_f32(cur.v[(size_t)j * D + LD * g + 4 * vt + i]), acc[vt][i]);
+                acc[vt][i] = fmaf(gt, bf16_bits_to_f32(cur.v[(size_t)j * D + 32 * (vt >> 1) + 8 * g + 4 * (vt & 1) + i]), acc[vt][i]);
           }
         }
         round_acc();
@@ -295,10 +310,10 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
         landed = true;
       }
       if (mine) {
-        unsigned short* dst = seg_out + ((cur.pb + col_p) * S + seg) * D + LD * g;
+        unsigned short* dst = seg_out + ((cur.pb + col_p) * S + seg) * D + 8 * g;
 #pragma unroll
-        for (int x = 0; x < VT / 2; ++x) *reinterpret_cast<bf16x8*>(dst + 8 * x) = o[x];
-        if constexpr (FOLD) {   // each head's columns from its own sums
+        for (int x = 0; x < VT / 2; ++x) put_sums(dst + 32 * x, __builtin_bit_cast(u32x4, o[x]));
+        if constexpr (FOLD) {   // each head's columns (runs of 32 and more) from its own sums, chosen ahead of the stores
           if ((LE * g) / (FE >> hs) == (col_p & ((1 << hs) - 1))) {
             unsigned short* ydst = fold.y + (((cur.pb + col_p) >> hs) * S + seg) * FE + LE * g;
 #pragma unroll
@@ -388,10 +403,7 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE>::NT)) void sta_few_kernel(
 // ------------------------------------------------------------------------------------------ host side
 template <int DQ, int D, int FE>
 static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
-  using Sh = FewShape<DQ, D, FE>;
-  auto kern = sta_few_kernel<DQ, D, FE>;
-  if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS) != hipSuccess)
-    return LASER_ERR_LAUNCH;
+  using Sh = FewShape<DQ, D, FE, false>;
   int cps = 0;
   while ((1 << cps) < a.C) ++cps;
   const int w = a.w < a.L ? a.w : a.L;     // (one segment either way; keeps index arithmetic in range)
@@ -406,10 +418,22 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
   const unsigned units = (unsigned)a.U * runs;   // <= U S, which fits an int
   const unsigned blocks = units < 256 ? units : 256u;
   const MulDiv dv = mul_div(runs);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(Sh::NT), Sh::LDS, a.stream, (const unsigned short*)a.q,
-                     (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens, a.cand_off, a.P, a.C, a.L, w, a.S, cps,
-                     (int)run, runs, units, dv, -1.4426950408889634f / a.gamma, (unsigned short*)a.seg_out, a.seg_cnt, fold);
-  return launch_status();
+  // Units of short histories hold little or nothing. Dealt out in turn, the fullest wave has half as much again as the mean, by
+  // ticket (an LDS counter) a workgroup's waves end together; with few units a wave the counter costs more than it evens out.
+  // d_in = 128, two rows, w = 10, uniform lengths: 2048 users 93 -> 84 us, full lengths 118 -> 112; 8 rows, w = 256, 1000 users
+  // (3.9 units a wave) 65.7 -> 63.1; 4 rows, w = 50, 256 users (2.5) 11.1 -> 11.2.
+  const bool deal = units > (unsigned)tuning_int("LASER_FEW_DEAL", 3) * blocks * Sh::NW;
+  auto launch = [&](auto shape, auto kern) {
+    using X = decltype(shape);
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS) != hipSuccess)
+      return LASER_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(X::NT), X::LDS, a.stream, (const unsigned short*)a.q,
+                       (const unsigned short*)a.k, (const unsigned short*)a.v, a.lens, a.cand_off, a.P, a.C, a.L, w, a.S, cps,
+                       (int)run, runs, units, dv, -1.4426950408889634f / a.gamma, (unsigned short*)a.seg_out, a.seg_cnt, fold);
+    return launch_status();
+  };
+  return deal ? launch(FewShape<DQ, D, FE, true>{}, sta_few_kernel<DQ, D, FE, true>)
+              : launch(FewShape<DQ, D, FE, false>{}, sta_few_kernel<DQ, D, FE, false>);
 }
 
 // From three query rows per user on the vector-ALU kernels are bound by their arithmetic and this one by HBM; with one or

@@ -175,3 +175,38 @@ def test_folded_histories_past_the_cache(rows):
         assert vec_rel_err(to_host_f64(g[u:u + 1]), ref) <= TOL["bf16"], u
         ref = to_host_f64(g[u]) @ to_host_f64(wv)
         assert vec_rel_err(to_host_f64(seg[u]), ref) <= TOL["bf16"], u
+
+
+# Launches of more than three units a wave, whose workgroups deal their units out by ticket: every unit is worked on exactly where it
+# belongs (outputs start as NaN). folded, rows (heads when folded), d_q, d, L, w, users
+@pytest.mark.parametrize("folded,rows,dq,d,L,w,U", [(False, 4, 32, 128, 330, 10, 1300), (False, 8, 64, 64, 200, 3, 500),
+                                                    (False, 3, 128, 128, 97, 33, 2100), (True, 2, 128, 128, 330, 10, 1200),
+                                                    (True, 4, 128, 128, 97, 7, 1100), (True, 1, 128, 64, 130, 65, 3300)])
+def test_units_dealt_by_ticket(folded, rows, dq, d, L, w, U):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(U)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()
+    nan = lambda *s: torch.full(s, float("nan"), device="cuda", dtype=torch.bfloat16)
+    lens = torch.randint(0, L + 1, (U,), device="cuda", generator=gen, dtype=torch.int32)
+    S, gamma = -(-L // w), 4.0
+    print(f"folded {folded} rows {rows} {dq}/{d} w {w} users {U}", flush=True)
+    if folded:
+        t, h, A, wv = rnd(U, 1, dq), rnd(U, L, dq), rnd(dq, rows * dq) / math.sqrt(dq), rnd(dq, d) / math.sqrt(dq)
+        q, sums = nan(U, rows, dq), nan(U, rows, S, dq)
+        seg, cnt = laser.laser_sta_folded_forward(t, h, A, wv, lens, w, gamma, rows, qf_work=q, g_work=sums, seg_out=nan(U, 1, S, d))
+        k = v = h
+    else:
+        q, k, v = rnd(U, rows, dq), rnd(U, L, dq), rnd(U, L, d)
+        sums, cnt = laser.laser_sta_forward(q, k, v, lens, w, gamma, seg_out=nan(U, rows, S, d))
+    torch.cuda.synchronize()
+    some = list(range(0, U, 97)) + [U - 1]
+    n = lens[some].cpu().numpy()
+    ref, _ = oracle.sta_forward(*(to_host_f64(x[some]) for x in (q, k, v)), n, w, gamma)
+    assert vec_rel_err(to_host_f64(sums[some]), ref) <= TOL["bf16"]
+    assert np.array_equal(cnt.cpu().numpy(), oracle.segment_counts(lens.cpu().numpy(), L, w))
+    empty = (cnt == 0)[:, None, :, None]
+    for x in (sums, seg) if folded else (sums,):
+        assert torch.isfinite(x).all() and not torch.where(empty, x, 0).any()
+    if folded:
+        ref = oracle.project_heads(to_host_f64(sums[some]).reshape(len(some), rows, S, dq), to_host_f64(wv), rows)
+        assert vec_rel_err(to_host_f64(seg[some]), ref.reshape(len(some), 1, S, d)) <= TOL["bf16"]
