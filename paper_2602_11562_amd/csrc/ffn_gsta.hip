@@ -11,7 +11,7 @@
 // with its products re-associated, which is exact).
 //
 // ffn_pool_kernel: the FFN tile of segment_ffn_tile.h on the valid rows (the first nv segments, the ones that hold a
-// valid item) of the pairs a wave walks with a grid stride, one pair after the other, cut into tiles of 32 as one
+// valid item) of the pairs a wave is dealt, one pair after the other, cut into tiles of 32 as one
 // stream: a tile holds rows of one pair, or the last rows of one followed by the first of the next, so that only the
 // wave's last tile is padded (with copies of its last row, which count as empty). The rows of the remaining segments
 // are never read (whatever H' holds there is not trusted): they, and the results of a pair without any valid
@@ -29,6 +29,10 @@
 // operations per word and the weighted sum row by row (a word, a weight from v_readlane, five to seven operations) were 350
 // of 1100 vector instructions, another hundred where two pairs met; the two products take 16 MFMAs. With the launches before
 // and behind it, 16384 pairs of 60 valid rows, d_ff = 128, rows not stored: 137.3 -> 127.2 us, with the views 145.5 -> 142.0.
+// A workgroup takes every (number of workgroups)-th pair, which sees every user's length, and deals them to its waves by their
+// valid rows (with waves a fixed 2048 pairs apart, all waves of 32 workgroups saw the same eight users of 64): lengths uniform in
+// [200, 1000], w = 10, 64 x 256 pairs, with the views and the launches around it 156 -> 145 us, 30 x 100 pairs 56 -> 47; by an LDS
+// counter instead, which would make the sums of a pair depend on the run, 147 and 50. Equal lengths 206 us either way.
 #include "segment_ffn_tile.h"
 
 namespace laser {
@@ -97,6 +101,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   // work, rows 3 slot + part of pitch RPP (16 rows read at once start in different banks)
   constexpr int RVB = 512, RPP = D * 2 + 16, RPB = 6 * RPP;
   constexpr int WPO = FM_ROWS * OP;        // the weights' parts: six rows of 64 bytes behind the patch's rows
+  constexpr int DECKS = 16, NO_PAIR = 255;
   static_assert(WPO + 6 * 64 <= FM_PATCH, "the weights' parts fit behind the patch's rows");
   __shared__ __attribute__((aligned(1024))) unsigned char W1L[FM_W1B];
   __shared__ __attribute__((aligned(1024))) unsigned char W2L[DFF * FM_ROWB];
@@ -104,6 +109,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char rvec[FM_WAVES * 2 * RVB];
   __shared__ __attribute__((aligned(16))) unsigned char rparts[FM_WAVES * RPB];
   __shared__ __attribute__((aligned(16))) float vecs[DFF + 3 * D];                    // b1, b2, ln_g, ln_b
+  __shared__ unsigned char dealt[DECKS][64];                                          // the waves' pairs, 64 at a time, eight a wave
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -111,8 +117,8 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   const unsigned land = __builtin_amdgcn_readfirstlane(ffn_lds_addr(opatch));
   unsigned char* rmine = rvec + wave * 2 * RVB;
   const unsigned rland = __builtin_amdgcn_readfirstlane(ffn_lds_addr(rmine));
-  const int stride = gridDim.x * FM_WAVES;
-  const int pr0 = blockIdx.x * FM_WAVES + wave;   // the wave's k-th pair is pr0 + k * stride
+  const int stride = gridDim.x;
+  const int pr0 = blockIdx.x;   // the workgroup's k-th pair is pr0 + k * stride
   // segments of pair p that hold a valid item (the first ones)
   auto valid_segments = [&](int p) {
     const int n = (valid_len(lens, pair_user(cand_off, U, C, p), L) + w - 1) / w;
@@ -120,13 +126,53 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   };
   constexpr int LPR = D / 8, RPI = 64 / LPR;
   const int nr = (MR && recent) ? (r < S ? r : S) : 0;
-  // The wave's first pair at or after its k-th that has a valid segment (nvk > 0), else nvk = 0. Every pair of the
+  ffn_park_weights<DFF>(__builtin_amdgcn_readfirstlane(ffn_lds_addr(W1L)), __builtin_amdgcn_readfirstlane(ffn_lds_addr(W2L)),
+                        vecs, w1, w2, b1, b2, ln_g, ln_b, tid);
+  // The workgroup's pairs, 64 at a time, are dealt to its waves by their valid segments: in that order (by number among equals)
+  // to waves 0 .. 7, 7 .. 0, 0 .. 7 and so on. Wave i works this out for the i-th 64 of every 512 and leaves each wave's pairs, by
+  // number, in LDS. With no more than a pair for every wave, and past the table, a wave's pairs are every eighth.
+  const int in_table = P > FM_WAVES * stride ? FM_WAVES * DECKS : 0;   // the pairs of a wave that are dealt this way
+  if (in_table) {
+    for (int c = wave; c < DECKS && pr0 + 64 * c * stride < P; c += FM_WAVES) {
+      const int p = pr0 + (64 * c + lane) * stride;
+      int key = 63 - lane;
+      if (p < P) {
+        const int n = (valid_len(lens, pair_user(cand_off, U, C, p), L) + w - 1) / w;
+        key += (n < S ? n : S) * 64;
+      }
+      int rank = 0;
+#pragma unroll
+      for (int j = 0; j < 64; ++j) rank += __builtin_amdgcn_readlane(key, j) > key ? 1 : 0;
+      const int turn = rank & (2 * FM_WAVES - 1), to = turn < FM_WAVES ? turn : 2 * FM_WAVES - 1 - turn;
+      int at = 0;
+#pragma unroll
+      for (int i = 0; i < FM_WAVES; ++i) {
+        const unsigned long long deck = __ballot(p < P && to == i);
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(deck >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)deck, 0));
+        at = to == i ? before : at;
+      }
+      dealt[c][lane] = NO_PAIR;
+      if (p < P) dealt[c][to * FM_WAVES + at] = (unsigned char)lane;
+    }
+    __syncthreads();
+  }
+  int turn = 0;   // pairs of this wave so far
+  // The wave's next pair that has a valid segment (nvk > 0), else nvk = 0. Every pair of the
   // wave is looked at here exactly once, in order, and gets what the tiles never touch: the rows of its segments
   // without a valid item leave as zeros, and a pair without any has p = 0 and a pooled maximum of zeros.
-  auto next_pair = [&](int k, int& nvk) {
+  auto next_pair = [&](int& nvk) {
     nvk = 0;
-    while (pr0 + k * stride < P) {
+    int k = 0;
+    while (pr0 + 64 * (turn / FM_WAVES) * stride < P) {
+      k = FM_WAVES * turn + wave;
+      if (turn < in_table) {
+        const int b = __builtin_amdgcn_readfirstlane(dealt[turn / FM_WAVES][wave * FM_WAVES + turn % FM_WAVES]);
+        if (b == NO_PAIR) break;
+        k = 64 * (turn / FM_WAVES) + b;
+      }
       const int p = pr0 + k * stride;
+      if (p >= P) break;
+      ++turn;
       nvk = valid_segments(p);
       if (out)
         for (int i = nvk + lane / LPR; i < S; i += RPI)
@@ -137,7 +183,6 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
       if (nvk > 0) break;
       if (MR && pool) pool[(size_t)p * (D / 2) + lane] = 0u;
       *reinterpret_cast<f32x2*>(z + (size_t)p * D + 2 * lane) = f32x2{0.0f, 0.0f};
-      ++k;
     }
     return k;
   };
@@ -157,7 +202,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     t.na = nvk - off < FM_ROWS ? nvk - off : FM_ROWS;
     t.kB = k; t.nvB = 0; t.nb = 0;
     if (t.some && off + t.na == nvk) {
-      t.kB = next_pair(k + 1, t.nvB);
+      t.kB = next_pair(t.nvB);
       const int room = FM_ROWS - t.na;
       t.nb = t.nvB < room ? t.nvB : room;
     }
@@ -167,7 +212,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     if (t.a0 + t.na < t.nvA) return make_tile(t.kA, t.nvA, t.a0 + t.na, t.ord);   // A goes on
     if (t.nb < t.nvB) return make_tile(t.kB, t.nvB, t.nb, t.ord + 1);             // B goes on (or starts)
     int nvn = 0, kn = t.kB;
-    if (t.nvB > 0) kn = next_pair(t.kB + 1, nvn);                                  // B ended here as well
+    if (t.nvB > 0) kn = next_pair(nvn);                                  // B ended here as well
     return make_tile(kn, nvn, 0, t.ord + 2);
   };
   auto fetch_r = [&](int p, int slot) {   // 512 bytes: 16 per lane of the lower half of the wave
@@ -213,10 +258,8 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   };
 
   int nv0 = 0;
-  const int k0 = next_pair(0, nv0);
+  const int k0 = next_pair(nv0);
   Tile cur = make_tile(k0, nv0, 0, 0);
-  ffn_park_weights<DFF>(__builtin_amdgcn_readfirstlane(ffn_lds_addr(W1L)), __builtin_amdgcn_readfirstlane(ffn_lds_addr(W2L)),
-                        vecs, w1, w2, b1, b2, ln_g, ln_b, tid);
   if (cur.some) fetch_tile(cur);
 
   ffn_wait_fetches();

@@ -373,3 +373,33 @@ def test_ffn_gsta_rows_of_the_largest_values():
         assert np.array_equal(to_host_f64(pool)[u], sh[u, :, :nv].max(axis=1))
     # one row carries all the weight; its score decides which, and ties of 24 bits do not occur
     assert vec_rel_err(to_host_f64(z), to_host_f64(z2)) <= 1e-4
+
+
+# How pairs are dealt to a workgroup's waves (64 at a time by valid segments, a table of 16 such; one pair a wave and less: in turn):
+# a pair fewer and more than that, a second 64 begun, and calls past the table. Every pair against the two calls in a row.
+@pytest.mark.parametrize("U,C,S", [(2, 1024, 9), (3, 683, 9), (25, 82, 40), (5, 3277, 3), (17, 15421, 2), (17, 15425, 2)])
+def test_ffn_gsta_every_pair_is_dealt_once(U, C, S):
+    import torch
+    d, w = 128, 4
+    gen = torch.Generator(device="cuda").manual_seed(U * C)
+    rnd = lambda *s, sd=1.0, dt=torch.bfloat16: (torch.randn(*s, device="cuda", generator=gen) * sd).to(dt)
+    f32 = torch.float32
+    seg, t0 = rnd(U, C, S, d), rnd(U, C, d)
+    gsta = [rnd(1, d, d, sd=d ** -0.5) for _ in range(3)]
+    ffn = [rnd(d, d, sd=d ** -0.5), rnd(d, sd=0.3, dt=f32), rnd(d, d, sd=d ** -0.5), rnd(d, sd=0.3, dt=f32), 1 + rnd(d, sd=0.2, dt=f32),
+           rnd(d, sd=0.1, dt=f32)]
+    lens = torch.randint(0, S * w + 1, (U,), device="cuda", generator=gen, dtype=torch.int32)
+    lens[0], lens[1] = S * w, 0
+    print(f"{U} x {C} pairs of {S}", flush=True)
+    nan = lambda *s, dt=torch.bfloat16: torch.full(s, float("nan"), device="cuda", dtype=dt)
+    s_one, z_one, pool, _ = laser.laser_ffn_gsta_forward(seg, t0, *gsta, lens, *ffn, S * w, w, seg_out=nan(U, C, S, d),
+                                                         z_out=nan(U, C, d, dt=f32), r=0, pool_out=nan(U, C, d))
+    s_two = laser.laser_segment_ffn_forward(seg, lens, *ffn, S * w, w)
+    z_two = laser.laser_gsta_forward(s_two, t0, *gsta, lens, S * w, w)
+    torch.cuda.synchronize()
+    assert torch.equal(s_one, s_two)
+    assert ((z_one - z_two).norm(dim=-1) <= 1e-5 * z_two.norm(dim=-1)).all()
+    cnt = ((lens + w - 1) // w)[:, None, None, None]
+    valid = torch.arange(S, device="cuda")[None, None, :, None] < cnt
+    top = torch.where(valid, s_two.float(), float("-inf")).amax(2)
+    assert torch.equal(pool.float(), torch.where(cnt[:, :, 0] > 0, top, 0.0))
