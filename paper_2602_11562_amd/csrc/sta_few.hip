@@ -437,8 +437,8 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
 }
 
 // From three query rows per user on the vector-ALU kernels are bound by their arithmetic and this one by HBM; with one or
-// two rows both are near HBM and the vector-ALU kernels, with four times the waves in flight, are the better ones, except
-// for two rows of 64-wide keys and values. Lengths uniform in [L / 5, L], us before and here:
+// two rows both are near HBM, and in launches that the cache holds the vector-ALU kernels, with four times the waves in flight, are
+// the better ones, except for two rows of 64-wide keys and values. Before units were dealt by ticket, lengths uniform in [L / 5, L], us before and here:
 //   U, C, L, w             d_q = 32, d = 128    64, 64          128, 128        64, 128
 //   1500, 1, 1000, 10        63 -> 70           52 -> 47        109 -> 118       79 -> 93
 //   1000, 1, 2048, 256       76 -> 84           53 -> 58        117 -> 127       90 -> 103
@@ -467,10 +467,31 @@ static bool few_fills(const StaArgs& a) {
   return a.w > 10 || items >= (a.C == 4 ? 32768 : 8192);
 }
 
+// One or two rows in a launch past the cache, whose units are dealt by ticket. Two rows: the better form from 150 MB on but for 32 /
+// 128 in segments of ten items and less (U, L, w, lengths uniform, us of the vector-ALU kernels and here: 2000, 1000, 25: 128 / 128 179 and
+// 132, 64 / 128 128 and 103, 32 / 128 103 and 88; 1500, 1000, 10: 128 / 128 117 and 113, 32 / 128 77.6 and 78.1; 2000, 2000, 512: 229 and
+// 214, 151 and 142). One row: from 256 MB on, where the vector-ALU kernel gives a wave whole segments (short ones) and these are
+// long enough to fill the tiles (2000, 1000, 25: 64 / 64 90 and 63, 128 / 128 160 and 124, 64 / 128 117 and 97, 32 / 128 97 and 83; 1000, 1000,
+// 13: 32 / 128 43.7 and 50.0, 64 / 128 53.2 and 57.6). Log-uniform lengths leave most units empty and are the least good case here: 700,
+// 3000, 50: 64 / 64 37 and 31, 32 / 128 40.7 and 41.2; 1500, 1000, 40, 32 / 64 18 and 25, which stays, as do 128 / 64.
+static bool few_preferred_large(const StaArgs& a) {
+  if (a.k == a.v) return false;   // (read once by the vector-ALU kernels)
+  const long long bytes = (long long)a.U * a.L * (a.d_q + a.d) * 2;
+  if (a.C == 2) return bytes >= 150000000 && a.w >= (a.d_q == 32 && a.d == 128 ? 11 : 8);
+  if (a.C != 1 || bytes < 256000000) return false;
+  switch (a.d_q * 1000 + a.d) {
+    case 64064: return a.w >= 10 && a.w < 128;
+    case 128128: return a.w >= 16 && a.w < 64;
+    case 64128: return a.w >= 24 && a.w <= 64;
+    case 32128: return a.w >= 24 && a.w <= 50;
+    default: return false;
+  }
+}
+
 bool sta_few_supports(const StaArgs& a) {
   if (a.dt != LASER_BF16 || a.C > 8 || a.heads != 1 || a.softmax) return false;
   if (!(a.d_q == 32 || a.d_q == 64 || a.d_q == 128) || !(a.d == 64 || a.d == 128)) return false;
-  return (a.C > 2 || (a.C == 2 && a.d_q == 64 && a.d == 64)) && few_fills(a);
+  return (a.C > 2 || (a.C == 2 && a.d_q == 64 && a.d == 64) || few_preferred_large(a)) && few_fills(a);
 }
 
 laser_status sta_few_launch(const StaArgs& a) {

@@ -140,7 +140,9 @@ def test_folded(name):
 
 
 # Histories past the last-level cache, which are read with the non-temporal hint. rows, L, d_q, d, w, users (lengths full)
-@pytest.mark.parametrize("rows,dq,d,w", [(3, 64, 64, 10), (1, 64, 64, 10), (1, 64, 64, 100), (3, 128, 128, 64)])
+@pytest.mark.parametrize("rows,dq,d,w", [(3, 64, 64, 10), (1, 64, 64, 10), (1, 64, 64, 100), (3, 128, 128, 64), (2, 128, 128, 64),
+                                         (1, 128, 128, 20), (1, 64, 128, 30), (1, 32, 128, 30), (2, 32, 128, 11), (1, 32, 128, 10),
+                                         (2, 32, 64, 8)])
 def test_histories_past_the_cache(rows, dq, d, w):
     import torch
     L = 1000
