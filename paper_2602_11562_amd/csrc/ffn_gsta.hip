@@ -29,10 +29,10 @@
 // operations per word and the weighted sum row by row (a word, a weight from v_readlane, five to seven operations) were 350
 // of 1100 vector instructions, another hundred where two pairs met; the two products take 16 MFMAs. With the launches before
 // and behind it, 16384 pairs of 60 valid rows, d_ff = 128, rows not stored: 137.3 -> 127.2 us, with the views 145.5 -> 142.0.
-// A workgroup takes every (number of workgroups)-th pair, which sees every user's length, and deals them to its waves by their
-// valid rows (with waves a fixed 2048 pairs apart, all waves of 32 workgroups saw the same eight users of 64): lengths uniform in
-// [200, 1000], w = 10, 64 x 256 pairs, with the views and the launches around it 156 -> 145 us, 30 x 100 pairs 56 -> 47; by an LDS
-// counter instead, which would make the sums of a pair depend on the run, 147 and 50. Equal lengths 206 us either way.
+// With waves a fixed 2048 pairs apart, all waves of 32 workgroups see the same eight users of 64, and the longest histories decide: where
+// that matters a workgroup takes every 256th pair, which sees every user, and deals them to its waves by their valid rows (lengths
+// uniform in [200, 1000], w = 10, 64 x 256 pairs, with the views and the launches around it 154 -> 141 us; by an LDS counter, which
+// would make the sums of a pair depend on the run, 145).
 #include "segment_ffn_tile.h"
 
 namespace laser {
@@ -83,11 +83,15 @@ __device__ __forceinline__ float ffn_half_max(float v) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+constexpr int FG_DECKS = 16;
+
 // MR: also the two other views of Sec. 3.4.4 of the transformed rows: pool [P, D] bf16, the component-wise maximum
 // over the segments that hold a valid item (zeros when there is none), taken from the parked rows (tile rows past the
 // last one are copies of it, so they leave the maximum alone); recent [P, r, D] bf16, the first r rows as they would
 // be stored. Either may be null.
-template <int DFF, bool MR>
+// DEAL: a workgroup takes every (number of workgroups)-th pair and deals them to its waves by their valid rows (at most 64 FG_DECKS
+// pairs a workgroup); without it a wave takes every (number of waves)-th pair.
+template <int DFF, bool MR, bool DEAL>
 __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     const unsigned short* seg, const int32_t* __restrict__ lens, const unsigned short* __restrict__ w1,
     const float* __restrict__ b1, const unsigned short* __restrict__ w2, const float* __restrict__ b2,
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   // work, rows 3 slot + part of pitch RPP (16 rows read at once start in different banks)
   constexpr int RVB = 512, RPP = D * 2 + 16, RPB = 6 * RPP;
   constexpr int WPO = FM_ROWS * OP;        // the weights' parts: six rows of 64 bytes behind the patch's rows
-  constexpr int DECKS = 16, NO_PAIR = 255;
+  constexpr int NO_PAIR = 255;
   static_assert(WPO + 6 * 64 <= FM_PATCH, "the weights' parts fit behind the patch's rows");
   __shared__ __attribute__((aligned(1024))) unsigned char W1L[FM_W1B];
   __shared__ __attribute__((aligned(1024))) unsigned char W2L[DFF * FM_ROWB];
@@ -109,7 +113,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char rvec[FM_WAVES * 2 * RVB];
   __shared__ __attribute__((aligned(16))) unsigned char rparts[FM_WAVES * RPB];
   __shared__ __attribute__((aligned(16))) float vecs[DFF + 3 * D];                    // b1, b2, ln_g, ln_b
-  __shared__ unsigned char dealt[DECKS][64];                                          // the waves' pairs, 64 at a time, eight a wave
+  __shared__ unsigned char dealt[DEAL ? FG_DECKS : 1][64];                                          // the waves' pairs, 64 at a time, eight a wave
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -117,8 +121,9 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   const unsigned land = __builtin_amdgcn_readfirstlane(ffn_lds_addr(opatch));
   unsigned char* rmine = rvec + wave * 2 * RVB;
   const unsigned rland = __builtin_amdgcn_readfirstlane(ffn_lds_addr(rmine));
-  const int stride = gridDim.x;
-  const int pr0 = blockIdx.x;   // the workgroup's k-th pair is pr0 + k * stride
+  // pairs pr0 + k * stride: the workgroup's, or the wave's
+  const int stride = DEAL ? gridDim.x : gridDim.x * FM_WAVES;
+  const int pr0 = DEAL ? blockIdx.x : blockIdx.x * FM_WAVES + wave;
   // segments of pair p that hold a valid item (the first ones)
   auto valid_segments = [&](int p) {
     const int n = (valid_len(lens, pair_user(cand_off, U, C, p), L) + w - 1) / w;
@@ -130,10 +135,11 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
                         vecs, w1, w2, b1, b2, ln_g, ln_b, tid);
   // The workgroup's pairs, 64 at a time, are dealt to its waves by their valid segments: in that order (by number among equals)
   // to waves 0 .. 7, 7 .. 0, 0 .. 7 and so on. Wave i works this out for the i-th 64 of every 512 and leaves each wave's pairs, by
-  // number, in LDS. With no more than a pair for every wave, and past the table, a wave's pairs are every eighth.
-  const int in_table = P > FM_WAVES * stride ? FM_WAVES * DECKS : 0;   // the pairs of a wave that are dealt this way
-  if (in_table) {
-    for (int c = wave; c < DECKS && pr0 + 64 * c * stride < P; c += FM_WAVES) {
+  // number, in LDS.
+  if constexpr (DEAL) {
+    for (int c = wave; c < FG_DECKS; c += FM_WAVES) {
+      dealt[c][lane] = NO_PAIR;
+      if (pr0 + 64 * c * stride >= P) continue;
       const int p = pr0 + (64 * c + lane) * stride;
       int key = 63 - lane;
       if (p < P) {
@@ -151,7 +157,6 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
         const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(deck >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)deck, 0));
         at = to == i ? before : at;
       }
-      dealt[c][lane] = NO_PAIR;
       if (p < P) dealt[c][to * FM_WAVES + at] = (unsigned char)lane;
     }
     __syncthreads();
@@ -163,16 +168,18 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   auto next_pair = [&](int& nvk) {
     nvk = 0;
     int k = 0;
-    while (pr0 + 64 * (turn / FM_WAVES) * stride < P) {
-      k = FM_WAVES * turn + wave;
-      if (turn < in_table) {
+    while (true) {
+      if constexpr (DEAL) {
+        if (turn == FG_DECKS * FM_WAVES) break;
         const int b = __builtin_amdgcn_readfirstlane(dealt[turn / FM_WAVES][wave * FM_WAVES + turn % FM_WAVES]);
         if (b == NO_PAIR) break;
         k = 64 * (turn / FM_WAVES) + b;
+      } else {
+        k = turn;
+        if (pr0 + k * stride >= P) break;
       }
-      const int p = pr0 + k * stride;
-      if (p >= P) break;
       ++turn;
+      const int p = pr0 + k * stride;
       nvk = valid_segments(p);
       if (out)
         for (int i = nvk + lane / LPR; i < S; i += RPI)
@@ -505,13 +512,23 @@ laser_status ffn_gsta_fused_launch(const FfnArgs& f, const GstaArgs& g) {
   long long blocks = ((long long)P + FM_WAVES - 1) / FM_WAVES;
   if (blocks > 256) blocks = 256;   // one workgroup per compute unit (LDS), each wave walking several pairs
   const bool views = g.pool_out != nullptr || g.recent_out != nullptr;
-#define LASER_FFN_POOL(FF, MRF)                                                                                       \
-  hipLaunchKernelGGL((ffn_pool_kernel<FF, MRF>), dim3((unsigned)blocks), dim3(FM_THREADS), 0, f.stream,               \
+  // Pairs are dealt where lengths differ and a pair fills most of a tile or more: lengths uniform, w = 10, d_ff = 128, with the views and
+  // the launches around it, in turn and dealt: S = 100 64 x 256 pairs 154 and 141 us, S = 48 94 x 200 115 and 110, S = 28 91.5 and 90.6;
+  // S = 20 82.1 and 82.8, S = 8 69.5 and 71.5 (two pairs share a tile however long they are); equal lengths, S = 100 201 either way.
+  const bool deal = f.lens != nullptr && f.S > 24 && P > FM_WAVES * blocks && P <= 64 * FG_DECKS * blocks;
+#define LASER_FFN_POOL(FF, MRF, DEAL)                                                                                       \
+  hipLaunchKernelGGL((ffn_pool_kernel<FF, MRF, DEAL>), dim3((unsigned)blocks), dim3(FM_THREADS), 0, f.stream,               \
                      (const unsigned short*)f.seg, f.lens, (const unsigned short*)f.w1, f.b1,                        \
                      (const unsigned short*)f.w2, f.b2, f.ln_g, f.ln_b, f.cand_off, f.U, P, f.C, f.L, f.w, f.S, f.eps, \
                      (unsigned short*)f.seg_out, g.z_out, (unsigned*)g.pool_out, (unsigned short*)g.recent_out, g.r)
-  if (f.d_ff == 64) { if (views) LASER_FFN_POOL(64, true); else LASER_FFN_POOL(64, false); }
-  else { if (views) LASER_FFN_POOL(128, true); else LASER_FFN_POOL(128, false); }
+#define LASER_FFN_POOL_AS(FF, MRF)                                                                                    \
+  do {                                                                                                                \
+    if (deal) LASER_FFN_POOL(FF, MRF, true);                                                                          \
+    else LASER_FFN_POOL(FF, MRF, false);                                                                              \
+  } while (0)
+  if (f.d_ff == 64) { if (views) LASER_FFN_POOL_AS(64, true); else LASER_FFN_POOL_AS(64, false); }
+  else { if (views) LASER_FFN_POOL_AS(128, true); else LASER_FFN_POOL_AS(128, false); }
+#undef LASER_FFN_POOL_AS
 #undef LASER_FFN_POOL
   s = launch_status();
   if (s != LASER_OK) return s;

@@ -80,10 +80,13 @@ __device__ __forceinline__ void ffn_fetch_rows(const unsigned short* rows0, int 
 // The wave's 32 rows from the landing area as the B operand of the first product: lane (l32, h) holds components
 // 16 ks + 8 h .. + 7 of row l32.
 __device__ __forceinline__ void ffn_read_rows(const unsigned char* land, int l32, int h, bf16x8 (&xreg)[FM_D / 16]) {
-  const unsigned char* row = land + l32 * FM_ROWB;
+  // (`land` is 1 KB-aligned, so the other chunks' addresses are the first one's with bits turned over; worked out from a value
+  // the compiler cannot tell from a fresh one: kept over the tiles, the eight addresses are spilled)
+  unsigned at = ffn_lds_addr(land) + l32 * FM_ROWB + ((h ^ (l32 & 15)) << 4);
+  asm volatile("" : "+v"(at));
 #pragma unroll
   for (int ks = 0; ks < FM_D / 16; ++ks)
-    xreg[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(row + (((2 * ks + h) ^ (l32 & 15)) << 4)));
+    xreg[ks] = __builtin_bit_cast(bf16x8, *(__attribute__((address_space(3))) const u32x4*)(size_t)(at ^ (ks << 5)));
 }
 
 // The compiler folds "lane offset + tile offset + constant" into one three-operand add per read; hiding the sum of

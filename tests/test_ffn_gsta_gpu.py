@@ -375,9 +375,11 @@ def test_ffn_gsta_rows_of_the_largest_values():
     assert vec_rel_err(to_host_f64(z), to_host_f64(z2)) <= 1e-4
 
 
-# How pairs are dealt to a workgroup's waves (64 at a time by valid segments, a table of 16 such; one pair a wave and less: in turn):
-# a pair fewer and more than that, a second 64 begun, and calls past the table. Every pair against the two calls in a row.
-@pytest.mark.parametrize("U,C,S", [(2, 1024, 9), (3, 683, 9), (25, 82, 40), (5, 3277, 3), (17, 15421, 2), (17, 15425, 2)])
+# How pairs come to a workgroup's waves (more than 24 segments: 64 at a time by valid segments, a table of 16 such; few segments, a pair
+# a wave and less, and more pairs than the table holds: in turn): a pair fewer and more than one a wave, a second 64 begun, either side
+# of the line. Every pair against the two calls in a row.
+@pytest.mark.parametrize("U,C,S", [(2, 1024, 25), (3, 683, 25), (25, 82, 40), (5, 3277, 25), (5, 3277, 24), (17, 1000, 33), (17, 15421, 2),
+                                   (17, 15421, 25)])
 def test_ffn_gsta_every_pair_is_dealt_once(U, C, S):
     import torch
     d, w = 128, 4
