@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "liblaser.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 SOURCES = ["laser_api.hip", "sta_generic.hip", "sta_f32.hip", "sta_mfma.hip", "sta_ring.hip", "sta_stream.hip", "sta_few.hip", "gsta_generic.hip",
-           "gsta_tiled.hip", "gsta_one.hip", "fused_forward.hip", "multires.hip", "segment_ffn.hip", "ffn_gsta.hip", "project.hip", "sta_backward.hip", "sta_backward_mfma.hip", "gsta_backward.hip", "gsta_backward_tile.hip"]
+           "gsta_tiled.hip", "gsta_one.hip", "gsta_project.hip", "fused_forward.hip", "multires.hip", "segment_ffn.hip", "ffn_gsta.hip", "project.hip", "sta_backward.hip", "sta_backward_mfma.hip", "gsta_backward.hip", "gsta_backward_tile.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

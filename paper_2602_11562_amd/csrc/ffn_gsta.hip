@@ -3,10 +3,10 @@
 // their softmax weights while they are still on chip, so the transformed H' is neither written nor read back
 // (it is written as well when the caller wants it). One layer, bf16, d = 128, d_ff in {64, 128}.
 //
-// Three launches, the outer two shared with the split form of GSTA (gsta_one.hip):
-//   gsta_r_kernel     r = (t0 W_q) W_k^T / sqrt(d)   tiles of 32 pairs, MFMA                       -> z rows
+// Three launches, the outer two shared with the split form of GSTA (gsta_project.hip):
+//   gsta_r_kernel     r = (t0 W_q) W_k^T / sqrt(d)   tiles of 16 pairs, MFMA                       -> z rows
 //   ffn_pool_kernel   below: a wave walks pairs       H' rows -> s rows (on chip), z rows (r) -> z rows (p)
-//   gsta_out_kernel   z = t0 + p W_v                  tiles of 32 pairs, MFMA             z rows -> z rows
+//   gsta_out_kernel   z = t0 + p W_v                  tiles of 16 pairs, MFMA             z rows -> z rows
 // with p = sum_i a_i s_i, a = softmax over the segments that hold a valid item of r . s_i (the attention equation
 // with its products re-associated, which is exact).
 //
