@@ -375,14 +375,27 @@ __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short*
   }
 }
 
-__global__ __launch_bounds__(256) void sta_bwd_dq_kernel(const float* __restrict__ dq_part, int groups, int row,
-                                                         long long total, float* __restrict__ dq_out) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;   // element of dq [U, C * dq]
+// dq[u] = the sum of the user's partial rows in the order of the runs: four consecutive elements a thread (row: pieces of a user; d_q is a
+// multiple of eight), sixteen runs' in flight. The launch is one trip to memory: with a 64-bit division, and a load awaited before the next, 2048 users x
+// 32 elements of 9 runs took the backward pass 195.7 us, now 193.4, 64 x 4096 of 8 runs 31.8 and 30.1.
+__global__ __launch_bounds__(64) void sta_bwd_dq_kernel(const float* __restrict__ dq_part, int groups, int row, MulDiv by_row,
+                                                        unsigned total, float* __restrict__ dq_out) {
+  typedef float Piece __attribute__((ext_vector_type(4)));
+  constexpr int AHEAD = 16;
+  const unsigned e = blockIdx.x * 64 + threadIdx.x;
   if (e >= total) return;
-  const long long u = e / row, r = e - u * row;
-  float s = 0.0f;
-  for (int g = 0; g < groups; ++g) s += dq_part[(u * groups + g) * row + r];
-  dq_out[e] = s;
+  const unsigned u = by_row.div(e), r = e - u * row;
+  const Piece* src = reinterpret_cast<const Piece*>(dq_part) + (size_t)u * groups * row + r;
+  Piece s = (Piece)(0.0f);
+  for (int g0 = 0; g0 < groups; g0 += AHEAD) {
+    Piece x[AHEAD];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) x[k] = src[(size_t)(g0 + k < groups ? g0 + k : groups - 1) * row];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+      if (g0 + k < groups) s += x[k];
+  }
+  reinterpret_cast<Piece*>(dq_out)[e] = s;
 }
 
 // runs of segments per user: enough workgroups to fill the machine a few times over, whole users when there are many
@@ -520,8 +533,10 @@ laser_status sta_backward_launch(const StaBwdArgs& a) {
   else sta_bwd_launch_q<float>(a, (unsigned)blocks, lds, spg, groups);
   if (launch_status() != LASER_OK) return LASER_ERR_LAUNCH;
   const long long total = (long long)a.U * a.C * a.d_q;
-  hipLaunchKernelGGL(sta_bwd_dq_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, a.stream, a.work, groups,
-                     a.C * a.d_q, total, a.dq);
+  const int row = a.C * a.d_q / 4;                     // (a.work and a.dq are 16-byte aligned)
+  const unsigned pieces = (unsigned)(total / 4);       // (total fits an int)
+  hipLaunchKernelGGL(sta_bwd_dq_kernel, dim3((pieces + 63) / 64), dim3(64), 0, a.stream, a.work, groups, row, mul_div((unsigned)row), pieces,
+                     a.dq);
   return launch_status();
 }
 
