@@ -224,20 +224,22 @@ __global__ __launch_bounds__(GB_THREADS) void gsta_bwd_kernel(const T* __restric
 }
 
 // dW[l][x][y] = sum over pairs of A[pair][l][x] * B[pair][l][y]: a contraction over the pairs, on the fp32 matrix
-// instructions. A workgroup owns a 16 x 16 tile of one matrix; its sixteen waves take every sixteenth run of four pairs (the
-// four k-slots of an MFMA, operands straight from the scratch in 64-byte runs, eight steps in flight) and add up in LDS in a
-// fixed order. With few tiles (d = 64, one or two layers) the pairs are cut into eight chunks as well, one per XCD (the
+// instructions. A workgroup owns a 16 x 16 tile of one matrix; its sixteen waves take every sixteenth run of sixteen pairs (16 bytes
+// a lane of either side, AHEAD runs requested at once, which cross a wave's place in LDS into the operands of four MFMAs) and add up
+// in LDS in a fixed order. With few tiles (d = 64, one or two layers) the pairs are cut into eight chunks as well, one per XCD (the
 // workgroup number modulo eight), whose matrices a second launch adds: the launch is bound by what the eight L2s fetch, and
 // so each fetches an eighth of the vectors instead of all. 4096 pairs, d = 64: 10.3 us for the two launches, 15 us without
 // chunks; 2048 pairs, d = 128: 9.8 us without, 12.9 us with them. (The form before, tiles of 32 x 32 on the vector ALUs in up
-// to 32 chunks: 25 and 30 us.)
+// to 32 chunks: 25 and 30 us. Operands fetched as they are, four bytes a lane: the whole pass of 1000 pairs, d = 64 20.3 -> 18.8 us,
+// 4096 21.6 -> 21.1; d = 128, 200 pairs 14.7 -> 14.3, 2048 38.7 -> 38.3.)
 constexpr int GB_CHUNKS = 8;
+template <int AHEAD>
 __global__ __launch_bounds__(1024) void gsta_bwd_w_kernel(const float* __restrict__ pv, int P, int M, int d, int chunks,
                                                           float* __restrict__ part, float* __restrict__ dwq,
                                                           float* __restrict__ dwk, float* __restrict__ dwv) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  constexpr int NW = 16, AHEAD = 8;
-  __shared__ f32x4 red[NW][64];
+  constexpr int NW = 16;
+  __shared__ __attribute__((aligned(16))) float stage[NW][2][16][16];   // a wave's 16 pairs x 16 columns of both sides; then its sums
   const int tiles = (d + 15) / 16;
   int bid = blockIdx.x;
   const int chunk = bid % chunks;
@@ -249,28 +251,37 @@ __global__ __launch_bounds__(1024) void gsta_bwd_w_kernel(const float* __restric
   const int which = bid % 3, l = bid / 3;   // 0: dW_v (p, do), 1: dW_k (dr, q'), 2: dW_q (t_l, dq')
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int x = tx * 16 + l16 < d ? tx * 16 + l16 : d - 1, y = ty * 16 + l16 < d ? ty * 16 + l16 : d - 1;
+  // a lane's piece: columns 4 (lane % 4) .. of pair lane / 4 of sixteen (past the matrix: its last ones, whose sums are not stored)
+  const int x = tx * 16 + 4 * (lane & 3) < d ? tx * 16 + 4 * (lane & 3) : d - 4, y = ty * 16 + 4 * (lane & 3) < d ? ty * 16 + 4 * (lane & 3) : d - 4;
   const float* a = pv + ((size_t)l * 6 + 2 * which) * d + x;
   const float* b = pv + ((size_t)l * 6 + 2 * which + 1) * d + y;
   const size_t stride = (size_t)M * 6 * d;
   const int per = ((P + chunks - 1) / chunks + 3) / 4 * 4;
   const int beg = chunk * per, end = beg + per < P ? beg + per : P;
-  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int p0 = beg + wave * 4; p0 < end; p0 += 4 * NW * AHEAD) {
-    float av[AHEAD], bv[AHEAD];
+  const f32x4 none = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 acc = none;
+  for (int p0 = beg + wave * 16; p0 < end; p0 += 16 * NW * AHEAD) {
+    f32x4 av[AHEAD], bv[AHEAD];
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s) {
-      const int p = p0 + s * 4 * NW + g;
+      const int p = p0 + s * 16 * NW + (lane >> 2);
       const size_t at = (size_t)(p < end ? p : end - 1) * stride;
-      av[s] = a[at];
-      bv[s] = b[at];
+      av[s] = *reinterpret_cast<const f32x4*>(a + at);
+      bv[s] = *reinterpret_cast<const f32x4*>(b + at);
     }
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s) {        // pairs past the end of the chunk add nothing
-      const bool ok = p0 + s * 4 * NW + g < end;
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? av[s] : 0.0f, ok ? bv[s] : 0.0f, acc, 0, 0, 0);
+      const bool ok = p0 + s * 16 * NW + (lane >> 2) < end;
+      *reinterpret_cast<f32x4*>(&stage[wave][0][lane >> 2][4 * (lane & 3)]) = ok ? av[s] : none;
+      *reinterpret_cast<f32x4*>(&stage[wave][1][lane >> 2][4 * (lane & 3)]) = ok ? bv[s] : none;
+      __builtin_amdgcn_wave_barrier();       // (LDS operations of a wave execute in order)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(stage[wave][0][4 * j + g][l16], stage[wave][1][4 * j + g][l16], acc, 0, 0, 0);
+      __builtin_amdgcn_wave_barrier();
     }
   }
+  f32x4(*red)[128] = reinterpret_cast<f32x4(*)[128]>(stage);   // (a wave's own place)
   red[wave][lane] = acc;
   __syncthreads();
   if (tid >= 256) return;
@@ -354,8 +365,9 @@ laser_status gsta_backward_launch(const GstaBwdArgs& a) {
   if (launch_status() != LASER_OK) return LASER_ERR_LAUNCH;
   const int wgs = gsta_bwd_workgroups(a.d, a.M), chunks = gsta_bwd_chunks((size_t)P, a.d, a.M);
   float* part = a.work + (size_t)P * a.M * 6 * a.d;
-  hipLaunchKernelGGL(gsta_bwd_w_kernel, dim3((unsigned)(chunks * wgs)), dim3(1024), 0, a.stream, a.work, P, a.M, a.d, chunks,
-                     part, a.dwq, a.dwk, a.dwv);
+  // (a wave's runs: P / chunks / 256)
+  auto kern = P / chunks >= 1024 ? gsta_bwd_w_kernel<4> : gsta_bwd_w_kernel<2>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(chunks * wgs)), dim3(1024), 0, a.stream, a.work, P, a.M, a.d, chunks, part, a.dwq, a.dwk, a.dwv);
   const laser_status st = launch_status();
   if (chunks == 1 || st != LASER_OK) return st;
   const long long per_matrix = (long long)a.M * a.d * a.d;
