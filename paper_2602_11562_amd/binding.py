@@ -53,6 +53,7 @@ def load_library() -> ctypes.CDLL:
         raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2602_11562_amd.build` "
                           "(there is no CPU or PyTorch fallback)")
     lib = ctypes.CDLL(LIB_PATH)
+    lib.forward_address = ctypes.cast(lib.laser_forward, ctypes.c_void_p).value
     vp, ip, i32, f32 = ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_float
     lib.laser_sta_forward.argtypes = [vp, vp, vp, ip, i32, i32, i32, i32, i32, i32, f32, i32, vp, ip, vp]
     lib.laser_sta_forward_variant.argtypes = lib.laser_sta_forward.argtypes + [i32]
@@ -157,9 +158,27 @@ def laser_gsta_kernel_name(C: int, S: int, d: int, dt: int, M: int = 1) -> str:
 
 # ----------------------------------------------------------------------------- tensor marshalling
 # A small request is a few microseconds of kernels: what every call does here is kept to attribute reads (the torch module is
-# looked up once, the stream's handle is read without building a Stream object, 3.0 -> 0.3 us). 16 candidates, L = 1024: the host part
-# of laser_forward 14.5 -> 11.0 us, 7.5 of them the call with its two launches.
+# looked up once, the stream's handle is read without building a Stream object, 3.0 -> 0.3 us), and laser_forward, the call of single
+# requests, hands tensors over in native code where they are of the ordinary form. 16 candidates, L = 1024, 8 us of kernels: passes in a
+# row 10.5 -> 8.5 us.
 _torch_module = None
+
+
+_fast_module = None
+
+
+def _fast():
+    """The native marshalling of calls of the ordinary form (csrc/binding_fast.cpp)."""
+    global _fast_module
+    if _fast_module is None:
+        _torch()     # (its libraries are the module's)
+        try:
+            from . import laser_fast
+        except ImportError as e:
+            raise ImportError("laser_fast.so is missing or was built for another torch: build it with "
+                              "`python -m paper_2602_11562_amd.build`") from e
+        _fast_module = laser_fast
+    return _fast_module
 
 
 def _torch():
@@ -723,6 +742,12 @@ def laser_forward(q, k, v, t0, wq, wk, wv, lens, w: int, gamma: float, seg_out=N
     """The whole path. Returns (H' [U,C,S,d], cnt [U,S] or None, z [U,C,d] fp32); with want_seg=False seg_out is passed
     as NULL (H' is never stored: the fused kernels, one layer only) and None comes back in its place."""
     torch = _torch()
+    if q.is_cuda and seg_out is not None and z_out is not None and (seg_cnt is not None or not want_cnt):
+        code = _fast().forward(load_library().forward_address, q, k, v, t0, wq, wk, wv, lens, w, gamma, seg_out, seg_cnt, z_out,
+                               _stream(stream))
+        if code is not None:
+            _check(code, "laser_forward")
+            return seg_out, seg_cnt, z_out
     U, C, d_q = q.shape
     L, d = v.shape[1], v.shape[2]
     M = wq.shape[0]

@@ -1,4 +1,4 @@
-"""Build liblaser.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Build liblaser.so (HIP kernels + C ABI) for gfx950 with hipcc and laser_fast.so (the binding's native part) with g++, in-tree.
 
     python -m paper_2602_11562_amd.build
 
@@ -17,6 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblaser.so")
+FAST = os.path.join(HERE, "laser_fast.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 SOURCES = ["laser_api.hip", "sta_generic.hip", "sta_f32.hip", "sta_mfma.hip", "sta_ring.hip", "sta_stream.hip", "sta_few.hip", "gsta_generic.hip",
@@ -51,7 +52,7 @@ def _compile(src: str, extra=()) -> str:
 
 
 def build_library(jobs: int = 6, tuning: bool = False, out: str = LIB) -> str:
-    """Compile every HIP source and link liblaser.so. Always rebuilds. `tuning` builds the variant whose launch
+    """Compile every HIP source and link liblaser.so, and the binding's native part beside it. Always rebuilds. `tuning` builds the variant whose launch
     shapes can be overridden through environment variables (parameter sweeps only; never the shipped library)."""
     os.makedirs(OBJDIR, exist_ok=True)
     extra = ("-DLASER_TUNING",) if tuning else ()
@@ -62,6 +63,26 @@ def build_library(jobs: int = 6, tuning: bool = False, out: str = LIB) -> str:
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    os.replace(tmp, out)
+    if out == LIB:
+        build_fast_binding()
+    return out
+
+
+def build_fast_binding(out: str = FAST) -> str:
+    """Compile the binding's native part (csrc/binding_fast.cpp) against the headers of the installed torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = out + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *["-I" + d for d in include_paths()], "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding_fast.cpp"),
+           "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch_python", "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on binding_fast.cpp:\n" + r.stderr[-4000:])
     os.replace(tmp, out)
     return out
 

@@ -134,6 +134,25 @@ def test_binding_refuses_host_tensors():
     with pytest.raises(ValueError):
         laser.laser_sta_forward(x, torch.zeros(1, 4, 8), torch.zeros(1, 4, 8), None, 2, 1.0,
                                 seg_out=torch.zeros(1, 2, 2, 8), want_cnt=False)
+    w = torch.zeros(1, 8, 8)
+    with pytest.raises(ValueError):
+        laser.laser_forward(x, torch.zeros(1, 4, 8), torch.zeros(1, 4, 8), x, w, w, w, None, 2, 1.0, seg_out=torch.zeros(1, 2, 2, 8),
+                            z_out=torch.zeros(1, 2, 8), want_cnt=False)
+
+
+def test_the_native_marshalling_leaves_every_other_form_alone():
+    """Host tensors, subclasses, no tensors, numbers of other types and too few arguments: None, whatever the address."""
+    import torch
+
+    class Sub(torch.Tensor):
+        pass
+    forward = binding._fast().forward
+    x = torch.zeros(1, 2, 8)
+    good = [x] * 7 + [None, 2, 1.0, x, None, x, None]
+    assert forward(1, *good) is None                      # (host tensors)
+    for at, other in ((0, None), (0, x.as_subclass(Sub)), (3, "t0"), (8, 2.0), (8, 1 << 40), (9, 1), (10, None), (13, "stream")):
+        assert forward(1, *good[:at], other, *good[at + 1:]) is None
+    assert forward(1, *good[:-1]) is None and forward() is None
 
 
 @pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
