@@ -11,8 +11,8 @@
 // the right operand of acc^T += V^T P^T as it sits (k-slots = items {4g..4g+3, 16+4g..16+4g+3} of lane group g, fetched in
 // that order by the transpose load). A tile that crosses the end of a block is multiplied once per block. The gates are
 // fp32 and stay so: they enter the product as three bf16 parts (24 bits), three MFMAs on the same V operand.
-// Accumulator rows are dealt so that a lane ends with D / 4 consecutive columns of its (segment, query row), which leave
-// as 16-byte stores; in the folded form the same registers, rounded to bf16, are the operand of the product with W_v (in
+// Accumulator rows are dealt so that a lane ends with eight consecutive columns of every 32 of its (segment, query row), which leave
+// as 16-byte stores, 64 bytes of a row from four lanes; in the folded form the same registers, rounded to bf16, are the operand of the product with W_v (in
 // LDS in operand order, once per workgroup), and H' leaves with the sums.
 // A zero gate times an item that is not finite would spread over the block's other segments. When a finished block holds a
 // value that is not finite, the block is computed again, item by item over each column's own segment.
@@ -509,8 +509,9 @@ laser_status sta_few_launch(const StaArgs& a) {
 
 // The folded form: a is STA over the raw items (C query rows per user, heads of each candidate next to each other), p the
 // projection of its sums
-// 2048 users x 1 candidate x 2 heads, L = 1000, w = 10, lengths uniform in [200, 1000]: 112 us; the vector-ALU kernel over
-// the raw items and the projection of its stored sums took 101 + 33 us. More than four query rows do not fit the ring. With
+// 2048 users x 1 candidate x 2 heads, L = 1000, w = 10, lengths uniform in [200, 1000]: 83 us repeated on one batch (106 with a fixed
+// share of units for every wave, the sums through the cache and in 16-byte pieces); the vector-ALU kernel over the raw items and the
+// projection of its stored sums took 101 + 33 us. More than four query rows do not fit the ring. With
 // one or two rows, long segments and few of them the separate launches are the better ones, as above (whole chain, L = 1000,
 // w = 1000: 16 users x 1 row 21 us, 35 here; 64 x 2 rows 32 and 36; 64 x 1, L = 4000, w = 500 the same time).
 bool sta_few_folded_supports(const StaArgs& a, const ProjHeadsArgs& p) {
