@@ -122,7 +122,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
   __builtin_assume(M > 0);                                        // (or the loads move behind a branch on it)
   __builtin_amdgcn_sched_barrier(0);                              // (widened any earlier, t waits for its load ahead of the others)
   f32x4 t = X::wide4(traw);
-  auto put_tile = [&](typename X::Act& b, const f32x4& x) { X::put4(b, l16, c4, x); };
+  auto put_tile = [&](typename X::Act& b, const f32x4& x) { X::template put4<PW>(b, l16, c4, x); };
   auto put_scratch = [&](int l, int slot, const f32x4& x) {       // one of the six vectors of a pair and layer
     if (mine4) *reinterpret_cast<f32x4*>(pv + (((size_t)(pbase + l16) * M + l) * 6 + slot) * D + c4) = x;
   };
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     for (int e = tid; e < PW * D; e += 4 * D) {                   // p: to the scratch, and as an operand where t goes on
       const int j = e / D, y = e % D;
       const float x = rr_of(j, l)[2 * RP + y];
-      if (more) X::put(ba, j, y, x);
+      if (more) X::template put<PW>(ba, j, y, x);
       if (pbase + j < P) pv[(((size_t)(pbase + j) * M + l) * 6) * D + y] = x;
     }
     if (more) {
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
           for (int k = 0; k < R; ++k) h[k] = ahead[k];
       }
       gather(i, acc, scale, [&](int j, int y, float x) {
-        X::put(bb, j, y, x);
+        X::template put<PW>(bb, j, y, x);
         if (pbase + j < P) pv[(((size_t)(pbase + j) * M + l) * 6 + 2) * D + y] = x;
       });
     }
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(4 * D) void gsta_bwd_tile_kernel(const T* __restric
     if (l > 0) X::load_rows(rv, wv + here - (size_t)D * D, n0, lane);
     __syncthreads();
     over_waves(scale, [&](int j, int y, float x) {
-      X::put(bb, j, y, x);
+      X::template put<PW>(bb, j, y, x);
       if (pbase + j < P) pv[(((size_t)(pbase + j) * M + l) * 6 + 2) * D + y] = x;
     });
     const f32x4 dq = X::template product<PW>(bb, ok_, lane);                   // dq' = dr W_k

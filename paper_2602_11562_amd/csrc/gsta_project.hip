@@ -25,7 +25,7 @@ __global__ __launch_bounds__(4 * D, 4) void gsta_r_kernel(const unsigned short* 
                                                           float* __restrict__ z) {
   typedef Prod<unsigned short, D> X;
   constexpr int NW = D / 16;
-  __shared__ __attribute__((aligned(16))) unsigned short bt[16 * X::PITCH];
+  __shared__ __attribute__((aligned(16))) unsigned short bt[16 * D];
   __shared__ __attribute__((aligned(16))) typename X::Act bq;
   __shared__ __attribute__((aligned(16))) unsigned char patches[NW][X::PATCH];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
@@ -44,14 +44,14 @@ __global__ __launch_bounds__(4 * D, 4) void gsta_r_kernel(const unsigned short* 
   const typename X::Operand oq = X::transposed(cq, patches[wave], lane);
   const float scale = 1.0f / sqrtf((float)D);
   for (; tile < tiles; tile += gridDim.x) {
-    *reinterpret_cast<u32x2*>(bt + row * X::PITCH + col) = raw;
+    *reinterpret_cast<u32x2*>(bt + X::template at<16>(0, row, col)) = raw;
     if (tile + (int)gridDim.x < tiles) raw = rows_of(tile + gridDim.x);
     __syncthreads();
     f32x4 q = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int k = 0; k < D / 32; ++k)
-      q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oq.x[k], *reinterpret_cast<const bf16x8*>(bt + l16 * X::PITCH + k * 32 + g * 8), q, 0, 0, 0);
-    X::put4(bq, l16, c4, q);
+      q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oq.x[k], *reinterpret_cast<const bf16x8*>(bt + X::template at<16>(0, l16, k * 32 + g * 8)), q, 0, 0, 0);
+    X::template put4<16>(bq, l16, c4, q);
     __syncthreads();   // (ahead of it every wave has read bt, ahead of the next tile's first one bq)
     const f32x4 r = X::template product<16>(bq, rk, lane) * scale;
     if (tile * 16 + l16 < P) *reinterpret_cast<f32x4*>(z + (size_t)(tile * 16 + l16) * D + c4) = r;
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(4 * D, 4) void gsta_out_kernel(const unsigned short
   typename X::Raw4 t = *reinterpret_cast<const typename X::Raw4*>(t0 + clamped(tile * 16 + l16) + c4);
   const typename X::Operand ov = X::transposed(cv, patches[wave], lane);
   for (int buf = 0; tile < tiles; tile += gridDim.x, buf ^= 1) {
-    X::put4(bp[buf], row, col, p);
+    X::template put4<16>(bp[buf], row, col, p);
     const f32x4 base = X::wide4(t);
     if (const int next = tile + gridDim.x; next < tiles) {
       p = *reinterpret_cast<const f32x4*>(z + clamped(next * 16 + row) + col);

@@ -96,16 +96,19 @@ __device__ __forceinline__ float softmax_ref(float m) { return m == -INFINITY ? 
 template <typename T, int D> struct Prod;
 
 template <int D> struct Prod<float, D> {
-  static constexpr int PITCH = D + 4;                       // 16 bytes past a multiple of 256: conflict-free row reads
+  static constexpr int PITCH = D + 4;                       // 16 bytes past a multiple of 256
   struct Act { float v[16 * PITCH]; };
+  template <int PW> static constexpr bool turned() { return false; }
   static constexpr int NCOL = D / 16;                       // 16-byte pieces of a wave's 16 columns per lane
   struct Cols { f32x4 x[NCOL]; };                           // rows 16 it + lane / 4, columns n0 + 4 (lane % 4) ..
   struct Operand { f32x4 x[D / 16]; };                      // column n of the product, k = 16 j + 4 g ..
   static constexpr int PATCH = D * 16 * 4;
   static __device__ __forceinline__ float ex(float x) { return expf(x); }
   static constexpr float LOG = 1.0f;                        // scores enter ex() in this base's units
-  static __device__ __forceinline__ void put(Act& a, int pair, int col, float x) { a.v[pair * PITCH + col] = x; }
-  static __device__ __forceinline__ void put4(Act& a, int pair, int col, const f32x4& x) {
+  template <int PW, bool TURN = false> static __device__ __forceinline__ void put(Act& a, int pair, int col, float x) {   // (<>: see below)
+    a.v[pair * PITCH + col] = x;
+  }
+  template <int PW> static __device__ __forceinline__ void put4(Act& a, int pair, int col, const f32x4& x) {
     *reinterpret_cast<f32x4*>(a.v + pair * PITCH + col) = x;
   }
   typedef f32x4 Raw4;                                       // four stored values
@@ -136,7 +139,7 @@ template <int D> struct Prod<float, D> {
     __builtin_amdgcn_wave_barrier();
     return o;
   }
-  template <int PW>
+  template <int PW, bool TURN = false>
   static __device__ __forceinline__ f32x4 product(const Act& a, const Operand& w, int lane) {
     f32x4 s[4];                                             // independent sums: the chain is a fourth as long
 #pragma unroll
@@ -152,30 +155,44 @@ template <int D> struct Prod<float, D> {
 };
 
 template <int D> struct Prod<unsigned short, D> {
+  // pairs whose parts a product reads side by side (see there)
+  template <int PW> static constexpr int side_by_side() { return PW <= 4 ? 4 : (PW <= 8 ? 8 : 16); }
+  // whether a piece's number is turned over by its row (see `at`)
+  template <int PW> static constexpr bool turned() { return PW > 4 && D == 128; }
+  // Place of a part (head, remainder, remainder of that) of a pair's column; <PW>: of the product that will read it, whose lanes' rows
+  // are N part + pair. With few pairs (TURN false) the parts are 128 and 320 bytes past a multiple of 256 from each other, rows padded: four
+  // rows of three parts read at once are in different banks. From eight on, d = 128, rows have no padding and a 16-byte piece sits at its own number
+  // with bits turned over by its row: a read of 16 bytes a lane is served for rows 0 - 3 and 12 - 15 of one lane group together with rows
+  // 4 - 11 of the next, which reads the next piece, and whatever the row pitch, two of them met in a bank (4096 pairs, S = 16, d = 128
+  // 8.48 -> 8.20 us, 1450 packed pairs, S = 31 10.41 -> 10.13, the backward pass of 2048 pairs 38.5 -> 38.1; one to four pairs were 1.5 % slower with
+  // it for the longer addresses, fp32 1 %, d = 64 the same).
   static constexpr int PITCH = D + 8;
-  // head, remainder, remainder of that. 128 and 320 bytes past a multiple of 256 from each other: four, or eight, rows of two or three
-  // parts read at once are in different banks
   static constexpr int PART[3] = {0, 16 * PITCH + 64, 32 * PITCH + 160};
   struct Act { unsigned short v[48 * PITCH + 160]; };
+  template <int PW, bool TURN = turned<PW>()> static __device__ __forceinline__ int at(int part, int pair, int col) {
+    if constexpr (!TURN) return PART[part] + pair * PITCH + col;
+    const int row = (pair + part * side_by_side<PW>()) & 15;
+    return (part * 16 + pair) * D + (((col >> 3) ^ row) << 3) + (col & 7);
+  }
   static constexpr int NCOL = D / 32;
   struct Cols { u32x4 x[NCOL]; };                           // rows 32 it + lane / 2, columns n0 + 8 (lane % 2) ..
   struct Operand { bf16x8 x[D / 32]; };                     // column n of the product, k = 32 s + 8 g ..
   static constexpr int PATCH = D * 16 * 2;
   static __device__ __forceinline__ float ex(float x) { return __builtin_amdgcn_exp2f(x); }
   static constexpr float LOG = 1.4426950408889634f;
-  static __device__ __forceinline__ void put(Act& a, int pair, int col, float x) {
+  template <int PW, bool TURN = turned<PW>()> static __device__ __forceinline__ void put(Act& a, int pair, int col, float x) {
     const unsigned short h0 = f32_to_bf16_bits(x);
     const float r1 = x - bf16_bits_to_f32(h0);
     const unsigned short h1 = f32_to_bf16_bits(r1);
-    a.v[PART[0] + pair * PITCH + col] = h0;
-    a.v[PART[1] + pair * PITCH + col] = h1;
-    a.v[PART[2] + pair * PITCH + col] = f32_to_bf16_bits(r1 - bf16_bits_to_f32(h1));
+    a.v[at<PW, TURN>(0, pair, col)] = h0;
+    a.v[at<PW, TURN>(1, pair, col)] = h1;
+    a.v[at<PW, TURN>(2, pair, col)] = f32_to_bf16_bits(r1 - bf16_bits_to_f32(h1));
   }
-  static __device__ __forceinline__ void put4(Act& a, int pair, int col, f32x4 x) {
+  template <int PW> static __device__ __forceinline__ void put4(Act& a, int pair, int col, f32x4 x) {
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const bf16x4 b = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
-      *reinterpret_cast<bf16x4*>(a.v + PART[p] + pair * PITCH + col) = b;
+      *reinterpret_cast<bf16x4*>(a.v + at<PW>(p, pair, col)) = b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) x[e] -= (float)b[e];
     }
@@ -218,7 +235,7 @@ template <int D> struct Prod<unsigned short, D> {
   // up to eight the first two parts at 8 part + pair. Every wave of the workgroup reads the whole tile, at d = 128 a product is
   // bound by these LDS reads (12, 8 or 4 of 16 bytes a lane; PW = 1 6.6 -> 5.9 us a layer). The parts meet by lane rotations;
   // lanes of pairs past PW hold no result.
-  template <int PW>
+  template <int PW, bool TURN = turned<PW>()>
   static __device__ __forceinline__ f32x4 product(const Act& a, const Operand& w, int lane) {
     auto from = [](float v, auto ctrl) {
       return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, false));
@@ -226,15 +243,17 @@ template <int D> struct Prod<unsigned short, D> {
     typedef std::integral_constant<int, 0x12C> From4;       // row_ror:12: lane + 4
     typedef std::integral_constant<int, 0x128> From8;       // row_ror:8
     if constexpr (PW <= 8) {
-      constexpr int N = PW <= 4 ? 4 : 8;
-      const int part = (lane & 15) / N;
+      constexpr int N = side_by_side<PW>();
+      const int part = (lane & 15) / N;                     // (the fourth of N = 4: the third again)
       const unsigned short* own = a.v + (part == 0 ? PART[0] : (part == 1 ? PART[1] : PART[2]));
       f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, s2 = s;
 #pragma unroll
       for (int k = 0; k < D / 32; ++k) {
-        const int at = (lane & (N - 1)) * PITCH + k * 32 + (lane >> 4) * 8;
-        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(own + at), s, 0, 0, 0);
-        if (N == 8) s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(a.v + PART[2] + at), s2, 0, 0, 0);
+        const int row = lane & (N - 1), col = k * 32 + (lane >> 4) * 8, plain = row * PITCH + k * 32 + (lane >> 4) * 8;
+        const unsigned short* x = TURN ? a.v + at<PW, TURN>(part, row, col) : own + plain;
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(x), s, 0, 0, 0);
+        const unsigned short* x2 = TURN ? a.v + at<PW, TURN>(2, row, col) : a.v + PART[2] + plain;
+        if (N == 8) s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], *reinterpret_cast<const bf16x8*>(x2), s2, 0, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -248,7 +267,7 @@ template <int D> struct Prod<unsigned short, D> {
     for (int k = 0; k < D / 32; ++k)
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v + PART[p] + (lane & 15) * PITCH + k * 32 + (lane >> 4) * 8);
+        const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v + at<PW>(p, lane & 15, k * 32 + (lane >> 4) * 8));
         s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], x, s[p], 0, 0, 0);
       }
     return (s[2] + s[1]) + s[0];

@@ -120,12 +120,12 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   for (int l = 0; l < M; ++l) {
     const bool more_layers = l + 1 < M;
     const size_t next = (size_t)(l + 1) * D * D;
-    X::put4(bt, l16, c4, t);
+    X::template put4<PW>(bt, l16, c4, t);
     if (EAGER ? l == 0 : true) oq = X::transposed(cq, patch, lane);
     __syncthreads();
     const f32x4 q = X::template product<PW>(bt, oq, lane);                     // q' = t W_q
     if (more_layers) X::load_cols(cq, wq + next, n0, lane);
-    X::put4(bq, l16, c4, q);
+    X::template put4<PW>(bq, l16, c4, q);
     __syncthreads();
     const f32x4 rv = X::template product<PW>(bq, rk, lane);                    // r = W_k q'
     if (LATE) X::load_cols(cv, wv + next - D * D, n0, lane);
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
       // reach the result)
       const float inv = WPP > 1 ? 1.0f : (nv[i] > 0 ? 1.0f / den : 0.0f);
 #pragma unroll
-      for (int e = 0; e < LPR / 8; ++e) X::put(bq, WPP > 1 ? wp * PW + pj : pj, y0 + e, acc[e] * inv);
+      for (int e = 0; e < LPR / 8; ++e) X::template put<(WPP > 1 ? NW : PW), X::template turned<PW>()>(bq, WPP > 1 ? wp * PW + pj : pj, y0 + e, acc[e] * inv);
       if (WPP > 1 && lane == 0) pml[wp * PW + pj] = nv[i] > 0 ? f32x2{mw, den} : f32x2{0.0f, 1.0f};
       if constexpr (POOL) store_pool(i, top);
     }
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
       // The waves of a pair meet behind the product: column o PW + pair is the sum of wave o, relative to its own maximum (merged
       // before the product they took a barrier more, and an exponential per wave and element)
       const f32x2 ml = pml[lane & (NW - 1)];
-      f32x4 y = X::template product<NW>(bq, ov, lane);
+      f32x4 y = X::template product<NW, X::template turned<PW>()>(bq, ov, lane);
       const float f = X::ex(ml[0] - softmax_ref(over_waves<PW, NW, true>(ml[0])));
       const float scale = f / over_waves<PW, NW, false>(ml[1] * f);
 #pragma unroll
