@@ -25,7 +25,7 @@ __global__ __launch_bounds__(4 * D, 4) void gsta_r_kernel(const unsigned short* 
                                                           float* __restrict__ z) {
   typedef Prod<unsigned short, D> X;
   constexpr int NW = D / 16;
-  __shared__ __attribute__((aligned(16))) unsigned short bt[16 * D];
+  __shared__ __attribute__((aligned(16))) unsigned short bt[X::template extent<16>(1)];   // (t0 is its own head)
   __shared__ __attribute__((aligned(16))) typename X::Act bq;
   __shared__ __attribute__((aligned(16))) unsigned char patches[NW][X::PATCH];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;

@@ -169,10 +169,18 @@ template <int D> struct Prod<unsigned short, D> {
   static constexpr int PITCH = D + 8;
   static constexpr int PART[3] = {0, 16 * PITCH + 64, 32 * PITCH + 160};
   struct Act { unsigned short v[48 * PITCH + 160]; };
-  template <int PW, bool TURN = turned<PW>()> static __device__ __forceinline__ int at(int part, int pair, int col) {
+  template <int PW, bool TURN = turned<PW>()> static constexpr __device__ __forceinline__ int at(int part, int pair, int col) {
     if constexpr (!TURN) return PART[part] + pair * PITCH + col;
     const int row = (pair + part * side_by_side<PW>()) & 15;
     return (part * 16 + pair) * D + (((col >> 3) ^ row) << 3) + (col & 7);
+  }
+  // shorts that an array needs to hold the first `parts` parts of 16 pairs: one more than their largest place
+  template <int PW, bool TURN = turned<PW>()> static constexpr __device__ int extent(int parts) {
+    int last = 0;
+    for (int part = 0; part < parts; ++part)
+      for (int pair = 0; pair < 16; ++pair)
+        for (int col = 0; col < D; ++col) last = at<PW, TURN>(part, pair, col) > last ? at<PW, TURN>(part, pair, col) : last;
+    return last + 1;
   }
   static constexpr int NCOL = D / 32;
   struct Cols { u32x4 x[NCOL]; };                           // rows 32 it + lane / 2, columns n0 + 8 (lane % 2) ..
@@ -273,5 +281,13 @@ template <int D> struct Prod<unsigned short, D> {
     return (s[2] + s[1]) + s[0];
   }
 };
+
+// every place of a vector's parts is inside Act, whichever product will read it
+template <int D, bool TURN> constexpr bool act_holds() {
+  typedef Prod<unsigned short, D> X;
+  const int n = sizeof(X::Act::v) / sizeof(unsigned short);
+  return X::template extent<4, TURN>(3) <= n && X::template extent<8, TURN>(3) <= n && X::template extent<16, TURN>(3) <= n;
+}
+static_assert(act_holds<64, false>() && act_holds<128, false>() && act_holds<128, true>(), "a part lies outside Act");
 
 }  // namespace laser
