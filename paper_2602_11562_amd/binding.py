@@ -159,25 +159,31 @@ def laser_gsta_kernel_name(C: int, S: int, d: int, dt: int, M: int = 1) -> str:
 # ----------------------------------------------------------------------------- tensor marshalling
 # A small request is a few microseconds of kernels: what every call does here is kept to attribute reads (the torch module is
 # looked up once, the stream's handle is read without building a Stream object, 3.0 -> 0.3 us), and laser_forward, the call of single
-# requests, hands tensors over in native code where they are of the ordinary form. 16 candidates, L = 1024, 8 us of kernels: passes in a
-# row 10.5 -> 8.5 us.
+# requests, is handed over in native code where every output is given and every tensor is a plain contiguous device tensor (16
+# candidates, L = 1024, 8 us of kernels: passes in a row 10.5 -> 8.5 us). Without outputs, and at every other entry point, the host part
+# is the one below.
 _torch_module = None
+_fast_module = None     # None: not looked for yet; False: not there, or not of this torch
 
 
-_fast_module = None
+def torch_stamp() -> str:
+    """The torch and the Python that laser_fast.so, which reads their objects through inlined accessors, has to be built against."""
+    import sysconfig
+    torch = _torch()
+    return f"{torch.__version__} {getattr(torch.version, 'git_version', '')} {sysconfig.get_config_var('SOABI')}"
 
 
 def _fast():
-    """The native marshalling of calls of the ordinary form (csrc/binding_fast.cpp)."""
+    """The native marshalling (csrc/binding_fast.cpp), or False: laser_forward then goes the way of every other call."""
     global _fast_module
     if _fast_module is None:
+        import importlib
         _torch()     # (its libraries are the module's)
         try:
-            from . import laser_fast
-        except ImportError as e:
-            raise ImportError("laser_fast.so is missing or was built for another torch: build it with "
-                              "`python -m paper_2602_11562_amd.build`") from e
-        _fast_module = laser_fast
+            found = importlib.import_module(".laser_fast", __package__)
+            _fast_module = found if getattr(found, "stamp", None) == torch_stamp() else False
+        except ImportError:
+            _fast_module = False
     return _fast_module
 
 
@@ -743,8 +749,9 @@ def laser_forward(q, k, v, t0, wq, wk, wv, lens, w: int, gamma: float, seg_out=N
     as NULL (H' is never stored: the fused kernels, one layer only) and None comes back in its place."""
     torch = _torch()
     if q.is_cuda and seg_out is not None and z_out is not None and (seg_cnt is not None or not want_cnt):
-        code = _fast().forward(load_library().forward_address, q, k, v, t0, wq, wk, wv, lens, w, gamma, seg_out, seg_cnt, z_out,
-                               _stream(stream))
+        fast = _fast()
+        code = fast.forward(load_library().forward_address, q, k, v, t0, wq, wk, wv, lens, w, gamma, seg_out, seg_cnt, z_out,
+                            _stream(stream)) if fast else None
         if code is not None:
             _check(code, "laser_forward")
             return seg_out, seg_cnt, z_out

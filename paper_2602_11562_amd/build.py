@@ -11,6 +11,7 @@ import os
 import shutil
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -65,8 +66,19 @@ def build_library(jobs: int = 6, tuning: bool = False, out: str = LIB) -> str:
         raise RuntimeError("link failed:\n" + r.stderr)
     os.replace(tmp, out)
     if out == LIB:
-        build_fast_binding()
+        build_fast_binding_or_do_without()
     return out
+
+
+def build_fast_binding_or_do_without() -> None:
+    """The binding's native part needs g++ and torch's headers. Without them the binding marshals every call in Python, and one built
+    earlier, for a library that is gone, must not stay."""
+    try:
+        build_fast_binding()
+    except (ImportError, OSError, RuntimeError) as e:
+        if os.path.exists(FAST):
+            os.remove(FAST)
+        warnings.warn(f"laser_fast.so was not built, laser_forward is marshalled in Python: {e}")
 
 
 def build_fast_binding(out: str = FAST) -> str:
@@ -75,9 +87,12 @@ def build_fast_binding(out: str = FAST) -> str:
 
     import torch
     from torch.utils.cpp_extension import include_paths
+
+    from .binding import torch_stamp
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     tmp = out + ".tmp"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DLASER_TORCH_STAMP="{torch_stamp()}"',
            *["-I" + d for d in include_paths()], "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding_fast.cpp"),
            "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch_python", "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,6 +1,7 @@
 // The marshalling of laser_forward in native code, for calls of the ordinary form: plain device tensors, contiguous, outputs given.
 // Anything else returns None, and the caller (binding.py) goes its own way, with its own checks and errors. A small request is 8 us
-// of kernels; attribute by attribute in Python, with ctypes, its host part took 10.5 us a call.
+// of kernels; attribute by attribute in Python, with ctypes, its host part took 10.5 us a call. Torch's accessors are inlined here, so
+// the module names the torch that it was built against (`stamp`), and the caller leaves it alone in any other.
 #include <torch/csrc/autograd/python_variable.h>
 
 typedef int (*Forward)(const void*, const void*, const void*, const void*, const void*, const void*, const void*, const int32_t*, int, int,
@@ -61,4 +62,11 @@ static PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 static PyMethodDef methods[] = {
     {"forward", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(forward)), METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
 static PyModuleDef module = {PyModuleDef_HEAD_INIT, "laser_fast", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
-PyMODINIT_FUNC PyInit_laser_fast() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_laser_fast() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "stamp", LASER_TORCH_STAMP) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

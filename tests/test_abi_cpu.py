@@ -3,6 +3,8 @@ on the host before anything is launched."""
 import ctypes
 import os
 import re
+import sys
+import types
 
 import pytest
 
@@ -153,6 +155,62 @@ def test_the_native_marshalling_leaves_every_other_form_alone():
     for at, other in ((0, None), (0, x.as_subclass(Sub)), (3, "t0"), (8, 2.0), (8, 1 << 40), (9, 1), (10, None), (13, "stream")):
         assert forward(1, *good[:at], other, *good[at + 1:]) is None
     assert forward(1, *good[:-1]) is None and forward() is None
+
+
+def test_the_native_part_carries_the_stamp_of_this_torch():
+    import torch
+    assert binding._fast().stamp == binding.torch_stamp()
+    assert torch.__version__ in binding.torch_stamp()
+
+
+@pytest.mark.parametrize("found", [None, types.SimpleNamespace(), types.SimpleNamespace(stamp="another torch")],
+                         ids=["missing", "without a stamp", "of another torch"])
+def test_laser_forward_without_the_native_part_goes_through_python(monkeypatch, found):
+    import torch
+
+    def forward(*args):
+        raise AssertionError("taken")
+    if found is not None:
+        found.forward = forward
+    monkeypatch.setitem(sys.modules, "paper_2602_11562_amd.laser_fast", found)     # (None: the import fails)
+    monkeypatch.delattr(laser, "laser_fast", raising=False)
+    monkeypatch.setattr(binding, "_fast_module", None)
+    monkeypatch.setattr(binding, "_stream", lambda stream: None)
+    calls = []
+    monkeypatch.setattr(binding, "_lib", types.SimpleNamespace(forward_address=1, laser_forward=lambda *args: calls.append(args) or 0))
+
+    class Device:      # what the Python path reads of a device tensor
+        is_cuda, dtype = True, torch.float32
+
+        def __init__(self, at, *shape):
+            self.at, self.shape = at, shape
+
+        def is_contiguous(self):
+            return True
+
+        def data_ptr(self):
+            return self.at
+    U, C, L, d, M, w, S = 1, 2, 4, 8, 1, 2, 2
+    q, k, v, t0 = Device(16, U, C, d), Device(32, U, L, d), Device(48, U, L, d), Device(64, U, C, d)
+    W, seg, z = Device(80, M, d, d), Device(96, U, C, S, d), Device(112, U, C, d)
+    for _ in range(2):
+        assert laser.laser_forward(q, k, v, t0, W, W, W, None, w, 1.0, seg_out=seg, z_out=z, want_cnt=False) == (seg, None, z)
+    assert calls == [(16, 32, 48, 64, 80, 80, 80, None, U, C, L, d, d, w, 1.0, M, laser.LASER_F32, 96, None, 112, None)] * 2
+
+
+@pytest.mark.parametrize("error", [ImportError("no torch"), FileNotFoundError("g++"), RuntimeError("g++ failed")])
+def test_the_library_builds_without_the_native_part(monkeypatch, tmp_path, error):
+    from paper_2602_11562_amd import build
+    old = tmp_path / "laser_fast.so"
+    old.write_bytes(b"of an older library")
+
+    def fails():
+        raise error
+    monkeypatch.setattr(build, "FAST", str(old))
+    monkeypatch.setattr(build, "build_fast_binding", fails)
+    with pytest.warns(UserWarning, match="laser_fast.so was not built"):
+        build.build_fast_binding_or_do_without()
+    assert not old.exists()
 
 
 @pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
