@@ -1,7 +1,12 @@
 """laser_forward through the binding's native marshalling and without it: the same results, and the same refusals."""
 import types
 
+import numpy as np
 import pytest
+
+import oracle
+
+from parity_util import TOL, to_host_f64, vec_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -32,8 +37,10 @@ def _call(monkeypatch, native, a, out, **kw):
         took.append(code is not None)
         return code
     monkeypatch.setattr(binding, "_fast_module", types.SimpleNamespace(forward=forward))
+    own = {k: v.clone() if v is not None else None for k, v in out.items()}
+    torch.cuda.synchronize()     # (the call may be on another stream than the copies)
     try:
-        r = laser.laser_forward(*a, **{k: v.clone() if v is not None else None for k, v in out.items()}, **kw)
+        r = laser.laser_forward(*a, **own, **kw)
         torch.cuda.synchronize()
     except Exception as e:
         r = type(e)
@@ -50,13 +57,17 @@ def test_native_and_plain_marshalling_agree(monkeypatch, dtype, lens, count, str
     if not count:
         out["seg_cnt"] = None
     if stream:
-        torch.cuda.synchronize()
         kw["stream"] = torch.cuda.Stream()
     one, took = _call(monkeypatch, True, a, out, **kw)
     two, _ = _call(monkeypatch, False, a, out, **kw)
     assert took == 1
-    for x, y in zip(one, two):
+    for x, y, fill in zip(one, two, (out["seg_out"], out["seg_cnt"], out["z_out"])):
         assert (x is None and y is None) or torch.equal(x, y)
+        assert x is None or not (x == fill).all(-1).any()     # (every row written, none left as it was)
+    q, k, v, n = (x if x is None else to_host_f64(x) for x in (a[0], a[1], a[2], a[7]))
+    seg, cnt = oracle.sta_forward(q, k, v, n, *a[8:])
+    assert vec_rel_err(to_host_f64(one[0]), seg) <= TOL["f32" if dtype == "float32" else "bf16"]
+    assert one[1] is None or np.array_equal(one[1].cpu().numpy(), cnt)
 
 
 @pytest.mark.parametrize("at,change", [(0, lambda t: t.transpose(0, 1)), (1, lambda t: t.float()), (2, lambda t: t.cpu()),
