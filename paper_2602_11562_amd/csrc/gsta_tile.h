@@ -108,7 +108,7 @@ template <int D> struct Prod<float, D> {
   template <int PW, bool TURN = false> static __device__ __forceinline__ void put(Act& a, int pair, int col, float x) {   // (<>: see below)
     a.v[pair * PITCH + col] = x;
   }
-  template <int PW> static __device__ __forceinline__ void put4(Act& a, int pair, int col, const f32x4& x) {
+  template <int PW, bool TURN = false> static __device__ __forceinline__ void put4(Act& a, int pair, int col, const f32x4& x) {
     *reinterpret_cast<f32x4*>(a.v + pair * PITCH + col) = x;
   }
   typedef f32x4 Raw4;                                       // four stored values
@@ -196,11 +196,11 @@ template <int D> struct Prod<unsigned short, D> {
     a.v[at<PW, TURN>(1, pair, col)] = h1;
     a.v[at<PW, TURN>(2, pair, col)] = f32_to_bf16_bits(r1 - bf16_bits_to_f32(h1));
   }
-  template <int PW> static __device__ __forceinline__ void put4(Act& a, int pair, int col, f32x4 x) {
+  template <int PW, bool TURN = turned<PW>()> static __device__ __forceinline__ void put4(Act& a, int pair, int col, f32x4 x) {
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const bf16x4 b = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
-      *reinterpret_cast<bf16x4*>(a.v + at<PW>(p, pair, col)) = b;
+      *reinterpret_cast<bf16x4*>(a.v + at<PW, TURN>(p, pair, col)) = b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) x[e] -= (float)b[e];
     }
@@ -275,7 +275,7 @@ template <int D> struct Prod<unsigned short, D> {
     for (int k = 0; k < D / 32; ++k)
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v + at<PW>(p, lane & 15, k * 32 + (lane >> 4) * 8));
+        const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.v + at<PW, TURN>(p, lane & 15, k * 32 + (lane >> 4) * 8));
         s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.x[k], x, s[p], 0, 0, 0);
       }
     return (s[2] + s[1]) + s[0];

@@ -40,6 +40,10 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   constexpr int WPP = PW < NW ? NW / PW : 1;                      // waves that share a pair's rows
   constexpr int PPW = PW > NW ? PW / NW : 1;                      // pairs of a wave
   constexpr int RP = D + 4;
+  // The turned layout of the vectors in LDS, but for the instances of two workgroups a compute unit (R < 4) whose 128 registers do not
+  // hold its longer addresses beside the rest: spilled, 2002 pairs, S = 2 took 8.5 us for 5.6, 9321 pairs, S = 11 17.9 for 15.6. One and two
+  // rows a lane of sixteen pairs fit, 0.96 of the time without it.
+  constexpr bool TURN = X::template turned<PW>() && !(RES && (PW == 8 ? R < 4 : R == 3));
   __shared__ __attribute__((aligned(16))) typename X::Act bt, bq; // t; q', then p
   __shared__ __attribute__((aligned(16))) float rr[PW * RP];      // r / sqrt(d)
   __shared__ __attribute__((aligned(16))) unsigned char patches[NW][X::PATCH];
@@ -120,14 +124,14 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   for (int l = 0; l < M; ++l) {
     const bool more_layers = l + 1 < M;
     const size_t next = (size_t)(l + 1) * D * D;
-    X::template put4<PW>(bt, l16, c4, t);
+    X::template put4<PW, TURN>(bt, l16, c4, t);
     if (EAGER ? l == 0 : true) oq = X::transposed(cq, patch, lane);
     __syncthreads();
-    const f32x4 q = X::template product<PW>(bt, oq, lane);                     // q' = t W_q
+    const f32x4 q = X::template product<PW, TURN>(bt, oq, lane);                     // q' = t W_q
     if (more_layers) X::load_cols(cq, wq + next, n0, lane);
-    X::template put4<PW>(bq, l16, c4, q);
+    X::template put4<PW, TURN>(bq, l16, c4, q);
     __syncthreads();
-    const f32x4 rv = X::template product<PW>(bq, rk, lane);                    // r = W_k q'
+    const f32x4 rv = X::template product<PW, TURN>(bq, rk, lane);                    // r = W_k q'
     if (LATE) X::load_cols(cv, wv + next - D * D, n0, lane);
     if (more_layers) X::load_rows(rk, wk + next, n0, lane);
     if (l16 < PW) *reinterpret_cast<f32x4*>(rr + l16 * RP + c4) = rv * scale;
@@ -197,7 +201,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
       // reach the result)
       const float inv = WPP > 1 ? 1.0f : (nv[i] > 0 ? 1.0f / den : 0.0f);
 #pragma unroll
-      for (int e = 0; e < LPR / 8; ++e) X::template put<(WPP > 1 ? NW : PW), X::template turned<PW>()>(bq, WPP > 1 ? wp * PW + pj : pj, y0 + e, acc[e] * inv);
+      for (int e = 0; e < LPR / 8; ++e) X::template put<(WPP > 1 ? NW : PW), TURN>(bq, WPP > 1 ? wp * PW + pj : pj, y0 + e, acc[e] * inv);
       if (WPP > 1 && lane == 0) pml[wp * PW + pj] = nv[i] > 0 ? f32x2{mw, den} : f32x2{0.0f, 1.0f};
       if constexpr (POOL) store_pool(i, top);
     }
@@ -206,12 +210,12 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
     if (EAGER && more_layers) oq = X::transposed(cq, patch, lane);
     __syncthreads();
     if constexpr (WPP == 1) {
-      t += X::template product<PW>(bq, ov, lane);                              // t += p W_v
+      t += X::template product<PW, TURN>(bq, ov, lane);                              // t += p W_v
     } else {
       // The waves of a pair meet behind the product: column o PW + pair is the sum of wave o, relative to its own maximum (merged
       // before the product they took a barrier more, and an exponential per wave and element)
       const f32x2 ml = pml[lane & (NW - 1)];
-      f32x4 y = X::template product<NW, X::template turned<PW>()>(bq, ov, lane);
+      f32x4 y = X::template product<NW, TURN>(bq, ov, lane);
       const float f = X::ex(ml[0] - softmax_ref(over_waves<PW, NW, true>(ml[0])));
       const float scale = f / over_waves<PW, NW, false>(ml[1] * f);
 #pragma unroll

@@ -26,6 +26,8 @@ GSTA_CASES = {
     "eight_pairs_a_workgroup_d64": ("bf16", 3, 1367, 40, 1, 64, 2),
     "sixteen_pairs_a_workgroup": ("bf16", 3, 700, 32, 1, 128, 2),
     "sixteen_pairs_a_workgroup_f32": ("f32", 3, 1400, 20, 1, 64, 1),
+    "eight_pairs_of_three_rows": ("bf16", 3, 417, 3, 1, 128, 2),       # one and two rows a lane
+    "eight_pairs_of_seven_rows": ("bf16", 3, 417, 7, 1, 128, 3),
     "sixteen_pairs_of_one_row": ("bf16", 3, 700, 1, 1, 128, 2),        # two and three rows a lane
     "sixteen_pairs_of_eight_rows": ("bf16", 3, 700, 8, 1, 128, 3),
     "sixteen_pairs_of_twelve_rows": ("bf16", 3, 1400, 12, 1, 128, 2),
