@@ -49,9 +49,14 @@ struct FewShape {
   static constexpr int KF = FOLD ? 0 : DQ / 16, VF = D / 16, F = KF + VF;         // and a tile's items
   static constexpr int KB = KF * 1024, QOFF = F * 1024, BUF = QOFF + QF * 1024;   // ring buffer: K, V, Q
   static constexpr int WVB = FOLD ? D * FE * 2 : 0;
-  static constexpr int WAVE = 2 * BUF, FIT = (FEW_LDS - WVB - (DEAL ? 16 : 0)) / WAVE;
+  static constexpr int WAVE = 2 * BUF, FIT = (FEW_LDS - WVB) / WAVE;
   static constexpr int NW = FIT < 8 ? FIT : 8;               // waves per workgroup, one workgroup per compute unit
-  static constexpr int NT = 64 * NW, TICKET = WVB + NW * WAVE, LDS = TICKET + (DEAL ? 16 : 0);
+  // the tickets' counter: behind the rings, or, where these fill the LDS (folded, FE = 64: 16 KB of W_v and eight rings of 18), in the
+  // place of the first word of W_v's last fragment, lane 63, which every wave then keeps in a register (with seven waves instead 150
+  // calls, most of them dealt, took 0.98 of their time in turn, so 0.965; 514 users x 2 rows, L = 776, w = 20, full 28.3, 29.7 and 28.1 us)
+  static constexpr bool FULL = DEAL && WVB + NW * WAVE + 16 > FEW_LDS;
+  static constexpr int NT = 64 * NW, TICKET = FULL ? WVB - 16 : WVB + NW * WAVE, LDS = WVB + NW * WAVE + (DEAL && !FULL ? 16 : 0);
+  static_assert(LDS <= FEW_LDS && (!FULL || FOLD), "the counter takes the place of a piece of W_v");
 };
 
 struct FewFold {
@@ -86,6 +91,12 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE, DEAL>::NT)) void sta_few_kerne
             (unsigned short)((raw[j >> 1] >> ((j & 1) * 16)) & 0xffffu);
       }
     }
+  }
+  unsigned under_ticket = 0;   // the word of W_v that the counter takes the place of
+  if constexpr (Sh::FULL) {
+    __syncthreads();
+    under_ticket = *reinterpret_cast<const unsigned*>(smem + Sh::TICKET);
+    __syncthreads();
   }
   if (DEAL && tid == 0) *reinterpret_cast<unsigned*>(smem + Sh::TICKET) = Sh::NW;
   if (FOLD || DEAL) __syncthreads();
@@ -300,7 +311,9 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE, DEAL>::NT)) void sta_few_kerne
           f32x4 r = zero4;
 #pragma unroll
           for (int ks = 0; ks < D / 32; ++ks) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(smem + ((et * (D / 32) + ks) * 64 + lane) * 16);
+            u32x4 raw = *reinterpret_cast<const u32x4*>(smem + ((et * (D / 32) + ks) * 64 + lane) * 16);
+            if (Sh::FULL && et == ET - 1 && ks == D / 32 - 1) raw[0] = lane == 63 ? under_ticket : raw[0];
+            const bf16x8 a = __builtin_bit_cast(bf16x8, raw);
             r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, o[ks], r, 0, 0, 0);
           }
 #pragma unroll

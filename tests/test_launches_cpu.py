@@ -180,6 +180,24 @@ def test_maxima_from_the_pass_over_the_rows(recorder, P, S, d, M, views, pool):
     assert bool(re.search(rf"gsta_tiled_kernelItLi{d}ELi16ELi4ELb0ELb1E", launch.kernel.decode())) == pool
 
 
+def folded(U, C, heads, L, d, w, lens=A):
+    return lambda lib: lib.laser_sta_folded_forward(A, A, A, A, lens, U, C, L, 128, d, w, 1.0, heads, BF16, A, A, A, A, None)
+
+
+def few(launch):
+    """(d_q, d, folded columns, units by ticket) of a launch of the kernel for few rows."""
+    m = re.search(r"14sta_few_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", launch.kernel.decode())
+    return m and tuple(int(x) for x in m.groups())
+
+
+@pytest.mark.parametrize("d,waves", [(64, 8), (128, 7)])
+def test_folded_calls_have_the_same_waves_by_ticket_and_in_turn(recorder, d, waves):
+    for U, dealt in ((100, 0), (8000, 1)):
+        launch = launches(recorder, folded(U, 2, 1, 1000, d, 20))[-1]
+        assert few(launch) == (128, 128, d, dealt)
+        assert launch.block == 64 * waves and launch.lds <= 160 * 1024 and launch.grid == 256
+
+
 @pytest.mark.parametrize("name", list(SETS))
 def test_backward_calls_with_two_sets_of_tiles(recorder, name):
     U, C, L, dq, d, w, grid, lds = SETS[name]

@@ -179,11 +179,14 @@ def test_folded_histories_past_the_cache(rows):
         assert vec_rel_err(to_host_f64(seg[u]), ref) <= TOL["bf16"], u
 
 
-# Launches of more than three units a wave, whose workgroups deal their units out by ticket: every unit is worked on exactly where it
-# belongs (outputs start as NaN). folded, rows (heads when folded), d_q, d, L, w, users
+# Launches of many units a wave, whose workgroups deal their units out by ticket, and some of fewer: every unit is worked on exactly
+# where it belongs (outputs start as NaN); folded with 64 columns, the tickets' counter is in a word's place of W_v. folded, rows (heads
+# when folded), d_q, d, L, w, users
 @pytest.mark.parametrize("folded,rows,dq,d,L,w,U", [(False, 4, 32, 128, 330, 10, 1300), (False, 8, 64, 64, 200, 3, 500),
                                                     (False, 3, 128, 128, 97, 33, 2100), (True, 2, 128, 128, 330, 10, 1200),
-                                                    (True, 4, 128, 128, 97, 7, 1100), (True, 1, 128, 64, 130, 65, 3300)])
+                                                    (True, 4, 128, 128, 97, 7, 1100), (True, 1, 128, 64, 130, 65, 3300),
+                                                    (False, 8, 64, 64, 200, 3, 5000), (True, 4, 128, 128, 97, 7, 5500),
+                                                    (True, 1, 128, 64, 130, 65, 5500), (True, 2, 128, 64, 97, 7, 7000)])
 def test_units_dealt_by_ticket(folded, rows, dq, d, L, w, U):
     import torch
     gen = torch.Generator(device="cuda").manual_seed(U)
