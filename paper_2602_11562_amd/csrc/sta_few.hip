@@ -434,10 +434,11 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
   const unsigned blocks = units < 256 ? units : 256u;
   const MulDiv dv = mul_div(runs);
   // Units of short histories hold little or nothing. Dealt out in turn, the fullest wave has half as much again as the mean, by
-  // ticket (an LDS counter) a workgroup's waves end together; with few units a wave the counter costs more than it evens out.
-  // d_in = 128, two rows, w = 10, uniform lengths: 2048 users 93 -> 84 us, full lengths 118 -> 112; 8 rows, w = 256, 1000 users
-  // (3.9 units a wave) 65.7 -> 63.1; 4 rows, w = 50, 256 users (2.5) 11.1 -> 11.2.
-  const bool deal = units > (unsigned)tuning_int("LASER_FEW_DEAL", 3) * blocks * Sh::NW;
+  // ticket (an LDS counter) a workgroup's waves end together; with few units a wave the counter costs more than it evens out, and
+  // with full lengths there is less to even out. 400 calls of 3 to 8 rows, mean (and worst) time by ticket over that in turn: 3 to 4
+  // units a wave 0.99 (1.09), 4 to 6 0.95 (1.05), with full lengths 0.99 (1.04), 6 to 10 0.92 (1.00), full 0.98 (1.03), more 0.93
+  // (1.01), full 0.97 (1.01). d_in = 128, two rows, w = 10, 2048 users, uniform lengths 93 -> 84 us, full 118 -> 112.
+  const bool deal = units > (unsigned)tuning_int("LASER_FEW_DEAL", a.lens != nullptr ? 4 : 6) * blocks * Sh::NW;
   auto launch = [&](auto shape, auto kern) {
     using X = decltype(shape);
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, X::LDS) != hipSuccess)

@@ -198,6 +198,16 @@ def test_folded_calls_have_the_same_waves_by_ticket_and_in_turn(recorder, d, wav
         assert launch.block == 64 * waves and launch.lds <= 160 * 1024 and launch.grid == 256
 
 
+# users, rows, items, d_q, d, w: units a wave in thousandths; by ticket past four with lengths given, past six without
+@pytest.mark.parametrize("U,C,L,dq,d,w,upw", [(2048, 3, 100, 64, 64, 50, 2000), (2048, 3, 200, 64, 64, 50, 4000), (2049, 3, 200, 64, 64, 50, 4002),
+                                              (2048, 3, 300, 64, 64, 50, 6000), (2049, 3, 300, 64, 64, 50, 6003),
+                                              (1024, 8, 240, 128, 128, 60, 4000), (1025, 8, 240, 128, 128, 60, 4004)])
+def test_units_by_ticket(recorder, U, C, L, dq, d, w, upw):
+    for lens, line in ((A, 4000), (None, 6000)):
+        launch, = launches(recorder, lambda lib: lib.laser_sta_forward(A, A, A, lens, U, C, L, dq, d, w, 1.0, BF16, A, A, None))
+        assert few(launch) == (dq, d, 0, int(upw > line))
+
+
 @pytest.mark.parametrize("name", list(SETS))
 def test_backward_calls_with_two_sets_of_tiles(recorder, name):
     U, C, L, dq, d, w, grid, lds = SETS[name]
