@@ -452,18 +452,15 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
               : launch(FewShape<DQ, D, FE, false>{}, sta_few_kernel<DQ, D, FE, false>);
 }
 
-// From three query rows per user on the vector-ALU kernels are bound by their arithmetic and this one by HBM; with one or
-// two rows both are near HBM, and in launches that the cache holds the vector-ALU kernels, with four times the waves in flight, are
-// the better ones, except for two rows of 64-wide keys and values. Before units were dealt by ticket, lengths uniform in [L / 5, L], us before and here:
+// From three query rows per user on the vector-ALU kernels are bound by their arithmetic and this one by HBM; with one or two rows both
+// are near HBM, and in launches that the cache holds the vector-ALU kernels, with four times the waves in flight, are the better ones,
+// except for two rows of 64-wide keys and values (past the cache: few_preferred_large). Lengths uniform in [L / 5, L], us there and here:
 //   U, C, L, w             d_q = 32, d = 128    64, 64          128, 128        64, 128
-//   1500, 1, 1000, 10        63 -> 70           52 -> 47        109 -> 118       79 -> 93
-//   1000, 1, 2048, 256       76 -> 84           53 -> 58        117 -> 127       90 -> 103
-//   1500, 2, 1000, 10        79 -> 83           72 -> 48        119 -> 126       90 -> 101
-//   1000, 2, 2048, 256       83 -> 85           57 -> 58        124 -> 131       97 -> 104
-//   1500, 4, 1000, 10       121 -> 102         142 -> 60        173 -> 139      131 -> 119
-//   256, 4, 1000, 50         19 -> 16           21 -> 15         32 -> 23        21 -> 18
-//   1000, 8, 2048, 256      252 -> 93          145 -> 65        236 -> 140      349 -> 114
-//   256, 8, 8000, 512       266 -> 91          157 -> 60        286 -> 135      382 -> 106
+//   1500, 3, 1000, 25        96 -> 56          119 -> 44        200 -> 86       119 -> 64
+//   1500, 4, 1000, 10       124 -> 96          146 -> 54        176 -> 128      131 -> 95
+//   256, 4, 1000, 50         18 -> 16           20 -> 11         30 -> 21        20 -> 17
+//   1000, 8, 2048, 256      250 -> 81          143 -> 67        230 -> 121      336 -> 96
+//   256, 8, 8000, 512       267 -> 82          153 -> 64        277 -> 125      383 -> 94
 // The table's calls fill the machine. In one that does not, the time is the chain of tiles of one run (two at least, and a
 // segment is one run however long it is), and up to six rows the vector-ALU kernels, whose four waves share a long segment
 // and which start faster, are the better ones: 1 user x 2, L = 2000, w = 512, 64 / 64 6.6 us there, 14.7 here; 16 x 3,
@@ -483,23 +480,40 @@ static bool few_fills(const StaArgs& a) {
   return a.w > 10 || items >= (a.C == 4 ? 32768 : 8192);
 }
 
-// One or two rows in a launch past the cache, whose units are dealt by ticket. Two rows: the better form from 150 MB on but for 32 /
-// 128 in segments of ten items and less (U, L, w, lengths uniform, us of the vector-ALU kernels and here: 2000, 1000, 25: 128 / 128 179 and
-// 132, 64 / 128 128 and 103, 32 / 128 103 and 88; 1500, 1000, 10: 128 / 128 117 and 113, 32 / 128 77.6 and 78.1; 2000, 2000, 512: 229 and
-// 214, 151 and 142). One row: from 256 MB on, where the vector-ALU kernel gives a wave whole segments (short ones) and these are
-// long enough to fill the tiles (2000, 1000, 25: 64 / 64 90 and 63, 128 / 128 160 and 124, 64 / 128 117 and 97, 32 / 128 97 and 83; 1000, 1000,
-// 13: 32 / 128 43.7 and 50.0, 64 / 128 53.2 and 57.6). Log-uniform lengths leave most units empty and are the least good case here: 700,
-// 3000, 50: 64 / 64 37 and 31, 32 / 128 40.7 and 41.2; 1500, 1000, 40, 32 / 64 18 and 25, which stays, as do 128 / 64.
+// One or two rows in a launch past the cache, whose units are dealt by ticket, against the vector-ALU kernels. With lengths given the
+// histories may hold a fraction of their arrays, which the cache then keeps, and a launch needs more to be the better one here;
+// segments longer than a tile that fill less than three quarters of their tiles (33 to 47 items, 65 to 71) are multiplied with too much of
+// nothing; with 400 items and more a wave is left with too few units.
+// 1950 calls of 60 to 8000 users and items, lengths full, uniform from nothing or a fifth on, or spread over the logarithm, mean (and
+// worst) time here over that there:
+//   one row, 64 / 64: w 10 .. 127 full from 256 MB 0.83 (1.04), with lengths from 400 MB 0.77 (1.15), below 0.88 (1.19)
+//     128 / 128: w 16 .. 32 full from 256 MB 0.92 (1.01), with lengths from 1 GB 0.89 (1.06), from 600 MB 0.89 (1.30); w 48 .. 63
+//       full 0.88 (1.01), with lengths from 600 MB 0.80 (1.12), below 0.93 (1.46)
+//     64 / 128: w 24 .. 32 and 48 .. 64 full from 300 MB 0.93 (1.04); with lengths w 48 .. 64 from 1 GB 0.87 (1.05), below 0.97
+//       (1.56), w 24 .. 32 0.97 (1.40)
+//     32 / 128, w 24 .. 50 full 0.95 (1.10), with lengths 0.98 (1.57), stays there, as do 128 / 64 and 32 / 64 (1500, 1000, 40, 32 / 64,
+//       lengths over the logarithm 18 us and 25)
+//   two rows, 32 / 64: w 8 .. 32 from 150 MB 0.66 (0.94); w 48 .. 399 full from 300 MB 0.88 (0.95), with lengths from 600 MB 0.79
+//       (0.98), below 0.96 (1.29)
+//     128 / 64: w 8 .. 200 from 150 MB 0.78 (1.08); w 201 .. 399 full from 300 MB 0.91 (0.94), with lengths from 600 MB 0.79 (0.88),
+//       below 0.91 (1.48)
+//     d = 128: w 8 (d_q = 32: 16) .. 399 full from 300 MB 0.91 (1.12), with lengths from 600 MB 0.81 (1.19), below 0.93 (1.45)
+//     w 400 and more, every width 1.02 (2.01)
 static bool few_preferred_large(const StaArgs& a) {
   if (a.k == a.v) return false;   // (read once by the vector-ALU kernels)
-  const long long bytes = (long long)a.U * a.L * (a.d_q + a.d) * 2;
-  if (a.C == 2) return bytes >= 150000000 && a.w >= (a.d_q == 32 && a.d == 128 ? 11 : 8);
-  if (a.C != 1 || bytes < 256000000) return false;
+  if (a.w > 32 && 4 * a.w < 3 * ((a.w + 31) / 32 * 32)) return false;   // 33 to 47, 65 to 71
+  const long long mb = (long long)a.U * a.L * (a.d_q + a.d) * 2 / 1000000;
+  const bool full = a.lens == nullptr;
+  if (a.C == 2) {
+    if (a.w < (a.d_q == 32 && a.d == 128 ? 16 : 8) || a.w >= 400) return false;
+    if (a.d == 64 && a.w <= (a.d_q == 128 ? 200 : 32)) return mb >= 150;
+    return mb >= (full ? 300 : 600);
+  }
+  if (a.C != 1) return false;
   switch (a.d_q * 1000 + a.d) {
-    case 64064: return a.w >= 10 && a.w < 128;
-    case 128128: return a.w >= 16 && a.w < 64;
-    case 64128: return a.w >= 24 && a.w <= 64;
-    case 32128: return a.w >= 24 && a.w <= 50;
+    case 64064: return a.w >= 10 && a.w < 128 && mb >= (full ? 256 : 400);
+    case 128128: return a.w >= 16 && a.w < 64 && mb >= (full ? 256 : (a.w <= 32 ? 1000 : 600));
+    case 64128: return a.w <= 64 && (full ? a.w >= 24 && mb >= 300 : a.w >= 48 && mb >= 1000);
     default: return false;
   }
 }

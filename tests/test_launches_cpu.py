@@ -208,6 +208,31 @@ def test_units_by_ticket(recorder, U, C, L, dq, d, w, upw):
         assert few(launch) == (dq, d, 0, int(upw > line))
 
 
+# rows, d_q, d, w, MB of histories from which a call goes to the matrix cores: with full lengths, with lengths (None: at no size)
+LARGE = [(1, 64, 64, 9, None, None), (1, 64, 64, 10, 256, 400), (1, 64, 64, 127, 256, 400), (1, 64, 64, 128, None, None),
+         (1, 128, 128, 15, None, None), (1, 128, 128, 16, 256, 1000), (1, 128, 128, 32, 256, 1000), (1, 128, 128, 33, None, None),
+         (1, 128, 128, 47, None, None), (1, 128, 128, 48, 256, 600), (1, 128, 128, 63, 256, 600), (1, 128, 128, 64, None, None),
+         (1, 64, 128, 23, None, None), (1, 64, 128, 24, 300, None), (1, 64, 128, 48, 300, 1000), (1, 64, 128, 64, 300, 1000),
+         (1, 64, 128, 72, None, None), (1, 32, 128, 30, None, None), (1, 32, 64, 30, None, None), (1, 128, 64, 30, None, None),
+         (2, 32, 64, 7, None, None), (2, 32, 64, 8, 150, 150), (2, 32, 64, 32, 150, 150), (2, 32, 64, 48, 300, 600), (2, 32, 64, 65, None, None),
+         (2, 32, 64, 72, 300, 600), (2, 32, 64, 399, 300, 600), (2, 32, 64, 400, None, None), (2, 128, 64, 200, 150, 150),
+         (2, 128, 64, 201, 300, 600), (2, 32, 128, 15, None, None), (2, 32, 128, 16, 300, 600), (2, 64, 128, 8, 300, 600),
+         (2, 128, 128, 399, 300, 600), (2, 128, 128, 400, None, None)]
+
+
+@pytest.mark.parametrize("C,dq,d,w,full,lens", LARGE)
+def test_one_and_two_rows_past_the_cache(recorder, C, dq, d, w, full, lens):
+    L = 2000
+    user = L * (dq + d) * 2
+    for given, line in ((None, full), (A, lens)):
+        least = -(-(line or 3000) * 1000000 // user)
+        for U, here in ((least, line is not None), (least - 1, False)):
+            launch, = launches(recorder, lambda lib: lib.laser_sta_forward(A, A, A + 0x10, given, U, C, L, dq, d, w, 1.0, BF16, A, A, None))
+            assert bool(few(launch)) == here, (U, launch.kernel)
+            launch, = launches(recorder, lambda lib: lib.laser_sta_forward(A, A, A, given, U, C, L, dq, d, w, 1.0, BF16, A, A, None))
+            assert not few(launch)      # (keys and values of one array are read once there)
+
+
 @pytest.mark.parametrize("name", list(SETS))
 def test_backward_calls_with_two_sets_of_tiles(recorder, name):
     U, C, L, dq, d, w, grid, lds = SETS[name]
