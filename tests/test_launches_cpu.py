@@ -242,6 +242,12 @@ def test_backward_calls_with_two_sets_of_tiles(recorder, name):
     assert (first.grid, first.lds) == (grid, lds)
 
 
+@pytest.mark.parametrize("S,ahead", [(1, 1), (2, 4), (4, 4), (5, 16), (16, 16), (17, 16)])
+def test_no_more_runs_in_flight_than_a_user_has(recorder, S, ahead):
+    last = launches(recorder, lambda lib: lib.laser_sta_backward(A, A, A, A, A, 3, 2, 10 * S, 24, 48, 10, 1.0, F32, A, A, A, A, 1 << 40, None))[-1]
+    assert f"17sta_bwd_dq_kernelILi{ahead}E" in last.kernel.decode()
+
+
 def gsta_backward(U, d, S, M, dt):
     return lambda lib: lib.laser_gsta_backward(A, A, A, A, A, A, A, U, 128, S * 8, d, 8, M, dt, A, A, A, A, A, A, 1 << 40, None)
 

@@ -39,6 +39,13 @@ CASES = {
     "forty_candidates": ("bf16", 40, 150, 64, 128, 16, [150, 17]),            # five blocks
     "ten_candidates_very_wide": ("bf16", 10, 100, 256, 256, 32, [100]),       # rows of 256 elements, 8 + 2
     "f32_paper_setting": ("f32", 1, 200, 32, 128, 10, [200, 33, 0]),
+    # the partial rows of a user that dq sums: one, up to four and up to sixteen at a time
+    "one_run": ("f32", 3, 20, 24, 48, 20, [20, 7, 0]),
+    "two_runs": ("bf16", 5, 21, 40, 32, 20, [21, 20, 3]),
+    "four_runs": ("f32", 3, 40, 24, 48, 10, [40, 31, 7]),
+    "five_runs": ("f32", 3, 41, 24, 48, 10, [41, 40]),
+    "sixteen_runs": ("f32", 2, 160, 16, 48, 10, [160, 1]),
+    "seventeen_runs": ("f32", 2, 161, 16, 48, 10, [161, 160]),
 }
 
 
