@@ -29,10 +29,10 @@
 // operations per word and the weighted sum row by row (a word, a weight from v_readlane, five to seven operations) were 350
 // of 1100 vector instructions, another hundred where two pairs met; the two products take 16 MFMAs. With the launches before
 // and behind it, 16384 pairs of 60 valid rows, d_ff = 128, rows not stored: 137.3 -> 127.2 us, with the views 145.5 -> 142.0.
-// With waves a fixed 2048 pairs apart, all waves of 32 workgroups see the same eight users of 64, and the longest histories decide: where
-// that matters a workgroup takes every 256th pair, which sees every user, and deals them to its waves by their valid rows (lengths
-// uniform in [200, 1000], w = 10, 64 x 256 pairs, with the views and the launches around it 154 -> 141 us; by an LDS counter, which
-// would make the sums of a pair depend on the run, 145).
+// With waves a fixed 2048 pairs apart, all waves of 32 workgroups see the same eight users of 64, and the longest histories
+// decide: where that matters a workgroup takes every 256th pair, which sees every user, and deals them to its waves by their
+// valid rows (lengths uniform in [200, 1000], w = 10, 64 x 256 pairs, with the views and the launches around it 154 -> 141 us; by
+// an LDS counter, which would make the sums of a pair depend on the run, 145).
 #include "segment_ffn_tile.h"
 
 namespace laser {
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char rvec[FM_WAVES * 2 * RVB];
   __shared__ __attribute__((aligned(16))) unsigned char rparts[FM_WAVES * RPB];
   __shared__ __attribute__((aligned(16))) float vecs[DFF + 3 * D];                    // b1, b2, ln_g, ln_b
-  __shared__ unsigned char dealt[DEAL ? FG_DECKS : 1][64];                                          // the waves' pairs, 64 at a time, eight a wave
+  __shared__ unsigned char dealt[DEAL ? FG_DECKS : 1][64];   // the waves' pairs, 64 at a time, eight a wave
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
       int rank = 0;
 #pragma unroll
       for (int j = 0; j < 64; ++j) rank += __builtin_amdgcn_readlane(key, j) > key ? 1 : 0;
-      const int turn = rank & (2 * FM_WAVES - 1), to = turn < FM_WAVES ? turn : 2 * FM_WAVES - 1 - turn;
+      const int lap = rank & (2 * FM_WAVES - 1), to = lap < FM_WAVES ? lap : 2 * FM_WAVES - 1 - lap;
       int at = 0;
 #pragma unroll
       for (int i = 0; i < FM_WAVES; ++i) {
@@ -226,7 +226,8 @@ __global__ __launch_bounds__(FM_THREADS) void ffn_pool_kernel(
     if (lane < 32) ffn_dma16(z + (size_t)p * D, (unsigned)(lane << 4), rland + (slot & 1) * RVB);
   };
   // r of the pairs that start in tile t (landed) in its parts, behind the last use of the parts before. The product wants a
-  // 16-group's components in the order 0..3, 8..11, 4..7, 12..15: word w (components 2 w, 2 w + 1) at 4 (w / 2 & 1) + 2 (w / 4) + w % 2.
+  // 16-group's components in the order 0..3, 8..11, 4..7, 12..15: word w (components 2 w, 2 w + 1) at 4 (w / 2 & 1) + 2
+  // (w / 4) + w % 2.
   unsigned char* rpmine = rparts + wave * RPB;
   // (Offsets of lanes that are used once per tile are worked out where they are used, from a lane number the compiler cannot tell
   // from a fresh value: kept across the products they are spilled, and a reload waits for the fetches before it.)
@@ -512,9 +513,10 @@ laser_status ffn_gsta_fused_launch(const FfnArgs& f, const GstaArgs& g) {
   long long blocks = ((long long)P + FM_WAVES - 1) / FM_WAVES;
   if (blocks > 256) blocks = 256;   // one workgroup per compute unit (LDS), each wave walking several pairs
   const bool views = g.pool_out != nullptr || g.recent_out != nullptr;
-  // Pairs are dealt where lengths differ and a pair fills most of a tile or more: lengths uniform, w = 10, d_ff = 128, with the views and
-  // the launches around it, in turn and dealt: S = 100 64 x 256 pairs 154 and 141 us, S = 48 94 x 200 115 and 110, S = 28 91.5 and 90.6;
-  // S = 20 82.1 and 82.8, S = 8 69.5 and 71.5 (two pairs share a tile however long they are); equal lengths, S = 100 201 either way.
+  // Pairs are dealt where lengths differ and a pair fills most of a tile or more: lengths uniform, w = 10, d_ff = 128, with the
+  // views and the launches around it, in turn and dealt: S = 100 64 x 256 pairs 154 and 141 us, S = 48 94 x 200 115 and 110,
+  // S = 28 91.5 and 90.6; S = 20 82.1 and 82.8, S = 8 69.5 and 71.5 (two pairs share a tile however long they are); equal
+  // lengths, S = 100 201 either way.
   const bool deal = f.lens != nullptr && f.S > 24 && P > FM_WAVES * blocks && P <= 64 * FG_DECKS * blocks;
 #define LASER_FFN_POOL(FF, MRF, DEAL)                                                                                       \
   hipLaunchKernelGGL((ffn_pool_kernel<FF, MRF, DEAL>), dim3((unsigned)blocks), dim3(FM_THREADS), 0, f.stream,               \

@@ -7,9 +7,9 @@
 // keeps its share of the matrices in registers over the tiles; fp32 factors (q', p) enter as three bf16 parts (24 bits), t0 is
 // bf16 as it is. The next tile's rows are on their way while one is multiplied.
 //
-// Bound by the start (launch, 64 or 32 KB of matrices a workgroup) and the chain of a tile. With FFN + GSTA between them, d = 128, against
-// a tile of 32 pairs a workgroup, W_q fetched by 64 two-byte loads a lane and the factors in two parts: 192 pairs 31.7 -> 27.9 us,
-// 3000 46.5 -> 42.6, 16384 141.6 -> 138.6, 27000 106.4 -> 95.5 (20 segments).
+// Bound by the start (launch, 64 or 32 KB of matrices a workgroup) and the chain of a tile. With FFN + GSTA between them,
+// d = 128, against a tile of 32 pairs a workgroup, W_q fetched by 64 two-byte loads a lane and the factors in two parts: 192
+// pairs 31.7 -> 27.9 us, 3000 46.5 -> 42.6, 16384 141.6 -> 138.6, 27000 106.4 -> 95.5 (20 segments).
 #include "gsta_tile.h"
 #include "laser_internal.h"
 
@@ -88,8 +88,8 @@ __global__ __launch_bounds__(4 * D, 4) void gsta_out_kernel(const unsigned short
   }
 }
 
-// Two workgroups on a compute unit (four of four waves at d = 64), each walking its share of the tiles (one: 27000 pairs 95.5 -> 97.0;
-// twice as many: 98.5, 16384 pairs 138.6 -> 144.1)
+// Two workgroups on a compute unit (four of four waves at d = 64), each walking its share of the tiles (one: 27000 pairs
+// 95.5 -> 97.0; twice as many: 98.5, 16384 pairs 138.6 -> 144.1)
 template <int D>
 static void launch_r(const GstaArgs& a) {
   const int P = gsta_pairs(a), tiles = (P + 15) / 16, most = 512 * 128 / D;

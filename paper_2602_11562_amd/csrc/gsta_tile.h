@@ -124,8 +124,8 @@ template <int D> struct Prod<float, D> {
       r.x[j] = *reinterpret_cast<const f32x4*>(W + n0 * D + j * 16 + (unsigned)((lane & 15) * D + (lane >> 4) * 4));
   }
   static __device__ __forceinline__ Operand transposed(const Cols& c, unsigned char* patch, int lane) {
-    // [D][16], row r of 64 bytes at place (r + r / 4) % 4 of its four rows: the four rows of a piece written at once, and the rows r,
-    // r + 4, r + 8, r + 12 read at once, are in different banks
+    // [D][16], row r of 64 bytes at place (r + r / 4) % 4 of its four rows: the four rows of a piece written at once, and the
+    // rows r, r + 4, r + 8, r + 12 read at once, are in different banks
     float* p = reinterpret_cast<float*>(patch);
     const int place = ((lane >> 4) * 4 + (((lane >> 2) + (lane >> 4)) & 3)) * 16 + (lane & 3) * 4;
 #pragma unroll
@@ -159,13 +159,14 @@ template <int D> struct Prod<unsigned short, D> {
   template <int PW> static constexpr int side_by_side() { return PW <= 4 ? 4 : (PW <= 8 ? 8 : 16); }
   // whether a piece's number is turned over by its row (see `at`)
   template <int PW> static constexpr bool turned() { return PW > 4 && D == 128; }
-  // Place of a part (head, remainder, remainder of that) of a pair's column; <PW>: of the product that will read it, whose lanes' rows
-  // are N part + pair. With few pairs (TURN false) the parts are 128 and 320 bytes past a multiple of 256 from each other, rows padded: four
-  // rows of three parts read at once are in different banks. From eight on, d = 128, rows have no padding and a 16-byte piece sits at its own number
-  // with bits turned over by its row: a read of 16 bytes a lane is served for rows 0 - 3 and 12 - 15 of one lane group together with rows
-  // 4 - 11 of the next, which reads the next piece, and whatever the row pitch, two of them met in a bank (4096 pairs, S = 16, d = 128
-  // 8.48 -> 8.20 us, 1450 packed pairs, S = 31 10.41 -> 10.13, the backward pass of 2048 pairs 38.5 -> 38.1; one to four pairs were 1.5 % slower with
-  // it for the longer addresses, fp32 1 %, d = 64 the same).
+  // Place of a part (head, remainder, remainder of that) of a pair's column; <PW>: of the product that will read it, whose lanes'
+  // rows are N part + pair. With few pairs (TURN false) the parts are 128 and 320 bytes past a multiple of 256 from each other,
+  // rows padded: four rows of three parts read at once are in different banks. From eight on, d = 128, rows have no padding and a
+  // 16-byte piece sits at its own number with bits turned over by its row: a read of 16 bytes a lane is served for rows 0 - 3 and
+  // 12 - 15 of one lane group together with rows 4 - 11 of the next, which reads the next piece, and whatever the row pitch, two
+  // of them met in a bank (4096 pairs, S = 16, d = 128 8.48 -> 8.20 us, 1450 packed pairs, S = 31 10.41 -> 10.13, the backward
+  // pass of 2048 pairs 38.5 -> 38.1; one to four pairs were 1.5 % slower with it for the longer addresses, fp32 1 %, d = 64 the
+  // same).
   static constexpr int PITCH = D + 8;
   static constexpr int PART[3] = {0, 16 * PITCH + 64, 32 * PITCH + 160};
   struct Act { unsigned short v[48 * PITCH + 160]; };

@@ -19,15 +19,15 @@
 // layers, d = 128: 100 pairs, S = 100 10.1 us (77 us on one workgroup per pair that walked the matrices row by row); 2048
 // pairs, S = 40 13.5 us, 4096 pairs, S = 32 17.8 us (16.3 and 31.2 us in the form with 32-pair tiles this one replaced);
 // fp32, 1200 pairs, S = 15, d = 64, two layers 8.2 us (34 us). Parts and patches laid out so that what is read at once is in
-// different banks, the next layer's W_q across its patch behind the pass, and the waves of a pair met behind the last product: another
-// layer of 100 pairs, d = 128, S = 8 2.65 -> 2.45 us (fp32 6.3 -> 5.95); 120 drawn calls 0.979 of the time.
+// different banks, the next layer's W_q across its patch behind the pass, and the waves of a pair met behind the last product:
+// another layer of 100 pairs, d = 128, S = 8 2.65 -> 2.45 us (fp32 6.3 -> 5.95); 120 drawn calls 0.979 of the time.
 #include "gsta_tile.h"
 #include "laser_internal.h"
 
 namespace laser {
 
-// PW: pairs per workgroup; R: row loads per lane and round; RES: one round holds every row (H' stays in registers); POOL: the maxima of
-// the pooled view from the pass over the rows (one layer, bf16, a wave's pairs its own)
+// PW: pairs per workgroup; R: row loads per lane and round; RES: one round holds every row (H' stays in registers); POOL: the
+// maxima of the pooled view from the pass over the rows (one layer, bf16, a wave's pairs its own)
 template <typename T, int D, int PW, int R, bool RES, bool POOL>
 __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) void gsta_tiled_kernel(const T* __restrict__ seg, const T* __restrict__ t0,
                                                           const T* __restrict__ wq, const T* __restrict__ wk,
@@ -40,9 +40,9 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   constexpr int WPP = PW < NW ? NW / PW : 1;                      // waves that share a pair's rows
   constexpr int PPW = PW > NW ? PW / NW : 1;                      // pairs of a wave
   constexpr int RP = D + 4;
-  // The turned layout of the vectors in LDS, but for the instances of two workgroups a compute unit (R < 4) whose 128 registers do not
-  // hold its longer addresses beside the rest: spilled, 2002 pairs, S = 2 took 8.5 us for 5.6, 9321 pairs, S = 11 17.9 for 15.6. One and two
-  // rows a lane of sixteen pairs fit, 0.96 of the time without it.
+  // The turned layout of the vectors in LDS, but for the instances of two workgroups a compute unit (R < 4) whose 128 registers
+  // do not hold its longer addresses beside the rest: spilled, 2002 pairs, S = 2 took 8.5 us for 5.6, 9321 pairs, S = 11 17.9 for
+  // 15.6. One and two rows a lane of sixteen pairs fit, 0.96 of the time without it.
   constexpr bool TURN = X::template turned<PW>() && !(RES && (PW == 8 ? R < 4 : R == 3));
   __shared__ __attribute__((aligned(16))) typename X::Act bt, bq; // t; q', then p
   __shared__ __attribute__((aligned(16))) float rr[PW * RP];      // r / sqrt(d)
@@ -62,8 +62,8 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
   const int pt = pbase + l16 < P ? pbase + l16 : P - 1;           // (rows of the tile past its pairs are not read back)
   const typename X::Raw4 traw = *reinterpret_cast<const typename X::Raw4*>(t0 + (size_t)pt * D + c4);
   // The oldest wave is served first: without a barrier here it has all of its requests in before the youngest has asked for what the
-  // first product waits for. d = 128, bf16, up to eight pairs (us): 100 pairs, S = 100, two layers 8.82 -> 8.62, 2048 x 40 13.75 -> 13.45,
-  // 4096 x 16, one layer 8.67 -> 8.53; sixteen pairs 10.26 -> 10.34, d = 64 and fp32 the same.
+  // first product waits for. d = 128, bf16, up to eight pairs (us): 100 pairs, S = 100, two layers 8.82 -> 8.62, 2048 x 40
+  // 13.75 -> 13.45, 4096 x 16, one layer 8.67 -> 8.53; sixteen pairs 10.26 -> 10.34, d = 64 and fp32 the same.
   if constexpr (D == 128 && sizeof(T) == 2 && PW <= 8) {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
@@ -127,11 +127,11 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
     X::template put4<PW, TURN>(bt, l16, c4, t);
     if (EAGER ? l == 0 : true) oq = X::transposed(cq, patch, lane);
     __syncthreads();
-    const f32x4 q = X::template product<PW, TURN>(bt, oq, lane);                     // q' = t W_q
+    const f32x4 q = X::template product<PW, TURN>(bt, oq, lane);               // q' = t W_q
     if (more_layers) X::load_cols(cq, wq + next, n0, lane);
     X::template put4<PW, TURN>(bq, l16, c4, q);
     __syncthreads();
-    const f32x4 rv = X::template product<PW, TURN>(bq, rk, lane);                    // r = W_k q'
+    const f32x4 rv = X::template product<PW, TURN>(bq, rk, lane);              // r = W_k q'
     if (LATE) X::load_cols(cv, wv + next - D * D, n0, lane);
     if (more_layers) X::load_rows(rk, wk + next, n0, lane);
     if (l16 < PW) *reinterpret_cast<f32x4*>(rr + l16 * RP + c4) = rv * scale;
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(4 * D, (RES && R < 4 && sizeof(T) == 2 ? 4 : 1)) vo
     if (EAGER && more_layers) oq = X::transposed(cq, patch, lane);
     __syncthreads();
     if constexpr (WPP == 1) {
-      t += X::template product<PW, TURN>(bq, ov, lane);                              // t += p W_v
+      t += X::template product<PW, TURN>(bq, ov, lane);                          // t += p W_v
     } else {
       // The waves of a pair meet behind the product: column o PW + pair is the sum of wave o, relative to its own maximum (merged
       // before the product they took a barrier more, and an exponential per wave and element)
@@ -288,14 +288,16 @@ static void launch_pairs(const GstaArgs& a, int P) {
   constexpr bool EIGHT = PW == 4 || PW == 8 || (sizeof(T) == 2 && (PW <= 2 || (PW == 16 && D == 128)));
   // Sixteen pairs of few rows, d = 128: with up to three rows a lane the registers suffice for two workgroups on a compute
   // unit, which hide each other's chains (two layers, four rows a lane -> the fewest: S = 4 8192 pairs 23.2 -> 17.1 us, 65536 pairs
-  // 165 -> 102; S = 12 23.4 -> 19.8 and 169 -> 119; three rows for 4096 pairs, one workgroup a compute unit, were slower: 13.4 -> 15.1)
+  // 165 -> 102; S = 12 23.4 -> 19.8 and 169 -> 119; three rows for 4096 pairs, one workgroup a compute unit, were slower:
+  // 13.4 -> 15.1)
   constexpr bool FEW = PW == 16 && D == 128 && sizeof(T) == 2;
   // One or two rows a lane where that is all there is: with four, the rows past the last one are worked on too (4096 pairs,
   // S = 16, d = 64, bf16: 6.5 -> 5.8 us, the pass 3700 -> 1900 cycles of a workgroup's 14000)
   auto streamed = [&]() {
     if constexpr (PW == 16 && sizeof(T) == 2) {
-      // The pooled maxima from the pass itself: read once more, the rows of many pairs with long blocks come from memory again (d = 64,
-      // lengths full: 35621 pairs x 229 473 -> 230 us, 17520 x 110 118 -> 67; without the views 0.92 .. 1.0 of the split form's times)
+      // The pooled maxima from the pass itself: read once more, the rows of many pairs with long blocks come from memory again
+      // (d = 64, lengths full: 35621 pairs x 229 473 -> 230 us, 17520 x 110 118 -> 67; without the views 0.92 .. 1.0 of the split
+      // form's times)
       if (a.M == 1 && a.pool_out != nullptr) {
         LASER_TILED_FORM(STREAM, false, true);
         return;
@@ -353,12 +355,15 @@ bool gsta_tile_supports(const GstaArgs& a) { return a.d == 64 || a.d == 128; }
 // Whether a one-layer bf16 batch runs on this kernel and not on the forms written for full machines (us, this kernel / the other,
 // lengths full). At d = 64 it does: S = 2 65536 pairs 0.54 of the time, S = 16 8192 pairs 7.7 / 11.0, 32768 0.67, S = 32 65536
 // 0.66, S = 64 8192 0.86, 65536 0.76; against the split form (longer blocks, up to 256) 37 calls past 16384 pairs, most with the
-// views, lengths full 0.92 .. 1.05, uniform 0.83 .. 1.04, log-uniform 0.49 .. 0.88. At d = 128 it does for blocks of up to three rows a
-// lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Against the split form S = 100 2048 pairs 14.3 / 26.7, S = 48 8192 0.74,
-// S = 128 0.90; past that line 0.75 .. 1.07, and 1.08 .. 1.31 with the views, when their maxima still came from a second reading.
-// Between, the one-kernel form is the better one once it fills a round of 256 workgroups of 32 pairs with more than half: S = 32
-// 4096 pairs 11.3 / 15.5, 5000 19.2 / 16.1, 8192 23.1 / 18.3, in its second round 10000 30.6 / 31.5, 12288 33.0 / 31.7, 32768 1.24
-// (9 calls of 13 to 32 segments 0.87, 31 with the views 0.76 .. 1.07, 0.89; those above 1.0 with 28 segments and more).
+// views, lengths full 0.92 .. 1.05, uniform 0.83 .. 1.04, log-uniform 0.49 .. 0.88. At d = 128 it does for blocks of up to three
+// rows a lane, S = 2 .. 12 with 3000 to 65536 pairs 0.58 .. 0.92. Up to 32 segments the one-kernel form is the better one once it
+// fills a round of 256 workgroups of 32 pairs with more than half, and again a little into its second round.
+// 500 calls at d = 128, 13 to 128 segments, 2500 to 50000 pairs without the views, this kernel's time over the other's, lengths full
+// and with lengths, mean (range): on this side of the lines 0.79 (0.59 .. 1.09), 0.74 (0.57 .. 0.95). On the other side S <= 32 4097
+// to 8192 pairs 1.14 (1.07 .. 1.24), 1.06 (0.94 .. 1.11), past 11264 1.04 (0.91 .. 1.20), 0.96 (0.81 .. 1.08); S = 33 .. 64 up to
+// 16384 pairs 1.02 (0.95 .. 1.09), 0.91 (0.73 .. 1.07), more 1.16 (1.00 .. 1.31), 1.11 (0.87 .. 1.36); S = 65 .. 128 1.05
+// (0.99 .. 1.18), 0.87 (0.59 .. 1.18). So past 8192 pairs with lengths given the lines, drawn for full ones and an earlier form of both
+// kernels, leave calls there that would be faster here.
 bool gsta_tile_preferred(const GstaArgs& a) {
   const int P = gsta_pairs(a);
   if (a.d == 64 || a.S <= 12) return true;

@@ -375,10 +375,11 @@ __global__ __launch_bounds__(256) void sta_bwd_wide_kernel(const unsigned short*
   }
 }
 
-// dq[u] = the sum of the user's partial rows in the order of the runs: four consecutive elements a thread (row: pieces of a user; d_q is a
-// multiple of eight), AHEAD runs' in flight. The launch is one trip to memory: with a 64-bit division, and a load awaited before the
-// next, 2048 users x 32 elements of 9 runs took the backward pass 195.7 us, now 193.4, 64 x 4096 of 8 runs 31.8 and 30.1. Places past the
-// last run repeat it, and repeats cost: sixteen for one run, 1879 users x 24192 elements 573 us, 5124 x 288 22.6; one 497 and 21.5.
+// dq[u] = the sum of the user's partial rows in the order of the runs: four consecutive elements a thread (row: pieces of a user;
+// d_q is a multiple of eight), AHEAD runs' in flight. The launch is one trip to memory: with a 64-bit division, and a load
+// awaited before the next, 2048 users x 32 elements of 9 runs took the backward pass 195.7 us, now 193.4, 64 x 4096 of 8 runs
+// 31.8 and 30.1. Places past the last run repeat it, and repeats cost: sixteen for one run, 1879 users x 24192 elements 573 us,
+// 5124 x 288 22.6; one 497 and 21.5.
 template <int AHEAD>
 __global__ __launch_bounds__(64) void sta_bwd_dq_kernel(const float* __restrict__ dq_part, int groups, int row, MulDiv by_row,
                                                         unsigned total, float* __restrict__ dq_out) {

@@ -12,8 +12,8 @@
 // that order by the transpose load). A tile that crosses the end of a block is multiplied once per block. The gates are
 // fp32 and stay so: they enter the product as three bf16 parts (24 bits), three MFMAs on the same V operand.
 // Accumulator rows are dealt so that a lane ends with eight consecutive columns of every 32 of its (segment, query row), which leave
-// as 16-byte stores, 64 bytes of a row from four lanes; in the folded form the same registers, rounded to bf16, are the operand of the product with W_v (in
-// LDS in operand order, once per workgroup), and H' leaves with the sums.
+// as 16-byte stores, 64 bytes of a row from four lanes; in the folded form the same registers, rounded to bf16, are the operand
+// of the product with W_v (in LDS in operand order, once per workgroup), and H' leaves with the sums.
 // A zero gate times an item that is not finite would spread over the block's other segments. When a finished block holds a
 // value that is not finite, the block is computed again, item by item over each column's own segment.
 //
@@ -51,9 +51,10 @@ struct FewShape {
   static constexpr int WVB = FOLD ? D * FE * 2 : 0;
   static constexpr int WAVE = 2 * BUF, FIT = (FEW_LDS - WVB) / WAVE;
   static constexpr int NW = FIT < 8 ? FIT : 8;               // waves per workgroup, one workgroup per compute unit
-  // the tickets' counter: behind the rings, or, where these fill the LDS (folded, FE = 64: 16 KB of W_v and eight rings of 18), in the
-  // place of the first word of W_v's last fragment, lane 63, which every wave then keeps in a register (with seven waves instead 150
-  // calls, most of them dealt, took 0.98 of their time in turn, so 0.965; 514 users x 2 rows, L = 776, w = 20, full 28.3, 29.7 and 28.1 us)
+  // the tickets' counter: behind the rings, or, where these fill the LDS (folded, FE = 64: 16 KB of W_v and eight rings of 18),
+  // in the place of the first word of W_v's last fragment, lane 63, which every wave then keeps in a register (with seven waves
+  // instead 150 calls, most of them dealt, took 0.98 of their time in turn, so 0.965; 514 users x 2 rows, L = 776, w = 20, full
+  // 28.3, 29.7 and 28.1 us)
   static constexpr bool FULL = DEAL && WVB + NW * WAVE + 16 > FEW_LDS;
   static constexpr int NT = 64 * NW, TICKET = FULL ? WVB - 16 : WVB + NW * WAVE, LDS = WVB + NW * WAVE + (DEAL && !FULL ? 16 : 0);
   static_assert(LDS <= FEW_LDS && (!FULL || FOLD), "the counter takes the place of a piece of W_v");
@@ -123,15 +124,16 @@ __global__ __launch_bounds__((FewShape<DQ, D, FE, DEAL>::NT)) void sta_few_kerne
   };
 
   // A unit of work is one run of a user's segments; a workgroup takes every (number of workgroups)-th one and its waves share
-  // them, in turn or by ticket, so that the waves in flight sweep the arrays front to back, with the runs of a user rotated so that no wave meets one run only. The fetches are two
-  // tiles ahead of the arithmetic across units, and every unit counts at least two tiles, so that this reaches into the
-  // next unit and no further.
+  // them, in turn or by ticket, so that the waves in flight sweep the arrays front to back, with the runs of a user rotated so
+  // that no wave meets one run only. The fetches are two tiles ahead of the arithmetic across units, and every unit counts at
+  // least two tiles, so that this reaches into the next unit and no further.
   struct Unit {
     int C, i_beg, i_ne, t_beg, t_end, ntile;
     size_t pb;
     const unsigned short *k, *v;
   };
-  // (read with the arguments: read where it is first wanted, it is another trip to memory ahead of the first unit, 0.2 us of every call)
+  // (read with the arguments: read where it is first wanted, it is another trip to memory ahead of the first unit, 0.2 us of
+  // every call)
   const unsigned blocks = gridDim.x;
   auto len_of = [&](unsigned it) { return it < units && lens != nullptr ? lens[dv.div(it)] : L; };
   // unit `it` of a user of (unclamped) length n: its counts, its empty segments; false: nothing to compute
@@ -452,9 +454,10 @@ static laser_status few_launch(const StaArgs& a, const FewFold& fold) {
               : launch(FewShape<DQ, D, FE, false>{}, sta_few_kernel<DQ, D, FE, false>);
 }
 
-// From three query rows per user on the vector-ALU kernels are bound by their arithmetic and this one by HBM; with one or two rows both
-// are near HBM, and in launches that the cache holds the vector-ALU kernels, with four times the waves in flight, are the better ones,
-// except for two rows of 64-wide keys and values (past the cache: few_preferred_large). Lengths uniform in [L / 5, L], us there and here:
+// From three query rows per user on the vector-ALU kernels are bound by their arithmetic and this one by HBM; with one or two
+// rows both are near HBM, and in launches that the cache holds the vector-ALU kernels, with four times the waves in flight, are
+// the better ones, except for two rows of 64-wide keys and values (past the cache: few_preferred_large). Lengths uniform in
+// [L / 5, L], us there and here:
 //   U, C, L, w             d_q = 32, d = 128    64, 64          128, 128        64, 128
 //   1500, 3, 1000, 25        96 -> 56          119 -> 44        200 -> 86       119 -> 64
 //   1500, 4, 1000, 10       124 -> 96          146 -> 54        176 -> 128      131 -> 95
@@ -480,19 +483,18 @@ static bool few_fills(const StaArgs& a) {
   return a.w > 10 || items >= (a.C == 4 ? 32768 : 8192);
 }
 
-// One or two rows in a launch past the cache, whose units are dealt by ticket, against the vector-ALU kernels. With lengths given the
-// histories may hold a fraction of their arrays, which the cache then keeps, and a launch needs more to be the better one here;
-// segments longer than a tile that fill less than three quarters of their tiles (33 to 47 items, 65 to 71) are multiplied with too much of
-// nothing; with 400 items and more a wave is left with too few units.
-// 1950 calls of 60 to 8000 users and items, lengths full, uniform from nothing or a fifth on, or spread over the logarithm, mean (and
-// worst) time here over that there:
+// One or two rows in a launch past the cache, whose units are dealt by ticket, against the vector-ALU kernels. With lengths given
+// the histories may hold a fraction of their arrays, which the cache then keeps, and a launch needs more to be the better one
+// here; segments longer than a tile that fill less than three quarters of their tiles (33 to 47 items, 65 to 71) are multiplied
+// with too much of nothing; with 400 items and more a wave is left with too few units. 1950 calls of 60 to 8000 users and items,
+// lengths full, uniform from nothing or a fifth on, or spread over the logarithm, mean (and worst) time here over that there:
 //   one row, 64 / 64: w 10 .. 127 full from 256 MB 0.83 (1.04), with lengths from 400 MB 0.77 (1.15), below 0.88 (1.19)
 //     128 / 128: w 16 .. 32 full from 256 MB 0.92 (1.01), with lengths from 1 GB 0.89 (1.06), from 600 MB 0.89 (1.30); w 48 .. 63
 //       full 0.88 (1.01), with lengths from 600 MB 0.80 (1.12), below 0.93 (1.46)
 //     64 / 128: w 24 .. 32 and 48 .. 64 full from 300 MB 0.93 (1.04); with lengths w 48 .. 64 from 1 GB 0.87 (1.05), below 0.97
 //       (1.56), w 24 .. 32 0.97 (1.40)
-//     32 / 128, w 24 .. 50 full 0.95 (1.10), with lengths 0.98 (1.57), stays there, as do 128 / 64 and 32 / 64 (1500, 1000, 40, 32 / 64,
-//       lengths over the logarithm 18 us and 25)
+//     32 / 128, w 24 .. 50 full 0.95 (1.10), with lengths 0.98 (1.57), stays there, as do 128 / 64 and 32 / 64 (1500, 1000, 40,
+//       32 / 64, lengths over the logarithm 18 us and 25)
 //   two rows, 32 / 64: w 8 .. 32 from 150 MB 0.66 (0.94); w 48 .. 399 full from 300 MB 0.88 (0.95), with lengths from 600 MB 0.79
 //       (0.98), below 0.96 (1.29)
 //     128 / 64: w 8 .. 200 from 150 MB 0.78 (1.08); w 201 .. 399 full from 300 MB 0.91 (0.94), with lengths from 600 MB 0.79 (0.88),
@@ -539,11 +541,11 @@ laser_status sta_few_launch(const StaArgs& a) {
 
 // The folded form: a is STA over the raw items (C query rows per user, heads of each candidate next to each other), p the
 // projection of its sums
-// 2048 users x 1 candidate x 2 heads, L = 1000, w = 10, lengths uniform in [200, 1000]: 83 us repeated on one batch (106 with a fixed
-// share of units for every wave, the sums through the cache and in 16-byte pieces); the vector-ALU kernel over the raw items and the
-// projection of its stored sums took 101 + 33 us. More than four query rows do not fit the ring. With
-// one or two rows, long segments and few of them the separate launches are the better ones, as above (whole chain, L = 1000,
-// w = 1000: 16 users x 1 row 21 us, 35 here; 64 x 2 rows 32 and 36; 64 x 1, L = 4000, w = 500 the same time).
+// 2048 users x 1 candidate x 2 heads, L = 1000, w = 10, lengths uniform in [200, 1000]: 83 us repeated on one batch (106 with a
+// fixed share of units for every wave, the sums through the cache and in 16-byte pieces); the vector-ALU kernel over the raw
+// items and the projection of its stored sums took 101 + 33 us. More than four query rows do not fit the ring. With one or two
+// rows, long segments and few of them the separate launches are the better ones, as above (whole chain, L = 1000, w = 1000: 16
+// users x 1 row 21 us, 35 here; 64 x 2 rows 32 and 36; 64 x 1, L = 4000, w = 500 the same time).
 bool sta_few_folded_supports(const StaArgs& a, const ProjHeadsArgs& p) {
   if (a.dt != LASER_BF16 || a.C > 4 || a.k != a.v || a.d_q != 128 || a.d != 128) return false;
   if (a.C <= 2 && a.w > 128 * a.C && (long long)a.U * a.S < 512) return false;
