@@ -16,6 +16,13 @@ static void* data_of(PyObject* o, at::ScalarType type) {
   return t.data_ptr();
 }
 
+// whether the number just read was no address: then nothing may be called with it, and nothing returned beside its error
+static bool no_address() {
+  const bool bad = PyErr_Occurred() != nullptr;
+  if (bad) PyErr_Clear();
+  return bad;
+}
+
 // forward(address of laser_forward, q, k, v, t0, wq, wk, wv, lens, w, gamma, seg_out, seg_cnt, z_out, stream) -> status, or None:
 // not a call of this form, nothing done
 static PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -24,6 +31,7 @@ static PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const auto fn = reinterpret_cast<Forward>(PyLong_AsVoidPtr(a[0]));
     int overflow = 0;
     const long w = PyLong_AsLongAndOverflow(a[9], &overflow);
+    if (no_address()) Py_RETURN_NONE;
     if (!fn || overflow || w != (int)w || w == 0 || !THPVariable_CheckExact(a[1])) Py_RETURN_NONE;
     const at::Tensor& q = THPVariable_Unpack(a[1]);
     const at::ScalarType type = q.scalar_type();
@@ -41,6 +49,7 @@ static PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (a[14] != Py_None) {
       if (!PyLong_CheckExact(a[14])) Py_RETURN_NONE;
       stream = PyLong_AsVoidPtr(a[14]);
+      if (no_address()) Py_RETURN_NONE;
     }
     const int64_t sizes[6] = {q.size(0), q.size(1), v.size(1), q.size(2), v.size(2), wq.size(0)};
     for (const int64_t s : sizes)

@@ -155,6 +155,8 @@ def test_the_native_marshalling_leaves_every_other_form_alone():
     for at, other in ((0, None), (0, x.as_subclass(Sub)), (3, "t0"), (8, 2.0), (8, 1 << 40), (9, 1), (10, None), (13, "stream")):
         assert forward(1, *good[:at], other, *good[at + 1:]) is None
     assert forward(1, *good[:-1]) is None and forward() is None
+    for address in (1 << 70, -(1 << 70)):
+        assert forward(address, *good) is None
 
 
 def test_the_native_part_carries_the_stamp_of_this_torch():
