@@ -242,6 +242,16 @@ def test_backward_calls_with_two_sets_of_tiles(recorder, name):
     assert (first.grid, first.lds) == (grid, lds)
 
 
+@pytest.mark.parametrize("C,w,mb", [(1, 64, 400), (2, 64, 150)])
+def test_packed_rows_past_the_cache_count_the_users_that_have_some(recorder, C, w, mb):
+    L, dq, d = 2000, 64 if C == 1 else 128, 64
+    least = -(-mb * 1000000 // (L * (dq + d) * 2))
+    for U in (least, 3 * least):
+        for P, here in ((least * C, True), (least * C - 1, False)):
+            launch = launches(recorder, lambda lib: lib.laser_sta_forward_ragged(A, A, A + 0x10, A, A, U, C, P, L, dq, d, w, 1.0, BF16, A, A, None))[0]
+            assert bool(few(launch)) == here, (U, P, launch.kernel)
+
+
 @pytest.mark.parametrize("S,ahead", [(1, 1), (2, 4), (4, 4), (5, 16), (16, 16), (17, 16)])
 def test_no_more_runs_in_flight_than_a_user_has(recorder, S, ahead):
     last = launches(recorder, lambda lib: lib.laser_sta_backward(A, A, A, A, A, 3, 2, 10 * S, 24, 48, 10, 1.0, F32, A, A, A, A, 1 << 40, None))[-1]
